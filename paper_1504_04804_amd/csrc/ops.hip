@@ -16,13 +16,21 @@ constexpr int EXP_PER_BLOCK = 2048;
 
 // ------------------------------------------------------------ scan helpers
 
-// Block sums of `val(i)` over tiles of TB elements.
-template <class F>
+// Up to this many tiles a scan's second kernel sums the tile sums before its
+// own tile itself (at most two loads per thread), which saves the one-block
+// kernel in between; above it that kernel scans them once.  A launch that has
+// nothing to do costs about 4.8 us in a chain of dependent kernels; 2048
+// tiles read 16 MB of sums from the L2s in all, under that.
+constexpr int SELF_TILES = 2048;
+constexpr int QB = 256;  // words per tile of bitmap -> queue (smaller: 64 words a wave to write)
+
+// Block sums of `val(i)` over tiles of BT elements.
+template <int BT, class F>
 __global__ void tile_sum_kernel(int64_t len, F val, int64_t* __restrict__ sums) {
-  __shared__ int64_t red[TB / FG_WAVE + 1];
-  const int64_t i = (int64_t)blockIdx.x * TB + threadIdx.x;
+  __shared__ int64_t red[BT / FG_WAVE + 1];
+  const int64_t i = (int64_t)blockIdx.x * BT + threadIdx.x;
   int64_t x = i < len ? val(i) : 0;
-  int64_t s = fg_block_sum<TB>(x, red);
+  int64_t s = fg_block_sum<BT>(x, red);
   if (threadIdx.x == 0) sums[blockIdx.x] = s;
 }
 
@@ -42,16 +50,29 @@ __global__ void scan_sums_kernel(int64_t cnt, int64_t* __restrict__ sums,
   if (threadIdx.x == 0) *total = carry;
 }
 
-// Exclusive scan of val(i) using the scanned tile sums; out[i] for i < len.
-template <class F>
+// The sum of everything before this block's tile: the scanned tile sum, or
+// (SELF) the sum of the raw tile sums before it.
+template <bool SELF, int BT>
+__device__ __forceinline__ int64_t tile_base(const int64_t* sums, int64_t* red) {
+  if (!SELF) return sums[blockIdx.x];
+  int64_t x = 0;
+  for (unsigned j = threadIdx.x; j < blockIdx.x; j += BT) x += sums[j];
+  return fg_block_sum<BT>(x, red);
+}
+
+// Exclusive scan of val(i) from the tile sums; out[i] for i < len.  With
+// SELF the last tile also writes the total.
+template <bool SELF, class F>
 __global__ void tile_scan_kernel(int64_t len, F val, const int64_t* __restrict__ sums,
-                                 int64_t* __restrict__ out) {
+                                 int64_t* __restrict__ out, int64_t* __restrict__ total) {
   __shared__ int64_t red[TB / FG_WAVE + 1];
   const int64_t i = (int64_t)blockIdx.x * TB + threadIdx.x;
   int64_t x = i < len ? val(i) : 0;
+  const int64_t base = tile_base<SELF, TB>(sums, red);
   int64_t tot = 0;
   int64_t ex = fg_block_excl_scan<TB>(x, red, &tot);
-  if (i < len) out[i] = sums[blockIdx.x] + ex;
+  if (i < len) out[i] = base + ex;
+  if (SELF && blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) *total = base + tot;
 }
 
 // Degree of frontier entry i; entries at or past the device-resident
@@ -82,9 +103,14 @@ struct ScanWs {
 template <class F>
 void run_scan(int64_t len, F f, ScanWs w, hipStream_t s) {
   const int64_t tiles = (len + TB - 1) / TB;
-  if (tiles > 0) tile_sum_kernel<<<(unsigned)tiles, TB, 0, s>>>(len, f, w.sums);
+  if (tiles > 0) tile_sum_kernel<TB><<<(unsigned)tiles, TB, 0, s>>>(len, f, w.sums);
+  if (tiles > 0 && tiles <= SELF_TILES) {
+    tile_scan_kernel<true><<<(unsigned)tiles, TB, 0, s>>>(len, f, w.sums, w.scan, w.total);
+    return;
+  }
   scan_sums_kernel<<<1, TB, 0, s>>>(tiles, w.sums, w.total);
-  if (tiles > 0) tile_scan_kernel<<<(unsigned)tiles, TB, 0, s>>>(len, f, w.sums, w.scan);
+  if (tiles > 0)
+    tile_scan_kernel<false><<<(unsigned)tiles, TB, 0, s>>>(len, f, w.sums, w.scan, w.total);
 }
 
 // -------------------------------------------------------------- advance
@@ -95,6 +121,24 @@ __device__ __forceinline__ int64_t scan_upper(const int64_t* scan, int64_t lo, i
   while (lo < hi) {
     int64_t mid = (lo + hi + 1) >> 1;
     if (scan[mid] <= t) lo = mid; else hi = mid - 1;
+  }
+  return lo;
+}
+
+// The same by a whole wave, 64 probes per step (every lane calls it with the
+// same arguments and gets the result): three dependent loads where the
+// halving search of one lane takes sixteen, which made the expansion of 1.1 M edges
+// 21 us (16 us now).
+__device__ __forceinline__ int64_t wave_scan_upper(const int64_t* scan, int64_t lo, int64_t hi,
+                                                   int64_t t) {
+  const int lane = fg_lane();
+  while (lo < hi) {
+    const int64_t step = (hi - lo + FG_WAVE - 1) / FG_WAVE;
+    const int64_t at = lo + (lane + 1) * step;  // probes ascend; those past hi count as greater
+    const int c = __popcll(__ballot(at <= hi && scan[at <= hi ? at : hi] <= t));
+    const int64_t top = lo + (c + 1) * step - 1;
+    lo += c * step;
+    hi = top < hi ? top : hi;
   }
   return lo;
 }
@@ -110,7 +154,7 @@ __global__ void advance_expand_kernel(int64_t len, const int32_t* __restrict__ q
                                       int32_t* __restrict__ out_src,
                                       int64_t* __restrict__ out_len) {
   __shared__ int64_t s_scan[EXP_PER_BLOCK + 1];
-  __shared__ int64_t s_lo, s_cnt;
+  __shared__ int64_t s_lo, s_hi;
   const int64_t T = *total;
   if (blockIdx.x == 0 && threadIdx.x == 0 && out_len) *out_len = T;
   const int64_t lim = T < capacity ? T : capacity;
@@ -118,14 +162,13 @@ __global__ void advance_expand_kernel(int64_t len, const int32_t* __restrict__ q
        t0 += (int64_t)gridDim.x * EXP_PER_BLOCK) {
     const int64_t t1 = (t0 + EXP_PER_BLOCK < lim ? t0 + EXP_PER_BLOCK : lim) - 1;
     __syncthreads();
-    if (threadIdx.x == 0) {
-      int64_t lo = scan_upper(scan, 0, len - 1, t0);
-      int64_t hi = scan_upper(scan, lo, len - 1, t1);
-      s_lo = lo;
-      s_cnt = hi - lo + 1;
+    const int wid = threadIdx.x / FG_WAVE;
+    if (wid < 2) {  // the first and the last entry of the slots, a wave each
+      const int64_t x = wave_scan_upper(scan, 0, len - 1, wid == 0 ? t0 : t1);
+      if (fg_lane() == 0) (wid == 0 ? s_lo : s_hi) = x;
     }
     __syncthreads();
-    const int64_t lo = s_lo, cnt = s_cnt;
+    const int64_t lo = s_lo, cnt = s_hi - lo + 1;
     const bool in_lds = cnt <= EXP_PER_BLOCK + 1;
     if (in_lds)
       for (int64_t j = threadIdx.x; j < cnt; j += blockDim.x) s_scan[j] = scan[lo + j];
@@ -150,6 +193,46 @@ __global__ void advance_expand_kernel(int64_t len, const int32_t* __restrict__ q
   }
 }
 
+// ------------------------------------------------ staged appends to a queue
+
+// A workgroup collects what it appends to the output queue in LDS and
+// reserves room for all of it with one atomic: the queue's counter is one
+// address for the whole launch, and atomics on one address are served one
+// after another, 11.3 ns each.
+template <int BT, int CAP>
+struct BlockStage {
+  int32_t* buf;   // LDS, CAP entries
+  int32_t* cnt;   // LDS
+  int32_t* base;  // LDS
+
+  // Appends the calling wave's kept lanes (at most CAP minus what is staged,
+  // which the caller ensures by its flushes).
+  __device__ __forceinline__ void push(bool keep, int32_t v) {
+    const uint64_t mask = __ballot(keep);
+    if (!mask) return;
+    int32_t pos = 0;
+    if (fg_lane() == 0) pos = atomicAdd(cnt, __popcll(mask));
+    pos = __builtin_amdgcn_readfirstlane(pos);
+    if (keep) buf[pos + fg_mbcnt(mask)] = v;
+  }
+
+  // Writes the staged entries out if more than `most` are staged.  Every
+  // thread of the workgroup calls it with the same `most`, after a barrier
+  // that follows the last push; pushes may follow at once (every thread has
+  // read the count by then).
+  __device__ __forceinline__ void flush_above(int32_t most, int32_t* out_q, int32_t* out_len) {
+    const int32_t c = *cnt;
+    __syncthreads();
+    if (c <= most) return;
+    if (threadIdx.x == 0) *base = atomicAdd(out_len, c);
+    __syncthreads();
+    const int32_t b = *base;
+    for (int32_t i = threadIdx.x; i < c; i += BT) out_q[b + i] = buf[i];
+    if (threadIdx.x == 0) *cnt = 0;
+    __syncthreads();
+  }
+};
+
 // --------------------------------------------------------------- filter
 
 __global__ void fill_i32_kernel(int32_t* p, int64_t count, int32_t value) {
@@ -158,100 +241,331 @@ __global__ void fill_i32_kernel(int32_t* p, int64_t count, int32_t value) {
     p[i] = value;
 }
 
+constexpr int FT_BT = 1024;
+constexpr int FT_R = 8;                  // edges per thread and tile
+constexpr int FT_TILE = FT_BT * FT_R;
+constexpr int FT_STAGE = 2 * FT_TILE;
+constexpr int FT_SLOTS = 4096;           // visited words a tile combines
+
 // Test-and-set of dst's visited bit; winners take depth / parent and are
 // appended to out_q.  The edge-frontier length is read from device memory
 // (`d_len`, clamped to `cap`) or taken from `h_len` when d_len is NULL.
-__global__ void filter_kernel(const int32_t* __restrict__ dst, const int32_t* __restrict__ src,
-                              const int64_t* __restrict__ d_len, int64_t h_len, int64_t cap,
-                              uint32_t* __restrict__ visited, int32_t d_new,
-                              int32_t* __restrict__ depth, int32_t* __restrict__ parent,
-                              int32_t* __restrict__ out_q, int32_t* __restrict__ out_len) {
+//
+// Atomics on one word are served one after another at the point of
+// coherence (11.3 ns each; 0.04 ns where the words lie in different lines,
+// 0.007 ns for consecutive words), and a scale-free edge frontier repeats
+// its hubs' few words: with one test-and-set per edge whose vertex looked
+// unvisited the kernel took 279 us on 1.1 M edges (R-MAT of 1 M vertices).
+// So a workgroup combines a tile first: its bits go into a direct-mapped
+// LDS table of visited words (a word's slot is its id modulo FT_SLOTS; of
+// two words in one slot one keeps it and the other waits for another round:
+// testing its edges in memory at once cost 150 us where a hub's word was the
+// one that lost), one atomic per word takes them to memory, neighbouring
+// slots by neighbouring lanes, and the edge that set a bit in the table first
+// wins the vertex if memory says the bit is new.  That takes 64 us (tiles of
+// 4096 edges 82 us, 2048 edges over 115 us: the hot lines get one request per
+// tile and round, which is what bounds it).  The look before that reads
+// past the caches (agent scope), so vertices that other workgroups have set
+// meanwhile are not tried again.
+__global__ __launch_bounds__(FT_BT) void filter_kernel(
+    const int32_t* __restrict__ dst, const int32_t* __restrict__ src,
+    const int64_t* __restrict__ d_len, int64_t h_len, int64_t cap,
+    uint32_t* __restrict__ visited, int32_t d_new, int32_t* __restrict__ depth,
+    int32_t* __restrict__ parent, int32_t* __restrict__ out_q, int32_t* __restrict__ out_len) {
+  __shared__ int32_t s_buf[FT_STAGE];
+  __shared__ int32_t s_tag[FT_SLOTS];
+  __shared__ uint32_t s_bits[FT_SLOTS];
+  __shared__ int32_t s_cnt, s_base;
   int64_t len = d_len ? *d_len : h_len;
   if (len > cap) len = cap;
-  const int lane = fg_lane();
-  const int64_t nth = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t k0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x - lane; k0 < len; k0 += nth) {
-    const int64_t k = k0 + lane;
-    bool won = false;
-    int32_t v = 0;
-    if (k < len) {
-      v = dst[k];
-      const uint32_t bit = 1u << (v & 31);
-      if (!(visited[v >> 5] & bit)) {
-        const uint32_t old = atomicOr(&visited[v >> 5], bit);
-        if (!(old & bit)) {
-          won = true;
-          depth[v] = d_new;
-          if (parent) parent[v] = src[k];
+  if ((int64_t)blockIdx.x * FT_TILE >= len) return;  // the whole workgroup
+  BlockStage<FT_BT, FT_STAGE> stage{s_buf, &s_cnt, &s_base};
+  if (threadIdx.x == 0) s_cnt = 0;
+  for (int64_t t0 = (int64_t)blockIdx.x * FT_TILE; t0 < len; t0 += (int64_t)gridDim.x * FT_TILE) {
+    int32_t v[FT_R];
+    uint32_t word[FT_R];
+    bool open[FT_R];
+#pragma unroll
+    for (int r = 0; r < FT_R; ++r) {
+      const int64_t k = t0 + r * FT_BT + threadIdx.x;
+      v[r] = k < len ? dst[k] : -1;
+    }
+#pragma unroll
+    for (int r = 0; r < FT_R; ++r)
+      word[r] = v[r] >= 0 ? fg_atomic_load_u32(&visited[v[r] >> 5]) : ~0u;
+    bool any = false;
+#pragma unroll
+    for (int r = 0; r < FT_R; ++r) {
+      open[r] = !((word[r] >> (v[r] & 31)) & 1u);
+      any = any || open[r];
+    }
+    // one round per word that shares a slot (each round settles at least the
+    // word that kept the slot, so the rounds end)
+    while (__syncthreads_or(any)) {
+      for (int i = threadIdx.x; i < FT_SLOTS; i += FT_BT) s_bits[i] = 0;
+#pragma unroll
+      for (int r = 0; r < FT_R; ++r)
+        if (open[r]) s_tag[(v[r] >> 5) & (FT_SLOTS - 1)] = v[r] >> 5;
+      __syncthreads();
+      bool first[FT_R];
+      any = false;
+#pragma unroll
+      for (int r = 0; r < FT_R; ++r) {
+        const int slot = (v[r] >> 5) & (FT_SLOTS - 1);
+        const uint32_t bit = 1u << (v[r] & 31);
+        first[r] = open[r] && s_tag[slot] == v[r] >> 5;
+        open[r] = open[r] && !first[r];
+        // an edge that is not the first of its vertex here is done
+        if (first[r]) first[r] = !(atomicOr(&s_bits[slot], bit) & bit);
+        any = any || open[r];
+      }
+      __syncthreads();
+      for (int i = threadIdx.x; i < FT_SLOTS; i += FT_BT) {
+        const uint32_t mine = s_bits[i];
+        if (mine) s_bits[i] = mine & ~atomicOr(&visited[s_tag[i]], mine);
+      }
+      __syncthreads();
+#pragma unroll
+      for (int r = 0; r < FT_R; ++r) {
+        const bool won =
+            first[r] && ((s_bits[(v[r] >> 5) & (FT_SLOTS - 1)] >> (v[r] & 31)) & 1u);
+        if (won) {
+          depth[v[r]] = d_new;
+          if (parent) parent[v[r]] = src[t0 + r * FT_BT + threadIdx.x];
         }
+        stage.push(won, v[r]);
       }
     }
-    const uint64_t mask = __ballot(won);
-    if (mask) {
-      int32_t pos = 0;
-      if (lane == 0) pos = atomicAdd(out_len, __popcll(mask));
-      pos = __shfl(pos, 0, FG_WAVE);
-      if (won) out_q[pos + fg_mbcnt(mask)] = v;
-    }
+    __syncthreads();
+    stage.flush_above(FT_STAGE - FT_TILE, out_q, out_len);
   }
+  stage.flush_above(0, out_q, out_len);
 }
 
 // ------------------------------------------------------------ pull step
 
-__global__ void pull_step_kernel(int32_t nwords, const int32_t* __restrict__ off,
-                                 const int32_t* __restrict__ col,
-                                 const uint64_t* __restrict__ nz,
-                                 const uint64_t* __restrict__ fbits,
-                                 uint64_t* __restrict__ visited,
-                                 uint64_t* __restrict__ next_bits, int32_t d_new,
-                                 int32_t* __restrict__ depth, int32_t* __restrict__ parent,
-                                 int32_t* __restrict__ out_q, int32_t* __restrict__ out_len,
-                                 int64_t* __restrict__ inspected) {
-  const int lane = fg_lane();
-  const int64_t gw = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / FG_WAVE;
-  const int64_t W = ((int64_t)gridDim.x * blockDim.x) / FG_WAVE;
-  int64_t insp = 0;
-  for (int64_t w = gw; w < nwords; w += W) {
-    const uint64_t vis = visited[w];
-    const uint64_t act = nz[w] & ~vis;
-    uint64_t nb = 0;
-    if (act) {
-      const int32_t v = (int32_t)(w * 64 + lane);
-      bool found = false;
-      int32_t pu = -1;
-      if ((act >> lane) & 1ull) {
-        const int32_t e = off[v + 1];
-        for (int32_t i = off[v]; i < e; ++i) {
-          const int32_t u = col[i];
-          insp++;
-          if ((fbits[u >> 6] >> (u & 63)) & 1ull) {
-            found = true;
-            pu = u;
-            break;
-          }
-        }
-      }
-      nb = __ballot(found);
-      if (found) {
-        depth[v] = d_new;
-        if (parent) parent[v] = pu;
-      }
-      if (nb) {
-        int32_t pos = 0;
-        if (lane == 0) pos = atomicAdd(out_len, __popcll(nb));
-        pos = __shfl(pos, 0, FG_WAVE);
-        if (found) out_q[pos + fg_mbcnt(nb)] = v;
-        if (lane == 0) visited[w] = vis | nb;
-      }
-    }
-    if (lane == 0) next_bits[w] = nb;
-  }
-  insp = fg_wave_sum(insp);
-  if (lane == 0 && inspected && insp) atomicAdd((unsigned long long*)inspected, (unsigned long long)insp);
+constexpr int PL_BT = 512;
+constexpr int PL_WAVES = PL_BT / FG_WAVE;
+constexpr int PL_STAGE = 2 * PL_BT;
+constexpr int PL_GRID = 1021;    // workgroups at most (odd, see below)
+constexpr int PL_LANE = 32;      // rows up to this length are scanned by their lane
+constexpr int PL_GROUP = 16;     // lanes that scan a longer row together ...
+constexpr int PL_GROUP_MAX = 260;  // ... up to this entry; the rest by a wave
+
+__device__ __forceinline__ bool bit_of(const uint32_t* bits, int32_t u) {
+  return (bits[u >> 5] >> (u & 31)) & 1u;
 }
 
-__global__ void zero_i64_kernel(int64_t* p) {
-  if (threadIdx.x == 0) *p = 0;
+// The first entry from `c` on, of `width` lanes times four, whose bit is set:
+// its place from c (-1 = none) in *at and its vertex in *got.  The lanes of
+// a group pass the same c and end; `first` is the group's first lane.  A
+// group without a row passes c >= end.
+__device__ __forceinline__ void probe_row(const int32_t* col, const uint32_t* fbits, int32_t c,
+                                          int32_t end, int first, int width, int32_t* at,
+                                          int32_t* got) {
+  const int lane = fg_lane();
+  int32_t u[4];
+  bool hit[4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int32_t k = c + r * width + (lane - first);
+    u[r] = k < end ? col[k] : -1;
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) hit[r] = u[r] >= 0 && bit_of(fbits, u[r]);
+  const uint64_t group = (width == FG_WAVE ? ~0ull : ((1ull << width) - 1ull)) << first;
+  *at = -1;
+#pragma unroll
+  for (int r = 3; r >= 0; --r) {
+    const uint64_t m = __ballot(hit[r]) & group;
+    const int l = m ? __builtin_ctzll(m) : first;
+    const int32_t x = __shfl(u[r], l, FG_WAVE);
+    if (m) {
+      *at = r * width + (l - first);
+      *got = x;
+    }
+  }
+}
+
+// One early-exit backward step: a lane per unvisited vertex of nonzero
+// degree.  The first four entries come from the head table (one coalesced
+// load instead of a random line per vertex); rows of up to PL_LANE entries
+// go on four at a time in their lane; longer rows are listed and taken by
+// groups of 16 lanes, 64 entries per step and four rows per wave, and what
+// is still open after 256 more by whole waves, 256 entries per step.  The
+// entries of a step are loaded together and counted up to the first hit, so
+// `inspected` is the early-exit count.
+// Bound by the latency of the dependent loads (column, then frontier word):
+// a step takes about 1.5 us whatever its width, so the rows in flight
+// count, and a workgroup takes words from all over the graph (word
+// blockIdx + j gridDim) because long rows lie together.  The largest grid is
+// odd: an R-MAT vertex's degree follows the bits of its id, and with 512
+// workgroups those whose words end in zeros took four times as long.
+// R-MAT of 1 M vertices, frontier of 2 %: 229 us with a lane per row and an
+// atomic per wave for each counter, 210 us with rows past 32 entries given
+// to waves one at a time, 89 us in groups of 16 lanes, 55 us with the words
+// spread and 512 threads (8 words) per workgroup.
+__global__ __launch_bounds__(PL_BT) void pull_step_kernel(
+    int32_t nwords, const int32_t* __restrict__ off, const int32_t* __restrict__ col,
+    const int4* __restrict__ head, const uint64_t* __restrict__ nz,
+    const uint32_t* __restrict__ fbits, uint64_t* __restrict__ visited,
+    uint64_t* __restrict__ next_bits, int32_t d_new, int32_t* __restrict__ depth,
+    int32_t* __restrict__ parent, int32_t* __restrict__ out_q, int32_t* __restrict__ out_len,
+    int64_t* __restrict__ inspected) {
+  __shared__ int32_t s_buf[PL_STAGE];
+  __shared__ int2 s_long[PL_BT];  // vertex, wave of this workgroup that holds its word
+  __shared__ int2 s_hub[PL_BT];
+  __shared__ unsigned long long s_new[PL_WAVES];
+  __shared__ int64_t s_red[PL_WAVES + 1];
+  __shared__ int32_t s_cnt, s_base, s_nlong, s_nhub;
+  BlockStage<PL_BT, PL_STAGE> stage{s_buf, &s_cnt, &s_base};
+  const int lane = fg_lane();
+  const int wid = threadIdx.x / FG_WAVE;
+  if (threadIdx.x == 0) s_cnt = 0;
+  int64_t insp = 0;
+  for (int64_t w0 = blockIdx.x; w0 < nwords; w0 += (int64_t)gridDim.x * PL_WAVES) {
+    const int64_t w = w0 + (int64_t)wid * gridDim.x;
+    const uint64_t vis = w < nwords ? visited[w] : ~0ull;
+    const uint64_t act = w < nwords ? nz[w] & ~vis : 0ull;
+    if (threadIdx.x == 0) s_nlong = s_nhub = 0;
+    __syncthreads();
+    const int32_t v = (int32_t)(w * 64 + lane);
+    int32_t i = 0, e = 0, pu = -1;
+    bool open = (act >> lane) & 1ull;
+    bool found = false;
+    if (open) {
+      i = off[v];
+      e = off[v + 1];
+      const int4 h = head[v];
+      const bool h0 = bit_of(fbits, h.x), h1 = bit_of(fbits, h.y);
+      const bool h2 = bit_of(fbits, h.z), h3 = bit_of(fbits, h.w);
+      // entries past the degree repeat the last one: a hit there is a hit
+      // of the last entry, found first
+      const int32_t d = e - i < 4 ? e - i : 4;
+      found = h0 || h1 || h2 || h3;
+      pu = h0 ? h.x : h1 ? h.y : h2 ? h.z : h.w;
+      insp += h0 ? 1 : h1 ? 2 : h2 ? 3 : d;
+      i += 4;
+      open = !found && i < e;
+    }
+    {
+      const bool listed = open && e - i > PL_LANE - 4;
+      const uint64_t mask = __ballot(listed);
+      if (mask) {
+        int32_t pos = 0;
+        if (lane == 0) pos = atomicAdd(&s_nlong, __popcll(mask));
+        pos = __builtin_amdgcn_readfirstlane(pos);
+        if (listed) s_long[pos + fg_mbcnt(mask)] = make_int2(v, wid);
+        open = open && !listed;
+      }
+    }
+    while (__ballot(open)) {
+      if (open) {
+        const int32_t l = e - 1;
+        const int32_t u0 = col[i], u1 = col[i + 1 < l ? i + 1 : l];
+        const int32_t u2 = col[i + 2 < l ? i + 2 : l], u3 = col[i + 3 < l ? i + 3 : l];
+        const bool h0 = bit_of(fbits, u0), h1 = bit_of(fbits, u1);
+        const bool h2 = bit_of(fbits, u2), h3 = bit_of(fbits, u3);
+        const int32_t d = e - i < 4 ? e - i : 4;
+        found = h0 || h1 || h2 || h3;
+        pu = h0 ? u0 : h1 ? u1 : h2 ? u2 : u3;
+        insp += h0 ? 1 : h1 ? 2 : h2 ? 3 : d;
+        i += 4;
+        open = !found && i < e;
+      }
+    }
+    {
+      const uint64_t nb = __ballot(found);
+      if (lane == 0) s_new[wid] = nb;
+    }
+    if (found) {
+      depth[v] = d_new;
+      if (parent) parent[v] = pu;
+    }
+    stage.push(found, v);
+    __syncthreads();
+    const int32_t nlong = s_nlong;
+    for (int32_t j0 = wid * (FG_WAVE / PL_GROUP); j0 < nlong; j0 += PL_BT / PL_GROUP) {
+      const int first = lane & ~(PL_GROUP - 1);
+      const int32_t j = j0 + lane / PL_GROUP;
+      int2 x = make_int2(0, 0);
+      int32_t c = 0, end = 0;
+      if (j < nlong) {
+        x = s_long[j];
+        c = off[x.x];
+        end = off[x.x + 1];
+      }
+      const int32_t stop = end - c > PL_GROUP_MAX ? c + PL_GROUP_MAX : end;
+      c += 4;
+      bool hit = false;  // the group's row is done; it waits for the wave's others
+      while (__ballot(c < stop)) {
+        int32_t at, got = -1;
+        probe_row(col, fbits, c, stop, first, PL_GROUP, &at, &got);
+        if (c < stop) {
+          hit = at >= 0;
+          if (lane == first) {
+            const int32_t took = stop - c < 4 * PL_GROUP ? stop - c : 4 * PL_GROUP;
+            insp += hit ? at + 1 : took;
+            if (hit) {
+              depth[x.x] = d_new;
+              if (parent) parent[x.x] = got;
+              atomicOr(&s_new[x.y], 1ull << (x.x & 63));
+            }
+          }
+          c = hit ? stop : c + 4 * PL_GROUP;
+        }
+      }
+      stage.push(hit && lane == first, x.x);
+      const bool more = lane == first && !hit && end > stop;
+      const uint64_t mask = __ballot(more);
+      if (mask) {
+        int32_t pos = 0;
+        if (lane == 0) pos = atomicAdd(&s_nhub, __popcll(mask));
+        pos = __builtin_amdgcn_readfirstlane(pos);
+        if (more) s_hub[pos + fg_mbcnt(mask)] = x;
+      }
+    }
+    __syncthreads();
+    const int32_t nhub = s_nhub;
+    for (int32_t j = wid; j < nhub; j += PL_WAVES) {
+      const int2 x = s_hub[j];
+      const int32_t end = off[x.x + 1];
+      for (int32_t c = off[x.x] + PL_GROUP_MAX; c < end; c += 4 * FG_WAVE) {
+        int32_t at, got = -1;
+        probe_row(col, fbits, c, end, 0, FG_WAVE, &at, &got);
+        if (at >= 0) {
+          if (lane == 0) {
+            insp += at + 1;
+            depth[x.x] = d_new;
+            if (parent) parent[x.x] = got;
+            atomicOr(&s_new[x.y], 1ull << (x.x & 63));
+          }
+          stage.push(lane == 0, x.x);
+          break;
+        }
+        if (lane == 0) insp += end - c < 4 * FG_WAVE ? end - c : 4 * FG_WAVE;
+      }
+    }
+    __syncthreads();
+    if (lane == 0 && w < nwords) {
+      const uint64_t nb = s_new[wid];
+      next_bits[w] = nb;
+      if (nb) visited[w] = vis | nb;
+    }
+    stage.flush_above(PL_STAGE - PL_BT, out_q, out_len);
+  }
+  stage.flush_above(0, out_q, out_len);
+  insp = fg_block_sum<PL_BT>(insp, s_red);
+  if (threadIdx.x == 0 && inspected && insp)
+    atomicAdd((unsigned long long*)inspected, (unsigned long long)insp);
+}
+
+// Clears the pull step's two counters.
+__global__ void pull_clear_kernel(int32_t* out_len, int64_t* inspected) {
+  if (threadIdx.x == 0) {
+    *out_len = 0;
+    if (inspected) *inspected = 0;
+  }
 }
 
 // ---------------------------------------------------------- conversions
@@ -265,19 +579,32 @@ __global__ void queue_to_bitmap_kernel(const int32_t* __restrict__ q, int64_t le
   }
 }
 
+// The set bits of QB words per workgroup, at their place in the queue (the
+// popcounts scanned here, the tiles before from the tile sums).  A wave
+// writes its words one after another, a lane per bit, so the stores of a
+// word are contiguous; empty words are skipped.
+template <bool SELF>
 __global__ void bitmap_to_queue_kernel(int64_t nwords, const uint64_t* __restrict__ bits,
-                                       const int64_t* __restrict__ scan,
+                                       const int64_t* __restrict__ sums,
                                        const int64_t* __restrict__ total,
                                        int32_t* __restrict__ out_q, int32_t* __restrict__ out_len) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i == 0) *out_len = (int32_t)*total;
-  if (i >= nwords) return;
-  uint64_t w = bits[i];
-  int64_t pos = scan[i];
-  while (w) {
-    const int b = __builtin_ctzll(w);
-    w &= w - 1;
-    out_q[pos++] = (int32_t)(i * 64 + b);
+  __shared__ int64_t red[QB / FG_WAVE + 1];
+  const int lane = fg_lane();
+  const int64_t i = (int64_t)blockIdx.x * QB + threadIdx.x;
+  const uint64_t w = i < nwords ? bits[i] : 0ull;
+  const int64_t base = tile_base<SELF, QB>(sums, red);
+  int64_t tot = 0;
+  const int64_t ex = fg_block_excl_scan<QB>((int64_t)__popcll(w), red, &tot);
+  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0)
+    *out_len = (int32_t)(SELF ? base + tot : *total);
+  const int32_t pos = (int32_t)(base + ex);
+  uint64_t some = __ballot(w != 0);
+  while (some) {
+    const int l = __builtin_ctzll(some);
+    some &= some - 1;
+    const uint64_t x = fg_readlane64(w, l);
+    const int32_t p = __builtin_amdgcn_readlane(pos, l);
+    if ((x >> lane) & 1ull) out_q[p + fg_mbcnt(x)] = (int32_t)((i - lane + l) * 64 + lane);
   }
 }
 
@@ -398,8 +725,8 @@ extern "C" fg_status fg_filter(const fg_graph* g, const int32_t* dst, const int3
   hipStream_t s = (hipStream_t)stream;
   fill_i32_kernel<<<1, 64, 0, s>>>(out_len, 1, 0);
   if (len > 0)
-    filter_kernel<<<grid_for(len, 256, 8192), 256, 0, s>>>(dst, src, len_dev, len, len, visited,
-                                                           iter + 1, depth, parent, out_q, out_len);
+    filter_kernel<<<grid_for(len, FT_TILE, 512), FT_BT, 0, s>>>(
+        dst, src, len_dev, len, len, visited, iter + 1, depth, parent, out_q, out_len);
   FG_HIP_TRY(hipGetLastError());
   return FG_OK;
 }
@@ -414,11 +741,10 @@ extern "C" fg_status fg_pull_step(const fg_graph* g, const uint64_t* frontier_bi
     return fg_set_error(FG_EUNSUPPORTED, "fg_pull_step: needs an undirected graph (FG_SYMMETRIC)");
   if (iter < 0) return fg_set_error(FG_EINVAL, "fg_pull_step: negative iteration");
   hipStream_t s = (hipStream_t)stream;
-  fill_i32_kernel<<<1, 64, 0, s>>>(out_len, 1, 0);
-  if (inspected) zero_i64_kernel<<<1, 64, 0, s>>>(inspected);
-  pull_step_kernel<<<grid_for(g->nwords, 4, 8192), 256, 0, s>>>(
-      g->nwords, g->off, g->col, g->nzmask, frontier_bits, visited, next_bits, iter + 1, depth,
-      parent, out_q, out_len, inspected);
+  pull_clear_kernel<<<1, 64, 0, s>>>(out_len, inspected);
+  pull_step_kernel<<<grid_for(g->nwords, PL_WAVES, PL_GRID), PL_BT, 0, s>>>(
+      g->nwords, g->off, g->col, g->head, g->nzmask, (const uint32_t*)frontier_bits, visited,
+      next_bits, iter + 1, depth, parent, out_q, out_len, inspected);
   FG_HIP_TRY(hipGetLastError());
   return FG_OK;
 }
@@ -446,10 +772,16 @@ extern "C" fg_status fg_bitmap_to_queue(const fg_graph* g, const uint64_t* bits,
     return fg_set_error(FG_ENOMEM, "fg_bitmap_to_queue: workspace of %zu bytes < required %zu",
                         ws_bytes, L.bytes);
   hipStream_t s = (hipStream_t)stream;
-  ScanWs sw{L.sums, L.scan, L.total};
-  run_scan(g->nwords, PopOf{bits}, sw, s);
-  bitmap_to_queue_kernel<<<grid_for(g->nwords, 256, 1 << 30), 256, 0, s>>>(
-      g->nwords, bits, L.scan, L.total, out_q, out_len);
+  const unsigned tiles = (unsigned)(((int64_t)g->nwords + QB - 1) / QB);
+  tile_sum_kernel<QB><<<tiles, QB, 0, s>>>((int64_t)g->nwords, PopOf{bits}, L.sums);
+  if (tiles <= SELF_TILES) {
+    bitmap_to_queue_kernel<true><<<tiles, QB, 0, s>>>(g->nwords, bits, L.sums, L.total, out_q,
+                                                      out_len);
+  } else {
+    scan_sums_kernel<<<1, TB, 0, s>>>(tiles, L.sums, L.total);
+    bitmap_to_queue_kernel<false><<<tiles, QB, 0, s>>>(g->nwords, bits, L.sums, L.total, out_q,
+                                                       out_len);
+  }
   FG_HIP_TRY(hipGetLastError());
   return FG_OK;
 }
@@ -475,7 +807,7 @@ fg_status fg_bfs_unfused(const fg_graph* g, int32_t src, void* ws, size_t ws_byt
     fg_status st = advance_impl(g, L.q[sel], len, nullptr, L.edst, L.esrc, g->m, L.misc, L, s);
     if (st != FG_OK) return st;
     fill_i32_kernel<<<1, 64, 0, s>>>(L.len32, 1, 0);
-    filter_kernel<<<grid_for(g->m > 0 ? g->m : 1, 256, 8192), 256, 0, s>>>(
+    filter_kernel<<<grid_for(g->m > 0 ? g->m : 1, FT_TILE, 512), FT_BT, 0, s>>>(
         L.edst, L.esrc, L.misc, 0, g->m, L.visited, k + 1, depth, parent, L.q[sel ^ 1], L.len32);
     int64_t h[1];
     int32_t nl = 0;

@@ -181,3 +181,123 @@ def test_graph_validation_errors(fg):
     with pytest.raises(fg.FGError) as e:
         fg.bfs_into(g, 0, depth, None, fg.bfs_opts(mode=1), ws=ws)
     assert e.value.status == fg.FG_ENOMEM
+
+
+@pytest.mark.parametrize("edges", [1, 8191, 8192, 8193, 12_800_000])
+def test_filter_tile_edges(fg, edges):
+    """Lengths at the filter's tile borders and past three tiles per workgroup
+    with every edge a winner (staged entries written out inside the loop)."""
+    n = max(64, edges)
+    g = fg.Graph(torch.zeros(n + 1, dtype=torch.int32, device="cuda"),
+                 torch.zeros(0, dtype=torch.int32, device="cuda"), validate=False)
+    announce(f"filter tile edges={edges}")
+    gen = torch.Generator(device="cuda").manual_seed(edges)
+    dst = torch.randperm(n, device="cuda", generator=gen)[:edges].to(torch.int32)
+    dst[edges // 2] = dst[0]  # one duplicate
+    src = torch.arange(edges, device="cuda", dtype=torch.int32)
+    visited = torch.zeros((n + 63) // 64 * 2, dtype=torch.int32, device="cuda")
+    depth = torch.full((n,), -1, dtype=torch.int32, device="cuda")
+    parent = torch.full((n,), -1, dtype=torch.int32, device="cuda")
+    out_q = torch.full((n,), -1, dtype=torch.int32, device="cuda")
+    out_len = torch.zeros(1, dtype=torch.int32, device="cuda")
+    fg.filter_(g, dst, src, edges, visited, 2, depth, parent, out_q, out_len)
+    k = int(to_np(out_len)[0])
+    want = torch.unique(dst)
+    assert torch.equal(torch.sort(out_q[:k]).values, want) and bool((out_q[k:] == -1).all())
+    assert torch.equal(torch.nonzero(depth == 3).flatten().int(), want)
+    assert torch.equal(dst[parent[want.long()].long()], want)
+    bits = (visited[torch.arange(n, device="cuda") >> 5] >> (torch.arange(n, device="cuda") & 31)) & 1
+    assert torch.equal(torch.nonzero(bits).flatten().int(), want)
+
+
+@pytest.mark.parametrize("hit", ["none", "first", "last", "random"])
+def test_pull_step_row_lengths(fg, hit):
+    """Rows around the lengths where the pull step changes how it scans (4, 32,
+    256 past the first four), their only frontier neighbour nowhere, first,
+    last or anywhere: parent, next bits and the early-exit count."""
+    rng = np.random.default_rng(7)
+    degs = [1, 2, 3, 4, 5, 7, 8, 9, 31, 32, 33, 35, 36, 37, 63, 64, 65, 67, 68, 69, 259, 260, 261,
+            515, 516, 517, 2000] * 5
+    H, P = len(degs), 2500
+    pairs = []
+    for v, d in enumerate(degs):
+        pairs += [(v, H + int(x)) for x in rng.choice(P, size=d, replace=False)]
+    off, col = synth.from_edge_pairs(H + P, pairs)
+    n = len(off) - 1
+    front = np.zeros(n, bool)
+    if hit == "random":
+        front[H + rng.choice(P, size=25, replace=False)] = True
+    seen = np.zeros(n, bool)
+    seen[H:] = True  # only the long rows' own vertices are candidates
+    exp_p = np.full(n, -1, np.int64)
+    insp = 0
+    if hit in ("first", "last"):
+        for v in range(H):
+            front[col[off[v] if hit == "first" else off[v + 1] - 1]] = True
+    for v in range(H):
+        at = np.flatnonzero(front[col[off[v]:off[v + 1]]])
+        if len(at):
+            exp_p[v] = col[off[v] + at[0]]
+            insp += int(at[0]) + 1
+        else:
+            insp += int(off[v + 1] - off[v])
+    nw = (n + 63) // 64
+    def words(mask):
+        m = np.zeros(nw * 64, np.uint64)
+        m[:n] = mask
+        return torch.from_numpy((m.reshape(nw, 64) << np.arange(64, dtype=np.uint64)).sum(1)
+                                .astype(np.uint64).view(np.int64)).cuda()
+    g = fg.Graph(off, col)
+    visited, fbits = words(seen), words(front)
+    nxt = torch.full((nw,), -1, dtype=torch.int64, device="cuda")
+    depth = torch.full((n,), -1, dtype=torch.int32, device="cuda")
+    parent = torch.full((n,), -1, dtype=torch.int32, device="cuda")
+    out_q = torch.empty(n, dtype=torch.int32, device="cuda")
+    out_len = torch.zeros(1, dtype=torch.int32, device="cuda")
+    cnt = torch.full((1,), 99, dtype=torch.int64, device="cuda")
+    announce(f"pull step row lengths hit={hit}")
+    fg.pull_step(g, fbits, visited, nxt, 4, depth, parent, out_q, out_len, cnt)
+    new = exp_p >= 0
+    assert np.array_equal(to_np(parent), exp_p)
+    assert np.array_equal(to_np(depth), np.where(new, 5, -1))
+    assert int(to_np(cnt)[0]) == insp
+    assert sorted(to_np(out_q)[:int(to_np(out_len)[0])].tolist()) == np.flatnonzero(new).tolist()
+    assert torch.equal(nxt, words(new)) and torch.equal(visited, words(seen | new))
+
+
+@pytest.mark.parametrize("n", [16384 * 2048, 16384 * 2048 + 1, 16384 * 2048 + 70_000])
+def test_bitmap_to_queue_many_tiles(fg, n):
+    """Both sides of the size at which the tile sums get a kernel of their own."""
+    g = fg.Graph(torch.zeros(n + 1, dtype=torch.int32, device="cuda"),
+                 torch.zeros(0, dtype=torch.int32, device="cuda"), validate=False)
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    q = torch.unique(torch.randint(n, (200_000,), device="cuda", generator=gen))
+    q = torch.unique(torch.cat([q, torch.tensor([0, 63, 64, n - 1], device="cuda")]))
+    bits = torch.zeros((n + 63) // 64, dtype=torch.int64, device="cuda")
+    bits.index_put_((q >> 6,), torch.ones_like(q) << (q & 63), accumulate=True)
+    out = torch.empty(n, dtype=torch.int32, device="cuda")
+    out_len = torch.zeros(1, dtype=torch.int32, device="cuda")
+    announce(f"bitmap to queue n={n}")
+    fg.bitmap_to_queue(g, bits, out, out_len, ws=g.workspace(fg.FG_PRIM_BFS_UNFUSED))
+    assert int(to_np(out_len)[0]) == q.numel()
+    assert torch.equal(out[:q.numel()], q.to(torch.int32))
+
+
+@pytest.mark.parametrize("length", [1024 * 2048, 1024 * 2048 + 1])
+def test_advance_many_tiles(fg, length):
+    """The same border for the advance's scan over the frontier's degrees."""
+    off, col = synth.grid_csr(1500, 1500)
+    g = fg.Graph(off, col, validate=False)
+    gen = torch.Generator(device="cuda").manual_seed(length)
+    q = torch.randperm(g.n, device="cuda", generator=gen)[:length].to(torch.int32)
+    announce(f"advance many tiles length={length}")
+    dst, src, tot = fg.advance(g, q)
+    o = torch.from_numpy(off).cuda().long()
+    deg = (o[1:] - o[:-1])[q.long()]
+    T = int(deg.sum())
+    assert int(to_np(tot)[0]) == T
+    wsrc = torch.repeat_interleave(q, deg)
+    first = torch.repeat_interleave(torch.cumsum(deg, 0) - deg, deg)
+    at = o[wsrc.long()] + torch.arange(T, device="cuda") - first
+    assert torch.equal(src[:T], wsrc)
+    assert torch.equal(dst[:T], torch.from_numpy(col).cuda()[at])
