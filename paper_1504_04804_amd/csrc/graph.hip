@@ -104,14 +104,25 @@ __global__ void degree_summary_kernel(int32_t n, int32_t nwords,
     mx = d > mx ? d : mx;
     cnt += d > 0;
   }
+  // one pair of atomics per workgroup: the two counters are single addresses,
+  // and with a pair per wave the kernel took 380 us at any size above 1 M
+  // vertices, all of it in them
+  __shared__ int32_t s_mx, s_cnt;
+  if (threadIdx.x == 0) s_mx = s_cnt = 0;
+  __syncthreads();
   for (int s = 32; s > 0; s >>= 1) {
     int32_t o = __shfl_xor(mx, s, 64);
     mx = o > mx ? o : mx;
     cnt += __shfl_xor(cnt, s, 64);
   }
   if (lane == 0) {
-    atomicMax(maxdeg, mx);
-    atomicAdd(nzcount, cnt);
+    atomicMax(&s_mx, mx);
+    atomicAdd(&s_cnt, cnt);
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    atomicMax(maxdeg, s_mx);
+    atomicAdd(nzcount, s_cnt);
   }
 }
 
@@ -133,9 +144,21 @@ __global__ void weight_summary_kernel(int64_t m, const uint32_t* __restrict__ w,
     const uint32_t o = __shfl_xor(x, d, 64);
     x = o > x ? o : x;
   }
+  __shared__ unsigned long long s_sum;
+  __shared__ uint32_t s_mx;
+  if (threadIdx.x == 0) {
+    s_sum = 0;
+    s_mx = 0;
+  }
+  __syncthreads();
   if (fg_lane() == 0) {
-    atomicAdd(sum, s);
-    atomicMax(mx, x);
+    atomicAdd(&s_sum, s);
+    atomicMax(&s_mx, x);
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {  // one pair of atomics per workgroup, as above
+    atomicAdd(sum, s_sum);
+    atomicMax(mx, s_mx);
   }
 }
 
@@ -265,13 +288,13 @@ extern "C" fg_status fg_graph_create_csr(int32_t n, int64_t m, const int32_t* ro
   }
 
   int blocks = (int)((g->nwords + 3) / 4);
-  if (blocks > 4096) blocks = 4096;
+  if (blocks > 2048) blocks = 2048;
   if (blocks < 1) blocks = 1;
   degree_summary_kernel<<<blocks, 256, 0, s>>>(n, g->nwords, g->off, g->col, g->nzmask, g->head,
                                                dsum, dsum + 1);
   if (g->w && m > 0) {
     int wb = (int)((m + 1023) / 1024);
-    if (wb > 4096) wb = 4096;
+    if (wb > 2048) wb = 2048;
     weight_summary_kernel<<<wb, 256, 0, s>>>(m, g->w, (unsigned long long*)(dsum + 4),
                                              (uint32_t*)(dsum + 6));
   }
