@@ -80,6 +80,24 @@ def test_degenerate(fg, orc):
     check(fg, orc, off, col, "parity")
 
 
+@pytest.mark.parametrize("deg", [3, 64, 1023, 1024, 1025, 1026, 9000])
+def test_components_joined_by_long_rows_alone(fg, orc, deg):
+    """Hubs outside the giant component whose only edge into it is past the
+    first two entries of both its rows, so the hub's own row has to hook it:
+    rows around the length at which they get a pass of their own."""
+    hubs, G = 5, 60_000
+    leaves = hubs * (deg - 1)
+    chain = np.arange(leaves, leaves + G - 1, dtype=np.int32)
+    eu, ev = [chain], [chain + 1]
+    for h in range(hubs):
+        hub = leaves + G + h
+        mine = np.arange(h * (deg - 1), (h + 1) * (deg - 1), dtype=np.int32)
+        eu += [np.full(deg, hub, np.int32)]
+        ev += [np.append(mine, np.int32(leaves + 100 + 7 * h))]
+    off, col = orc.csr_from_edges(leaves + G + hubs, np.concatenate(eu), np.concatenate(ev))
+    check(fg, orc, off, col, f"joined by rows of {deg}")
+
+
 def test_directed_graph_rejected(fg):
     off = np.array([0, 1, 1], np.int32)
     col = np.array([1], np.int32)
