@@ -760,7 +760,8 @@ fg_status fg_cc(const fg_graph* g, int32_t* label, int64_t* components, void* ws
  * vertex changed by at most tol times its previous rank (tol > 0), or
  * after max_iter iterations (tol = 0 runs exactly max_iter).  rank: device
  * double[n], the output.  ws: fg_workspace_bytes(g, FG_PRIM_PR, 0) bytes
- * (any contents).  stats (device, may be NULL): iterations run, and per
+ * (any contents; about 42n + 6.2m, for renumbered copies of the columns.
+ * About 20n bytes, the minimum, are enough for a slower form).  stats (device, may be NULL): iterations run, and per
  * iteration frontier[i] = vertices whose change exceeded the threshold,
  * inspected[i] = m.  Nothing is read back: every one of the max_iter
  * iterations is enqueued and those after convergence return at once.

@@ -124,3 +124,53 @@ def test_argument_errors(fg):
 def test_workload_rmat22(fg, orc):
     off, col, _ = workloads.graph("rmat22")
     check(fg, orc, off, col, "rmat22", max_iter=20)
+
+
+@pytest.mark.parametrize("pad", range(8))
+def test_planned_form_row_classes(fg, orc, pad):
+    """Rows at the lengths where the planned form changes how it sums them (a
+    lane, 8, 16, 64 lanes, segments of 2048 entries), numbers at every place
+    of the last group of eight, no vertex without edges; the ranks of two
+    calls are the same bits."""
+    degs = [1, 2, 7, 8, 9, 62, 63, 64, 65, 255, 256, 257, 1023, 1024, 1025, 2047, 2048, 2049,
+            4095, 4096, 4097, 6200]
+    H, P = len(degs), 7000 + pad
+    rng = np.random.default_rng(pad)
+    eu = np.concatenate([np.full(d, h) for h, d in enumerate(degs)] + [np.arange(P)])
+    ev = np.concatenate([rng.choice(P, size=d, replace=False) + H for d in degs]
+                        + [(np.arange(P) + 1) % P])
+    eu[-P:] += H
+    ev[-P:] += H
+    off, col = orc.csr_from_edges(H + P, eu.astype(np.int32), ev.astype(np.int32))
+    assert (np.diff(off) > 0).all()
+    a, _ = check(fg, orc, off, col, f"row classes pad={pad}", max_iter=2 + pad)
+    b, _ = check(fg, orc, off, col, f"row classes pad={pad} again", max_iter=2 + pad)
+    assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("n", [2, 64, 4095, 4096, 4097, 8193])
+def test_planned_form_numbering_tiles(fg, orc, n):
+    # sparse random graphs (many empty rows) at the tile sizes of the numbering
+    rng = np.random.default_rng(n)
+    eu = rng.integers(0, n, n).astype(np.int32)
+    ev = rng.integers(0, n, n).astype(np.int32)
+    off, col = orc.csr_from_edges(n, eu, ev)
+    check(fg, orc, off, col, f"tiles n={n}", max_iter=6)
+    check(fg, orc, off, col, f"tiles n={n} tol", tol=1e-3, max_iter=50)
+
+
+def test_workspace_without_room_for_the_plan(fg, orc):
+    """A workspace of the direct form's size is still taken."""
+    off, col = synth.rmat_csr(13)
+    n = len(off) - 1
+    up = lambda x: (x + 255) // 256 * 256
+    ws = torch.zeros(2 * up(8 * n) + up(4 * n) + 256, dtype=torch.uint8, device="cuda")
+    g = fg.Graph(off, col)
+    assert ws.numel() < g.workspace_bytes(fg.FG_PRIM_PR)
+    rank = torch.empty(n, dtype=torch.float64, device="cuda")
+    announce("pagerank small workspace")
+    fg.pagerank_into(g, rank, 0.85, 0.0, 10, ws=ws)
+    want, it = orc.pagerank(off, col, 0.85, 0.0, 10)
+    got = to_np(rank)
+    assert (np.abs(got - want) / want).max() <= bound(off, it)
+    g.close()
