@@ -469,14 +469,15 @@ typedef struct {
                             fg_sssp default on graphs of mean degree <= 8,
                             twice it on others; UINT32_MAX = no threshold) */
   int32_t big_degree;    /* vertices of at least this degree are relaxed in
-                            64-edge chunks by many waves (0 = 256)           */
+                            64-edge chunks by many waves (0 = 64)            */
   int32_t blocks_per_cu; /* persistent launch width (0 = default)            */
   int32_t grid_blocks;   /* workgroups of the persistent launch (0 = every CU
                             x blocks_per_cu)                                 */
   int32_t dense_lanes;   /* a vertex with at least this many frontier lanes is
                             relaxed by one wave across its lanes; fewer lanes
                             are relaxed one (edge, lane) pair per thread
-                            (0 = 16)                                         */
+                            (0 = 16 on graphs of mean degree <= 8, 8 on
+                            others)                                          */
   int32_t split_lanes;   /* lanes whose near frontier is empty wait until this
                             many can split in one scan of the far list (0 = 8) */
   int32_t split_wait;    /* ... or until they have waited this many
@@ -760,7 +761,7 @@ fg_status fg_cc(const fg_graph* g, int32_t* label, int64_t* components, void* ws
  * vertex changed by at most tol times its previous rank (tol > 0), or
  * after max_iter iterations (tol = 0 runs exactly max_iter).  rank: device
  * double[n], the output.  ws: fg_workspace_bytes(g, FG_PRIM_PR, 0) bytes
- * (any contents; about 42n + 6.2m, for renumbered copies of the columns.
+ * (any contents; about 37n + 6.2m, for renumbered copies of the columns.
  * About 20n bytes, the minimum, are enough for a slower form).  stats (device, may be NULL): iterations run, and per
  * iteration frontier[i] = vertices whose change exceeded the threshold,
  * inspected[i] = m.  Nothing is read back: every one of the max_iter

@@ -136,6 +136,7 @@ struct MpParams {
   int32_t pend_lane[MAXL];
   int32_t pend_src[MAXL];
   uint32_t delta;
+  uint32_t w_max;       // largest weight
   int32_t big_deg;
   int32_t dense;        // lanes from which a vertex is relaxed lane-parallel
   int32_t split_lanes;  // idle lanes that trigger a split of the far list
@@ -154,14 +155,21 @@ struct Lds {
   ull w_m[PWAVES][FG_WAVE];
   ull redu[PWAVES];
   int64_t red64[PWAVES];
+  FlushLds<PWAVES> fl;
   uint32_t T[MAXL];
   uint32_t Tnext[MAXL];
   uint32_t minl[MAXL];
   int32_t flag;
   int32_t ackbad;  // workgroup 0: a hand-off acknowledgement wait failed
-  // team mode: this member's share of the frontier (vertex, first edge, end
-  // edge) for the current and the next level, counters over three slots,
-  // block scan-gather arrays, exchange results
+  int32_t red32[PWAVES + 1];
+};
+
+// The team build's LDS.  The build without it is left with 52 KB, so two
+// workgroups fit a CU.
+struct TeamLds : Lds {
+  // this member's share of the frontier (vertex, first edge, end edge) for
+  // the current and the next level, counters over three slots, block
+  // scan-gather arrays, exchange results
   int32_t lq_v[2][QCAP];
   int32_t lq_b[2][QCAP];
   int32_t lq_e[2][QCAP];
@@ -175,7 +183,15 @@ struct Lds {
   ull b_m[PB];
   ull tnear;
   int64_t tfar;
-  int32_t red32[PWAVES + 1];
+};
+
+template <bool TEAM>
+struct KernelLds {
+  typedef Lds type;
+};
+template <>
+struct KernelLds<true> {
+  typedef TeamLds type;
 };
 
 __device__ __forceinline__ uint32_t sat_add(uint32_t a, uint32_t b) {
@@ -238,58 +254,109 @@ struct Out {
   ull fbase;
 };
 
+// Word updates of the edges relaxed last, whose results are looked at one
+// group later (lane r: edge r of the group).
+struct Pending {
+  bool any;      // wave-uniform
+  ull mn, mf;    // lanes given to the near / far word of v
+  ull oldn, oldf;
+  int32_t v;
+};
+
+// Lists the vertices whose near / far word was 0 before the pending updates.
+__device__ __forceinline__ void finish_pending(Pending& H, const Out& O,
+                                               WaveStage<int32_t, STAGE>& st, PileStage& fst) {
+  if (!H.any) return;
+  H.any = false;
+  st.push(H.mn != 0ull && H.oldn == 0ull, H.v, O.qcnt, 0ull, O.Qn);
+  fst.push(H.mf != 0ull && H.oldf == 0ull, H.v, O.fpos, O.fcnt, O.fbase, O.pile);
+}
+
 // Relax the edges [e0, e1) of u for the lanes in m (one wave, lane = query
-// lane).  Lanes of m get dist[u][lane] + w; four edges per step keep four
-// distance loads in flight.
+// lane).  64 edges' columns and weights come with one load each; their
+// distance rows EPG at a time, the next group on its way while the current
+// one's atomics are, and a group's word updates are finished under the next
+// group's atomics.
+//
+// Bound by instruction issue, so an edge is kept to an add, three compares
+// and scalar work: lanes outside m carry an infinite distance through a
+// saturating add instead of a mask, the places behind a row's end repeat its
+// last edge (relaxing it twice changes nothing), the row addresses are
+// scalar, and overflow is looked for only if the largest weight could cause
+// it.  The 42 M edge visits of 64 queries on R-MAT of 300 k vertices:
+// 12.1 ms with four edges per step, 64-bit sums and masks per edge.
+//
+// The rows are read at agent scope: a copy in this CU's L1 would miss what
+// others have lowered since the last barrier, and each late attempt is one
+// more atomic on a hub's row (57 ns each, one after another).
+constexpr int EPG = 8;
 __device__ void relax_edges(const MpParams& P, const Lds& L, int32_t u, int32_t e0, int32_t e1,
                             ull m, const Out& O, WaveStage<int32_t, STAGE>& st, PileStage& fst,
-                            ull& nearb, bool& ovf) {
+                            Pending& H, ull& nearb, bool& ovf) {
   const int lane = fg_lane();
-  const bool act = (m >> lane) & 1ull;
-  const uint32_t du = P.dist[(int64_t)u * MAXL + lane];
+  const uint32_t du = (m >> lane) & 1ull ? P.dist[(int64_t)u * MAXL + lane] : DIST_INF;
   const uint32_t Tl = L.T[lane];
-  for (int32_t j = e0; j < e1; j += 4) {
-    int32_t v[4];
-    uint32_t wt[4];
+  const bool may_ovf = __ballot(du != DIST_INF && du >= DIST_INF - P.w_max) != 0ull;
+  for (int32_t c = e0; c < e1; c += FG_WAVE) {
+    const int32_t k = e1 - c < FG_WAVE ? e1 - c : FG_WAVE;
+    const int32_t vl = P.col[c + (lane < k ? lane : k - 1)];
+    const uint32_t wl = P.w[c + (lane < k ? lane : k - 1)];
+    uint32_t nx[EPG];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int32_t jj = j + r < e1 ? j + r : e1 - 1;
-      v[r] = P.col[jj];
-      wt[r] = P.w[jj];
-    }
-    uint32_t cur[4];
+    for (int r = 0; r < EPG; ++r)
+      nx[r] = fg_atomic_load_u32(
+          P.dist + (int64_t)__builtin_amdgcn_readlane(vl, r) * MAXL + lane);
+    for (int32_t g = 0; g < k; g += EPG) {
+      uint32_t cur[EPG], nd[EPG], old[EPG];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) cur[r] = P.dist[(int64_t)v[r] * MAXL + lane];
-    int code[4];
+      for (int r = 0; r < EPG; ++r) cur[r] = nx[r];
+      if (g + EPG < k) {
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      code[r] = 0;
-      const ull nd = (ull)du + (ull)wt[r];
-      if (act && j + r < e1) {
-        if (nd >= (ull)DIST_INF) {
-          ovf = true;  // a distance would not fit the uint32 output
-        } else if ((uint32_t)nd < cur[r]) {
-          const uint32_t old = atomicMin(&P.dist[(int64_t)v[r] * MAXL + lane], (uint32_t)nd);
-          if ((uint32_t)nd < old) code[r] = (uint32_t)nd < Tl ? 1 : 2;
-        }
+        for (int r = 0; r < EPG; ++r)
+          nx[r] = fg_atomic_load_u32(
+              P.dist + (int64_t)__builtin_amdgcn_readlane(vl, g + EPG + r) * MAXL + lane);
       }
-    }
-    ull mn[4], mf[4];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      mn[r] = __ballot(code[r] == 1);
-      mf[r] = __ballot(code[r] == 2);
+      for (int r = 0; r < EPG; ++r)
+        nd[r] = __builtin_elementwise_add_sat(
+            du, (uint32_t)__builtin_amdgcn_readlane((int)wl, g + r));
+      if (may_ovf) {
+#pragma unroll
+        for (int r = 0; r < EPG; ++r)
+          if (du != DIST_INF && nd[r] == DIST_INF) ovf = true;  // does not fit the output
+      }
+      // old is only set and read where the row can improve: nothing to wait
+      // for in the branches
+#pragma unroll
+      for (int r = 0; r < EPG; ++r)
+        if (nd[r] < cur[r])
+          old[r] = atomicMin(P.dist + (int64_t)__builtin_amdgcn_readlane(vl, g + r) * MAXL + lane,
+                             nd[r]);
+      finish_pending(H, O, st, fst);
+      ull mn[EPG], mf[EPG], all = 0ull;
+#pragma unroll
+      for (int r = 0; r < EPG; ++r) {
+        const ull won = __ballot(nd[r] < cur[r] && nd[r] < old[r]);
+        const ull below = __ballot(nd[r] < Tl);
+        mn[r] = won & below;
+        mf[r] = won & ~below;
+        nearb |= mn[r];
+        all |= won;
+      }
+      if (!all) continue;
+      // lane r publishes edge r's lanes
+      H.any = true;
+      H.mn = H.mf = 0ull;
+#pragma unroll
+      for (int r = 0; r < EPG; ++r)
+        if (lane == r) {
+          H.mn = mn[r];
+          H.mf = mf[r];
+        }
+      H.v = __shfl(vl, g + lane, FG_WAVE);
+      if (H.mn) H.oldn = atomicOr(&O.Fn[H.v], H.mn);
+      if (H.mf) H.oldf = atomicOr(&P.Ff[H.v], H.mf);
     }
-    nearb |= mn[0] | mn[1] | mn[2] | mn[3];
-    // lane r publishes edge r's lanes
-    const ull myn = lane == 0 ? mn[0] : lane == 1 ? mn[1] : lane == 2 ? mn[2] : lane == 3 ? mn[3] : 0ull;
-    const ull myf = lane == 0 ? mf[0] : lane == 1 ? mf[1] : lane == 2 ? mf[2] : lane == 3 ? mf[3] : 0ull;
-    const int32_t myv = lane == 0 ? v[0] : lane == 1 ? v[1] : lane == 2 ? v[2] : v[3];
-    bool firstn = false, firstf = false;
-    if (myn) firstn = atomicOr(&O.Fn[myv], myn) == 0ull;
-    if (myf) firstf = atomicOr(&P.Ff[myv], myf) == 0ull;
-    st.push(firstn, myv, O.qcnt, 0ull, O.Qn);
-    fst.push(firstf, myv, O.fpos, O.fcnt, O.fbase, O.pile);
   }
 }
 
@@ -305,7 +372,7 @@ __device__ __forceinline__ void relax_one(const MpParams& P, const Lds& L, int32
     return;
   }
   uint32_t* dp = &P.dist[(int64_t)v * MAXL + l];
-  if ((uint32_t)nd >= *dp) return;
+  if ((uint32_t)nd >= fg_atomic_load_u32(dp)) return;
   const uint32_t old = atomicMin(dp, (uint32_t)nd);
   if ((uint32_t)nd >= old) return;
   const ull bit = 1ull << l;
@@ -378,7 +445,7 @@ __device__ __forceinline__ ull team_clear_next(const MpParams& P, uint32_t level
   return 0;
 }
 
-__device__ bool team_fast(const MpParams& P, Lds& L, uint32_t T, uint32_t level, int32_t bcnt,
+__device__ bool team_fast(const MpParams& P, TeamLds& L, uint32_t T, uint32_t level, int32_t bcnt,
                           int32_t bdeg, int32_t lim, ull cleared) {
   if (threadIdx.x == 0) {
     ull* w = &P.ctl->team_word[level % 3].v;
@@ -418,7 +485,7 @@ __device__ bool team_fast(const MpParams& P, Lds& L, uint32_t T, uint32_t level,
   return L.flag == 0;
 }
 
-__device__ bool team_records(const MpParams& P, Lds& L, uint32_t T, uint32_t seq, int odd) {
+__device__ bool team_records(const MpParams& P, TeamLds& L, uint32_t T, uint32_t seq, int odd) {
   const int tid = threadIdx.x;
   if (tid < FG_WAVE) {
     uint32_t* abort_flag = P.ctl->bar + FG_BAR_STRIDE;
@@ -475,7 +542,7 @@ __device__ __forceinline__ int32_t wave_reserve(int32_t w, int32_t* counter) {
   return base + incl - w;
 }
 
-__device__ __forceinline__ void wave_put(Lds& L, int nxt, bool won, int32_t pos, int32_t v,
+__device__ __forceinline__ void wave_put(TeamLds& L, int nxt, bool won, int32_t pos, int32_t v,
                                          int32_t vb, int32_t ve, int32_t* Qo, ull* ovf,
                                          ull ovf_base) {
   const bool over = won && pos >= QCAP;
@@ -515,7 +582,7 @@ struct MpRun {
 // Near iterations as a team of T members (blockIdx.x < T), at most `budget`.
 // Returns false on a device error; *levels = iterations run; *handback = 1
 // when the frontier met on entry does not suit the mode.
-__device__ bool mp_team(const MpParams& P, MpRun& R, Lds& L, uint32_t T, TeamSync& ts,
+__device__ bool mp_team(const MpParams& P, MpRun& R, TeamLds& L, uint32_t T, TeamSync& ts,
                         TeamBases& tb, int32_t budget, int32_t kbase, int32_t* levels,
                         int* handback, bool& ovf, ull& edges, ull& edge_lanes) {
   const int tid = threadIdx.x;
@@ -732,7 +799,7 @@ __device__ bool mp_team(const MpParams& P, MpRun& R, Lds& L, uint32_t T, TeamSyn
 // which costs more than the team saves on graphs of high mean degree.
 template <bool TEAM>
 __global__ __launch_bounds__(PB) void mssp_persistent(MpParams P) {
-  __shared__ Lds L;
+  __shared__ typename KernelLds<TEAM>::type L;
   fg_grid_sync gs{P.ctl->bar, gridDim.x, 0u};
   const int64_t tid = (int64_t)blockIdx.x * PB + threadIdx.x;
   const int64_t nth = (int64_t)gridDim.x * PB;
@@ -763,10 +830,11 @@ __global__ __launch_bounds__(PB) void mssp_persistent(MpParams P) {
     ull mask = 0;
     for (int i = 0; i < P.npend; ++i) mask |= 1ull << P.pend_lane[i];
     const ull reused = mask & used;
-    for (int64_t v = tid; v < P.n; v += nth) {
-      uint32_t* row = P.dist + v * MAXL;
-      for (int i = 0; i < P.npend; ++i) row[P.pend_lane[i]] = DIST_INF;
-    }
+    // a wave per row, lane = query lane (a thread per row wrote its 64 words
+    // one by one: 155 us on 300 k vertices)
+    const bool mine = (mask >> lane) & 1ull;
+    for (int64_t v = gw; v < P.n; v += W)
+      if (mine) P.dist[v * MAXL + lane] = DIST_INF;
     if (reused) {
       // clear the lanes' bits and rebuild the far list without them
       int32_t* nl = P.far[psel ^ 1];
@@ -833,9 +901,9 @@ __global__ __launch_bounds__(PB) void mssp_persistent(MpParams P) {
         if (blockIdx.x < (uint32_t)P.team) {
           MpRun R{it, qsel, fsel, psel, swait, qlen, plen, fbase, live, nearl};
           int hb = 0;
-          if (!mp_team(P, R, L, (uint32_t)P.team, ts, tb, P.k_iters - k, k, &nl, &hb, ovf, edges,
-                       edge_lanes))
-            ok = false;
+          if constexpr (TEAM)
+            ok = mp_team(P, R, L, (uint32_t)P.team, ts, tb, P.k_iters - k, k, &nl, &hb, ovf, edges,
+                         edge_lanes);
           it = R.it;
           qsel = R.qsel;
           fsel = R.fsel;
@@ -941,6 +1009,7 @@ __global__ __launch_bounds__(PB) void mssp_persistent(MpParams P) {
     O.fbase = sl ? kbase : fbase;
     WaveStage<int32_t, STAGE> st{L.stage[wid], 0};
     PileStage fst{L.fstage[wid], 0};
+    Pending H{};
     ull nearb = 0, stayb = 0;
     __syncthreads();  // minl initialised
 
@@ -956,11 +1025,17 @@ __global__ __launch_bounds__(PB) void mssp_persistent(MpParams P) {
       int32_t* sb = L.w_b[wid];
       int32_t* sd = L.w_d[wid];
       ull* sm = L.w_m[wid];
-      for (int64_t base = gw * FG_WAVE; base < qlen; base += W * FG_WAVE) {
+      // a wave's share of the list is dealt in at least four pieces where
+      // there are that many entries (a vertex can be much more work than
+      // another), consecutive pieces to different workgroups
+      const int64_t fair = (qlen + 4 * W - 1) / (4 * W);
+      const int64_t per = fair < FG_WAVE ? fair : FG_WAVE;
+      for (int64_t base = ((int64_t)wid * gridDim.x + blockIdx.x) * per; base < qlen;
+           base += W * per) {
         const int64_t i = base + lane;
         int32_t u = 0, b = 0, d = 0;
         ull m = 0;
-        if (i < qlen) {
+        if (lane < per && i < qlen) {
           u = Qc[i];
           m = Fc[u];
           if (m) {
@@ -1006,7 +1081,7 @@ __global__ __launch_bounds__(PB) void mssp_persistent(MpParams P) {
           const int32_t bj = __builtin_amdgcn_readlane(b, j);
           const int32_t dj = __builtin_amdgcn_readlane(d, j);
           const ull mj = fg_readlane64(m, j);
-          relax_edges(P, L, uj, bj, bj + dj, mj, O, st, fst, nearb, ovf);
+          relax_edges(P, L, uj, bj, bj + dj, mj, O, st, fst, H, nearb, ovf);
         }
         // (edge, lane) pairs of the sparse vertices
         const int32_t items = (!big && !dense) ? d * pc : 0;
@@ -1037,6 +1112,7 @@ __global__ __launch_bounds__(PB) void mssp_persistent(MpParams P) {
         }
       }
     }
+    finish_pending(H, O, st, fst);
     // ---- splits of the lanes with an empty near frontier
     if (sl) {
       const int32_t* pile = P.far[psel];
@@ -1073,8 +1149,15 @@ __global__ __launch_bounds__(PB) void mssp_persistent(MpParams P) {
         fst.push(keep, v, O.fpos, O.fcnt, O.fbase, O.pile);
       }
     }
-    st.flush(O.qcnt, 0ull, O.Qn);
-    fst.flush(O.fpos, O.fcnt, O.fbase, O.pile);
+    {
+      ull pos[2];
+      const int32_t cnt[2] = {st.cnt, fst.cnt};
+      ull* const ctr[2] = {O.qcnt, O.fpos};
+      ull* const also[2] = {nullptr, O.fcnt};
+      block_reserve(L.fl, cnt, ctr, also, pos);
+      put_staged(st, pos[0], 0ull, O.Qn);
+      put_staged(fst, pos[1], O.fbase, O.pile);
+    }
     {
       const ull bn = block_or(nearb, L.redu);
       const ull bs = block_or(stayb, L.redu);
@@ -1090,13 +1173,19 @@ __global__ __launch_bounds__(PB) void mssp_persistent(MpParams P) {
     const int64_t nd = (int64_t)fg_atomic_load_u64(&C->dcnt[s].v);
     if (nd > 0) {
       ull nb2 = 0;
-      for (int64_t i = gw; i < nd; i += W) {
-        const int4 dsc = P.desc[i];
+      // the next chunk's descriptor and row end are loaded under the current one
+      int64_t i = (int64_t)wid * gridDim.x + blockIdx.x;
+      int4 nxt = i < nd ? P.desc[i] : make_int4(0, 0, 0, 0);
+      int32_t nend = P.off[nxt.x + 1];
+      for (; i < nd; i += W) {
+        const int4 dsc = nxt;
+        const int32_t e_end = nend;
+        if (i + W < nd) nxt = P.desc[i + W];
+        nend = P.off[nxt.x + 1];
         const ull m = (ull)(uint32_t)dsc.z | ((ull)(uint32_t)dsc.w << 32);
-        const int32_t e_end = P.off[dsc.x + 1];
         const int32_t e1 = dsc.y + CHS < e_end ? dsc.y + CHS : e_end;
         if (__popcll(m) >= P.dense) {
-          relax_edges(P, L, dsc.x, dsc.y, e1, m, O, st, fst, nb2, ovf);
+          relax_edges(P, L, dsc.x, dsc.y, e1, m, O, st, fst, H, nb2, ovf);
           continue;
         }
         // few lanes: one edge per thread, lane after lane
@@ -1112,8 +1201,16 @@ __global__ __launch_bounds__(PB) void mssp_persistent(MpParams P) {
           fst.push(ff, v, O.fpos, O.fcnt, O.fbase, O.pile);
         }
       }
-      st.flush(O.qcnt, 0ull, O.Qn);
-      fst.flush(O.fpos, O.fcnt, O.fbase, O.pile);
+      finish_pending(H, O, st, fst);
+      {
+        ull pos[2];
+        const int32_t cnt[2] = {st.cnt, fst.cnt};
+        ull* const ctr[2] = {O.qcnt, O.fpos};
+        ull* const also[2] = {nullptr, O.fcnt};
+        block_reserve(L.fl, cnt, ctr, also, pos);
+        put_staged(st, pos[0], 0ull, O.Qn);
+        put_staged(fst, pos[1], O.fbase, O.pile);
+      }
       const ull bn = block_or(nb2, L.redu);
       if (threadIdx.x == 0 && bn) atomicOr(&C->nearw[s].v, bn);
       if (!(ok = gs.sync_acquire(&L.flag))) break;
@@ -1239,7 +1336,7 @@ MpLayout mp_layout(const fg_graph* g, void* ws) {
   return L;
 }
 
-int g_mp_occ[64];
+int g_mp_occ[2][64];
 
 uint32_t default_delta(const fg_graph* g) {
   if (g->m <= 0 || g->nonzero_degree <= 0) return 1u;
@@ -1325,17 +1422,6 @@ extern "C" fg_status fg_mssp_step(fg_mssp* b, int32_t k_iters, void* stream) {
   FG_HIP_TRY(hipGetDevice(&dev));
   fg_device_props pr = fg_props(dev);
   if (!pr.coop) return fg_set_error(FG_EUNSUPPORTED, "fg_mssp_step: no cooperative launch");
-  if (dev >= 0 && dev < 64 && g_mp_occ[dev] == 0) {
-    int nb = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, mssp_persistent<true>, PB, 0) !=
-            hipSuccess ||
-        nb < 1)
-      nb = 1;
-    g_mp_occ[dev] = nb;
-  }
-  int bpc = (dev >= 0 && dev < 64) ? g_mp_occ[dev] : 1;
-  if (bpc > 2) bpc = 2;
-  if (b->opts.blocks_per_cu > 0 && b->opts.blocks_per_cu < bpc) bpc = b->opts.blocks_per_cu;
   const fg_graph* g = b->g;
   MpParams P;
   memset(&P, 0, sizeof(P));
@@ -1355,6 +1441,7 @@ extern "C" fg_status fg_mssp_step(fg_mssp* b, int32_t k_iters, void* stream) {
   P.state = b->lay.state;
   P.ctl = b->lay.ctl;
   P.k_iters = k_iters;
+  P.w_max = g->w_max;
   P.npend = b->npend;
   for (int i = 0; i < b->npend; ++i) {
     P.pend_lane[i] = b->pend_lane[i];
@@ -1367,9 +1454,13 @@ extern "C" fg_status fg_mssp_step(fg_mssp* b, int32_t k_iters, void* stream) {
   uint32_t dd = default_delta(g);
   if (!low_deg && dd < DIST_INF / 2) dd *= 2;
   P.delta = b->opts.delta > 0 ? b->opts.delta : dd;
-  P.big_deg = b->opts.big_degree > 0 ? b->opts.big_degree : 4 * CHS;
+  P.big_deg = b->opts.big_degree > 0 ? b->opts.big_degree : CHS;
   if (P.big_deg > 65536) P.big_deg = 65536;  // keeps a wave's (edge, lane) count in int32
-  P.dense = b->opts.dense_lanes > 0 ? b->opts.dense_lanes : 16;
+  // lanes from which a vertex is relaxed by a wave across its lanes: a wave
+  // step there costs what eight (edge, lane) pairs' share of a pair step does
+  // (64 lanes, R-MAT of 300 k vertices: 4, 8, 16, 32 lanes 3.84, 3.85, 4.27,
+  // over 7 ms); on grids lanes rarely meet and 16 stays
+  P.dense = b->opts.dense_lanes > 0 ? b->opts.dense_lanes : (low_deg ? 16 : 8);
   // defaults by graph shape: on graphs of mean degree <= 8 (grids,
   // road-like graphs: long, thin near frontiers) idle lanes wait to split
   // together and near iterations of medium frontiers run as a team; on
@@ -1379,19 +1470,29 @@ extern "C" fg_status fg_mssp_step(fg_mssp* b, int32_t k_iters, void* stream) {
   P.split_lanes = b->opts.split_lanes > 0 ? b->opts.split_lanes : 8;
   P.split_wait = b->opts.split_wait > 0 ? b->opts.split_wait : (low_deg ? 8 : 1);
   void* args[] = {&P};
-  int grid = pr.cus * bpc;
-  if (b->opts.grid_blocks > 0 && b->opts.grid_blocks < grid) grid = b->opts.grid_blocks;
   const int lanes_in = __builtin_popcountll(b->admitted);
   P.team = b->opts.team_blocks > 0 ? b->opts.team_blocks
            : (b->opts.team_blocks < 0 || !low_deg) ? 1
            : (lanes_in >= 4 ? DEF_TEAM_WIDE : DEF_TEAM);
   if (P.team > TEAM_MAX) P.team = TEAM_MAX;
+  const int build = P.team > 1 ? 1 : 0;
+  const void* kern = build ? (const void*)mssp_persistent<true>
+                           : (const void*)mssp_persistent<false>;
+  if (dev >= 0 && dev < 64 && g_mp_occ[build][dev] == 0) {
+    int nb = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, kern, PB, 0) != hipSuccess || nb < 1)
+      nb = 1;
+    g_mp_occ[build][dev] = nb;
+  }
+  int bpc = (dev >= 0 && dev < 64) ? g_mp_occ[build][dev] : 1;
+  if (bpc > 2) bpc = 2;
+  if (b->opts.blocks_per_cu > 0 && b->opts.blocks_per_cu < bpc) bpc = b->opts.blocks_per_cu;
+  int grid = pr.cus * bpc;
+  if (b->opts.grid_blocks > 0 && b->opts.grid_blocks < grid) grid = b->opts.grid_blocks;
   if (P.team > grid) P.team = grid;
   P.team_e = b->opts.team_edges > 0 ? b->opts.team_edges : DEF_TEAM_E;
   if (P.team_e > TW_CAP - 1) P.team_e = TW_CAP - 1;
 
-  const void* kern = P.team > 1 ? (const void*)mssp_persistent<true>
-                                : (const void*)mssp_persistent<false>;
   FG_HIP_TRY(hipLaunchCooperativeKernel(kern, dim3(grid), dim3(PB), args, 0,
                                         (hipStream_t)stream));
   b->npend = 0;

@@ -209,3 +209,49 @@ def test_overflow_and_errors(fg):
     b2.admit(1, 2)
     with pytest.raises(fg.FGError):
         b2.admit(1, 0)  # already pending
+
+
+@pytest.mark.parametrize("opts", [dict(dense_lanes=1, big_degree=4096), dict(dense_lanes=1),
+                                  dict(dense_lanes=65, big_degree=4096), dict()])
+def test_row_lengths_at_group_borders(fg, orc, opts):
+    """Rows at the borders of the relaxation's groups of 8 edges and steps of
+    64, more vertices than the waves of a launch take in one piece each."""
+    degs = [1, 7, 8, 9, 15, 16, 17, 63, 64, 65, 71, 72, 73, 127, 128, 129, 200] * 8
+    H, P = len(degs), 20_000
+    rng = np.random.default_rng(11)
+    eu = np.concatenate([np.full(d, h) for h, d in enumerate(degs)] + [H + np.arange(P - 1)])
+    ev = np.concatenate([H + rng.choice(P, size=d, replace=False) for d in degs]
+                        + [H + 1 + np.arange(P - 1)])
+    off, col = orc.csr_from_edges(H + P, eu.astype(np.int32), ev.astype(np.int32))
+    w = synth.weights(off, col)
+    g = fg.Graph(off, col, weights=w)
+    srcs = {i: int(s) for i, s in enumerate(rng.choice(H + P, size=64, replace=False))}
+    announce(f"mssp rows at group borders {opts}")
+    check_lanes(orc, run_batch(fg, g, srcs, fg.mssp_opts(delta=500, **opts)), off, col, w, srcs)
+
+
+@pytest.mark.parametrize("last,fits", [(0xFFFFFFFE - 3, True), (0xFFFFFFFF - 3, False)])
+def test_largest_distance_in_lane_parallel_rows(fg, last, fits):
+    """A row whose largest weight brings a distance to 2^32 - 2 (fits) or
+    2^32 - 1 (reported), relaxed across lanes with the saturating sums."""
+    # directed: 0 -3-> 1, 1 -last-> 2, 1 -1-> 3..12 (an edge back from 2 would
+    # itself sum to more than 2^32 - 1, which is reported too)
+    off = np.array([0, 1, 12] + [12] * 11, np.int32)
+    col = np.array([1, 2] + list(range(3, 13)), np.int32)
+    w = np.array([3, last] + [1] * 10, np.uint32)
+    g = fg.Graph(off, col, weights=w, symmetric=False)
+    b = fg.MsspBatch(g, 8, fg.mssp_opts(dense_lanes=1, delta=0xFFFFFFFF))
+    for lane in range(8):
+        b.admit(lane, 0)
+    announce(f"mssp largest distance last={last}")
+    b.step(64)
+    if fits:
+        done, _ = b.poll()
+        assert done == 0xFF
+        for lane in (0, 7):
+            d = to_np(b.read(lane)).astype(np.uint32)
+            assert d[2] == 0xFFFFFFFE and d[1] == 3 and (d[3:] == 4).all()
+    else:
+        with pytest.raises(fg.FGError) as e:
+            b.poll()
+        assert e.value.status == fg.FG_EOVERFLOW
