@@ -49,6 +49,7 @@ constexpr int32_t DEF_BIG_DEG = 64;
 constexpr ull KEY_INF = ~0ull;
 constexpr uint32_t DIST_INF = 0xFFFFFFFFu;
 constexpr int FSTAGE = 256;
+
 constexpr int64_t SMALL_FAR = 4 * PB;  // piles workgroup 0 splits alone
 // Team mode (medium frontiers; see team_mode): LDS queue entries per member,
 // widest team, packed team word fields, and the frontier shape it takes.
@@ -109,6 +110,7 @@ struct SsspParams {
   const int32_t* __restrict__ col;
   const uint32_t* __restrict__ w;
   int32_t n;
+  int64_t m;
   int32_t nw32;  // ceil(n / 32)
   int32_t src;
   uint32_t* dist;
@@ -220,6 +222,7 @@ struct Lds {
   uint32_t b_d[PB];
   int64_t red[PWAVES + 1];
   int32_t red32[PWAVES + 1];
+  FlushLds<PWAVES> fl;
   int32_t newcnt;
   int32_t flag;
   int32_t ackbad;  // workgroup 0: a hand-off acknowledgement wait failed
@@ -327,14 +330,23 @@ __device__ void phase_a(const SsspParams& P, const St& S, Lds& L) {
   int32_t* pile = P.far[S.fsel];
   ull* fpos = &P.ctl->farpos.v;
   ull* fcnt = &P.ctl->fcnt[S.ph % 3].v;
-  const int64_t gw = (int64_t)blockIdx.x * PWAVES + wid;
+  // a wave's share of the list is dealt in at least four pieces where there
+  // are that many entries (a vertex can be much more work than another),
+  // consecutive pieces to different workgroups.  64 entries to each of the
+  // first waves kept 58 of 4096 busy on a list of 3691; with one queue
+  // atomic per workgroup (block_reserve) R-MAT, 16 edges per vertex, one
+  // source: n = 5000 405 -> 305 us, 60 k 608 -> 425, 1 M 1490 -> 1210,
+  // 4 M 3470 -> 3138
   const int64_t W = (int64_t)gridDim.x * PWAVES;
+  const int64_t fair = (S.qlen + 4 * W - 1) / (4 * W);
+  const int64_t per = fair < FG_WAVE ? fair : FG_WAVE;
   int64_t insp = 0;
-  for (int64_t base = gw * FG_WAVE; base < S.qlen; base += W * FG_WAVE) {
+  for (int64_t base = ((int64_t)wid * gridDim.x + blockIdx.x) * per; base < S.qlen;
+       base += W * per) {
     const int64_t i = base + lane;
     int32_t u = 0, b = 0, deg = 0;
     uint32_t du = 0;
-    if (i < S.qlen) {
+    if (lane < per && i < S.qlen) {
       u = Qin[i];
       b = P.off[u];
       deg = P.off[u + 1] - b;
@@ -386,9 +398,16 @@ __device__ void phase_a(const SsspParams& P, const St& S, Lds& L) {
       fst.push(r == R_FAR, v, fpos, fcnt, S.fbase, pile);
     }
   }
-  st.flush(&C.q.v, B.q, Qout);
-  fst.flush(fpos, fcnt, S.fbase, pile);
-  dst.flush(&C.desc.v, B.desc, P.desc);
+  {
+    ull pos[3];
+    const int32_t cnt[3] = {st.cnt, fst.cnt, dst.cnt};
+    ull* const ctr[3] = {&C.q.v, fpos, &C.desc.v};
+    ull* const also[3] = {nullptr, fcnt, nullptr};
+    block_reserve(L.fl, cnt, ctr, also, pos);
+    put_staged(st, pos[0], B.q, Qout);
+    put_staged(fst, pos[1], S.fbase, pile);
+    put_staged(dst, pos[2], B.desc, P.desc);
+  }
   const int64_t tot = fg_block_sum<PB>(insp, L.red);
   if (threadIdx.x == 0 && tot) atomicAdd(&C.insp.v, (ull)tot);
 }
@@ -397,7 +416,6 @@ __device__ void phase_a(const SsspParams& P, const St& S, Lds& L) {
 __device__ void phase_b(const SsspParams& P, const St& S, int64_t ndesc, Lds& L) {
   const int lane = fg_lane();
   const int wid = threadIdx.x / FG_WAVE;
-  const int64_t gw = (int64_t)blockIdx.x * PWAVES + wid;
   const int64_t W = (int64_t)gridDim.x * PWAVES;
   int32_t* Qout = P.q[S.qsel ^ 1];
   uint32_t* inq_nxt = P.inq[(S.k + 1) & 1];
@@ -408,30 +426,45 @@ __device__ void phase_b(const SsspParams& P, const St& S, int64_t ndesc, Lds& L)
   int32_t* pile = P.far[S.fsel];
   ull* fpos = &P.ctl->farpos.v;
   ull* fcnt = &P.ctl->fcnt[S.ph % 3].v;
-  for (int64_t i = gw; i < ndesc; i += W) {
-    const int2 dsc = P.desc[i];
-    const int32_t u = dsc.x;
-    const int32_t e_end = P.off[u + 1];
-    const int32_t e1 = dsc.y + CH < e_end ? dsc.y + CH : e_end;
+  // consecutive descriptors go to different workgroups; the next one is
+  // loaded under the current one, and the columns and weights do not wait
+  // for the row's end (places behind it are loaded and not used)
+  int64_t i = (int64_t)wid * gridDim.x + blockIdx.x;
+  int2 nxt = i < ndesc ? P.desc[i] : make_int2(0, 0);
+  for (; i < ndesc; i += W) {
+    const int32_t u = nxt.x, e0 = nxt.y;
+    if (i + W < ndesc) nxt = P.desc[i + W];
     const uint32_t du = (uint32_t)(P.key[u] >> 32);
+    const int32_t end = P.off[u + 1];
     int32_t vv[CH / FG_WAVE];
     uint32_t ww[CH / FG_WAVE];
 #pragma unroll
     for (int r = 0; r < CH / FG_WAVE; ++r) {
-      const int32_t e = dsc.y + r * FG_WAVE + lane;
-      vv[r] = e < e1 ? P.col[e] : -1;
-      ww[r] = e < e1 ? P.w[e] : 0u;
+      const int64_t e = (int64_t)e0 + r * FG_WAVE + lane;
+      const int64_t at = e < P.m ? e : P.m - 1;
+      vv[r] = P.col[at];
+      ww[r] = P.w[at];
     }
+    // one edge per lane after the other: with four in flight together (keys,
+    // then atomics, then membership bits) the heavy iterations of R-MAT 22
+    // took 13 % longer, because a check that is a few microseconds older lets
+    // more of the atomics through
 #pragma unroll
     for (int r = 0; r < CH / FG_WAVE; ++r) {
       const int32_t v = vv[r];
-      const int rr = v >= 0 ? relax(v, u, du, ww[r], S.T, inq_nxt, P) : R_NONE;
+      const bool in = (int64_t)e0 + r * FG_WAVE + lane < end;
+      const int rr = in ? relax(v, u, du, ww[r], S.T, inq_nxt, P) : R_NONE;
       st.push(rr == R_NEAR, v, &C.q.v, B.q, Qout);
       fst.push(rr == R_FAR, v, fpos, fcnt, S.fbase, pile);
     }
   }
-  st.flush(&C.q.v, B.q, Qout);
-  fst.flush(fpos, fcnt, S.fbase, pile);
+  ull pos[2];
+  const int32_t cnt[2] = {st.cnt, fst.cnt};
+  ull* const ctr[2] = {&C.q.v, fpos};
+  ull* const also[2] = {nullptr, fcnt};
+  block_reserve(L.fl, cnt, ctr, also, pos);
+  put_staged(st, pos[0], B.q, Qout);
+  put_staged(fst, pos[1], S.fbase, pile);
 }
 
 // Split of the far pile by the whole grid (the current frontier is empty):
@@ -471,8 +504,13 @@ __device__ void split_full(const SsspParams& P, const St& S, uint32_t Tnew, Lds&
     st.push(r == R_NEAR, v, sq, 0ull, Q);
     fst.push(r == R_FAR, v, fpos, fcnt, kbase, keep);
   }
-  st.flush(sq, 0ull, Q);
-  fst.flush(fpos, fcnt, kbase, keep);
+  ull pos[2];
+  const int32_t cnt[2] = {st.cnt, fst.cnt};
+  ull* const ctr[2] = {sq, fpos};
+  ull* const also[2] = {nullptr, fcnt};
+  block_reserve(L.fl, cnt, ctr, also, pos);
+  put_staged(st, pos[0], 0ull, Q);
+  put_staged(fst, pos[1], kbase, keep);
   const uint32_t bm = block_min(mn, L.redm);
   if (threadIdx.x == 0 && bm != DIST_INF) atomicMin(&P.ctl->fmin[S.ph % 3], bm);
 }
@@ -1328,6 +1366,7 @@ extern "C" fg_status fg_sssp(const fg_graph* g, int32_t src, const fg_sssp_opts*
   P.col = g->col;
   P.w = g->w;
   P.n = g->n;
+  P.m = g->m;
   P.nw32 = (int32_t)(((int64_t)g->n + 31) / 32);
   P.src = src;
   P.dist = dist;
