@@ -294,8 +294,13 @@ typedef struct {
                              frontier Bellman-Ford).  Results do not depend
                              on it.                                          */
   int32_t team_blocks;    /* workgroups that run medium frontiers from LDS
-                             queues as a team (0 = 32 on graphs of mean
-                             degree <= 8, no team on others; -1 = no team) */
+                             queues as a team (0 = no team on graphs of mean
+                             degree > 8; on others 32, or with every field
+                             but delta 0 and no row over 256 entries an
+                             asynchronous team of up to 64, as wide as the
+                             vertex count asks for, that makes its splits
+                             itself and hands over to the whole grid where
+                             fronts are wide; -1 = no team)                  */
   int32_t team_edges;     /* ... while the frontier's degree sum is at most
                              this (0 = 65536)                                */
 } fg_sssp_opts;

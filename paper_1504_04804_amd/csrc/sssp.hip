@@ -69,6 +69,20 @@ struct CtrSlot {
   Line64 insp;
 };
 
+struct AsyncCtl {
+  ull rec[2][TEAM_MAX];  // per member: queue length, levels run, out of room
+  ull lev_cnt[FG_TRACE_MAX];   // vertices relaxed / entries read per level
+  ull lev_insp[FG_TRACE_MAX];
+  uint32_t arrive;
+  uint32_t exit;
+  uint32_t farcnt[3];  // far pile entries, by splits so far mod 3
+  uint32_t fmin[3];    // smallest distance a split kept, by split number mod 3
+  uint32_t failed;
+  ull insp;
+  ull reached;
+  ull t_start;
+};
+
 // Zero when a launch starts (fresh workspaces are zero-filled; the last
 // workgroup of each launch clears it again).
 struct alignas(256) SsspCtl {
@@ -78,7 +92,8 @@ struct alignas(256) SsspCtl {
   uint32_t sm_ack;  // waiters that have read a hand-back (monotone)
   uint32_t pad0b[63];
   uint32_t exit_count;
-  uint32_t pad1[63];
+  uint32_t async_done;  // the asynchronous team finished (1) or handed over (2)
+  uint32_t pad1[62];
   uint32_t overflow;
   uint32_t pad2[63];
   Line64 reached;
@@ -96,9 +111,16 @@ struct alignas(256) SsspCtl {
   // level words, and the overflow counter of the global queue
   uint32_t team_arrive;
   uint32_t pad4[63];
-  ull team_rec[2][TEAM_MAX][2];
-  Line64 team_word[3];
-  Line64 team_ovf;
+  union {
+    struct {
+      ull team_rec[2][TEAM_MAX][2];
+      Line64 team_word[3];
+      Line64 team_ovf;
+    };
+    AsyncCtl as;  // the asynchronous team's fields (see sssp_async)
+  };
+  static_assert(sizeof(AsyncCtl) <= sizeof(ull[2][TEAM_MAX][2]) + 4 * sizeof(Line64),
+                "the control block does not grow");
   int32_t pub_k, pub_qsel, pub_force, pub_fsel;
   int64_t pub_qlen, pub_insp_sum, pub_flen;
   ull pub_fbase;
@@ -130,6 +152,9 @@ struct SsspParams {
   int32_t clock_khz;
   int32_t team;     // workgroups of a team (<= 1: no team mode)
   int64_t team_e;   // largest frontier degree sum a team takes
+  const int4* __restrict__ head;  // first four neighbours per vertex
+  int32_t behind;   // asynchronous team: the level-synchronous kernel follows;
+                    // that kernel: launched behind the team
 };
 
 struct St {
@@ -1065,12 +1090,570 @@ __device__ bool team_mode(const SsspParams& P, St& S, Lds& L, uint32_t T, TeamSy
   }
 }
 
+// ---- asynchronous team (graphs of mean degree <= 8) ----------------------
+//
+// The near iterations of long, thin frontiers are a chain of memory trips,
+// and a team that synchronises in every one of them (or hands each split
+// back to the whole grid) pays for the exchange as well: 6.5 us per
+// iteration on a 1024 x 1024 grid.  Here T workgroups, alone in the launch,
+// each relax their own LDS queue level after level and meet only every SA_K
+// levels, when their queue is empty.  Keys are label-correcting anyway (a
+// vertex is queued whenever its distance strictly improves, with the
+// distance it got), so members may drift apart: distances and smallest-id
+// predecessors do not depend on the order.
+//
+// A queue entry carries what its relaxation needs: distance, row, the first
+// four neighbours and their weights, loaded by the lane that queues the
+// vertex while its atomicMin is on its way.  A level is then one trip (the
+// atomics, with those loads beside them) instead of three.  Neighbours that
+// the entry's distance cannot improve (the vertex it was reached from) are
+// dropped from the entry.  Vertices that improve to the threshold or more
+// are collected in LDS and entered in the far pile when the member runs out
+// of near work, with the membership bits that keep every vertex in the pile
+// once, off the chain.
+//
+// When the members meet and no near work is left, the pile is split by all
+// of them (as elsewhere: below the old threshold stale, below the new one
+// near, the rest kept), without leaving the kernel.  A near vertex that finds
+// its LDS queue full goes to the far pile instead, and the next split keeps
+// the threshold and takes everything below it as near (an entry that is stale
+// is then relaxed once more, which changes nothing).
+//
+// Where the near work of all members grows past SA_WIDE vertices each, the
+// fronts are wide and the whole grid is faster: from SA_GIVE_UP members on
+// the team hands its state over (near vertices, far pile, thresholds) to the
+// level-synchronous kernel launched behind it, which goes on from there and
+// otherwise returns at once.
+
+// Measured (1024 x 1024 grid, three sources): 22.5, 12.2 and 14.8 ms with
+// the team and the splits by the whole grid, 6.5, 4.2 and 4.9 ms here (2434
+// levels in the 6.5 ms: 2.7 us each); 50 x 50: 0.50 -> 0.31 ms.  The 6.5 ms
+// with 16, 32, 64 members (32 levels between meetings): 9.5, 7.5, 6.4 ms (a
+// wide front takes more rounds of fewer members); with 8, 16, 32 levels
+// between meetings (64 members): 7.3, 6.5, 6.4 ms, 300 x 250: 1.19, 1.11,
+// 1.09 ms, and the second source 4.6, 4.2, 4.5 ms.
+
+constexpr int SQ = 1280;       // LDS queue entries per member
+constexpr int SA_FAR = 2048;   // far vertices collected per member
+constexpr int SA_K = 16;       // levels between two meetings
+constexpr int SA_ROUND = PB / 4;  // vertices a level takes at once
+constexpr int SA_BREAK = 1024; // queue length from which a member meets at once
+constexpr int SA_WIDE = 512;   // near vertices per member from which it hands over
+constexpr int SA_T = 64;       // most members
+constexpr int SA_SIDE = 16;    // one member per so many vertices of a square's side
+constexpr int SA_GIVE_UP = 16; // members from which wide fronts are left to the whole grid
+constexpr int32_t SA_DEG = 256;  // largest degree of the graphs it is tried on
+
+struct SaLds {
+  int32_t qv[2][SQ];
+  uint32_t qd[2][SQ];
+  int32_t qb[2][SQ];
+  int32_t qe[2][SQ];
+  int4 qh[2][SQ];
+  uint4 qw[2][SQ];
+  int32_t fb[SA_FAR];
+  int32_t b_sc[PB];
+  int32_t b_u[PB];
+  int32_t b_b[PB];
+  uint32_t b_d[PB];
+  int32_t cnt[2];
+  int32_t big[2];  // by level parity: a vertex of degree > 4 is in the queue
+  int32_t fcnt;
+  int32_t ovf;
+  int32_t flag;
+  int32_t tot, pre, mx, lev, anyo;
+  uint32_t redm[PWAVES];
+  int32_t red32[PWAVES + 1];
+  int64_t red[PWAVES + 1];
+};
+
+// A queued vertex with everything its relaxation needs.
+struct SaEntry {
+  int32_t v;
+  uint32_t d;
+  int32_t b, e;
+  int4 h;
+  uint4 w;
+};
+
+// Row, first neighbours and their weights of x.v (its loads are issued here
+// and waited for where the values are used).
+__device__ __forceinline__ void sa_load(const SsspParams& P, SaEntry& x) {
+  x.b = P.off[x.v];
+  x.e = P.off[x.v + 1];
+  x.h = P.head[x.v];
+  const int64_t l = P.m - 1;
+  const int64_t b = x.b;
+  x.w.x = P.w[b < l ? b : l];
+  x.w.y = P.w[b + 1 < l ? b + 1 : l];
+  x.w.z = P.w[b + 2 < l ? b + 2 : l];
+  x.w.w = P.w[b + 3 < l ? b + 3 : l];
+}
+
+// Drops the neighbour u at distance du from x's first four where x cannot
+// lower u's key (an equal distance could still lower its predecessor).
+__device__ __forceinline__ void sa_drop(SaEntry& x, int32_t u, uint32_t du) {
+  x.h.x = x.h.x == u && sat_add(x.d, x.w.x) > du ? -1 : x.h.x;
+  x.h.y = x.h.y == u && sat_add(x.d, x.w.y) > du ? -1 : x.h.y;
+  x.h.z = x.h.z == u && sat_add(x.d, x.w.z) > du ? -1 : x.h.z;
+  x.h.w = x.h.w == u && sat_add(x.d, x.w.w) > du ? -1 : x.h.w;
+}
+
+// Queues the kept lanes' entries (every lane of the wave takes part); true
+// where there was no room.
+__device__ __forceinline__ bool sa_put(SaLds& L, int q, bool keep, const SaEntry& x) {
+  const int32_t pos = wave_reserve(keep ? 1 : 0, &L.cnt[q]);
+  if (!keep) return false;
+  if (pos >= SQ) {
+    L.ovf = 1;
+    return true;
+  }
+  L.qv[q][pos] = x.v;
+  L.qd[q][pos] = x.d;
+  L.qb[q][pos] = x.b;
+  L.qe[q][pos] = x.e;
+  L.qh[q][pos] = x.h;
+  L.qw[q][pos] = x.w;
+  return false;
+}
+
+// Enters the kept lanes' vertices that are not in it yet into the far pile
+// (every lane of the wave takes part).  After `split` splits the pile is
+// far[split & 1] and its length farcnt[split % 3].
+__device__ __forceinline__ void sa_enter(const SsspParams& P, uint32_t split, bool keep,
+                                         int32_t v) {
+  bool fresh = false;
+  if (keep) {
+    const uint32_t bit = 1u << (v & 31);
+    fresh = !(atomicOr(&P.infar[v >> 5], bit) & bit);
+  }
+  const uint64_t m = __ballot(fresh);
+  if (!m) return;
+  uint32_t base = 0;
+  if (fg_lane() == 0) base = atomicAdd(&P.ctl->as.farcnt[split % 3], (uint32_t)__popcll(m));
+  base = __builtin_amdgcn_readfirstlane(base);
+  // every vertex is in the pile at most once, so it never outgrows n
+  if (fresh) fg_st_shared(&P.far[split & 1][base + fg_mbcnt(m)], v);
+}
+
+// Collects the kept lanes' vertices in LDS; what does not fit is entered at
+// once.
+__device__ __forceinline__ void sa_far(const SsspParams& P, SaLds& L, uint32_t split, bool keep,
+                                       int32_t v) {
+  const int32_t pos = wave_reserve(keep ? 1 : 0, &L.fcnt);
+  if (keep && pos < SA_FAR) L.fb[pos] = v;
+  if (__ballot(keep && pos >= SA_FAR)) sa_enter(P, split, keep && pos >= SA_FAR, v);
+}
+
+// Enters what was collected (the whole workgroup, behind a barrier).
+__device__ __forceinline__ void sa_flush(const SsspParams& P, SaLds& L, uint32_t split) {
+  const int32_t c = L.fcnt < SA_FAR ? L.fcnt : SA_FAR;
+  for (int32_t i0 = 0; i0 < c; i0 += PB) {
+    const int32_t i = i0 + (int32_t)threadIdx.x;
+    sa_enter(P, split, i < c, i < c ? L.fb[i] : 0);
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) L.fcnt = 0;
+  __syncthreads();
+}
+
+enum { SA_NONE = 0, SA_NEAR = 1, SA_FARV = 2 };
+
+// Relaxes x.v through u with candidate distance du + wt; x gets its entry's
+// fields while the atomic is on its way.
+__device__ __forceinline__ int sa_relax(const SsspParams& P, SaEntry& x, int32_t u, uint32_t du,
+                                        uint32_t wt, uint32_t T) {
+  x.d = sat_add(du, wt);
+  if (x.d == DIST_INF) {
+    __hip_atomic_store(&P.ctl->overflow, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return SA_NONE;
+  }
+  if (x.v == P.src) return SA_NONE;
+  const ull old = atomicMin(&P.key[x.v], ((ull)x.d << 32) | (ull)(uint32_t)u);
+  sa_load(P, x);
+  if (x.d >= (uint32_t)(old >> 32)) return SA_NONE;
+  sa_drop(x, u, du);
+  return x.d < T ? SA_NEAR : SA_FARV;
+}
+
+// The members' records of meeting `seq`, published and read by all: L.tot,
+// L.pre (entries of the members before this one), L.mx, L.lev, L.anyo
+// (members that ran out of room since the meeting before).
+__device__ __forceinline__ bool sa_meet(const SsspParams& P, SaLds& L, TeamSync& ts, uint32_t seq,
+                                        int32_t c, int32_t lev) {
+  AsyncCtl& A = P.ctl->as;
+  const uint32_t T = ts.T;
+  if (T > 1) {
+    if (threadIdx.x == 0) {
+      __hip_atomic_store(&A.rec[seq & 1][blockIdx.x],
+                         ((ull)(L.ovf ? 1 : 0) << 63) | ((ull)(uint32_t)lev << 32) |
+                             (ull)(uint32_t)c,
+                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      L.ovf = 0;
+    }
+    if (!ts.sync_acquire(&L.flag)) return false;
+    if (threadIdx.x < FG_WAVE) {
+      ull r = 0;
+      if (threadIdx.x < T)
+        r = __hip_atomic_load(&A.rec[seq & 1][threadIdx.x], __ATOMIC_RELAXED,
+                              __HIP_MEMORY_SCOPE_AGENT);
+      const int32_t n = (int32_t)(uint32_t)r;
+      const int32_t incl = fg_wave_incl_scan(n);
+      const int32_t o = fg_wave_sum((int32_t)(r >> 63));
+      int32_t mx = n, ml = (int32_t)((r >> 32) & 0x7fffffffu);
+#pragma unroll
+      for (int d = FG_WAVE / 2; d > 0; d >>= 1) {
+        const int32_t a = __shfl_xor(mx, d, FG_WAVE), b = __shfl_xor(ml, d, FG_WAVE);
+        mx = a > mx ? a : mx;
+        ml = b > ml ? b : ml;
+      }
+      const int32_t before = __builtin_amdgcn_readlane(incl - n, blockIdx.x);
+      if (threadIdx.x == 0) {
+        L.tot = __builtin_amdgcn_readlane(incl, FG_WAVE - 1);
+        L.pre = before;
+        L.mx = mx;
+        L.lev = ml;
+        L.anyo = o;
+      }
+    }
+  } else if (threadIdx.x == 0) {
+    L.tot = L.mx = c;
+    L.pre = 0;
+    L.lev = lev;
+    L.anyo = L.ovf;
+    L.ovf = 0;
+  }
+  __syncthreads();
+  return true;
+}
+
+__global__ __launch_bounds__(PB) void sssp_async(SsspParams P) {
+  __shared__ SaLds L;
+  const int tid = threadIdx.x;
+  const uint32_t T = gridDim.x;
+  AsyncCtl& A = P.ctl->as;
+  TeamSync ts{&A.arrive, P.ctl->bar + FG_BAR_STRIDE, T, 0u};
+  const int64_t gt = (int64_t)blockIdx.x * PB + tid, gn = (int64_t)T * PB;
+  if (blockIdx.x == 0) {
+    if (tid < 3)
+      __hip_atomic_store(&A.fmin[tid], DIST_INF, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (tid == 0) fg_st_shared(&A.t_start, (ull)wall_clock64());
+  }
+  for (int64_t v = gt; v < P.n; v += gn)
+    fg_st_shared(&P.key[v], v == P.src ? (ull)(uint32_t)P.src : KEY_INF);
+  for (int64_t i = gt; i < P.nw32; i += gn) fg_st_shared(&P.infar[i], 0u);
+  if (tid == 0) {
+    L.cnt[0] = L.cnt[1] = L.big[0] = L.big[1] = L.fcnt = L.ovf = 0;
+    if (blockIdx.x == 0) {
+      SaEntry x;
+      x.v = P.src;
+      x.d = 0;
+      if (P.m > 0) sa_load(P, x); else x.b = x.e = 0;
+      L.qv[0][0] = x.v;
+      L.qd[0][0] = 0u;
+      L.qb[0][0] = x.b;
+      L.qe[0][0] = x.e;
+      L.qh[0][0] = x.h;
+      L.qw[0][0] = x.w;
+      L.cnt[0] = 1;
+    }
+  }
+  bool ok = T == 1 || ts.sync_acquire(&L.flag);
+  __syncthreads();
+
+  int cur = 0;
+  uint32_t Tn = P.delta;   // near threshold
+  uint32_t Tnext = sat_add(P.delta, P.delta);
+  int32_t done_levels = 0; // levels before this super-step (the longest member's)
+  uint32_t seq = 0, split = 0;
+  int64_t insp = 0;
+  bool finished = false;
+  bool spilled = false;    // near vertices are in the far pile
+  bool wide = false;       // handed over to the kernel behind
+  // every super-step relaxes at least one strict improvement; the bound only
+  // keeps the kernel finite
+  for (uint32_t step = 0; ok && step < 0x40000000u; ++step) {
+    int32_t lev = 0;
+    for (; lev < SA_K; ++lev) {
+      const int32_t cnt = L.cnt[cur] < SQ ? L.cnt[cur] : SQ;
+      // (the same in every thread: behind a barrier)
+      if (cnt == 0 || (lev > 0 && T > 1 && cnt > SA_BREAK)) break;
+      const int nxt = cur ^ 1;
+      const int par = lev & 1;
+      int64_t here = 0;
+      bool big = false;
+      for (int32_t c0 = 0; c0 < cnt; c0 += PB / 4) {
+        const int32_t i = c0 + tid / 4;
+        const int j = tid & 3;
+        int32_t d = 0;
+        if (i < cnt) d = L.qe[cur][i] - L.qb[cur][i];
+        big |= d > 4;
+        int r = SA_NONE;
+        SaEntry x;
+        x.v = 0;
+        if (j < d && d <= 4) {
+          x.v = ((const int32_t*)&L.qh[cur][i])[j];
+          if (x.v >= 0) {
+            r = sa_relax(P, x, L.qv[cur][i], L.qd[cur][i], ((const uint32_t*)&L.qw[cur][i])[j], Tn);
+            here++;
+          }
+        }
+        const bool full = sa_put(L, nxt, r == SA_NEAR, x);
+        sa_far(P, L, split, full || r == SA_FARV, x.v);
+      }
+      if (big) L.big[par] = 1;
+      __syncthreads();
+      if (tid == 0) {
+        L.cnt[cur] = 0;  // every thread has read it
+        L.big[par ^ 1] = 0;
+      }
+      if (L.big[par]) {
+        // longer rows: block scan-gather over their entries
+        for (int32_t c0 = 0; c0 < cnt; c0 += PB) {
+          const int32_t i = c0 + tid;
+          int32_t d = 0;
+          if (i < cnt) {
+            d = L.qe[cur][i] - L.qb[cur][i];
+            L.b_u[tid] = L.qv[cur][i];
+            L.b_b[tid] = L.qb[cur][i];
+            L.b_d[tid] = L.qd[cur][i];
+          }
+          if (d <= 4) d = 0;
+          int32_t all = 0;
+          const int32_t ex = fg_block_excl_scan<PB>(d, L.red32, &all);
+          L.b_sc[tid] = ex;
+          __syncthreads();
+          const int32_t nc = cnt - c0 < PB ? cnt - c0 : PB;
+          for (int32_t t0 = 0; t0 < all; t0 += PB) {
+            const int32_t t = t0 + tid;
+            int r = SA_NONE;
+            SaEntry x;
+            x.v = 0;
+            if (t < all) {
+              const int32_t jj = upper_idx(L.b_sc, nc, t);
+              const int32_t e = L.b_b[jj] + (t - L.b_sc[jj]);
+              x.v = P.col[e];
+              r = sa_relax(P, x, L.b_u[jj], L.b_d[jj], P.w[e], Tn);
+              here++;
+            }
+            const bool full = sa_put(L, nxt, r == SA_NEAR, x);
+            sa_far(P, L, split, full || r == SA_FARV, x.v);
+          }
+          __syncthreads();
+        }
+      }
+      insp += here;
+      if (P.stats && done_levels + lev < FG_TRACE_MAX) {
+        const int64_t h = fg_block_sum<PB>(here, L.red);
+        if (tid == 0) {
+          atomicAdd(&A.lev_cnt[done_levels + lev], (ull)cnt);
+          if (h) atomicAdd(&A.lev_insp[done_levels + lev], (ull)h);
+        }
+      }
+      __syncthreads();
+      cur = nxt;
+    }
+    // every append of the levels is behind a barrier here
+    const int32_t mine = L.cnt[cur] < SQ ? L.cnt[cur] : SQ;
+    if (mine == 0) sa_flush(P, L, split);
+    if (!(ok = sa_meet(P, L, ts, seq++, mine, lev))) break;
+    spilled = spilled || L.anyo > 0;
+    done_levels += L.lev;
+    if (P.behind && (int64_t)L.tot > (int64_t)T * SA_WIDE && L.tot <= P.n) {
+      // hand over: near vertices to the global queue, collected far ones to
+      // the pile
+      for (int32_t i = tid; i < mine; i += PB) fg_st_shared(&P.q[0][L.pre + i], L.qv[cur][i]);
+      sa_flush(P, L, split);
+      wide = true;
+      break;
+    }
+    // no near work anywhere: split the far pile until there is some
+    while (L.tot == 0) {
+      const uint32_t plen = __hip_atomic_load(&A.farcnt[split % 3], __ATOMIC_RELAXED,
+                                              __HIP_MEMORY_SCOPE_AGENT);
+      if (plen == 0) {
+        finished = true;
+        break;
+      }
+      const bool again = spilled;
+      const uint32_t Tnew = again ? Tn : Tnext;
+      const int32_t* pile = P.far[split & 1];
+      const int64_t lo = (int64_t)plen * blockIdx.x / T, hi = (int64_t)plen * (blockIdx.x + 1) / T;
+      // the next split's slots: last read before the meeting that ended the
+      // split before this one, next used behind the one that ends this one
+      if (blockIdx.x == 0 && tid == 0) {
+        __hip_atomic_store(&A.fmin[(split + 1) % 3], DIST_INF, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&A.farcnt[(split + 2) % 3], 0u, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+      }
+      uint32_t mn = DIST_INF;
+      for (int64_t i0 = lo; i0 < hi; i0 += PB) {
+        const int64_t i = i0 + tid;
+        SaEntry x;
+        x.v = 0;
+        bool near = false, keep = false, listed = false;
+        if (i < hi) {
+          x.v = pile[i];
+          x.d = (uint32_t)(__hip_atomic_load(&P.key[x.v], __ATOMIC_RELAXED,
+                                             __HIP_MEMORY_SCOPE_AGENT) >> 32);
+          sa_load(P, x);
+          listed = true;
+          keep = x.d >= Tnew;
+          near = !keep && (again || x.d >= Tn);
+          if (keep) mn = x.d < mn ? x.d : mn;
+        }
+        if (sa_put(L, cur, near, x)) keep = true;  // no room: it stays in the pile
+        if (listed && !keep) atomicAnd(&P.infar[x.v >> 5], ~(1u << (x.v & 31)));
+        // kept entries move to the other pile, their bits stay set
+        const uint64_t m = __ballot(keep);
+        if (m) {
+          uint32_t base = 0;
+          if (fg_lane() == 0) base = atomicAdd(&A.farcnt[(split + 1) % 3], (uint32_t)__popcll(m));
+          base = __builtin_amdgcn_readfirstlane(base);
+          if (keep) fg_st_shared(&P.far[(split + 1) & 1][base + fg_mbcnt(m)], x.v);
+        }
+      }
+      mn = block_min(mn, L.redm);
+      if (tid == 0 && mn != DIST_INF) atomicMin(&A.fmin[split % 3], mn);
+      __syncthreads();
+      const int32_t got = L.cnt[cur] < SQ ? L.cnt[cur] : SQ;
+      if (!(ok = sa_meet(P, L, ts, seq++, got, 0))) break;
+      spilled = L.anyo > 0;
+      if (!again) {
+        Tn = Tnew;
+        Tnext = sat_add(L.tot > 0 ? Tnew
+                                  : __hip_atomic_load(&A.fmin[split % 3], __ATOMIC_RELAXED,
+                                                      __HIP_MEMORY_SCOPE_AGENT),
+                        P.delta);
+      }
+      split++;
+    }
+    if (!ok || finished) break;
+    // even shares where one member holds more than a round's work and more
+    // than twice its share
+    if (T > 1 && L.mx > SA_ROUND && (int64_t)L.mx * T > 2 * (int64_t)L.tot && L.tot <= P.n) {
+      const int32_t have = L.cnt[cur] < SQ ? L.cnt[cur] : SQ;
+      const int32_t pre = L.pre, tot = L.tot;
+      int32_t* G = P.q[0];
+      for (int32_t i = tid; i < have; i += PB) fg_st_shared(&G[pre + i], L.qv[cur][i]);
+      if (!(ok = ts.sync_acquire(&L.flag))) break;
+      const int32_t lo = (int32_t)((int64_t)tot * blockIdx.x / T);
+      const int32_t hi = (int32_t)((int64_t)tot * (blockIdx.x + 1) / T);
+      for (int32_t i = tid; i < hi - lo; i += PB) {
+        SaEntry x;
+        x.v = G[lo + i];
+        // the key may be lower by now than when the vertex was queued
+        x.d = (uint32_t)(__hip_atomic_load(&P.key[x.v], __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_AGENT) >> 32);
+        sa_load(P, x);
+        L.qv[cur][i] = x.v;
+        L.qd[cur][i] = x.d;
+        L.qb[cur][i] = x.b;
+        L.qe[cur][i] = x.e;
+        L.qh[cur][i] = x.h;
+        L.qw[cur][i] = x.w;
+      }
+      __syncthreads();
+      if (tid == 0) L.cnt[cur] = hi - lo;
+    }
+    __syncthreads();
+  }
+  int32_t reached = 0;
+  if (finished) {
+    for (int64_t v = gt; v < P.n; v += gn) {
+      const ull kk = P.key[v];
+      const bool r = kk != KEY_INF;
+      P.dist[v] = r ? (uint32_t)(kk >> 32) : 0xFFFFFFFFu;
+      if (P.parent) P.parent[v] = r ? (int32_t)(uint32_t)kk : -1;
+      reached += r;
+    }
+  }
+  const int32_t rb = fg_block_sum<PB>(reached, L.red32);
+  const int64_t ib = fg_block_sum<PB>(insp, L.red);
+  if (tid == 0) {
+    if (rb) atomicAdd(&A.reached, (ull)rb);
+    if (ib) atomicAdd(&A.insp, (ull)ib);
+    if (!finished && !wide)
+      __hip_atomic_store(&A.failed, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    L.flag = __hip_atomic_fetch_add(&A.exit, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) ==
+             T - 1;
+  }
+  __syncthreads();
+  if (!L.flag) return;
+  // the last member writes the record and leaves the control block zero
+  // (but for the word that the kernel behind it reads and clears)
+  const bool failed = __hip_atomic_load(&A.failed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u;
+  const ull total = __hip_atomic_load(&A.insp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (P.stats) {
+    uint32_t* sw = (uint32_t*)P.stats;
+    for (int i = tid; i < (int)(sizeof(fg_run_stats) / 4); i += PB) sw[i] = 0u;
+  }
+  __syncthreads();
+  if (P.stats && tid < FG_TRACE_MAX) {
+    fg_run_stats* st = P.stats;
+    const int64_t now = (int64_t)wall_clock64();
+    if (tid < done_levels) {
+      st->frontier[tid] = (int64_t)__hip_atomic_load(&A.lev_cnt[tid], __ATOMIC_RELAXED,
+                                                     __HIP_MEMORY_SCOPE_AGENT);
+      st->inspected[tid] = (int64_t)__hip_atomic_load(&A.lev_insp[tid], __ATOMIC_RELAXED,
+                                                      __HIP_MEMORY_SCOPE_AGENT);
+      st->t_end[tid] = now;  // levels are not timed one by one
+    }
+    if (tid == 0) {
+      st->status = failed ? FG_EDEVICE
+                   : __hip_atomic_load(&P.ctl->overflow, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                       ? FG_EOVERFLOW
+                       : FG_OK;
+      st->iterations = done_levels;
+      st->reached = (int64_t)__hip_atomic_load(&A.reached, __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_AGENT);
+      st->edges_inspected = (int64_t)total;
+      st->grid_blocks = (int32_t)T;
+      st->clock_khz = P.clock_khz;
+      st->t_start = (int64_t)__hip_atomic_load(&A.t_start, __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_AGENT);
+    }
+  }
+  if (tid == 0 && P.behind) {
+    SsspCtl* c = P.ctl;
+    if (wide) {
+      c->pub_k = done_levels;
+      c->pub_qlen = L.tot;
+      c->pub_insp_sum = (int64_t)total;
+      c->pub_fsel = (int32_t)(split & 1);
+      c->pub_flen = (int64_t)__hip_atomic_load(&A.farcnt[split % 3], __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_AGENT);
+      // near vertices in the pile are below the threshold, where a split
+      // would take them for stale: nothing is below 0
+      c->pub_T = spilled ? 0u : Tn;
+      c->pub_Tnext = spilled ? Tn : Tnext;
+    }
+    c->async_done = wide ? 2u : 1u;
+  }
+  if (tid == 0 && !wide) P.ctl->overflow = 0u;
+  if (tid == 0 && failed) P.ctl->bar[FG_BAR_STRIDE] = 0u;  // the abort flag
+  __syncthreads();
+  uint32_t* aw = (uint32_t*)&A;
+  for (int i = tid; i < (int)(sizeof(AsyncCtl) / 4); i += PB) aw[i] = 0u;
+}
+
 // TEAM = false compiles the kernel without the team episodes: their code
 // raises the register pressure (and the spills) of the whole kernel, which
 // is not worth it on graphs whose frontiers rarely suit a team.
 template <bool TEAM>
 __global__ __launch_bounds__(PB) void sssp_persistent(SsspParams P) {
   __shared__ Lds L;
+  const bool resume = P.behind && P.ctl->async_done == 2u;
+  if (P.behind && !resume) {
+    // the asynchronous team has answered: the last workgroup out clears
+    if (threadIdx.x == 0 &&
+        atomicAdd(&P.ctl->exit_count, 1u) == gridDim.x - 1) {
+      P.ctl->exit_count = 0u;
+      P.ctl->async_done = 0u;
+    }
+    return;
+  }
   fg_grid_sync gs{P.ctl->bar, gridDim.x, 0u};
   St S = {};
   S.qlen = 1;
@@ -1085,24 +1668,37 @@ __global__ __launch_bounds__(PB) void sssp_persistent(SsspParams P) {
   TeamBases tb = {};
   const int64_t tid = (int64_t)blockIdx.x * PB + threadIdx.x;
   const int64_t nth = (int64_t)gridDim.x * PB;
-  // init: every key infinite except the source, membership bitmaps clear
-  if (blockIdx.x == 0 && P.stats) {
+  // init: every key infinite except the source, membership bitmaps clear;
+  // or what the asynchronous team handed over
+  if (blockIdx.x == 0 && P.stats && !resume) {
     uint32_t* sw = (uint32_t*)P.stats;
     for (int i = threadIdx.x; i < (int)(sizeof(fg_run_stats) / 4); i += PB) sw[i] = 0u;
   }
-  for (int64_t v = tid; v < P.n; v += nth)
-    P.key[v] = v == P.src ? (ull)(uint32_t)P.src : KEY_INF;
+  if (resume) {
+    const SsspCtl* c = P.ctl;
+    S.k = c->pub_k;
+    S.qlen = c->pub_qlen;
+    S.insp_sum = c->pub_insp_sum;
+    S.fsel = c->pub_fsel;
+    S.flen = c->pub_flen;
+    S.fbase = 0ull - (ull)S.flen;  // the pile's next append goes to index flen
+    S.T = c->pub_T;
+    S.Tnext = c->pub_Tnext;
+  } else {
+    for (int64_t v = tid; v < P.n; v += nth)
+      P.key[v] = v == P.src ? (ull)(uint32_t)P.src : KEY_INF;
+  }
   for (int64_t i = tid; i < P.nw32; i += nth) {
     P.inq[0][i] = 0u;
     P.inq[1][i] = 0u;
-    P.infar[i] = 0u;
+    if (!resume) P.infar[i] = 0u;
   }
   if (tid == 0) {
-    P.q[0][0] = P.src;
+    if (!resume) P.q[0][0] = P.src;
     P.ctl->fmin[0] = DIST_INF;
   }
   if (!gs.sync(&L.flag)) ok = false;
-  if (blockIdx.x == 0 && threadIdx.x == 0 && P.stats) {
+  if (blockIdx.x == 0 && threadIdx.x == 0 && P.stats && !resume) {
     P.stats->t_start = (int64_t)wall_clock64();
     P.stats->clock_khz = P.clock_khz;
   }
@@ -1396,7 +1992,27 @@ extern "C" fg_status fg_sssp(const fg_graph* g, int32_t src, const fg_sssp_opts*
   P.team_e = o.team_edges > 0 ? o.team_edges : DEF_TEAM_E;
   if (P.team_e > TW_CAP - 1) P.team_e = TW_CAP - 1;
   P.clock_khz = pr.clock_khz;
+  P.head = g->head;
   void* args[] = {&P};
+  // The asynchronous team answers where the team build would run by default,
+  // unless the caller sets how frontiers are dealt with.  Its width follows
+  // the width of a front (a member per 16 vertices of the side of a square
+  // of n vertices): a level is one trip up to 256 vertices per member, and
+  // members more than that only meet more slowly.  Rows past SA_DEG entries
+  // are left to the whole grid from the start.
+  const bool tuned = o.small_frontier > 0 || o.small_edges > 0 || o.big_degree > 0 ||
+                     o.blocks_per_cu > 0 || o.grid_blocks > 0 || o.team_blocks != 0 ||
+                     o.team_edges > 0;
+  if (low_deg && !tuned && g->max_degree <= SA_DEG) {
+    int T = 1;
+    while (T < SA_T && (int64_t)T * SA_SIDE * T * SA_SIDE < (int64_t)g->n) T *= 2;
+    if (T > pr.cus) T = pr.cus;
+    // below SA_GIVE_UP members (16 k vertices) the team never gives up
+    P.behind = T >= SA_GIVE_UP ? 1 : 0;
+    FG_HIP_TRY(hipLaunchCooperativeKernel((const void*)sssp_async, dim3(T), dim3(PB), args, 0,
+                                          (hipStream_t)stream));
+    if (!P.behind) return FG_OK;
+  }
   const void* kern = P.team > 1 ? (const void*)sssp_persistent<true>
                                 : (const void*)sssp_persistent<false>;
   FG_HIP_TRY(hipLaunchCooperativeKernel(kern, dim3(grid), dim3(PB), args, 0, (hipStream_t)stream));

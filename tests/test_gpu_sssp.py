@@ -179,3 +179,85 @@ def test_config_rmat22_sssp_sampled(fg, orc):
     g = fg.Graph(off, col, weights=w)
     for s in synth.sources(off, 64)[:2]:
         check(fg, orc, g, off, col, w, int(s))
+
+
+@pytest.mark.parametrize("rows,cols,delta,wmax", [
+    (1, 2, 0, 64), (1, 5000, 0, 64), (60, 50, 0, 64), (128, 128, 0, 64),
+    (129, 128, 0, 64), (300, 250, 0, 64), (300, 250, 5, 64), (300, 250, 0xFFFFFFFF, 64),
+    (257, 260, 0, 0), (257, 260, 40, 1), (260, 270, 300, 3), (700, 900, 0, 64)])
+def test_async_team(fg, orc, rows, cols, delta, wmax):
+    """The default path of low-degree graphs: one to sixteen members; tiny and
+    no thresholds (near vertices that find no room in LDS); zero weights (a
+    neighbour that a vertex was reached from may still be its predecessor)."""
+    off, col = synth.grid_csr(rows, cols)
+    w = synth.weights(off, col) if wmax == 64 else synth.weights(off, col) % np.uint32(wmax + 1)
+    g = fg.Graph(off, col, weights=w)
+    n = rows * cols
+    for s in (0, n // 2 + cols // 3 if n > 2 else 0, n - 1):
+        st = check(fg, orc, g, off, col, w, s, delta=delta)
+        assert st.grid_blocks <= 64 or n > 16384  # from sixteen members on the team may hand over
+        st = check(fg, orc, g, off, col, w, s, delta=delta)  # the workspace is left ready
+    d, p, st = fg.sssp(g, 0, parents=False, delta=delta)
+    assert np.array_equal(to_np(d), orc.dijkstra(off, col, w, 0)[0])
+
+
+def test_async_team_long_rows_and_handover(fg, orc):
+    """Rows past the four entries carried in the queue, a directed graph, and
+    a vertex whose neighbours do not fit the members' queues (the
+    level-synchronous kernel takes over), then a plain query again."""
+    rng = np.random.default_rng(3)
+    n = 9000
+    eu = np.concatenate([np.arange(n - 1), rng.integers(0, n, 2 * n)]).astype(np.int32)
+    ev = np.concatenate([np.arange(1, n), rng.integers(0, n, 2 * n)]).astype(np.int32)
+    off, col = orc.csr_from_edges(n, eu, ev)
+    assert len(col) <= 8 * n and np.diff(off).max() > 8
+    w = synth.weights(off, col)
+    g = fg.Graph(off, col, weights=w)
+    for s in (0, 17, n - 1):
+        assert check(fg, orc, g, off, col, w, s).grid_blocks == 8
+    keep = rng.random(len(col)) < 0.7  # directed: rows lose entries at random
+    deg = np.add.reduceat(np.append(keep, False).astype(np.int64), off[:-1]) * (np.diff(off) > 0)
+    doff = np.concatenate([[0], np.cumsum(deg)]).astype(np.int32)
+    dcol, dw = col[keep], w[keep]
+    gd = fg.Graph(doff, dcol, weights=dw, symmetric=False)
+    for s in (0, 4000):
+        check(fg, orc, gd, doff, dcol, dw, s)
+    # wide fronts on sixteen and on 64 members: handed over to the whole grid
+    for size in (60_000, 400_000):
+        eu, ev = rng.integers(0, size, (2, 2 * size)).astype(np.int32)
+        off, col = orc.csr_from_edges(size, eu, ev)
+        w = synth.weights(off, col)
+        g = fg.Graph(off, col, weights=w)
+        for delta in (0, 20, 0xFFFFFFFF):
+            for s in (0, 5):
+                st = check(fg, orc, g, off, col, w, int(col[off[s]]) if off[s + 1] > off[s] else s,
+                           delta=delta)
+                assert st.grid_blocks in (256, 16, 64)
+    assert st.grid_blocks == 256
+
+
+def test_async_team_near_vertices_without_room(fg, orc):
+    """Hubs (below the degree at which the team is not tried) whose neighbours
+    do not fit the members' queues: they wait in the far pile."""
+    hubs, per = 60, 250
+    n = hubs * per + hubs
+    leaves = np.arange(hubs, n, dtype=np.int32)
+    eu = np.concatenate([leaves % hubs, np.zeros(hubs - 1)]).astype(np.int32)
+    ev = np.concatenate([leaves, np.arange(1, hubs)]).astype(np.int32)
+    off, col = orc.csr_from_edges(n, eu, ev)
+    assert np.diff(off).max() > 256
+    w = synth.weights(off, col) % np.uint32(3)
+    g = fg.Graph(off, col, weights=w)
+    for s in (0, 1, n - 1):
+        check(fg, orc, g, off, col, w, s)
+    # the same below the border: a path of hubs
+    eu = np.concatenate([leaves % hubs, np.arange(hubs - 1)]).astype(np.int32)
+    ev = np.concatenate([leaves, np.arange(1, hubs)]).astype(np.int32)
+    off, col = orc.csr_from_edges(n, eu, ev)
+    assert 250 < np.diff(off).max() <= 256
+    for mod in (1, 3, 65):
+        w = synth.weights(off, col) % np.uint32(mod)
+        g = fg.Graph(off, col, weights=w)
+        for s in (0, 1, n - 1):
+            assert check(fg, orc, g, off, col, w, s, delta=0xFFFFFFFF).grid_blocks <= 8
+            check(fg, orc, g, off, col, w, s)
