@@ -198,7 +198,10 @@ void fg_bfs_opts_default(fg_bfs_opts* opts);
  * FG_MODE_DO).  depth: device int32[n], receives the hop distance from src
  * or -1.  parent: device int32[n] or NULL; receives a BFS-tree predecessor
  * (parent[src] = src, -1 if unreached); which of several valid parents is
- * chosen may differ between runs.  ws: device workspace of at least
+ * chosen may differ between runs.  Small graphs (up to 32768 vertices, or
+ * 20480 vertices and 2^18 entries in FG_MODE_PUSH) are traversed by one
+ * workgroup unless an option says how to spread a traversal over the card;
+ * with async_levels, where no row has more than 256 entries.  ws: device workspace of at least
  * fg_workspace_bytes(g, FG_PRIM_BFS or FG_PRIM_BFS_UNFUSED, 0) bytes.
  * stats: device fg_run_stats* or NULL.  opts may be NULL (defaults).
  * Errors: FG_EINVAL (src out of range, NULL depth/ws, bad opts),

@@ -24,6 +24,7 @@
 #include <string.h>
 
 #include <mutex>
+#include <type_traits>
 
 #include "frontier.h"
 
@@ -60,7 +61,6 @@ constexpr int32_t DEF_BIG_DEG = 64;
 constexpr int32_t DEF_TEAM = 24;
 constexpr int64_t DEF_TEAM_E = 65536;
 
-typedef unsigned __int128 u128;
 typedef unsigned long long ull;
 
 // Counters of one iteration parity.  Iteration k appends through slot k&1;
@@ -154,6 +154,7 @@ struct BfsParams {
   // the asynchronous traversal ran out of queue room
   int32_t async_k;
   int32_t async_fallback;
+  int32_t solo_long;  // bfs_solo: the graph has rows of more than SOLO_ROW entries
   // the traversal's workgroups: [blk0, blk0 + nblk) of the launch (a launch
   // may run two traversals side by side on disjoint ranges).  The
   // level-synchronous kernel always starts at workgroup 0 (blk0 = 0: its
@@ -238,7 +239,7 @@ __device__ __forceinline__ void set_bases(St& S, const Bases& b) {
 // Direction rule of Sec. VI-A for the iteration described by S (k >= 1):
 // FV = |Q| m / n, BV = |U| n / |P|, U = n - |P|; forward->backward when
 // FV > do_a BV (once), backward->forward when FV < do_b BV.  Exact in
-// 128-bit integers: FV > (a/b) BV  <=>  b |Q| m |P| > a |U| n n.
+// 128-bit products: FV > (a/b) BV  <=>  b |Q| m |P| > a |U| n n.
 template <int MODE>
 __device__ __forceinline__ void decide(St& S, const BfsParams& P) {
   S.prevdir = S.dir;
@@ -246,15 +247,21 @@ __device__ __forceinline__ void decide(St& S, const BfsParams& P) {
     S.dir = DIR_PUSH;
     return;
   }
-  const u128 lhs = (u128)(ull)S.qlen * (ull)P.m * (ull)S.p;
-  const u128 rhs = (u128)(ull)((int64_t)P.n - S.p) * (ull)P.n * (ull)P.n;
-  if (S.dir == DIR_PUSH) {
-    if (!S.switched && lhs * P.a_den > rhs * P.a_num) {
+  if (S.dir == DIR_PUSH && S.switched) return;
+  const bool fwd = S.dir == DIR_PUSH;
+  // n, m and the counts are below 2^31, the fractions' terms below 2^32:
+  // each side is a product of two words below 2^63
+  const ull l0 = (ull)S.qlen * (ull)P.m, l1 = (ull)S.p * (fwd ? P.a_den : P.b_den);
+  const ull r0 = (ull)((int64_t)P.n - S.p) * (ull)P.n,
+            r1 = (ull)P.n * (fwd ? P.a_num : P.b_num);
+  const ull lh = __umul64hi(l0, l1), ll = l0 * l1, rh = __umul64hi(r0, r1), rl = r0 * r1;
+  if (fwd) {
+    if (lh > rh || (lh == rh && ll > rl)) {
       S.dir = DIR_PULL;
       S.switched = 1;
       S.switches++;
     }
-  } else if (lhs * P.b_den < rhs * P.b_num) {
+  } else if (lh < rh || (lh == rh && ll < rl)) {
     S.dir = DIR_PUSH;
     S.switches++;
   }
@@ -1654,6 +1661,460 @@ __global__ __launch_bounds__(PB) void bfs_persistent(BfsParams P) {
   bfs_persistent_run<MODE, MULTI>(P, L);
 }
 
+// ---- small graphs: the whole traversal in one workgroup -----------------
+//
+// A traversal of a few thousand vertices is all latency: of 93 us on an
+// R-MAT graph of 4096 vertices the launch of a whole co-resident grid took
+// 17, its init fill and first grid barrier 10, and each level a grid barrier
+// or a hand-off and three dependent trips to memory.  Here one workgroup (an
+// ordinary launch) holds everything that its waves share in LDS: the visited
+// set, the list of all vertices reached so far (in level order, so a frontier
+// is a range of it) and the record.  A level costs the trip for offsets and
+// head entries, one more for the columns where rows are longer than four,
+// and one workgroup barrier (two with rows of more than SOLO_ROW entries,
+// which all waves take in CH-entry chunks; three in a pull).  Every wave
+// takes one piece of the frontier, then further ones through an LDS counter.
+// Same levels, directions and counts as the kernel above; no workspace is
+// touched.
+// Measured, R-MAT, direction-optimizing: n = 4096 90 -> 27 us, 16 k 104-126
+// -> 40-57, 32 k (0.4 to 1.3 M entries) 106-143 -> 55-66 (the pull's 16
+// rounds of 2048 vertices; the bound on n is the LDS room of two lists);
+// push-only, one word per vertex: n = 1000 192 -> 48 us, 8 k (0.24 M
+// entries) 159 -> 137, but 16 k (0.6 M) 181 -> 283 and 32 k (1.2 M) 191 ->
+// 625 in a build without the bounds: hence SOLO_KM.  Grids, push: 31 x 33
+// 118 -> 64 us (0.9 us per level), 100 x 100 352 -> 215; asynchronous 122 ->
+// 64 and 284 -> 215; 180 x 180 direction-optimizing 795 -> 537.
+constexpr int32_t SOLO_N = 32768;
+constexpr int64_t SOLO_M = 2 << 20;
+constexpr int32_t SOLO_KN = 20480;
+constexpr int64_t SOLO_KM = 1 << 18;
+constexpr int32_t SOLO_ROW = CH;
+
+// Visited set and outputs of a push-only traversal: one word per vertex,
+// depth << 16 | parent, lowered with an LDS atomicMin.  A vertex is found by
+// the lane that sees it untouched; another of the same level can only lower
+// the parent, so parents are the smallest-id neighbours one level closer.
+// depth and parent are written from the words at the end, in order.
+struct SoloKeys {
+  uint16_t q[SOLO_KN];  // vertices reached, in order
+  uint16_t list[SOLO_KM / SOLO_ROW];  // long rows
+  uint32_t key[SOLO_KN];
+};
+
+// ... of a direction-optimizing one: a bitmap; depth and parent are written
+// where a vertex is found, and -1 at the end.
+struct SoloBits {
+  uint16_t q[SOLO_N];
+  uint16_t list[SOLO_N];  // pull: unvisited vertices; push: long rows
+  uint32_t vis[SOLO_N / 32];
+  uint32_t nb[SOLO_N / 32];  // found by the pull in progress
+};
+
+template <class V>
+struct SoloLds : V {
+  int32_t w_sc[PWAVES][FG_WAVE];
+  int32_t w_u[PWAVES][FG_WAVE];
+  int32_t w_b[PWAVES][FG_WAVE];
+  int32_t w_e[PWAVES][FG_WAVE];
+  // per level mod 3: vertices found, entries dealt, CSR entries read, long
+  // rows / pull candidates listed.  A level clears the next one's slot: its
+  // last readers, two levels before, are behind the barrier in between.
+  int32_t found[3];
+  int32_t next[3];
+  int32_t insp[3];
+  int32_t nlist[3];
+  int64_t red[PWAVES + 1];
+  fg_run_stats st;
+};
+
+// A level: its counter slot, the depth of what it finds, and where the list
+// goes on.
+struct SoloLevel {
+  int sl;
+  int32_t d_new;
+  int32_t qhi;
+};
+
+// Test-and-set of up to R targets per lane (v[r] < 0: none); winners get
+// their depth and parent and join the list.  Every lane must take part.
+template <int R>
+__device__ __forceinline__ void solo_visit(const BfsParams& P, SoloLds<SoloKeys>& L,
+                                           const SoloLevel& K, const int32_t (&v)[R],
+                                           const int32_t (&pu)[R]) {
+  uint32_t w[R];
+  bool won[R];
+  int32_t c = 0;
+  const uint32_t dk = (uint32_t)K.d_new << 16;
+#pragma unroll
+  for (int r = 0; r < R; ++r) w[r] = v[r] >= 0 ? L.key[v[r]] : 0u;
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const uint32_t k = dk | (uint32_t)pu[r];
+    won[r] = w[r] > k && atomicMin(&L.key[v[r]], k) == ~0u;
+    c += won[r];
+  }
+  if (!__ballot(c > 0)) return;
+  int32_t pos = K.qhi + wave_reserve(c, &L.found[K.sl]);
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+    if (won[r]) L.q[pos++] = (uint16_t)v[r];
+}
+
+template <int R>
+__device__ __forceinline__ void solo_visit(const BfsParams& P, SoloLds<SoloBits>& L, const SoloLevel& K,
+                                           const int32_t (&v)[R], const int32_t (&pu)[R]) {
+  uint32_t w[R];
+  bool won[R];
+  int32_t c = 0;
+#pragma unroll
+  for (int r = 0; r < R; ++r) w[r] = v[r] >= 0 ? L.vis[v[r] >> 5] : ~0u;
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const uint32_t bit = 1u << (v[r] & 31);
+    won[r] = !(w[r] & bit) && !(atomicOr(&L.vis[v[r] >> 5], bit) & bit);
+    c += won[r];
+  }
+  if (!__ballot(c > 0)) return;
+  int32_t pos = K.qhi + wave_reserve(c, &L.found[K.sl]);
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    if (won[r]) {
+      L.q[pos++] = (uint16_t)v[r];
+      P.depth[v[r]] = K.d_new;
+      if (P.parent) P.parent[v[r]] = pu[r];
+    }
+  }
+}
+
+// Lanes hold rows (first entry b, `d` entries, vertex u) in sc / su / sb
+// (sc their prefix); the wave takes entries [t0, T) in steps of 4 x 64.
+template <class V>
+__device__ __forceinline__ void solo_gather(const BfsParams& P, SoloLds<V>& L, const SoloLevel& K,
+                                            const int32_t* sc, const int32_t* su,
+                                            const int32_t* sb, int32_t T) {
+  const int lane = fg_lane();
+  for (int32_t t0 = 0; t0 < T; t0 += 4 * FG_WAVE) {
+    int32_t v[4], pu[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int32_t t = t0 + r * FG_WAVE + lane;
+      const int32_t tc = t < T ? t : T - 1;
+      const int32_t j = upper_idx(sc, FG_WAVE, tc);
+      pu[r] = su[j];
+      v[r] = P.col[sb[j] + (tc - sc[j])];
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      if (t0 + r * FG_WAVE + lane >= T) v[r] = -1;
+    solo_visit<4>(P, L, K, v, pu);
+  }
+}
+
+template <class V>
+__device__ void solo_push(const BfsParams& P, SoloLds<V>& L, const SoloLevel& K, int32_t qlo, int32_t qlen,
+                          int32_t& insp) {
+  const int lane = fg_lane();
+  const int wid = threadIdx.x / FG_WAVE;
+  int32_t* sc = L.w_sc[wid];
+  int32_t* su = L.w_u[wid];
+  int32_t* sb = L.w_b[wid];
+  int32_t* se = L.w_e[wid];
+  // one piece per wave without asking, the others as the waves get free
+  int32_t per = (qlen + PWAVES - 1) / PWAVES;
+  if (per > FG_WAVE) per = FG_WAVE;
+  for (int32_t base = wid * per; base < qlen;) {
+    int32_t u = 0, b = 0, deg = 0;
+    int4 hd = make_int4(0, 0, 0, 0);
+    if (lane < per && base + lane < qlen) {
+      u = L.q[qlo + base + lane];
+      b = P.off[u];
+      deg = P.off[u + 1] - b;
+      hd = P.head[u];
+    }
+    insp += deg;
+    const bool big = deg > SOLO_ROW;
+    const uint64_t bm = __ballot(big);
+    if (bm) {
+      const int32_t pos = wave_reserve(big ? 1 : 0, &L.nlist[K.sl]);
+      if (big) L.list[pos] = (uint16_t)u;
+    }
+    // the first four entries of each row, lane by lane
+    const int32_t v[4] = {deg > 0 && !big ? hd.x : -1, deg > 1 && !big ? hd.y : -1,
+                          deg > 2 && !big ? hd.z : -1, deg > 3 && !big ? hd.w : -1};
+    const int32_t pu[4] = {u, u, u, u};
+    solo_visit<4>(P, L, K, v, pu);
+    // the others laid over the lanes
+    const int32_t d = big || deg <= 4 ? 0 : deg - 4;
+    const int32_t inc = fg_wave_incl_scan(d);
+    const int32_t T = __builtin_amdgcn_readlane(inc, FG_WAVE - 1);
+    if (T > 0) {
+      wave_lds_fence();
+      sc[lane] = inc - d;
+      su[lane] = u;
+      sb[lane] = b + 4;
+      wave_lds_fence();
+      solo_gather(P, L, K, sc, su, sb, T);
+      wave_lds_fence();
+    }
+    if (qlen <= PWAVES * per) break;
+    if (lane == 0) base = atomicAdd(&L.next[K.sl], per);
+    base = PWAVES * per + __builtin_amdgcn_readfirstlane(base);
+  }
+  if (!P.solo_long) return;
+  __syncthreads();
+  const int32_t nbig = L.nlist[K.sl];
+  for (int32_t r0 = 0; r0 < nbig; r0 += FG_WAVE) {
+    int32_t u = 0, b = 0, deg = 0;
+    if (r0 + lane < nbig) {
+      u = L.list[r0 + lane];
+      b = P.off[u];
+      deg = P.off[u + 1] - b;
+    }
+    const int32_t nch = (deg + CH - 1) / CH;
+    const int32_t inc = fg_wave_incl_scan(nch);
+    const int32_t NC = __builtin_amdgcn_readlane(inc, FG_WAVE - 1);
+    wave_lds_fence();
+    sc[lane] = inc - nch;
+    su[lane] = u;
+    sb[lane] = b;
+    se[lane] = b + deg;
+    wave_lds_fence();
+    for (int32_t c = wid; c < NC; c += PWAVES) {
+      const int32_t j = upper_idx(sc, FG_WAVE, c);
+      const int32_t e0 = sb[j] + (c - sc[j]) * CH, e1 = se[j];
+      int32_t v[4], pu[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int32_t e = e0 + r * FG_WAVE + lane;
+        v[r] = P.col[e < e1 ? e : e1 - 1];
+        pu[r] = su[j];
+      }
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        if (e0 + r * FG_WAVE + lane >= e1) v[r] = -1;
+      solo_visit<4>(P, L, K, v, pu);
+    }
+    wave_lds_fence();
+  }
+}
+
+__device__ __forceinline__ bool solo_seen(const SoloLds<SoloBits>& L, int32_t u) {
+  return (L.vis[u >> 5] >> (u & 31)) & 1u;
+}
+
+// Pull: the unvisited vertices of nonzero degree are listed, two per lane
+// probe their first four neighbours from the head table, the rest of a row
+// is read four entries at a time up to 16 and by the whole wave after that.
+__device__ void solo_pull(const BfsParams& P, SoloLds<SoloBits>& L, const SoloLevel& K, int32_t& insp) {
+  const int lane = fg_lane();
+  const int32_t nbytes = (P.n + 7) / 8;
+  const uint8_t* nz8 = (const uint8_t*)P.nz;
+  const uint8_t* vis8 = (const uint8_t*)L.vis;
+  for (int32_t i0 = 0; i0 < nbytes; i0 += PB) {
+    const int32_t i = i0 + threadIdx.x;
+    uint32_t x = i < nbytes ? (uint32_t)nz8[i] & ~(uint32_t)vis8[i] & 0xffu : 0u;
+    int32_t pos = wave_reserve(__popc(x), &L.nlist[K.sl]);
+    while (x) {
+      const int b = __builtin_ctz(x);
+      x &= x - 1;
+      L.list[pos++] = (uint16_t)(i * 8 + b);
+    }
+  }
+  __syncthreads();
+  const int32_t tot = L.nlist[K.sl];
+  for (;;) {
+    int32_t base = 0;
+    if (lane == 0) base = atomicAdd(&L.next[K.sl], 2 * FG_WAVE);
+    base = __builtin_amdgcn_readfirstlane(base);
+    if (base >= tot) break;
+    int32_t v[2], b[2], e[2];
+    int4 hd[2];
+    bool mine[2];
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      const int32_t a = base + s * FG_WAVE + lane;
+      mine[s] = a < tot;
+      v[s] = L.list[mine[s] ? a : base];
+      b[s] = P.off[v[s]];
+      e[s] = P.off[v[s] + 1];
+      hd[s] = P.head[v[s]];
+    }
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      const int32_t u[4] = {hd[s].x, hd[s].y, hd[s].z, hd[s].w};
+      const int32_t dg = e[s] - b[s];
+      int32_t h = -1, pu = -1, ins = 0;
+#pragma unroll
+      for (int j = 3; j >= 0; --j)
+        if (j < dg && solo_seen(L, u[j])) {
+          h = j;
+          pu = u[j];
+        }
+      ins = h >= 0 ? h + 1 : min(4, dg);
+      bool more = mine[s] && h < 0 && dg > 4;
+      for (int32_t i0 = 4; i0 < 16 && __ballot(more); i0 += 4) {
+        if (more) {
+          int32_t x[4];
+#pragma unroll
+          for (int j = 0; j < 4; ++j) x[j] = P.col[min(b[s] + i0 + j, e[s] - 1)];
+#pragma unroll
+          for (int j = 3; j >= 0; --j)
+            if (i0 + j < dg && solo_seen(L, x[j])) {
+              h = i0 + j;
+              pu = x[j];
+            }
+          ins = h >= 0 ? h + 1 : min(i0 + 4, dg);
+          more = h < 0 && dg > i0 + 4;
+        }
+      }
+      uint64_t pend = __ballot(more);
+      while (pend) {
+        const int l = __builtin_ctzll(pend);
+        pend &= pend - 1;
+        const int32_t lb = __builtin_amdgcn_readlane(b[s], l);
+        const int32_t le = __builtin_amdgcn_readlane(e[s], l);
+        int32_t hit = -1, hu = -1;
+        for (int32_t i0 = lb + 16; i0 < le && hit < 0; i0 += FG_WAVE) {
+          const int32_t i = i0 + lane;
+          const int32_t x = P.col[i < le ? i : le - 1];
+          const uint64_t m = __ballot(i < le && solo_seen(L, x));
+          if (m) {
+            const int f = __builtin_ctzll(m);
+            hit = i0 + f - lb;
+            hu = __builtin_amdgcn_readlane(x, f);
+          }
+        }
+        if (lane == l) {
+          ins = hit >= 0 ? hit + 1 : le - lb;
+          h = hit;
+          pu = hu;
+        }
+      }
+      const bool found = mine[s] && h >= 0;
+      if (mine[s]) insp += ins;
+      const int32_t pos = K.qhi + wave_reserve(found ? 1 : 0, &L.found[K.sl]);
+      if (found) {
+        L.q[pos] = (uint16_t)v[s];
+        atomicOr(&L.nb[v[s] >> 5], 1u << (v[s] & 31));
+        P.depth[v[s]] = K.d_new;
+        if (P.parent) P.parent[v[s]] = pu;
+      }
+    }
+  }
+  __syncthreads();
+  for (int32_t i = threadIdx.x; i < (P.n + 31) / 32; i += PB) {
+    L.vis[i] |= L.nb[i];
+    L.nb[i] = 0u;
+  }
+}
+
+__device__ __forceinline__ void solo_init(const BfsParams& P, SoloLds<SoloBits>& L) {
+  for (int32_t i = threadIdx.x; i < (P.n + 31) / 32; i += PB) {
+    L.vis[i] = i == (P.src >> 5) ? 1u << (P.src & 31) : 0u;
+    L.nb[i] = 0u;
+  }
+  if (threadIdx.x == 0) {
+    P.depth[P.src] = 0;
+    if (P.parent) P.parent[P.src] = P.src;
+  }
+}
+__device__ __forceinline__ void solo_init(const BfsParams& P, SoloLds<SoloKeys>& L) {
+  for (int32_t v = threadIdx.x; v < P.n; v += PB) L.key[v] = v == P.src ? (uint32_t)v : ~0u;
+}
+__device__ __forceinline__ void solo_finish(const BfsParams& P, const SoloLds<SoloBits>& L) {
+  for (int32_t v = threadIdx.x; v < P.n; v += PB) {
+    if (solo_seen(L, v)) continue;
+    P.depth[v] = -1;
+    if (P.parent) P.parent[v] = -1;
+  }
+}
+__device__ __forceinline__ void solo_finish(const BfsParams& P, const SoloLds<SoloKeys>& L) {
+  for (int32_t v = threadIdx.x; v < P.n; v += PB) {
+    const uint32_t k = L.key[v];
+    P.depth[v] = k == ~0u ? -1 : (int32_t)(k >> 16);
+    if (P.parent) P.parent[v] = k == ~0u ? -1 : (int32_t)(k & 0xffffu);
+  }
+}
+
+template <class V>
+__global__ __launch_bounds__(PB) void bfs_solo(BfsParams P) {
+  constexpr int MODE = std::is_same<V, SoloBits>::value ? FG_MODE_DO : FG_MODE_PUSH;
+  __shared__ SoloLds<V> L;
+  const int tid = threadIdx.x;
+  solo_init(P, L);
+  for (int i = tid; i < (int)(sizeof(fg_run_stats) / 4); i += PB) ((uint32_t*)&L.st)[i] = 0u;
+  if (tid == 0) {
+    L.q[0] = (uint16_t)P.src;
+    for (int i = 0; i < 3; ++i) L.found[i] = L.next[i] = L.insp[i] = L.nlist[i] = 0;
+  }
+  St S = {};
+  S.dir = DIR_PUSH;
+  S.prevdir = DIR_PUSH;
+  S.qlen = 1;
+  S.p = 1;
+  int32_t qlo = 0;
+  int64_t late = 0;
+  __syncthreads();
+  if (tid == 0) {
+    L.st.t_start = (int64_t)wall_clock64();
+    L.st.clock_khz = P.clock_khz;
+  }
+  while (S.qlen > 0) {
+    const SoloLevel K{S.k % 3, S.k + 1, qlo + (int32_t)S.qlen};
+    if (tid == 0) {
+      const int nx = (S.k + 1) % 3;
+      L.found[nx] = L.next[nx] = L.insp[nx] = L.nlist[nx] = 0;
+      if (S.k < FG_TRACE_MAX) {
+        L.st.dir[S.k] = (int8_t)S.dir;
+        L.st.frontier[S.k] = S.qlen;
+      }
+    }
+    int32_t insp = 0;
+    if constexpr (MODE == FG_MODE_DO) {
+      if (S.dir == DIR_PUSH)
+        solo_push(P, L, K, qlo, (int32_t)S.qlen, insp);
+      else
+        solo_pull(P, L, K, insp);
+    } else {
+      solo_push(P, L, K, qlo, (int32_t)S.qlen, insp);
+    }
+    // past the record's trace only the sum is wanted, at the end
+    if (S.k < FG_TRACE_MAX) {
+      insp = fg_wave_sum(insp);
+      if (fg_lane() == 0 && insp) atomicAdd(&L.insp[K.sl], insp);
+    } else {
+      late += insp;
+    }
+    __syncthreads();
+    const int32_t found = L.found[K.sl];
+    if (tid == 0 && S.k < FG_TRACE_MAX) {
+      const int32_t read = L.insp[K.sl];
+      L.st.inspected[S.k] = read;
+      L.st.t_end[S.k] = (int64_t)wall_clock64();
+      S.insp_sum += read;
+    }
+    S.k++;
+    qlo = K.qhi;
+    S.qlen = found;
+    S.p += found;
+    decide<MODE>(S, P);
+  }
+  solo_finish(P, L);
+  late = fg_block_sum<PB>(late, L.red);
+  if (tid == 0) {
+    L.st.status = FG_OK;
+    L.st.iterations = S.k;
+    L.st.reached = S.p;
+    L.st.edges_inspected = S.insp_sum + late;
+    L.st.direction_switches = S.switches;
+    L.st.grid_blocks = 1;
+  }
+  __syncthreads();
+  if (P.stats)
+    for (int i = tid; i < (int)(sizeof(fg_run_stats) / 4); i += PB)
+      ((uint32_t*)P.stats)[i] = ((const uint32_t*)&L.st)[i];
+}
+
 // ---- asynchronous push mode (high-diameter graphs) ----------------------
 //
 // A team of T workgroups (the whole launch) runs K push levels between two
@@ -2279,6 +2740,22 @@ static BfsParams bfs_params(const fg_graph* g, int32_t src, const fg_bfs_opts& o
   return P;
 }
 
+// One workgroup runs the traversal alone (bfs_solo): small graphs, unless the
+// caller sets how a traversal is spread over the card.  A push-only one reads
+// every row, at a quarter of the rate of the whole card, so its bound on the
+// entries is lower (and holds for a direction rule that hardly ever pulls).
+// The asynchronous mode is taken over where no row is long.
+static bool solo_fits(const fg_graph* g, const fg_bfs_opts& o) {
+  const bool tuned = o.small_frontier || o.small_edges || o.big_degree || o.blocks_per_cu ||
+                     o.team_edges || o.grid_blocks;
+  if (tuned) return false;
+  if (o.mode == FG_MODE_PUSH && o.async_levels > 1)
+    return g->n <= SOLO_KN && g->m <= SOLO_KM && g->max_degree <= SOLO_ROW;
+  if (o.team_blocks) return false;
+  if (o.mode == FG_MODE_PUSH) return g->n <= SOLO_KN && g->m <= SOLO_KM;
+  return g->n <= SOLO_N && g->m <= (o.do_a_num <= o.do_a_den ? SOLO_M : SOLO_KM);
+}
+
 // Workgroups of an asynchronous team.
 static int async_team(const fg_bfs_opts& o, const fg_device_props& pr) {
   int T = o.team_blocks > 0 ? o.team_blocks : DEF_TEAM;
@@ -2323,6 +2800,15 @@ static fg_status bfs_launch(const fg_graph* g, int32_t src, const fg_bfs_opts& o
                                               ? persistent_blocks_per_cu<FG_MODE_DO>(dev)
                                               : persistent_blocks_per_cu<FG_MODE_PUSH>(dev));
   BfsParams P = bfs_params(g, src, o, lay, depth, parent, stats, pr, grid, srcs, nsrc, out_stride);
+
+  if (!srcs && solo_fits(g, o)) {
+    P.solo_long = g->max_degree > SOLO_ROW;
+    void* sargs[] = {&P};
+    FG_HIP_TRY(hipLaunchKernel(o.mode == FG_MODE_DO ? (const void*)bfs_solo<SoloBits>
+                                                    : (const void*)bfs_solo<SoloKeys>,
+                               dim3(1), dim3(PB), sargs, 0, s));
+    return FG_OK;
+  }
 
   if (o.mode == FG_MODE_PUSH && o.async_levels > 1 && !srcs) {
     // asynchronous push: keys, the team's launch, outputs and record, and

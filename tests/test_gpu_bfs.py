@@ -218,3 +218,60 @@ def test_workspace_alignment_checked(fg, orc):
     fg.bfs_into(g, 0, depth, None, fg.bfs_opts(), ws=big[256:256 + need])
     assert np.array_equal(to_np(depth), orc.bfs(off, col, 0)[0])
     g.close()
+
+
+def _hubs(orc, n, edges, degs, seed):
+    """Random graph of n vertices with rows of about the given lengths."""
+    rng = np.random.default_rng(seed)
+    u = [rng.integers(0, n, edges).astype(np.int32)]
+    v = [rng.integers(0, n, edges).astype(np.int32)]
+    for i, d in enumerate(degs):
+        hub = (i * 37 + 5) % n
+        to = rng.permutation(n)[:d].astype(np.int32)
+        u.append(np.full(len(to), hub, np.int32))
+        v.append(to)
+    return orc.csr_from_edges(n, np.concatenate(u), np.concatenate(v))
+
+
+# one workgroup up to 32768 vertices (direction-optimizing) and up to 20480
+# vertices and 2^18 entries (push, and a direction rule above 1); both sides
+# of each bound, rows at and past the length that all waves share (256), rows
+# that a pull reads past its 4th and 16th entry
+@pytest.mark.parametrize("n,edges,degs", [
+    (1, 0, []), (2, 1, []), (33, 20, []), (64, 300, []), (1025, 900, [255, 256, 257, 1000]),
+    (5000, 40000, [4999, 3000, 700]), (20480, 30000, [300]), (20481, 30000, [300]),
+    (16384, 127000, []), (16384, 135000, []), (32767, 40000, [20000]), (32768, 400000, [32767]),
+    (32769, 40000, []), (9000, 4000, [9, 17, 64, 80, 81] * 20)])
+def test_one_workgroup(fg, orc, n, edges, degs):
+    off, col = _hubs(orc, n, edges, degs, seed=n + edges)
+    g = fg.Graph(off, col)
+    m = len(col)
+    for src in sorted({0, 5 % n, n - 1}):
+        st = check_bfs(fg, orc, g, off, col, src, "do")
+        assert (st.grid_blocks == 1) == (n <= 32768 and m <= 1 << 21)
+        st = check_bfs(fg, orc, g, off, col, src, "push")
+        assert (st.grid_blocks == 1) == (n <= 20480 and m <= 1 << 18)
+        st = check_bfs(fg, orc, g, off, col, src, "do", do_a=(1000, 1), do_b=(1, 10))
+        assert (st.grid_blocks == 1) == (n <= 32768 and m <= 1 << 18)
+        # pulls and pushes in turn
+        check_bfs(fg, orc, g, off, col, src, "do", do_a=(1, 100000), do_b=(10, 1))
+        st = check_bfs(fg, orc, g, off, col, src, "do", team_blocks=2)
+        assert st.grid_blocks > 1
+    depth, parent, st = fg.bfs(g, 0, mode=MODES["push"], parents=False)
+    assert parent is None and np.array_equal(to_np(depth), orc.bfs(off, col, 0)[0])
+    depth, parent, st = fg.bfs(g, 0, parents=False)
+    assert parent is None and np.array_equal(to_np(depth), orc.bfs(off, col, 0)[0])
+    g.close()
+
+
+def test_one_workgroup_long_diameter(fg, orc):
+    """More levels than the record traces, on both kinds of visited set."""
+    for rows, cols in ((1, 20480), (3, 6000), (2, 16384)):
+        off, col = synth.grid_csr(rows, cols)
+        g = fg.Graph(off, col)
+        for mode in ("do", "push"):
+            st = check_bfs(fg, orc, g, off, col, cols // 3, mode)
+            assert (st.grid_blocks == 1) == (mode == "do" or g.n <= 20480)
+            if mode == "push":
+                assert st.edges_inspected == len(col)
+        g.close()
