@@ -14,8 +14,9 @@
 // one gather per frontier vertex.
 //
 // fg_package is stable: each peer buffer lists its vertices in frontier
-// order.  Three kernels: per-tile bucket counts, a scan of the tile counts,
-// and a scatter that ranks entries inside each tile with wave ballots.
+// order.  Per-tile bucket counts, then a scatter that ranks entries inside
+// each tile with wave ballots; the tiles' bases are added up by the scatter
+// itself, on very long frontiers by a scan kernel between the two.
 #include <string.h>
 
 #include <vector>
@@ -36,7 +37,17 @@ struct fg_share {
 namespace {
 
 constexpr int KB = 1024;        // threads per block
-constexpr int TILE = 4 * KB;    // frontier entries per tile
+constexpr int PER = 4;          // frontier entries per thread of a tile
+constexpr int TILE = PER * KB;  // frontier entries per tile
+// Where the tiles' counts (tiles of SPER entries per thread, times nparts) are
+// at most SELF_CNTS, each tile adds up those before it by itself instead of
+// a scan kernel in between (16-bit counts, so the twice as many tiles need no
+// more workspace).  2 partitions, with the scan and without: 0.52 M entries
+// (4 partitions) 15.7 and 11.0 us, 1 M 44.1 and 41.7, 4.2 M 151 and 149,
+// 9.4 M 330 and 325, 25 M 948 and 944.  A tile's sum reads up to 64 KB; past
+// that the sums, whose total grows with the square, are left to the scan.
+constexpr int SPER = 2;
+constexpr int64_t SELF_CNTS = 32768;
 constexpr int MAXP = 16;        // partitions (owner fits 4 bits)
 
 // Frontier length: the host value, or the smaller of it and the device-
@@ -47,25 +58,53 @@ __device__ __forceinline__ int32_t eff_len(int32_t len, const int32_t* len_dev) 
   return d < len ? (d < 0 ? 0 : d) : len;
 }
 
-__global__ void pkg_count_kernel(const int32_t* __restrict__ frontier, int32_t hlen,
-                                 const int32_t* __restrict__ len_dev,
-                                 const uint32_t* __restrict__ route, int32_t n_local,
-                                 int32_t part, int32_t nparts, int32_t* __restrict__ tile_cnt) {
+// A thread's entries of a tile: place j * KB + threadIdx.x of the tile for j in
+// [0, PER), their bucket (-1 past the end) and route word, all loads of a kind
+// in flight together (places past the end read the tile's first entry).
+template <int PER>
+__device__ __forceinline__ void tile_entries(const int32_t* __restrict__ frontier, int32_t len,
+                                             const uint32_t* __restrict__ route, int32_t n_local,
+                                             int32_t part, int64_t t0, int32_t (&v)[PER],
+                                             uint32_t (&r)[PER], int32_t (&b)[PER]) {
+#pragma unroll
+  for (int j = 0; j < PER; ++j) {
+    const int64_t i = t0 + j * KB + threadIdx.x;
+    b[j] = i < len ? part : -1;
+    v[j] = frontier[i < len ? i : t0];
+  }
+  // hosted vertices need no table: their lanes read entry 0 together
+#pragma unroll
+  for (int j = 0; j < PER; ++j) r[j] = route[v[j] >= n_local ? v[j] : 0];
+#pragma unroll
+  for (int j = 0; j < PER; ++j)
+    if (b[j] >= 0 && v[j] >= n_local) b[j] = (int32_t)(r[j] >> 28);
+}
+
+// Bucket counts of each tile of PER * KB entries.
+template <int PER, class C>
+__global__ __launch_bounds__(KB) void pkg_count_kernel(
+    const int32_t* __restrict__ frontier, int32_t hlen, const int32_t* __restrict__ len_dev,
+    const uint32_t* __restrict__ route, int32_t n_local, int32_t part, int32_t nparts,
+    C* __restrict__ tile_cnt) {
   __shared__ int32_t cnt[MAXP];
   const int32_t len = eff_len(hlen, len_dev);
   if (threadIdx.x < MAXP) cnt[threadIdx.x] = 0;
   __syncthreads();
-  const int64_t t0 = (int64_t)blockIdx.x * TILE;
-  for (int j = 0; j < TILE / KB; ++j) {
-    const int64_t i = t0 + j * KB + threadIdx.x;
-    if (i < len) {
-      const int32_t v = frontier[i];
-      const int32_t b = v < n_local ? part : (int32_t)(route[v] >> 28);
-      atomicAdd(&cnt[b], 1);
+  const int64_t t0 = (int64_t)blockIdx.x * PER * KB;
+  if (t0 < len) {
+    int32_t v[PER], b[PER];
+    uint32_t r[PER];
+    tile_entries<PER>(frontier, len, route, n_local, part, t0, v, r, b);
+    for (int p = 0; p < nparts; ++p) {
+      int32_t c = 0;
+#pragma unroll
+      for (int j = 0; j < PER; ++j) c += __popcll(__ballot(b[j] == p));
+      if (fg_lane() == 0 && c) atomicAdd(&cnt[p], c);
     }
   }
   __syncthreads();
-  if (threadIdx.x < nparts) tile_cnt[(int64_t)blockIdx.x * nparts + threadIdx.x] = cnt[threadIdx.x];
+  if (threadIdx.x < nparts)
+    tile_cnt[(int64_t)blockIdx.x * nparts + threadIdx.x] = (C)cnt[threadIdx.x];
 }
 
 // In place exclusive scan of tile counts per bucket; totals to counts[].
@@ -94,69 +133,118 @@ __global__ void pkg_scan_kernel(int32_t tiles, int32_t nparts, int32_t* __restri
   }
 }
 
-__global__ void pkg_scatter_kernel(const int32_t* __restrict__ frontier, int32_t hlen,
-                                   const int32_t* __restrict__ len_dev,
-                                   const uint32_t* __restrict__ route,
-                                   const int32_t* __restrict__ l2g, int32_t n_local, int32_t part,
-                                   int32_t nparts, const int32_t* __restrict__ depth,
-                                   const int32_t* __restrict__ parent,
-                                   const int32_t* __restrict__ tile_base, int64_t cap,
-                                   int32_t* __restrict__ ids_out, int32_t* __restrict__ depth_out,
-                                   int32_t* __restrict__ parent_out,
-                                   int32_t* __restrict__ local_out) {
-  __shared__ int32_t wcnt[KB / FG_WAVE][MAXP];
-  __shared__ int32_t run[MAXP];
+// Ranks a tile's entries per bucket and writes them out.  SELF: the tile adds
+// up the counts of the tiles before it by itself (beside its own loads) and
+// the last tile writes the totals; otherwise tile_base holds scanned counts.
+// Bound by the gathers (route, depth, parent and l2g of vertices in any
+// order) and by the trips one after another: all of a thread's entries are in
+// flight together, and the ranking takes two barriers for the tile (with
+// four rounds of 1024, three barriers each, and 131 tiles of 4096 it took
+// 19 us for 0.54 M entries, as 512 threads of four entries 17.6; the whole
+// call 33.7 -> 27.7 us, 60 000 entries in 8 partitions 28.1 -> 15.7.  256
+// threads of eight entries: 29.0 and 18.5 for the two calls).
+template <int PER, class C, bool SELF>
+__global__ __launch_bounds__(KB) void pkg_scatter_kernel(
+    const int32_t* __restrict__ frontier, int32_t hlen, const int32_t* __restrict__ len_dev,
+    const uint32_t* __restrict__ route, const int32_t* __restrict__ l2g, int32_t n_local,
+    int32_t part, int32_t nparts, const int32_t* __restrict__ depth,
+    const int32_t* __restrict__ parent, const C* __restrict__ tile_base, int64_t cap,
+    int32_t* __restrict__ ids_out, int32_t* __restrict__ depth_out,
+    int32_t* __restrict__ parent_out, int32_t* __restrict__ local_out,
+    int32_t* __restrict__ counts, int32_t* __restrict__ local_count) {
+  constexpr int W = KB / FG_WAVE;
+  static_assert(PER * W <= FG_WAVE, "one lane per wave and entry of a tile");
+  __shared__ int32_t wcnt[MAXP][PER * W];  // entries per bucket, by place and wave; then their prefix
+  __shared__ int32_t base[MAXP];
   const int32_t len = eff_len(hlen, len_dev);
   const int lane = fg_lane();
   const int wid = threadIdx.x / FG_WAVE;
-  if (threadIdx.x < MAXP) run[threadIdx.x] = threadIdx.x < nparts
-                                                 ? tile_base[(int64_t)blockIdx.x * nparts + threadIdx.x]
-                                                 : 0;
-  const int64_t t0 = (int64_t)blockIdx.x * TILE;
-  for (int j = 0; j < TILE / KB; ++j) {
-    const int64_t i = t0 + j * KB + threadIdx.x;
-    int32_t v = 0, b = -1;
-    uint32_t r = 0;
-    if (i < len) {
-      v = frontier[i];
-      if (v < n_local) {
-        b = part;
+  const int64_t t0 = (int64_t)blockIdx.x * PER * KB;
+  const bool last = SELF && blockIdx.x == gridDim.x - 1;
+  if (t0 >= len && !last) return;
+  if (threadIdx.x < MAXP) base[threadIdx.x] = 0;
+  int32_t v[PER], b[PER], dv[PER], pg[PER], in_wave[PER];
+  uint32_t r[PER];
+  if (t0 < len) {
+    tile_entries<PER>(frontier, len, route, n_local, part, t0, v, r, b);
+#pragma unroll
+    for (int j = 0; j < PER; ++j) dv[j] = depth[v[j] >= n_local ? v[j] : 0];
+    if (parent_out) {
+#pragma unroll
+      for (int j = 0; j < PER; ++j) pg[j] = parent[v[j] >= n_local ? v[j] : 0];
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < PER; ++j) b[j] = -1;
+  }
+  // rank within the wave for each entry's bucket, and per-wave totals
+#pragma unroll
+  for (int j = 0; j < PER; ++j) in_wave[j] = 0;
+  for (int p = 0; p < nparts; ++p) {
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      const uint64_t m = __ballot(b[j] == p);
+      if (b[j] == p) in_wave[j] = fg_mbcnt(m);
+      if (lane == 0) wcnt[p][j * W + wid] = __popcll(m);
+    }
+  }
+  __syncthreads();
+  if (SELF) {
+    // threads in rows of nparts: each adds up its bucket over every
+    // (KB / nparts)-th tile before this one
+    const int rows = KB / nparts;
+    const int p = threadIdx.x % nparts, r0 = threadIdx.x / nparts;
+    int32_t s = 0;
+    if (r0 < rows)
+      for (int64_t t = r0; t < blockIdx.x; t += rows) s += (int32_t)tile_base[t * nparts + p];
+    if (s) atomicAdd(&base[p], s);
+  } else if (threadIdx.x < nparts) {
+    base[threadIdx.x] = (int32_t)tile_base[(int64_t)blockIdx.x * nparts + threadIdx.x];
+  }
+  int32_t own = 0;
+  for (int p = wid; p < nparts; p += W) {
+    const int32_t c = lane < PER * W ? wcnt[p][lane] : 0;
+    const int32_t incl = fg_wave_incl_scan(c);
+    if (lane < PER * W) wcnt[p][lane] = incl - c;
+    // a wave has at most MAXP / W buckets; lane k keeps the k-th one's total
+    const int32_t all = __builtin_amdgcn_readlane(incl, FG_WAVE - 1);
+    if (lane == p / W) own = all;
+  }
+  if (parent_out && t0 < len) {
+    // only the parents of entries that leave are looked up (others may hold
+    // anything)
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      if (b[j] < 0 || b[j] == part) pg[j] = -1;
+      const int32_t g = l2g[pg[j] >= 0 ? pg[j] : 0];
+      pg[j] = pg[j] >= 0 ? g : -1;
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < PER; ++j) {
+    if (b[j] < 0) continue;
+    const int32_t pos = base[b[j]] + wcnt[b[j]][j * W + wid] + in_wave[j];
+    if (b[j] == part) {
+      if (local_out) local_out[pos] = v[j];
+    } else {
+      const int64_t slot = (int64_t)b[j] * cap + pos;
+      ids_out[slot] = (int32_t)(r[j] & 0x0FFFFFFFu);
+      depth_out[slot] = dv[j];
+      if (parent_out) parent_out[slot] = pg[j];
+    }
+  }
+  if (last) {
+    const int p = wid + lane * W;
+    if (p < nparts) {
+      const int32_t all = base[p] + own;
+      if (p == part) {
+        counts[p] = 0;
+        if (local_count) *local_count = all;
       } else {
-        r = route[v];
-        b = (int32_t)(r >> 28);
+        counts[p] = all;
       }
     }
-    // rank within the wave for this lane's bucket, and per-wave bucket totals
-    int32_t in_wave = 0;
-    for (int p = 0; p < nparts; ++p) {
-      const uint64_t m = __ballot(b == p);
-      if (b == p) in_wave = fg_mbcnt(m);
-      if (lane == 0) wcnt[wid][p] = __popcll(m);
-    }
-    __syncthreads();
-    int32_t before = 0;
-    if (b >= 0) {
-      for (int w = 0; w < wid; ++w) before += wcnt[w][b];
-    }
-    const int32_t pos = (b >= 0 ? run[b] : 0) + before + in_wave;
-    if (b == part) {
-      if (local_out) local_out[pos] = v;
-    } else if (b >= 0) {
-      const int64_t slot = (int64_t)b * cap + pos;
-      ids_out[slot] = (int32_t)(r & 0x0FFFFFFFu);
-      depth_out[slot] = depth[v];
-      if (parent_out) {
-        const int32_t pv = parent[v];
-        parent_out[slot] = pv >= 0 ? l2g[pv] : -1;
-      }
-    }
-    __syncthreads();
-    if (threadIdx.x < nparts) {
-      int32_t s = 0;
-      for (int w = 0; w < KB / FG_WAVE; ++w) s += wcnt[w][threadIdx.x];
-      run[threadIdx.x] += s;
-    }
-    __syncthreads();
   }
 }
 
@@ -422,18 +510,30 @@ extern "C" fg_status fg_package(const fg_share* s, const int32_t* frontier, int3
     return fg_set_error(FG_ENOMEM, "fg_package: workspace of %zu bytes < required %zu", ws_bytes,
                         need);
   hipStream_t hs = (hipStream_t)stream;
+  int32_t* parent_out = parent ? out->parent : nullptr;
+  const int64_t small = ((int64_t)len + SPER * KB - 1) / (SPER * KB);
+  if (len > 0 && small * s->nparts <= SELF_CNTS) {
+    uint16_t* cnt = (uint16_t*)ws;
+    pkg_count_kernel<SPER, uint16_t><<<(int)small, KB, 0, hs>>>(frontier, len, len_dev, s->route, s->n_local,
+                                                    s->part, s->nparts, cnt);
+    pkg_scatter_kernel<SPER, uint16_t, true><<<(int)small, KB, 0, hs>>>(
+        frontier, len, len_dev, s->route, s->l2g, s->n_local, s->part, s->nparts, depth, parent,
+        cnt, out->capacity, out->ids, out->depth, parent_out, out->local, out->counts,
+        out->local_count);
+    FG_HIP_TRY(hipGetLastError());
+    return FG_OK;
+  }
   const int32_t tiles = (int32_t)(((int64_t)len + TILE - 1) / TILE);
   int32_t* tile_cnt = (int32_t*)ws;
   if (tiles > 0)
-    pkg_count_kernel<<<tiles, KB, 0, hs>>>(frontier, len, len_dev, s->route, s->n_local,
-                                           s->part, s->nparts, tile_cnt);
+    pkg_count_kernel<PER, int32_t><<<tiles, KB, 0, hs>>>(frontier, len, len_dev, s->route, s->n_local,
+                                               s->part, s->nparts, tile_cnt);
   pkg_scan_kernel<<<1, KB, 0, hs>>>(tiles, s->nparts, tile_cnt, out->counts, s->part,
                                     out->local_count);
   if (tiles > 0)
-    pkg_scatter_kernel<<<tiles, KB, 0, hs>>>(frontier, len, len_dev, s->route, s->l2g, s->n_local,
-                                             s->part, s->nparts, depth, parent, tile_cnt, out->capacity,
-                                             out->ids, out->depth, parent ? out->parent : nullptr,
-                                             out->local);
+    pkg_scatter_kernel<PER, int32_t, false><<<tiles, KB, 0, hs>>>(
+        frontier, len, len_dev, s->route, s->l2g, s->n_local, s->part, s->nparts, depth, parent,
+        tile_cnt, out->capacity, out->ids, out->depth, parent_out, out->local, nullptr, nullptr);
   FG_HIP_TRY(hipGetLastError());
   return FG_OK;
 }

@@ -113,3 +113,28 @@ def test_config_rmat24_quarter_share(fg, orc):
     for k in range(len(cnt) - 1):
         fr = np.flatnonzero(depth == k + 1).astype(np.int32)
         check_package(fg, orc, sh, want, fr, depth, parent, 4)
+
+
+# the tile of 2048 entries (16-bit counts, summed by the tiles themselves) at
+# its edges, up to 32768 counts and past them (tiles of 4096 and a scan
+# between), 16 partitions and 1
+@pytest.mark.parametrize("n,nparts,lens", [
+    (70000, 16, (0, 1, 63, 64, 511, 513, 2047, 2048, 2049, 6143, 70000)),
+    (3000, 1, (1, 2049, 3000)), (9000, 3, (8999,)),
+    (5_000_000, 16, (2048 * 2048, 2048 * 2048 + 1))])
+def test_package_tiles(fg, orc, n, nparts, lens):
+    rng = np.random.default_rng(n)
+    u, v = (rng.integers(0, n, 2 * n).astype(np.int32) for _ in range(2))
+    off, col = orc.csr_from_edges(n, u, v)
+    owner = rng.integers(0, nparts, n).astype(np.uint8)
+    owner[rng.random(n) < 0.9 * (n > 1 << 20)] = nparts - 1
+    sh, want = check_share(fg, orc, off, col, owner, nparts, nparts - 1)
+    nt = want["n_total"]
+    assert max(lens) <= nt or n < 1 << 20
+    depth = rng.integers(0, 9, nt).astype(np.int32)
+    parent = rng.integers(-1, nt, nt).astype(np.int32)
+    # a vertex without a parent leaves with -1: the word before l2g[0]
+    want["l2g"] = np.concatenate([np.int32([-1]), want["l2g"]])[1:]
+    for L in lens:
+        fr = rng.permutation(nt)[:min(L, nt)].astype(np.int32)
+        check_package(fg, orc, sh, want, fr, depth, parent, nparts)
