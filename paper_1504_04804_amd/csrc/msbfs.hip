@@ -68,8 +68,7 @@ struct MsState {
   ull live;        // lanes with a non-empty current frontier
   ull used;        // lanes admitted at least once
   int32_t start[MAXL];
-  ull edges;  // adjacency entries read since open (push: whole lists; pull:
-              // up to the early exit)
+  ull edges;  // adjacency entries read since open
   ull verts;  // vertex visits since open (push: active; pull: every vertex)
   int32_t aborted;  // a step stopped early (a workgroup wait hit its limit)
   int32_t pad[11];
@@ -132,6 +131,7 @@ struct MsParams {
   int32_t push_div;  // pull -> push when active vertices < n / push_div
   int32_t team;      // workgroups of a team (<= 1: no team mode)
   int64_t team_e;    // largest frontier degree sum a team takes
+  int32_t has_long;  // the graph has rows of more than LONG_PULL entries
 };
 
 struct Lds {
@@ -141,6 +141,7 @@ struct Lds {
   int32_t w_sc[PWAVES][FG_WAVE];
   int32_t w_u[PWAVES][FG_WAVE];
   int32_t w_b[PWAVES][FG_WAVE];
+  FlushLds<PWAVES> fl;
   int64_t red[PWAVES + 1];
   int32_t red32[PWAVES + 1];
   ull redu[PWAVES + 1];
@@ -212,7 +213,38 @@ __device__ __forceinline__ bool claim(const MsParams& P, ull* Fn, int32_t v, ull
   return atomicOr(&Fn[v], nw) == 0ull;
 }
 
-// ---- push expansion (scan-gather for low degree, descriptors for high)
+// claim() for four edges per lane (v[r] < 0: none) with the checks, the
+// test-and-sets and the next-word atomics of the four in flight together.
+__device__ __forceinline__ void claim4(const MsParams& P, ull* Fn, const int32_t (&v)[4],
+                                       const ull (&fu)[4], int32_t it1, const int32_t* start,
+                                       ull& got, bool (&first)[4]) {
+  ull nw[4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) nw[r] = v[r] >= 0 ? fu[r] & ~P.visit[v[r]] : 0ull;
+#pragma unroll
+  for (int r = 0; r < 4; ++r)
+    if (nw[r]) nw[r] &= ~atomicOr(&P.visit[v[r]], nw[r]);
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    first[r] = false;
+    if (nw[r]) first[r] = atomicOr(&Fn[v[r]], nw[r]) == 0ull;
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    got |= nw[r];
+    ull bits = nw[r];
+    while (bits) {
+      const int l = __builtin_ctzll(bits);
+      bits &= bits - 1;
+      P.depth[(int64_t)l * P.n + v[r]] = it1 - start[l];
+    }
+  }
+}
+
+// ---- push expansion (scan-gather for low degree, descriptors for high).
+// The list is dealt in pieces of at least a quarter of a wave's share,
+// consecutive pieces to different workgroups; a workgroup's staged entries
+// are flushed with one atomic per counter.
 __device__ void push_expand(const MsParams& P, const MsState& S, int32_t k, int64_t qlen,
                             ull qbase, ull dbase, Lds& L, ull& got, uint32_t& ecnt, uint32_t& vcnt) {
   const int lane = fg_lane();
@@ -229,13 +261,14 @@ __device__ void push_expand(const MsParams& P, const MsState& S, int32_t k, int6
   CtrSlot& C = P.ctl->slot[k & 1];
   WaveStage<int32_t, STAGE> st{L.stage[wid], 0};
   WaveStage<int4, DSTAGE> dst{L.dstage[wid], 0};
-  const int64_t gw = (int64_t)blockIdx.x * PWAVES + wid;
   const int64_t W = (int64_t)gridDim.x * PWAVES;
-  for (int64_t base = gw * FG_WAVE; base < qlen; base += W * FG_WAVE) {
+  const int64_t fair = (qlen + 4 * W - 1) / (4 * W);
+  const int64_t per = fair < FG_WAVE ? fair : FG_WAVE;
+  for (int64_t base = ((int64_t)wid * gridDim.x + blockIdx.x) * per; base < qlen; base += W * per) {
     const int64_t i = base + lane;
     int32_t u = 0, b = 0, deg = 0;
     ull fu = 0;
-    if (i < qlen) {
+    if (lane < per && i < qlen) {
       u = Qin[i];
       b = P.off[u];
       deg = P.off[u + 1] - b;
@@ -276,55 +309,132 @@ __device__ void push_expand(const MsParams& P, const MsState& S, int32_t k, int6
     sb[lane] = b;
     sf[lane] = fu;
     wave_lds_fence();
-    for (int32_t t0 = 0; t0 < T; t0 += FG_WAVE) {
-      const int32_t t = t0 + lane;
-      bool first = false;
-      int32_t v = 0;
-      if (t < T) {
-        const int32_t j = upper_idx(sc, FG_WAVE, t);
-        v = P.col[sb[j] + (t - sc[j])];
-        first = claim(P, Fn, v, sf[j], it1, L.start, got);
+    for (int32_t t0 = 0; t0 < T; t0 += 4 * FG_WAVE) {
+      int32_t v[4];
+      ull f[4];
+      bool first[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int32_t t = t0 + r * FG_WAVE + lane;
+        const int32_t tc = t < T ? t : T - 1;
+        const int32_t j = upper_idx(sc, FG_WAVE, tc);
+        v[r] = P.col[sb[j] + (tc - sc[j])];
+        f[r] = t < T ? sf[j] : 0ull;
       }
-      st.push(first, v, &C.q.v, qbase, Qout);
+      claim4(P, Fn, v, f, it1, L.start, got, first);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) st.push(first[r], v[r], &C.q.v, qbase, Qout);
     }
   }
-  st.flush(&C.q.v, qbase, Qout);
-  dst.flush(&C.desc.v, dbase, P.desc);
+  ull pos[2];
+  const int32_t cnt[2] = {st.cnt, dst.cnt};
+  ull* const ctr[2] = {&C.q.v, &C.desc.v};
+  ull* const also[2] = {nullptr, nullptr};
+  block_reserve(L.fl, cnt, ctr, also, pos);
+  put_staged(st, pos[0], qbase, Qout);
+  put_staged(dst, pos[1], dbase, P.desc);
 }
 
 __device__ void push_desc(const MsParams& P, const MsState& S, int32_t k, int64_t ndesc,
                           ull qbase, Lds& L, ull& got) {
   const int lane = fg_lane();
   const int wid = threadIdx.x / FG_WAVE;
-  const int64_t gw = (int64_t)blockIdx.x * PWAVES + wid;
   const int64_t W = (int64_t)gridDim.x * PWAVES;
   int32_t* Qout = P.q[S.qsel ^ 1];
   ull* Fn = P.F[S.fsel ^ 1];
   const int32_t it1 = S.it + 1;
   CtrSlot& C = P.ctl->slot[k & 1];
   WaveStage<int32_t, STAGE> st{L.stage[wid], 0};
-  for (int64_t i = gw; i < ndesc; i += W) {
-    const int4 dsc = P.desc[i];
-    const int32_t u = dsc.x;
-    const int32_t e_end = P.off[u + 1];
-    const int32_t e1 = dsc.y + CH < e_end ? dsc.y + CH : e_end;
+  // consecutive descriptors go to different workgroups; the next one is
+  // loaded under the current one, and the columns do not wait for the row's
+  // end (places behind it are loaded and not used)
+  static_assert(CH == 4 * FG_WAVE, "one claim4 per descriptor");
+  int64_t i = (int64_t)wid * gridDim.x + blockIdx.x;
+  int4 nxt = i < ndesc ? P.desc[i] : make_int4(0, 0, 0, 0);
+  for (; i < ndesc; i += W) {
+    const int4 dsc = nxt;
+    if (i + W < ndesc) nxt = P.desc[i + W];
+    const int32_t e_end = P.off[dsc.x + 1];
+    int32_t v[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int64_t e = (int64_t)dsc.y + r * FG_WAVE + lane;
+      v[r] = P.col[e < P.m ? e : P.m - 1];
+    }
     const ull fu = desc_lanes(dsc);
-    int32_t vv[CH / FG_WAVE];
+    ull f[4];
+    bool first[4];
 #pragma unroll
-    for (int r = 0; r < CH / FG_WAVE; ++r) {
-      const int32_t e = dsc.y + r * FG_WAVE + lane;
-      vv[r] = e < e1 ? P.col[e] : -1;
-    }
+    for (int r = 0; r < 4; ++r) f[r] = (int64_t)dsc.y + r * FG_WAVE + lane < e_end ? fu : 0ull;
+    claim4(P, Fn, v, f, it1, L.start, got, first);
 #pragma unroll
-    for (int r = 0; r < CH / FG_WAVE; ++r) {
-      const int32_t v = vv[r];
-      const bool first = v >= 0 && claim(P, Fn, v, fu, it1, L.start, got);
-      st.push(first, v, &C.q.v, qbase, Qout);
-    }
+    for (int r = 0; r < 4; ++r) st.push(first[r], v[r], &C.q.v, qbase, Qout);
   }
-  st.flush(&C.q.v, qbase, Qout);
+  ull pos[1];
+  const int32_t cnt[1] = {st.cnt};
+  ull* const ctr[1] = {&C.q.v};
+  ull* const also[1] = {nullptr};
+  block_reserve(L.fl, cnt, ctr, also, pos);
+  put_staged(st, pos[0], qbase, Qout);
 }
 
+// Places `pos` on of the long list and `dpos` on of the chunks: a wave's
+// staged long vertices with their CH-entry chunks (the head's four entries
+// left out).  Every lane of the wave must take part.
+__device__ void put_long(const MsParams& P, int32_t* sc, int32_t* su, int32_t* sb,
+                         const int32_t* stage, int32_t cnt, int32_t* Qlong, int64_t pos,
+                         int64_t dpos) {
+  const int lane = fg_lane();
+  for (int32_t i0 = 0; i0 < cnt; i0 += FG_WAVE) {
+    int32_t v = 0, b = 0, nch = 0;
+    if (i0 + lane < cnt) {
+      v = stage[i0 + lane];
+      b = P.off[v] + 4;
+      nch = (P.off[v + 1] - b + CH - 1) / CH;
+      fg_st_shared(&Qlong[pos + i0 + lane], v);
+    }
+    const int32_t inc = fg_wave_incl_scan(nch);
+    const int32_t T = __builtin_amdgcn_readlane(inc, FG_WAVE - 1);
+    wave_lds_fence();
+    sc[lane] = inc - nch;
+    su[lane] = v;
+    sb[lane] = b;
+    wave_lds_fence();
+    for (int32_t t = lane; t < T; t += FG_WAVE) {
+      const int32_t j = upper_idx(sc, FG_WAVE, t);
+      fg_st_shared(&P.desc[dpos + t], make_int4(su[j], sb[j] + (t - sc[j]) * CH, 0, 0));
+    }
+    dpos += T;
+    wave_lds_fence();
+  }
+}
+
+// Rows of the pull with more than the head's four entries and no early end
+// among them, R * 8 further entries each at most: eight lanes take a row, R
+// entries per lane in flight together.  sc / su / sb / sf hold the rows
+// (owner lane, first entry left, end, wanted lanes) at places [0, cnt); the
+// lanes found go back to sf.  Every lane of the wave must take part.
+template <int R>
+__device__ __forceinline__ void pull_rows(const MsParams& P, const ull* Fc, const int32_t* sb,
+                                          const int32_t* se, ull* sf, int32_t cnt) {
+  const int lane = fg_lane();
+  for (int32_t i0 = 0; i0 < cnt; i0 += FG_WAVE / 8) {
+    const int32_t i = i0 + lane / 8;
+    const int32_t ic = i < cnt ? i : cnt - 1;
+    const int32_t b = sb[ic] + lane % 8, e = se[ic];
+    const ull w = sf[ic];
+    int32_t u[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) u[r] = P.col[8 * r < e - b ? b + 8 * r : e - 1];
+    ull x = 0;
+#pragma unroll
+    for (int r = 0; r < R; ++r) x |= Fc[u[r]];
+    x &= w;
+#pragma unroll
+    for (int d = 1; d < 8; d <<= 1) x |= __shfl_xor(x, d, FG_WAVE);
+    if (lane % 8 == 0 && i < cnt) sf[i] = x;
+  }
+}
 
 // ---------------------------------------------------------------- team mode
 //
@@ -727,16 +837,18 @@ __global__ __launch_bounds__(PB) void msbfs_persistent(MsParams P) {
   const int64_t nth = (int64_t)gridDim.x * PB;
   const int lane = fg_lane();
   const int wid = threadIdx.x / FG_WAVE;
-  const int64_t gw = (int64_t)blockIdx.x * PWAVES + wid;
   const int64_t W = (int64_t)gridDim.x * PWAVES;
-  MsState S = *P.state;  // read by every workgroup before anyone writes it
-  bool ok = gs.sync(&L.flag);
+  const int64_t gwm = (int64_t)wid * gridDim.x + blockIdx.x;  // consecutive ones in different workgroups
+  // the scalars are read by every workgroup before anyone writes them: the
+  // last workgroup out does (start[] is read behind the admissions' barrier)
+  MsState S = *P.state;
+  bool ok = true;
   // per-parity bases of the monotone counters, as scalars (a dynamically
   // indexed array would live in scratch memory)
   ull qb0 = 0, qb1 = 0, db0 = 0, db1 = 0, cb0 = 0, cb1 = 0;
 
   // ---- admissions: clear reused lanes, fill their depth rows, seed sources
-  if (ok && P.npend > 0) {
+  if (P.npend > 0) {
     ull mask = 0;
     for (int i = 0; i < P.npend; ++i) mask |= 1ull << P.pend_lane[i];
     const ull reused = mask & S.used;
@@ -746,30 +858,46 @@ __global__ __launch_bounds__(PB) void msbfs_persistent(MsParams P) {
         P.F[0][v] &= ~reused;
         P.F[1][v] &= ~reused;
       }
+      ok = gs.sync(&L.flag);
     }
+    // rows -1 but at their source, whole 16-byte words between the ends
     for (int i = 0; i < P.npend; ++i) {
       int32_t* row = P.depth + (int64_t)P.pend_lane[i] * P.n;
-      for (int64_t v = tid; v < P.n; v += nth) row[v] = -1;
-    }
-    ok = gs.sync(&L.flag);
-    if (ok && tid == 0) {
-      MsState* st = P.state;
-      int64_t ql = S.qlen;
-      for (int i = 0; i < P.npend; ++i) {
-        const int32_t l = P.pend_lane[i], s = P.pend_src[i];
-        const ull bit = 1ull << l;
-        P.visit[s] |= bit;
-        if (S.mode == 0 && P.F[S.fsel][s] == 0ull) P.q[S.qsel][ql++] = s;
-        P.F[S.fsel][s] |= bit;
-        P.depth[(int64_t)l * P.n + s] = 0;
-        st->start[l] = S.it;
+      const int32_t s = P.pend_src[i];
+      const int64_t lead = (-((intptr_t)row >> 2)) & 3;
+      const int64_t h = lead < P.n ? lead : P.n;
+      const int64_t n4 = (P.n - h) / 4;
+      int4* r4 = (int4*)(row + h);
+      const int64_t s4 = s >= h ? (s - h) >> 2 : -1;
+      for (int64_t q = tid; q < n4; q += nth) {
+        int4 x = make_int4(-1, -1, -1, -1);
+        if (q == s4) ((int32_t*)&x)[(s - h) & 3] = 0;
+        r4[q] = x;
       }
-      if (S.mode == 1) ql = S.qlen + P.npend;  // pull: an estimate is enough
-      S.qlen = ql;
-      S.live |= mask;
-      S.used |= mask;
-      P.ctl->pub_qlen = ql;
-      P.ctl->pub_live = S.live;
+      if (tid < h) row[tid] = tid == s ? 0 : -1;
+      const int64_t t = h + 4 * n4 + tid;
+      if (t < P.n) row[t] = t == s ? 0 : -1;
+    }
+    if (ok && blockIdx.x == 0 && wid == 0) {
+      // a lane per query (their words, in the same wave, with atomics: two
+      // may have one source)
+      MsState* st = P.state;
+      bool fresh = false;
+      int32_t s = 0;
+      if (lane < P.npend) {
+        const int32_t l = P.pend_lane[lane];
+        s = P.pend_src[lane];
+        atomicOr(&P.visit[s], 1ull << l);
+        fresh = atomicOr(&P.F[S.fsel][s], 1ull << l) == 0ull;
+        fg_st_shared(&st->start[l], S.it);
+      }
+      const uint64_t fm = __ballot(fresh);
+      if (S.mode == 0 && fresh) fg_st_shared(&P.q[S.qsel][S.qlen + fg_mbcnt(fm)], s);
+      if (lane == 0) {
+        // pull: an estimate is enough
+        P.ctl->pub_qlen = S.qlen + (S.mode == 1 ? P.npend : __popcll(fm));
+        P.ctl->pub_live = S.live | mask;
+      }
     }
     ok = ok && gs.sync(&L.flag);
     S.qlen = P.ctl->pub_qlen;
@@ -872,7 +1000,7 @@ __global__ __launch_bounds__(PB) void msbfs_persistent(MsParams P) {
       const ull* Fc = P.F[S.fsel];
       ull* Fn = P.F[S.fsel ^ 1];
       WaveStage<int32_t, STAGE> st{L.stage[wid], 0};
-      for (int64_t v0 = gw * FG_WAVE; v0 < P.n; v0 += W * FG_WAVE) {
+      for (int64_t v0 = gwm * FG_WAVE; v0 < P.n; v0 += W * FG_WAVE) {
         const int64_t v = v0 + lane;
         bool act = false;
         if (v < P.n) {
@@ -881,7 +1009,12 @@ __global__ __launch_bounds__(PB) void msbfs_persistent(MsParams P) {
         }
         st.push(act, (int32_t)v, &C.cnt.v, cbp, P.q[S.qsel]);
       }
-      st.flush(&C.cnt.v, cbp, P.q[S.qsel]);
+      ull pos[1];
+      const int32_t cnt[1] = {st.cnt};
+      ull* const ctr[1] = {&C.cnt.v};
+      ull* const also[1] = {nullptr};
+      block_reserve(L.fl, cnt, ctr, also, pos);
+      put_staged(st, pos[0], cbp, P.q[S.qsel]);
       if (!(ok = gs.sync_acquire(&L.flag))) break;
       const ull ct = fg_atomic_load_u64(&C.cnt.v);
       S.qlen = (int64_t)(ct - cbp);
@@ -889,16 +1022,27 @@ __global__ __launch_bounds__(PB) void msbfs_persistent(MsParams P) {
       S.mode = 0;
     }
     if (want_pull) {
-      // ---- pull: lane per vertex, early exit when every wanted lane is
-      // seen.  The first four neighbours come from the head table (one
-      // coalesced load); lists of up to 32 go on four entries at a time,
-      // longer ones are scanned by the whole wave, 64 entries per step.
+      // ---- pull: lane per vertex.  The first four neighbours come from the
+      // head table (one coalesced load); where they do not cover the wanted
+      // lanes, rows of up to LONG_PULL entries are compacted and read by eight
+      // lanes each (four entries at a time by their own lane, up to seven
+      // dependent trips, and one row after another from 33 entries on, the
+      // first pull of R-MAT 20 with 64 lanes took 255 us; 179 now, the gather
+      // rate of a frontier word table twice an L2), longer ones are listed and
+      // cut into CH-entry chunks.  The lists' entries take one atomic per
+      // counter and workgroup, not per wave and 64 vertices.
       const ull* Fc = P.F[S.fsel];
       ull* Fn = P.F[S.fsel ^ 1];
       int32_t* Qlong = P.q[S.qsel ^ 1];  // queues are idle while pulling
       ull lor = 0;
       int32_t act = 0;
-      for (int64_t v0 = gw * FG_WAVE; v0 < P.n; v0 += W * FG_WAVE) {
+      WaveStage<int32_t, STAGE> lst{L.stage[wid], 0};  // long vertices
+      int32_t lch = 0;                                 // ... their chunks
+      // at most one piece per wave: spread over the workgroups; more: a
+      // workgroup's pieces adjacent (grid 400 x 500, 64 lanes: 9.27 ms
+      // spread, 9.05 adjacent; R-MAT of 60 000, 30 lanes: 454 and 463 us)
+      const int64_t first = P.n <= W * FG_WAVE ? gwm : (int64_t)blockIdx.x * PWAVES + wid;
+      for (int64_t v0 = first * FG_WAVE; v0 < P.n; v0 += W * FG_WAVE) {
         const int64_t v = v0 + lane;
         ull vis = ~0ull, nw = 0;
         int32_t b = 0, e = 0;
@@ -917,43 +1061,47 @@ __global__ __launch_bounds__(PB) void msbfs_persistent(MsParams P) {
           const ull f0 = Fc[hd.x], f1 = Fc[hd.y], f2 = Fc[hd.z], f3 = Fc[hd.w];
           nw = (f0 | (d > 1 ? f1 : 0ull) | (d > 2 ? f2 : 0ull) | (d > 3 ? f3 : 0ull)) & want;
         }
-        bool shortl = want && nw != want && e - b > 4 && e - b <= 32;
-        for (int32_t i0 = 4; i0 < 32 && __ballot(shortl); i0 += 4) {
-          if (shortl) {
-            const int32_t i = b + i0, l = e - 1;
-            const int32_t u0 = P.col[i], u1 = P.col[i + 1 < l ? i + 1 : l],
-                          u2 = P.col[i + 2 < l ? i + 2 : l], u3 = P.col[i + 3 < l ? i + 3 : l];
-            const ull g = Fc[u0] | Fc[u1] | Fc[u2] | Fc[u3];
-            ecnt += (uint32_t)(e - i < 4 ? e - i : 4);
-            nw |= g & want;
-            if (nw == want || i + 4 >= e) shortl = false;
-          }
-        }
-        const bool lng = want && nw != want && e - b > LONG_PULL;
-        if (lng) {
+        const bool more = want && nw != want && e - b > 4;
+        const bool lng = more && e - b > LONG_PULL;
+        const uint64_t lm = __ballot(lng);
+        if (lm) {
           // listed for the chunked scan; the lanes found so far stay in Fn
-          const int32_t nch = (e - b - 4 + CH - 1) / CH;
-          fg_st_shared(&Qlong[atomicAdd(&C.q.v, 1ull) - qbp], (int32_t)v);
-          const int64_t d0 = (int64_t)(atomicAdd(&C.desc.v, (ull)nch) - dbp);
-          for (int32_t c = 0; c < nch; ++c)
-            fg_st_shared(&P.desc[d0 + c], make_int4((int32_t)v, b + 4 + c * CH, 0, 0));
-        }
-        uint64_t pend = __ballot(want && nw != want && e - b > 32 && !lng);
-        while (pend) {
-          const int l = __builtin_ctzll(pend);
-          pend &= pend - 1;
-          const int32_t lb = __builtin_amdgcn_readlane(b, l) + 4;
-          const int32_t le = __builtin_amdgcn_readlane(e, l);
-          const ull lw = fg_readlane64(want, l);
-          ull acc = fg_readlane64(nw, l);
-          for (int32_t i0 = lb; i0 < le && (acc & lw) != lw; i0 += FG_WAVE) {
-            const int32_t i = i0 + lane;
-            ull x = 0;
-            if (i < le) x = Fc[P.col[i]] & lw;
-            if (lane == 0) ecnt += (uint32_t)(le - i0 < FG_WAVE ? le - i0 : FG_WAVE);
-            acc |= fg_wave_or64(x);
+          if (lst.cnt + FG_WAVE > STAGE) {
+            ull at[2] = {0, 0};
+            if (lane == 0) {
+              at[0] = atomicAdd(&C.q.v, (ull)lst.cnt);
+              at[1] = atomicAdd(&C.desc.v, (ull)lch);
+            }
+            wave_lds_fence();
+            put_long(P, L.w_sc[wid], L.w_u[wid], L.w_b[wid], lst.buf, lst.cnt, Qlong,
+                     (int64_t)(fg_uni(at[0]) - qbp), (int64_t)(fg_uni(at[1]) - dbp));
+            lst.cnt = 0;
+            lch = 0;
           }
-          if (lane == l) nw = acc & lw;
+          if (lng) lst.buf[lst.cnt + fg_mbcnt(lm)] = (int32_t)v;
+          lst.cnt += __popcll(lm);
+          lch += fg_wave_sum(lng ? (e - b - 4 + CH - 1) / CH : 0);
+        }
+        // up to 16 further entries, then up to 60: compacted, eight lanes a row
+        for (int pass = 0; pass < 2; ++pass) {
+          const bool mine = more && !lng && (e - b > 20) == (pass == 1);
+          const uint64_t pm = __ballot(mine);
+          if (!pm) continue;
+          const int32_t at = fg_mbcnt(pm), cnt = __popcll(pm);
+          wave_lds_fence();
+          if (mine) {
+            L.w_b[wid][at] = b + 4;
+            L.w_u[wid][at] = e;
+            L.w_f[wid][at] = want & ~nw;
+            ecnt += (uint32_t)(e - b - 4);
+          }
+          wave_lds_fence();
+          if (pass == 0)
+            pull_rows<2>(P, Fc, L.w_b[wid], L.w_u[wid], L.w_f[wid], cnt);
+          else
+            pull_rows<8>(P, Fc, L.w_b[wid], L.w_u[wid], L.w_f[wid], cnt);
+          wave_lds_fence();
+          if (mine) nw |= L.w_f[wid][at];
         }
         if (v < P.n) {
           if (nw && !lng) fg_st_shared(&P.visit[v], vis | nw);
@@ -969,6 +1117,15 @@ __global__ __launch_bounds__(PB) void msbfs_persistent(MsParams P) {
         }
         lor |= nw;
         act += nw != 0ull;
+      }
+      if (P.has_long) {
+        ull pos[2];
+        const int32_t cnt[2] = {lst.cnt, lch};
+        ull* const ctr[2] = {&C.q.v, &C.desc.v};
+        ull* const also[2] = {nullptr, nullptr};
+        block_reserve(L.fl, cnt, ctr, also, pos);
+        put_long(P, L.w_sc[wid], L.w_u[wid], L.w_b[wid], lst.buf, lst.cnt, Qlong,
+                 (int64_t)(pos[0] - qbp), (int64_t)(pos[1] - dbp));
       }
       {
         const ull bor = block_or(lor, L.redu);
@@ -988,7 +1145,7 @@ __global__ __launch_bounds__(PB) void msbfs_persistent(MsParams P) {
         qbp = lt;
         dbp = dt;
         if (nch > 0) {
-          for (int64_t i = gw; i < nch; i += W) {
+          for (int64_t i = gwm; i < nch; i += W) {
             const int4 dsc = P.desc[i];
             const int32_t v = dsc.x;
             const ull want = S.live & ~P.visit[v];
@@ -1083,28 +1240,52 @@ __global__ __launch_bounds__(PB) void msbfs_persistent(MsParams P) {
       if (bv) atomicAdd(&P.state->verts, (ull)bv);
     }
   }
-  if (tid == 0) {
-    MsState* st = P.state;
-    st->it = S.it;
-    st->mode = S.mode;
-    st->qsel = S.qsel;
-    st->fsel = S.fsel;
-    st->qlen = S.qlen;
-    st->live = ok ? S.live : 0ull;
-    st->used = S.used;
-    if (!ok) st->aborted = 1;
-  }
   __syncthreads();
   if (threadIdx.x == 0) {
     const uint32_t done = __hip_atomic_fetch_add(&P.ctl->exit_count, 1u, __ATOMIC_ACQ_REL,
                                                  __HIP_MEMORY_SCOPE_AGENT);
     L.flag = done == gridDim.x - 1;
+    if (L.flag) {
+      // the last one out: everyone has read the old state
+      MsState* st = P.state;
+      // a wait that failed in any workgroup has set the abort flag
+      if (__hip_atomic_load(P.ctl->bar + FG_BAR_STRIDE, __ATOMIC_RELAXED,
+                            __HIP_MEMORY_SCOPE_AGENT))
+        ok = false;
+      st->it = S.it;
+      st->mode = S.mode;
+      st->qsel = S.qsel;
+      st->fsel = S.fsel;
+      st->qlen = S.qlen;
+      st->live = ok ? S.live : 0ull;
+      st->used = S.used;
+      if (!ok) st->aborted = 1;
+    }
   }
   __syncthreads();
   if (L.flag) {
     uint32_t* w = (uint32_t*)P.ctl;
     for (int i = threadIdx.x; i < (int)(sizeof(MsCtl) / 4); i += PB) w[i] = 0u;
   }
+}
+
+// A lane's depths to the caller's array: 16-byte words where both are aligned
+// alike.
+__global__ __launch_bounds__(1024) void ms_read_kernel(const int32_t* __restrict__ row,
+                                                       int32_t* __restrict__ out, int32_t n) {
+  const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t nth = (int64_t)gridDim.x * blockDim.x;
+  if ((((uintptr_t)row ^ (uintptr_t)out) & 15) != 0) {
+    for (int64_t i = tid; i < n; i += nth) out[i] = row[i];
+    return;
+  }
+  const int64_t lead = (-((intptr_t)row >> 2)) & 3;
+  const int64_t h = lead < n ? lead : n;
+  const int64_t n4 = (n - h) / 4;
+  for (int64_t i = tid; i < n4; i += nth) ((int4*)(out + h))[i] = ((const int4*)(row + h))[i];
+  if (tid < h) out[tid] = row[tid];
+  const int64_t t = h + 4 * n4 + tid;
+  if (t < n) out[t] = row[t];
 }
 
 struct MsLayout {
@@ -1252,6 +1433,7 @@ extern "C" fg_status fg_msbfs_step(fg_msbfs* b, int32_t k_iters, void* stream) {
     P.pend_src[i] = b->pend_src[i];
   }
   P.big_deg = b->opts.big_degree > 0 ? b->opts.big_degree : 64;
+  P.has_long = g->max_degree > LONG_PULL;
   P.pull_div = b->opts.pull_div > 0 ? b->opts.pull_div : 64;
   // back to push at the same size as the switch to pull (grid 2048², 64
   // lanes: 105 ms, against 125 ms at n / 512; R-MAT 23 flat at 6.8-7.0 ms)
@@ -1311,9 +1493,24 @@ extern "C" fg_status fg_msbfs_read(fg_msbfs* b, int32_t lane, int32_t* depth, vo
   if (!b || !depth) return fg_set_error(FG_EINVAL, "fg_msbfs_read: NULL argument");
   if (lane < 0 || lane >= b->lanes)
     return fg_set_error(FG_EINVAL, "fg_msbfs_read: lane=%d outside [0, %d)", lane, b->lanes);
-  FG_HIP_TRY(hipMemcpyAsync(depth, b->lay.depth + (size_t)lane * b->g->n,
-                            sizeof(int32_t) * (size_t)b->g->n, hipMemcpyDeviceToDevice,
-                            (hipStream_t)stream));
+  const int32_t* row = b->lay.depth + (size_t)lane * b->g->n;
+  const size_t bytes = sizeof(int32_t) * (size_t)b->g->n;
+  hipStream_t s = (hipStream_t)stream;
+  // into memory of this device by a kernel (a runtime copy of a batch's rows
+  // costs the host 10 us each, a launch 3), into anything else by the runtime
+  hipPointerAttribute_t at;
+  int dev = -1;
+  const bool here = hipGetDevice(&dev) == hipSuccess &&
+                    hipPointerGetAttributes(&at, depth) == hipSuccess &&
+                    at.type == hipMemoryTypeDevice && at.device == dev;
+  if (!here) {
+    FG_HIP_TRY(hipMemcpyAsync(depth, row, bytes, hipMemcpyDeviceToDevice, s));
+    return FG_OK;
+  }
+  int blocks = (int)((b->g->n + 4095) / 4096);
+  if (blocks > 1024) blocks = 1024;
+  void* args[] = {(void*)&row, (void*)&depth, (void*)&b->g->n};
+  FG_HIP_TRY(hipLaunchKernel((const void*)ms_read_kernel, dim3(blocks), dim3(1024), args, 0, s));
   return FG_OK;
 }
 

@@ -207,3 +207,44 @@ def test_config_grid2048_64_sources(fg):
     for lane in range(0, 64, 9):
         r0, c0 = divmod(int(srcs[lane]), R)
         assert np.array_equal(to_np(b.read(lane)), np.abs(rr - r0) + np.abs(cc - c0))
+
+
+# pull rows at the edges of their classes: the head's four entries, sixteen
+# more (two per lane of eight), up to 64, and the listed ones past that, on one
+# workgroup (whose waves' lists of long rows fill up on the way) and on all
+@pytest.mark.parametrize("n,deg,blocks", [(9000, 70, 1), (4099, 64, 0), (4099, 65, 3), (3001, 20, 0),
+                                          (3001, 21, 0), (3001, 5, 2), (3001, 4, 0), (1, 0, 0),
+                                          (70001, 24, 0)])
+def test_pull_row_classes(fg, orc, n, deg, blocks):
+    # vertex v's neighbours: v +- 1, +- k (mod n), so that most rows have
+    # exactly `deg` entries, and one vertex of 300
+    off_v = np.arange(n, dtype=np.int64)
+    steps = [1 + i * max(1, n // (4 * deg + 4)) for i in range(deg // 2)]
+    u = np.concatenate([off_v] * len(steps) + [np.zeros(0, np.int64)])
+    v = np.concatenate([(off_v + s) % n for s in steps] + [np.zeros(0, np.int64)])
+    if n > 1000:
+        u = np.concatenate([u, np.full(300, 17)])
+        v = np.concatenate([v, np.arange(300) * (n // 300)])
+    off, col = orc.csr_from_edges(n, u.astype(np.int32), v.astype(np.int32))
+    g = fg.Graph(off, col)
+    rng = np.random.default_rng(deg)
+    srcs = {i: int(s) for i, s in enumerate(rng.integers(0, n, 13))}
+    announce(f"msbfs pull rows n={n} deg={deg} blocks={blocks}")
+    for pull_div in (1, 1 << 20):
+        b = fg.MsBatch(g, 13, fg.msbfs_opts(grid_blocks=blocks, pull_div=pull_div,
+                                            push_div=1 << 20))
+        for rep in range(2):  # the second time over reused lanes
+            for lane, s in srcs.items():
+                b.admit(lane, s)
+            b.run(k_iters=3 + rep)
+            check_lanes(fg, orc, b, off, col, srcs)
+            srcs = {lane: (s + 1) % n for lane, s in srcs.items()}
+        # into a row that is not aligned as the lane's
+        out = torch.full((n + 3,), -5, dtype=torch.int32, device="cuda")
+        for o in range(4):
+            b.read(3, out[o:o + n] if o + n <= n + 3 else out[:n])
+            torch.cuda.synchronize()
+            o = o if o + n <= n + 3 else 0
+            assert np.array_equal(to_np(out[o:o + n]), to_np(b.read(3)))
+        b.close()
+    g.close()
