@@ -423,10 +423,15 @@ __device__ __forceinline__ void block_flush(WaveStage<T, CAP>& st, ull* total, u
   __syncthreads();
 }
 
+// (The phases are inlined by force: left to the compiler's limits, a small
+// change made it call one of them in bfs_corun, with LDS through flat accesses
+// and the registers around the call in scratch memory, and a step of 14 ms
+// took 17 to 22.)
+//
 // ---- push, full grid, phase A: each wave takes 64-entry chunks of the
 // frontier (static stride).  Vertices below big_deg are expanded by a
 // wave-level scan-gather; the others become CH-edge descriptors.
-__device__ void push_phase_a(const BfsParams& P, const BfsJob& J, const St& S, Lds& L,
+__device__ __forceinline__ void push_phase_a(const BfsParams& P, const BfsJob& J, const St& S, Lds& L,
                              uint32_t nblocks) {
   const int lane = fg_lane();
   const int wid = threadIdx.x / FG_WAVE;
@@ -520,7 +525,7 @@ __device__ void push_phase_a(const BfsParams& P, const BfsJob& J, const St& S, L
 // ---- push, full grid, phase B: waves take descriptors in turn; the CH
 // edges of a descriptor are contiguous, so each round is one coalesced read
 // of 64 column indices and no search is needed.
-__device__ void push_phase_b(const BfsParams& P, const BfsJob& J, const St& S, int64_t ndesc, Lds& L,
+__device__ __forceinline__ void push_phase_b(const BfsParams& P, const BfsJob& J, const St& S, int64_t ndesc, Lds& L,
                              uint32_t nblocks) {
   const int lane = fg_lane();
   const int wid = threadIdx.x / FG_WAVE;
@@ -565,7 +570,7 @@ __device__ void push_phase_b(const BfsParams& P, const BfsJob& J, const St& S, i
 // source reaches first): every wave lists the frontier's CH-edge chunks
 // itself (one lane per vertex, a wave scan of the chunk counts) and takes
 // chunks gw, gw + W, ...; no descriptors in memory, one grid barrier.
-__device__ void push_tiny(const BfsParams& P, const BfsJob& J, const St& S, Lds& L) {
+__device__ __forceinline__ void push_tiny(const BfsParams& P, const BfsJob& J, const St& S, Lds& L) {
   const int lane = fg_lane();
   const int wid = threadIdx.x / FG_WAVE;
   const int32_t* Qin = P.q[S.qsel];
@@ -679,6 +684,32 @@ __device__ __forceinline__ int32_t probe4(const BfsParams& P, const uint64_t* Vi
 // up to three more probe steps per round.)  Writes the next visited bitmap
 // Vout = Vin | found (whole words, no atomics).
 constexpr int PULL_DEFER = STAGE;  // set-aside vertices per wave
+// candidates per bitmap word, over a wave's batch, from which a lane per bit
+// is used (R-MAT 22, the first pull, 152 workgroups: 76 us laid over the
+// lanes, 71 a lane per bit, 68 with four words in flight, which the register
+// file of bfs_corun has no room for; 256 workgroups 58 and 54.  From 8 or
+// from 24 candidates: the same.)
+constexpr int32_t PULL_DENSE = 16;
+constexpr int PULL_W = 2;  // words per round of that loop
+// added to the degree counter by a workgroup that found too many to list
+constexpr ull PULL_OVER = 1ull << 40;
+
+// Vertices a wave found in a pull, as long as they are few: a small level is
+// then listed already when the direction turns to push, without a pass over
+// the bitmaps and a grid barrier (the first push after R-MAT 22's pulls: 9.9
+// -> 6.2 us; the listing costs a pull 2).
+constexpr int PULL_LIST = 64;
+
+struct FoundList {
+  int32_t* buf;
+  int32_t cnt;  // found; listed only up to PULL_LIST
+  __device__ __forceinline__ void add(bool found, int32_t v) {
+    const uint64_t m = __ballot(found);
+    const int32_t c = __popcll(m);
+    if (found && cnt + c <= PULL_LIST) buf[cnt + fg_mbcnt(m)] = v;
+    cnt += c;
+  }
+};
 
 // The found vertex v (bit `bit` of batch word jw): depth, parent, next bit.
 __device__ __forceinline__ void pull_found(const BfsParams& P, const BfsJob& J, uint64_t* nbw, int32_t v,
@@ -690,9 +721,9 @@ __device__ __forceinline__ void pull_found(const BfsParams& P, const BfsJob& J, 
 
 // Resumes the set-aside vertices dv[0..cnt) (entries from the fifth on);
 // dj holds jw << 6 | bit.  Every lane of the wave must take part.
-__device__ void pull_resume(const BfsParams& P, const BfsJob& J, const uint64_t* Vin, uint64_t* nbw,
+__device__ __forceinline__ void pull_resume(const BfsParams& P, const BfsJob& J, const uint64_t* Vin, uint64_t* nbw,
                             const int32_t* dv, const uint16_t* dj, int32_t cnt, int32_t d_new,
-                            int32_t& insp, int32_t& ndeg, int32_t& nnew) {
+                            int32_t& insp, FoundList& fl) {
   const int lane = fg_lane();
   for (int32_t a0 = 0; a0 < cnt; a0 += FG_WAVE) {
     const int32_t a = a0 + lane;
@@ -759,13 +790,12 @@ __device__ void pull_resume(const BfsParams& P, const BfsJob& J, const uint64_t*
     if (found) {
       const int32_t jb = dj[a];
       pull_found(P, J, nbw, v, pu, d_new, jb >> 6, jb & 63);
-      ndeg += e - b;
-      nnew++;
     }
+    fl.add(found, v);
   }
 }
 
-__device__ void pull_phase(const BfsParams& P, const BfsJob& J, const St& S, Lds& L) {
+__device__ __forceinline__ void pull_phase(const BfsParams& P, const BfsJob& J, const St& S, Lds& L) {
   const int lane = fg_lane();
   const int wid = threadIdx.x / FG_WAVE;
   const int64_t gw = (int64_t)blockIdx.x * PWAVES + wid;
@@ -780,7 +810,8 @@ __device__ void pull_phase(const BfsParams& P, const BfsJob& J, const St& S, Lds
   int32_t* dv = L.stage[wid];
   uint16_t* dj = (uint16_t*)L.dstage[wid];
   static_assert(sizeof(L.dstage[0]) >= PULL_DEFER * sizeof(uint16_t), "set-aside list fits");
-  int32_t insp = 0, ndeg = 0, nnew = 0;
+  int32_t insp = 0;
+  FoundList fl{&L.lq_v[0][0] + wid * PULL_LIST, 0};
   for (int64_t t0 = 0; gw + t0 * W < P.nwords; t0 += FG_WAVE) {
     const int64_t wj = gw + (t0 + lane) * W;  // this lane's word of the batch
     uint64_t vis = 0, act = 0;
@@ -796,14 +827,129 @@ __device__ void pull_phase(const BfsParams& P, const BfsJob& J, const St& S, Lds
     nbw[lane] = 0;
     wave_lds_fence();
     int32_t ndef = 0;
-    // two candidates per lane and round: the offsets and head entries of
+    if (tot >= PULL_DENSE * __popcll(__ballot(wj < P.nwords))) {
+      // many candidates: a lane per bit, PULL_W words per round, with
+      // coalesced head entries and outputs.  The first neighbour alone is
+      // probed first (a sorted row's is its best connected), the other three
+      // where that is not visited, and only what is still open has its
+      // offsets loaded.
+      for (int32_t j0 = 0; j0 < FG_WAVE; j0 += PULL_W) {
+        uint64_t a[PULL_W];
+#pragma unroll
+        for (int r = 0; r < PULL_W; ++r) a[r] = fg_readlane64(act, j0 + r);
+        uint64_t ar = 0;
+        int32_t r0 = 0;
+#pragma unroll
+        for (int r = PULL_W - 1; r >= 0; --r)
+          if (a[r]) {
+            ar = a[r];
+            r0 = r;
+          }
+        if (!ar) continue;
+        if (ndef > PULL_DEFER - PULL_W * FG_WAVE) {
+          pull_resume(P, J, Vin, nbw, dv, dj, ndef, d_new, insp, fl);
+          wave_lds_fence();
+          ndef = 0;
+        }
+        const int64_t w0 = (gw + (t0 + j0) * W) * 64;
+        // a candidate, read by the lanes without one
+        const int32_t spare = (int32_t)(w0 + r0 * W * 64 + __builtin_ctzll(ar));
+        int32_t v[PULL_W], pu[PULL_W], ins[PULL_W];
+        int4 hd[PULL_W];
+        bool open[PULL_W], found[PULL_W];
+#pragma unroll
+        for (int r = 0; r < PULL_W; ++r) {
+          open[r] = (a[r] >> lane) & 1ull;
+          v[r] = open[r] ? (int32_t)(w0 + r * W * 64 + lane) : spare;
+          hd[r] = P.head[v[r]];
+        }
+        uint64_t wx[PULL_W];
+#pragma unroll
+        for (int r = 0; r < PULL_W; ++r) wx[r] = Vin[hd[r].x >> 6];
+        bool any = false;
+#pragma unroll
+        for (int r = 0; r < PULL_W; ++r) {
+          found[r] = open[r] && ((wx[r] >> (hd[r].x & 63)) & 1ull);
+          pu[r] = hd[r].x;
+          ins[r] = found[r] ? 1 : 0;
+          open[r] = open[r] && !found[r];
+          any |= open[r];
+        }
+        if (__ballot(any)) {
+          uint64_t wv[PULL_W][3];
+#pragma unroll
+          for (int r = 0; r < PULL_W; ++r) {
+            wv[r][0] = Vin[(open[r] ? hd[r].y : hd[r].x) >> 6];
+            wv[r][1] = Vin[(open[r] ? hd[r].z : hd[r].x) >> 6];
+            wv[r][2] = Vin[(open[r] ? hd[r].w : hd[r].x) >> 6];
+          }
+          // entries past the degree repeat the last one: they are not found
+          // first
+          int32_t b[PULL_W], e[PULL_W];
+          any = false;
+#pragma unroll
+          for (int r = 0; r < PULL_W; ++r) {
+            const bool f3 = (wv[r][2] >> (hd[r].w & 63)) & 1ull;
+            const bool f2 = (wv[r][1] >> (hd[r].z & 63)) & 1ull;
+            const bool f1 = (wv[r][0] >> (hd[r].y & 63)) & 1ull;
+            if (open[r] && (f1 | f2 | f3)) {
+              found[r] = true;
+              open[r] = false;
+              pu[r] = f1 ? hd[r].y : f2 ? hd[r].z : hd[r].w;
+              ins[r] = f1 ? 2 : f2 ? 3 : 4;
+            }
+            any |= open[r];
+          }
+          if (__ballot(any)) {
+#pragma unroll
+            for (int r = 0; r < PULL_W; ++r) {
+              b[r] = P.off[open[r] ? v[r] : spare];
+              e[r] = P.off[(open[r] ? v[r] : spare) + 1];
+            }
+#pragma unroll
+            for (int r = 0; r < PULL_W; ++r) {
+              const int32_t dg = e[r] - b[r];
+              if (open[r]) ins[r] = min(4, dg);
+              const bool defer = open[r] && dg > 4;
+              const uint64_t dm = __ballot(defer);
+              if (defer) {
+                const int32_t pos = ndef + fg_mbcnt(dm);
+                dv[pos] = v[r];
+                dj[pos] = (uint16_t)(((j0 + r) << 6) | lane);
+              }
+              ndef += __popcll(dm);
+            }
+          }
+        }
+#pragma unroll
+        for (int r = 0; r < PULL_W; ++r) {
+          insp += ins[r];
+          const uint64_t fm = __ballot(found[r]);
+          if (!fm) continue;
+          if (found[r]) {
+            J_depth(P, J)[v[r]] = d_new;
+            if (J_parent(P, J)) J_parent(P, J)[v[r]] = pu[r];
+          }
+          // deferred bits of this word come later (the list is emptied only
+          // between rounds)
+          if (lane == 0) nbw[j0 + r] = fm;
+          fl.add(found[r], v[r]);
+        }
+      }
+      wave_lds_fence();
+      if (ndef > 0) pull_resume(P, J, Vin, nbw, dv, dj, ndef, d_new, insp, fl);
+      wave_lds_fence();
+      if (wj < P.nwords) fg_st_shared(&Vout[wj], vis | nbw[lane]);
+      continue;
+    }
+    // few: two candidates per lane and round: the offsets and head entries of
     // both, then the eight visited words of their first four neighbours,
     // are in flight together (lanes past the list take candidate 0 again,
     // a valid vertex, and discard the result)
     for (int32_t a0 = 0; a0 < tot; a0 += 2 * FG_WAVE) {
       if (ndef > PULL_DEFER - 2 * FG_WAVE) {
         // room for a whole round: resume what is set aside now
-        pull_resume(P, J, Vin, nbw, dv, dj, ndef, d_new, insp, ndeg, nnew);
+        pull_resume(P, J, Vin, nbw, dv, dj, ndef, d_new, insp, fl);
         wave_lds_fence();
         ndef = 0;
       }
@@ -851,9 +997,8 @@ __device__ void pull_phase(const BfsParams& P, const BfsJob& J, const St& S, Lds
         insp += !mine[s2] ? 0 : (h >= 0 ? h + 1 : min(4, dg));
         if (found) {
           pull_found(P, J, nbw, v[s2], pu, d_new, jw[s2], bit[s2]);
-          ndeg += dg;
-          nnew++;
         }
+        fl.add(found, v[s2]);
         const uint64_t dm = __ballot(defer);
         if (defer) {
           const int32_t pos = ndef + fg_mbcnt(dm);
@@ -864,24 +1009,46 @@ __device__ void pull_phase(const BfsParams& P, const BfsJob& J, const St& S, Lds
       }
     }
     wave_lds_fence();
-    if (ndef > 0) pull_resume(P, J, Vin, nbw, dv, dj, ndef, d_new, insp, ndeg, nnew);
+    if (ndef > 0) pull_resume(P, J, Vin, nbw, dv, dj, ndef, d_new, insp, fl);
     wave_lds_fence();
     if (wj < P.nwords) fg_st_shared(&Vout[wj], vis | nbw[lane]);
   }
   const int32_t tot = fg_block_sum<PB>(insp, L.red32);
-  const int32_t tdeg = fg_block_sum<PB>(ndeg, L.red32);
-  const int32_t tn = fg_block_sum<PB>(nnew, L.red32);
+  __syncthreads();
+  if (lane == 0) L.red32[wid] = fl.cnt;
+  __syncthreads();
+  int32_t before = 0, tn = 0;
+  bool over = false;
+#pragma unroll
+  for (int i = 0; i < PWAVES; ++i) {
+    const int32_t c = L.red32[i];
+    over |= c > PULL_LIST;
+    before += i < wid ? c : 0;
+    tn += c;
+  }
   CtrSlot& C = P.ctl->slot[S.k & 1];
   if (threadIdx.x == 0) {
     if (tot) atomicAdd(&C.insp.v, (ull)tot);
-    if (tdeg) atomicAdd(&C.deg.v, (ull)tdeg);
-    if (tn) atomicAdd(&C.q.v, (ull)tn);
+    if (over) atomicAdd(&C.deg.v, PULL_OVER);
+    L.bcast[0] = tn ? (int64_t)(atomicAdd(&C.q.v, (ull)tn) - get_bases(S).q) : 0;
   }
+  if (tn == 0 || over) return;  // the same in every thread
+  __syncthreads();
+  // the listed vertices into the queue, and their degree sum
+  int32_t* Q = P.q[S.qsel];
+  int32_t deg = 0;
+  for (int32_t i = lane; i < fl.cnt; i += FG_WAVE) {
+    const int32_t v = fl.buf[i];
+    fg_st_shared(&Q[L.bcast[0] + before + i], v);
+    deg += P.off[v + 1] - P.off[v];
+  }
+  deg = fg_block_sum<PB>(deg, L.red32);
+  if (threadIdx.x == 0) atomicAdd(&C.deg.v, (ull)deg);
 }
 
 // ---- backward -> forward switch: the new frontier is the set difference
 // of the current and the previous visited bitmap, listed into Q[qsel].
-__device__ void bitmap_diff_to_queue(const BfsParams& P, const St& S, Lds& L) {
+__device__ __forceinline__ void bitmap_diff_to_queue(const BfsParams& P, const St& S, Lds& L) {
   // each workgroup lists a contiguous range of bitmap words (a multiple of
   // 64 words, 64 per wave and step) and reserves its queue slots with one
   // atomic per step
@@ -1121,7 +1288,7 @@ __device__ __forceinline__ void wave_put(Lds& L, int nxt, bool won, int32_t pos,
 }
 
 template <int MODE>
-__device__ bool lds_mode(const BfsParams& P, const BfsJob& J, St& S, Lds& L, uint32_t T, TeamSync& ts,
+__device__ __forceinline__ bool lds_mode(const BfsParams& P, const BfsJob& J, St& S, Lds& L, uint32_t T, TeamSync& ts,
                          TeamBases& tb) {
   const int tid = threadIdx.x;
   const int lane = fg_lane();
@@ -1371,8 +1538,10 @@ __device__ __forceinline__ void bfs_persistent_run(const BfsParams& P, Lds& L) {
       // every workgroup has left the previous traversal: the workgroups
       // clear the control block for the next one, a share each, all but the
       // grid barrier (in use; its counters are monotone); the init barrier
-      // below publishes the clear
-      if (!gs.sync(&L.flag)) {
+      // below publishes the clear.  Shared outputs have to be in memory
+      // before others write the same places; separate ones need no write-back
+      // here (3.7 us of the 31 between two traversals of R-MAT 22)
+      if (!(P.out_stride == 0 ? gs.sync(&L.flag) : gs.sync_acquire(&L.flag))) {
         ok = false;
         break;
       }
@@ -1458,10 +1627,13 @@ __device__ __forceinline__ void bfs_persistent_run(const BfsParams& P, Lds& L) {
   trace_iter(S, P, J);
   while (ok && S.qlen > 0) {
     // backward -> forward: list the last pull's discoveries first
+    // (a small level's are listed by the pull itself)
     if (MODE == FG_MODE_DO && S.dir == DIR_PUSH && S.prevdir == DIR_PULL) {
-      bitmap_diff_to_queue(P, S, L);
-      if (!(ok = gs.sync_acquire(&L.flag))) break;
-      S.auxbase = fg_atomic_load_u64(&P.ctl->aux.v);
+      if (S.qdeg < 0) {
+        bitmap_diff_to_queue(P, S, L);
+        if (!(ok = gs.sync_acquire(&L.flag))) break;
+        S.auxbase = fg_atomic_load_u64(&P.ctl->aux.v);
+      }
       S.prevdir = DIR_PUSH;
     }
     // qdeg < 0: not known after a full-grid push; the LDS modes take it
@@ -1588,8 +1760,8 @@ __device__ __forceinline__ void bfs_persistent_run(const BfsParams& P, Lds& L) {
     const int64_t insp = (int64_t)(it - B.insp);
     B.q = qt;
     B.insp = it;
-    // only a pull adds up the degrees of what it finds
-    S.qdeg = S.dir == DIR_PULL ? (int64_t)(gt - B.deg) : -1;
+    // only a pull that lists what it finds adds up the degrees
+    S.qdeg = S.dir == DIR_PULL && gt - B.deg < PULL_OVER ? (int64_t)(gt - B.deg) : -1;
     B.deg = gt;
     set_bases(S, B);
     trace_insp(S.k, insp, P, J);

@@ -275,3 +275,21 @@ def test_one_workgroup_long_diameter(fg, orc):
             if mode == "push":
                 assert st.edges_inspected == len(col)
         g.close()
+
+
+# the pull's two ways through a wave's words (a lane per bit, candidates laid
+# over the lanes) on one workgroup, whose waves find too many to list, on a few
+# and on all; pulls and pushes in turn, so that a listed frontier, an unlisted
+# one and an empty one are each taken over by a push
+@pytest.mark.parametrize("n,edges,degs", [
+    (64, 200, [50]), (4097, 9000, [900, 30, 18]), (40001, 60000, [20000]),
+    (40000, 15000, [39999]), (131072, 1300000, [300, 200]), (262143, 250000, [100000, 64])])
+@pytest.mark.parametrize("blocks", [1, 7, 0])
+def test_pull_words(fg, orc, n, edges, degs, blocks):
+    off, col = _hubs(orc, n, edges, degs, seed=n + 1)
+    g = fg.Graph(off, col)
+    kw = dict(grid_blocks=blocks) if blocks else dict(team_blocks=2)
+    for src in sorted({0, 5 % n, 42 % n, n - 1}):
+        for do_b in ((1, 10), (1, 1), (1000, 1)):
+            check_bfs(fg, orc, g, off, col, src, "do", do_a=(1, 100000), do_b=do_b, **kw)
+    g.close()
