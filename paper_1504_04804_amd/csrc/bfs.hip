@@ -103,7 +103,6 @@ struct alignas(256) BfsCtl {
   int64_t pub_qlen, pub_p, pub_insp_sum;
   int32_t pub_switches;
   int64_t pub_qdeg;
-  ull pub_b[8];
   // asynchronous push mode (bfs_async and its finalising kernels; cleared
   // by async_init_kernel at the start of each such traversal):
   uint32_t as_arrive;          // team barrier arrivals
@@ -200,10 +199,7 @@ struct St {
   int64_t qdeg;      // sum of the degrees of Q (edges a push would read)
   int64_t p;         // |P|: vertices with a depth, Q included
   int64_t insp_sum;  // CSR entries read so far
-  // last read value of slot[p].{q, desc, insp}; kept as scalars so the
-  // parity select does not force the state into scratch memory
-  ull b0q, b0desc, b0insp, b0deg;
-  ull b1q, b1desc, b1insp, b1deg;
+  uint32_t bsel;     // bit p: where the bases of counter slot p are (Lds::bases)
   ull auxbase;
 };
 
@@ -211,30 +207,6 @@ struct Bases {
   ull q, desc, insp, deg;
 };
 
-
-__device__ __forceinline__ ull sel(bool odd, ull a1, ull a0) {
-  // branch-free select on a wave-uniform parity
-  const ull m = 0ull - (ull)odd;
-  return (a1 & m) | (a0 & ~m);
-}
-
-__device__ __forceinline__ Bases get_bases(const St& S) {
-  const bool odd = S.k & 1;
-  return Bases{sel(odd, S.b1q, S.b0q), sel(odd, S.b1desc, S.b0desc), sel(odd, S.b1insp, S.b0insp),
-               sel(odd, S.b1deg, S.b0deg)};
-}
-
-__device__ __forceinline__ void set_bases(St& S, const Bases& b) {
-  const bool odd = S.k & 1;
-  S.b1q = sel(odd, b.q, S.b1q);
-  S.b1desc = sel(odd, b.desc, S.b1desc);
-  S.b1insp = sel(odd, b.insp, S.b1insp);
-  S.b1deg = sel(odd, b.deg, S.b1deg);
-  S.b0q = sel(odd, S.b0q, b.q);
-  S.b0desc = sel(odd, S.b0desc, b.desc);
-  S.b0insp = sel(odd, S.b0insp, b.insp);
-  S.b0deg = sel(odd, S.b0deg, b.deg);
-}
 
 // Direction rule of Sec. VI-A for the iteration described by S (k >= 1):
 // FV = |Q| m / n, BV = |U| n / |P|, U = n - |P|; forward->backward when
@@ -388,9 +360,37 @@ struct Lds {
   int32_t newcnt;
   int32_t flag;
   int32_t ackbad;  // workgroup 0: a hand-off acknowledgement wait failed
-  int64_t bcast[20];
+  int64_t bcast[10];
+  ull bases[2][2][4];  // see get_bases
   int32_t tsum[6];
 };
+
+// Values of counter slot k & 1 when iteration k began.  They are kept in LDS
+// (as kernel state in registers they were spilled): the next ones go to the
+// pair's other half, whose last reader is a level of this slot behind.
+__device__ __forceinline__ Bases get_bases(const Lds& L, const St& S) {
+  const ull* b = L.bases[S.k & 1][(S.bsel >> (S.k & 1)) & 1u];
+  return Bases{fg_uni(b[0]), fg_uni(b[1]), fg_uni(b[2]), fg_uni(b[3])};
+}
+
+__device__ __forceinline__ void set_bases(Lds& L, St& S, const Bases& b) {
+  S.bsel ^= 1u << (S.k & 1);
+  if (threadIdx.x == 0) {
+    ull* to = L.bases[S.k & 1][(S.bsel >> (S.k & 1)) & 1u];
+    to[0] = b.q;
+    to[1] = b.desc;
+    to[2] = b.insp;
+    to[3] = b.deg;
+  }
+}
+
+// This wave's index in its workgroup, as a scalar of its own at each use: the
+// LDS addresses made from it are not kept in vector registers across phases.
+__device__ __forceinline__ int wave_id() {
+  int w = __builtin_amdgcn_readfirstlane(threadIdx.x / FG_WAVE);
+  asm volatile("" : "+s"(w));
+  return w;
+}
 
 // The final flush of every wave's staged entries with one global atomic
 // per workgroup: the waves' counts meet in LDS, thread 0 reserves the
@@ -402,7 +402,7 @@ template <class T, int CAP>
 __device__ __forceinline__ void block_flush(WaveStage<T, CAP>& st, ull* total, ull base, T* out,
                                             Lds& L) {
   const int lane = fg_lane();
-  const int wid = threadIdx.x / FG_WAVE;
+  const int wid = wave_id();
   __syncthreads();
   if (lane == 0) L.red32[wid] = st.cnt;
   __syncthreads();
@@ -434,7 +434,7 @@ __device__ __forceinline__ void block_flush(WaveStage<T, CAP>& st, ull* total, u
 __device__ __forceinline__ void push_phase_a(const BfsParams& P, const BfsJob& J, const St& S, Lds& L,
                              uint32_t nblocks) {
   const int lane = fg_lane();
-  const int wid = threadIdx.x / FG_WAVE;
+  const int wid = wave_id();
   const int32_t* Qin = P.q[S.qsel];
   int32_t* Qout = P.q[S.qsel ^ 1];
   uint32_t* vis32 = (uint32_t*)P.vis[S.cur];
@@ -443,19 +443,49 @@ __device__ __forceinline__ void push_phase_a(const BfsParams& P, const BfsJob& J
   int32_t* su = L.w_u[wid];
   int32_t* sb = L.w_b[wid];
   CtrSlot& C = P.ctl->slot[S.k & 1];
-  const Bases B = get_bases(S);
+  const Bases B = get_bases(L, S);
   WaveStage<int32_t, STAGE> st{L.stage[wid], 0};
   int32_t* se = L.w_e[wid];
-  // work items are dealt wave-major over the workgroups (item i to
-  // workgroup i mod G): a level with few items spreads them over as many
-  // CUs instead of filling the first workgroups' waves
+  // the frontier is dealt in pieces of a quarter of a wave's share (4 to 64
+  // vertices), consecutive pieces to different workgroups: 12 616 vertices
+  // with 13.4 M edges (R-MAT of 4 M vertices) take 35 us to the slowest
+  // workgroup, in pieces of 64 57, in pieces of one 57 as well
   const int64_t gw = (int64_t)wid * nblocks + blockIdx.x;
   const int64_t W = (int64_t)nblocks * PWAVES;
+  const int64_t fair = (S.qlen + 4 * W - 1) / (4 * W);
+  const int64_t per = fair < 4 ? 4 : fair < FG_WAVE ? fair : FG_WAVE;
+  // room for all of the workgroup's descriptors with one atomic: the waves
+  // count theirs first (the second look at the offsets hits the caches)
+  int32_t mine = 0;
+  for (int64_t base = gw * per; base < S.qlen; base += W * per) {
+    const int64_t i = base + lane;
+    int32_t nd = 0;
+    if (lane < per && i < S.qlen) {
+      const int32_t u = Qin[i];
+      const int32_t deg = P.off[u + 1] - P.off[u];
+      if (deg >= P.big_deg) nd = (deg + CH - 1) / CH;
+    }
+    mine += nd;
+  }
+  mine = fg_wave_sum(mine);
+  __syncthreads();
+  if (lane == 0) L.red32[wid] = mine;
+  __syncthreads();
+  int32_t before = 0, btot = 0;
+#pragma unroll
+  for (int i = 0; i < PWAVES; ++i) {
+    const int32_t x = L.red32[i];
+    before += i < wid ? x : 0;
+    btot += x;
+  }
+  if (threadIdx.x == 0) L.bcast[0] = btot ? (int64_t)(atomicAdd(&C.desc.v, (ull)btot) - B.desc) : 0;
+  __syncthreads();
+  int64_t dpos = L.bcast[0] + before;
   int64_t insp = 0;
-  for (int64_t base = gw * FG_WAVE; base < S.qlen; base += W * FG_WAVE) {
+  for (int64_t base = gw * per; base < S.qlen; base += W * per) {
     const int64_t i = base + lane;
     int32_t u = 0, b = 0, deg = 0;
-    if (i < S.qlen) {
+    if (lane < per && i < S.qlen) {
       u = Qin[i];
       b = P.off[u];
       deg = P.off[u + 1] - b;
@@ -473,11 +503,9 @@ __device__ __forceinline__ void push_phase_a(const BfsParams& P, const BfsJob& J
       sb[lane] = b;
       se[lane] = b + deg;
       wave_lds_fence();
-      // one reservation for all of the wave's descriptors, then 64 written
-      // per step (a wave holding an R-MAT source's hubs writes thousands)
-      ull pos = 0;
-      if (lane == 0) pos = atomicAdd(&C.desc.v, (ull)ND);
-      pos = __shfl(pos, 0, FG_WAVE) - B.desc;
+      // 64 written per step (a wave can hold thousands)
+      const int64_t pos = dpos;
+      dpos += ND;
       for (int32_t t0 = 0; t0 < ND; t0 += FG_WAVE) {
         const int32_t t = t0 + lane;
         if (t < ND) {
@@ -528,7 +556,7 @@ __device__ __forceinline__ void push_phase_a(const BfsParams& P, const BfsJob& J
 __device__ __forceinline__ void push_phase_b(const BfsParams& P, const BfsJob& J, const St& S, int64_t ndesc, Lds& L,
                              uint32_t nblocks) {
   const int lane = fg_lane();
-  const int wid = threadIdx.x / FG_WAVE;
+  const int wid = wave_id();
   // work items are dealt wave-major over the workgroups (item i to
   // workgroup i mod G): a level with few items spreads them over as many
   // CUs instead of filling the first workgroups' waves
@@ -538,7 +566,7 @@ __device__ __forceinline__ void push_phase_b(const BfsParams& P, const BfsJob& J
   uint32_t* vis32 = (uint32_t*)P.vis[S.cur];
   const int32_t d_new = S.k + 1;
   CtrSlot& C = P.ctl->slot[S.k & 1];
-  const Bases B = get_bases(S);
+  const Bases B = get_bases(L, S);
   WaveStage<int32_t, STAGE> st{L.stage[wid], 0};
   // the next descriptor is loaded while the current one is processed
   int4 nd = gw < ndesc ? P.desc[gw] : make_int4(0, 0, 0, 0);
@@ -566,49 +594,49 @@ __device__ __forceinline__ void push_phase_b(const BfsParams& P, const BfsJob& J
   block_flush(st, &C.q.v, B.q, Qout, L);
 }
 
-// ---- push, full grid, frontier of at most 64 vertices (the hubs an R-MAT
-// source reaches first): every wave lists the frontier's CH-edge chunks
-// itself (one lane per vertex, a wave scan of the chunk counts) and takes
-// chunks gw, gw + W, ...; no descriptors in memory, one grid barrier.
-__device__ __forceinline__ void push_tiny(const BfsParams& P, const BfsJob& J, const St& S, Lds& L) {
+// ---- push, full grid, a short frontier (up to PB vertices) of long rows:
+// every workgroup lists all of its CH-edge chunks itself (one thread per
+// vertex, a block scan of the chunk counts) and its waves take chunks gw,
+// gw + W, ...: no descriptors in memory and one grid barrier, where phase A
+// and the barrier behind it took 33 of the 75 us of 397 vertices with 1.05 M
+// edges (R-MAT 20; 44 now; 1020 vertices with 4.2 M edges of R-MAT 22 142 ->
+// 102 us).  Returns false, with nothing done, where the mean degree
+// is below the descriptors' (most lanes of a chunk would idle).
+__device__ __forceinline__ bool push_chunks(const BfsParams& P, const BfsJob& J, const St& S,
+                                            Lds& L) {
   const int lane = fg_lane();
-  const int wid = threadIdx.x / FG_WAVE;
+  const int tid = threadIdx.x;
   const int32_t* Qin = P.q[S.qsel];
   int32_t* Qout = P.q[S.qsel ^ 1];
   uint32_t* vis32 = (uint32_t*)P.vis[S.cur];
   const int32_t d_new = S.k + 1;
-  int32_t* sc = L.w_sc[wid];
-  int32_t* su = L.w_u[wid];
-  int32_t* sb = L.w_b[wid];
-  int32_t* se = L.w_e[wid];
-  CtrSlot& C = P.ctl->slot[S.k & 1];
-  const Bases B = get_bases(S);
-  WaveStage<int32_t, STAGE> st{L.stage[wid], 0};
+  // the queues of the LDS modes are idle here
+  int32_t* sc = L.b_sc;
+  int32_t* su = L.b_u;
+  int32_t* sb = L.b_b;
+  int32_t* se = L.lq_e[0];
   int32_t u = 0, b = 0, deg = 0;
-  if (lane < S.qlen) {
-    u = Qin[lane];
+  if (tid < S.qlen) {
+    u = Qin[tid];
     b = P.off[u];
     deg = P.off[u + 1] - b;
   }
-  const int32_t nch = (deg + CH - 1) / CH;
-  const int32_t incl = fg_wave_incl_scan(nch);
-  const int32_t NC = __builtin_amdgcn_readlane(incl, FG_WAVE - 1);
-  wave_lds_fence();
-  sc[lane] = incl - nch;
-  su[lane] = u;
-  sb[lane] = b;
-  se[lane] = b + deg;
-  wave_lds_fence();
-  // work items are dealt wave-major over the workgroups (item i to
-  // workgroup i mod G): a level with few items spreads them over as many
-  // CUs instead of filling the first workgroups' waves
-  const int64_t gw = (int64_t)wid * fgb_n(P) + blockIdx.x;
+  const int32_t tot = fg_block_sum<PB>(deg, L.red32);
+  if (S.qlen > FG_WAVE && tot < P.big_deg * (int32_t)S.qlen) return false;  // the same in every workgroup
+  int32_t NC = 0;
+  const int32_t ex = fg_block_excl_scan<PB>((deg + CH - 1) / CH, L.red32, &NC);
+  sc[tid] = ex;
+  su[tid] = u;
+  sb[tid] = b;
+  se[tid] = b + deg;
+  __syncthreads();
+  CtrSlot& C = P.ctl->slot[S.k & 1];
+  const Bases B = get_bases(L, S);
+  WaveStage<int32_t, STAGE> st{L.stage[wave_id()], 0};
+  const int64_t gw = (int64_t)wave_id() * fgb_n(P) + blockIdx.x;
   const int64_t W = (int64_t)fgb_n(P) * PWAVES;
-  static_assert(CH == 4 * FG_WAVE, "one visit4 per chunk");
   for (int64_t c = gw; c < NC; c += W) {
-    // the last vertex whose first chunk is at or before c (vertices without
-    // chunks share their successor's start and are never picked)
-    const int32_t j = upper_idx(sc, FG_WAVE, (int32_t)c);
+    const int32_t j = upper_idx(sc, (int32_t)S.qlen, (int32_t)c);
     const int32_t e0 = sb[j] + ((int32_t)c - sc[j]) * CH;
     const int32_t e1 = e0 + CH < se[j] ? e0 + CH : se[j];
     int32_t v[4], pu[4];
@@ -626,8 +654,8 @@ __device__ __forceinline__ void push_tiny(const BfsParams& P, const BfsJob& J, c
   }
   block_flush(st, &C.q.v, B.q, Qout, L);
   // the frontier's degree sum, once
-  const int32_t tot = fg_wave_sum(deg);
-  if (blockIdx.x == 0 && threadIdx.x == 0 && tot) atomicAdd(&C.insp.v, (ull)tot);
+  if (blockIdx.x == 0 && tid == 0) atomicAdd(&C.insp.v, (ull)tot);
+  return true;
 }
 
 // Position of the r-th set bit (r = 0 first) of x; x has more than r bits set.
@@ -686,11 +714,9 @@ __device__ __forceinline__ int32_t probe4(const BfsParams& P, const uint64_t* Vi
 constexpr int PULL_DEFER = STAGE;  // set-aside vertices per wave
 // candidates per bitmap word, over a wave's batch, from which a lane per bit
 // is used (R-MAT 22, the first pull, 152 workgroups: 76 us laid over the
-// lanes, 71 a lane per bit, 68 with four words in flight, which the register
-// file of bfs_corun has no room for; 256 workgroups 58 and 54.  From 8 or
-// from 24 candidates: the same.)
+// lanes, 71 a lane per bit; 256 workgroups 58 and 54.  From 8 or from 24
+// candidates: the same; with four words in flight instead of two too.)
 constexpr int32_t PULL_DENSE = 16;
-constexpr int PULL_W = 2;  // words per round of that loop
 // added to the degree counter by a workgroup that found too many to list
 constexpr ull PULL_OVER = 1ull << 40;
 
@@ -795,9 +821,10 @@ __device__ __forceinline__ void pull_resume(const BfsParams& P, const BfsJob& J,
   }
 }
 
+template <int PULL_W>
 __device__ __forceinline__ void pull_phase(const BfsParams& P, const BfsJob& J, const St& S, Lds& L) {
   const int lane = fg_lane();
-  const int wid = threadIdx.x / FG_WAVE;
+  const int wid = wave_id();
   const int64_t gw = (int64_t)blockIdx.x * PWAVES + wid;
   const int64_t W = (int64_t)fgb_n(P) * PWAVES;
   const uint64_t* Vin = P.vis[S.cur];
@@ -1030,7 +1057,7 @@ __device__ __forceinline__ void pull_phase(const BfsParams& P, const BfsJob& J, 
   if (threadIdx.x == 0) {
     if (tot) atomicAdd(&C.insp.v, (ull)tot);
     if (over) atomicAdd(&C.deg.v, PULL_OVER);
-    L.bcast[0] = tn ? (int64_t)(atomicAdd(&C.q.v, (ull)tn) - get_bases(S).q) : 0;
+    L.bcast[0] = tn ? (int64_t)(atomicAdd(&C.q.v, (ull)tn) - get_bases(L, S).q) : 0;
   }
   if (tn == 0 || over) return;  // the same in every thread
   __syncthreads();
@@ -1053,7 +1080,7 @@ __device__ __forceinline__ void bitmap_diff_to_queue(const BfsParams& P, const S
   // 64 words, 64 per wave and step) and reserves its queue slots with one
   // atomic per step
   const int lane = fg_lane();
-  const int wid = threadIdx.x / FG_WAVE;
+  const int wid = wave_id();
   const uint64_t* Vnew = P.vis[S.cur];
   const uint64_t* Vold = P.vis[S.cur ^ 1];
   int32_t* Q = P.q[S.qsel];
@@ -1513,25 +1540,39 @@ __device__ __forceinline__ bool lds_mode(const BfsParams& P, const BfsJob& J, St
   }
 }
 
-// MODE is FG_MODE_DO or FG_MODE_PUSH (one kernel per mode).
+// The kernel's first argument, read again from here on: what a phase needs of
+// it is loaded (by scalar loads) where the phase begins.  Left to itself the
+// compiler loads all of it once, ahead of the loops over traversals and levels,
+// runs out of scalar registers and keeps it in scratch memory: a build of the
+// list kernel with 174 spilled registers took 5 to 9 us more for every level,
+// with this and wave_id() it has 5, the one-source kernels none.
+__device__ __forceinline__ const BfsParams& reread_args() {
+  auto p = (const __attribute__((address_space(4))) BfsParams*)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  return *(const BfsParams*)p;
+}
+
+// MODE is FG_MODE_DO or FG_MODE_PUSH (one kernel per mode).  P: the kernel's
+// first argument.
 template <int MODE, bool MULTI>
-__device__ __forceinline__ void bfs_persistent_run(const BfsParams& P, Lds& L) {
-  fg_grid_sync gs{P.ctl->bar, fgb_n(P), 0u};
+__device__ __forceinline__ void bfs_persistent_run(const BfsParams& P0, Lds& L) {
+  fg_grid_sync gs{P0.ctl->bar, fgb_n(P0), 0u};
   bool ok = true;
   // one traversal, or (MULTI, a build of its own: the loop around the
-  // traversal raises the register pressure) P.nsrc traversals in turn
-  const int32_t njobs = MULTI ? P.nsrc : 1;
+  // traversal raises the register pressure) P0.nsrc traversals in turn
+  const int32_t njobs = MULTI ? P0.nsrc : 1;
   // queued behind an asynchronous traversal: run only if that one gave up
-  if (P.async_fallback &&
-      __hip_atomic_load(&P.ctl->as_state, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0)
+  if (P0.async_fallback &&
+      __hip_atomic_load(&P0.ctl->as_state, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0)
     return;
   // shared outputs (fg_bfs_many, out_stride 0): once one traversal of this
   // launch has completed, the outputs hold -1 exactly outside its visited
-  // set (kept in P.reached), so the next traversal writes only what it
+  // set (kept in P0.reached), so the next traversal writes only what it
   // reaches and afterwards resets the vertices the previous one reached and
   // it did not, instead of filling 8n bytes first
   bool have_prev = false;
   for (int32_t job = 0; job < njobs && ok; ++job) {
+  const BfsParams& P = reread_args();
   BfsJob J{job, P.src};
   if (MULTI) {
     if (job > 0) {
@@ -1576,6 +1617,8 @@ __device__ __forceinline__ void bfs_persistent_run(const BfsParams& P, Lds& L) {
   TeamBases tb = {};
   const bool shared_out = MULTI && P.out_stride == 0;
   const bool incremental = shared_out && have_prev;
+  // every reader is behind the barrier that ends the set-up
+  if (threadIdx.x < 16) (&L.bases[0][0][0])[threadIdx.x] = 0;
   // a1: depth = parent = -1 except at the source, visited = {src}, Q = {src}
   {
     const int64_t tid = (int64_t)blockIdx.x * PB + threadIdx.x;
@@ -1626,6 +1669,7 @@ __device__ __forceinline__ void bfs_persistent_run(const BfsParams& P, Lds& L) {
   S.qdeg = fg_uni((int32_t)(P.off[J.src + 1] - P.off[J.src]));
   trace_iter(S, P, J);
   while (ok && S.qlen > 0) {
+    const BfsParams& P = reread_args();
     // backward -> forward: list the last pull's discoveries first
     // (a small level's are listed by the pull itself)
     if (MODE == FG_MODE_DO && S.dir == DIR_PUSH && S.prevdir == DIR_PULL) {
@@ -1647,7 +1691,7 @@ __device__ __forceinline__ void bfs_persistent_run(const BfsParams& P, Lds& L) {
       sm_seen++;
       const bool member = small_ep ? blockIdx.x == 0 : blockIdx.x < (uint32_t)P.team;
       if (member) {
-        if (!lds_mode<MODE>(P, J, S, L, small_ep ? 1u : (uint32_t)P.team, ts, tb)) ok = false;
+        if (!lds_mode<MODE>(reread_args(), J, S, L, small_ep ? 1u : (uint32_t)P.team, ts, tb)) ok = false;
         if (blockIdx.x == 0 && threadIdx.x == 0) {
           BfsCtl* c = P.ctl;
           // every waiter of the previous hand-back has read it (on a
@@ -1667,14 +1711,6 @@ __device__ __forceinline__ void bfs_persistent_run(const BfsParams& P, Lds& L) {
             c->pub_p = S.p;
             c->pub_insp_sum = S.insp_sum;
             c->pub_switches = S.switches;
-            c->pub_b[0] = S.b0q;
-            c->pub_b[1] = S.b0desc;
-            c->pub_b[2] = S.b0insp;
-            c->pub_b[3] = S.b0deg;
-            c->pub_b[4] = S.b1q;
-            c->pub_b[5] = S.b1desc;
-            c->pub_b[6] = S.b1insp;
-            c->pub_b[7] = S.b1deg;
             __hip_atomic_fetch_add(&c->sm_signal, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
             ack_need += fgb_n(P) - (small_ep ? 1u : (uint32_t)P.team);
           }
@@ -1700,7 +1736,6 @@ __device__ __forceinline__ void bfs_persistent_run(const BfsParams& P, Lds& L) {
             L.bcast[7] = c->pub_p;
             L.bcast[8] = c->pub_insp_sum;
             L.bcast[9] = c->pub_switches;
-            for (int i = 0; i < 8; ++i) L.bcast[10 + i] = (int64_t)c->pub_b[i];
             fg_handoff_ack(&P.ctl->sm_ack);
           }
         }
@@ -1719,58 +1754,47 @@ __device__ __forceinline__ void bfs_persistent_run(const BfsParams& P, Lds& L) {
         S.p = fg_uni(L.bcast[7]);
         S.insp_sum = fg_uni(L.bcast[8]);
         S.switches = fg_uni((int32_t)L.bcast[9]);
-        S.b0q = fg_uni((ull)L.bcast[10]);
-        S.b0desc = fg_uni((ull)L.bcast[11]);
-        S.b0insp = fg_uni((ull)L.bcast[12]);
-        S.b0deg = fg_uni((ull)L.bcast[13]);
-        S.b1q = fg_uni((ull)L.bcast[14]);
-        S.b1desc = fg_uni((ull)L.bcast[15]);
-        S.b1insp = fg_uni((ull)L.bcast[16]);
-        S.b1deg = fg_uni((ull)L.bcast[17]);
         __syncthreads();
       }
       continue;
     }
-    CtrSlot& C = P.ctl->slot[S.k & 1];
-    Bases B = get_bases(S);
-    if ((MODE != FG_MODE_DO || S.dir == DIR_PUSH) && S.qlen <= FG_WAVE) {
-      push_tiny(P, J, S, L);
+    if ((MODE != FG_MODE_DO || S.dir == DIR_PUSH) && S.qlen <= PB &&
+               push_chunks(reread_args(), J, S, L)) {
       if (!(ok = gs.sync_acquire(&L.flag))) break;
       S.qsel ^= 1;
     } else if (MODE != FG_MODE_DO || S.dir == DIR_PUSH) {
-      push_phase_a(P, J, S, L, fgb_n(P));
+      push_phase_a(reread_args(), J, S, L, fgb_n(P));
       if (!(ok = gs.sync_acquire(&L.flag))) break;
-      const ull dt = fg_atomic_load_u64(&C.desc.v);
-      const int64_t ndesc = (int64_t)(dt - B.desc);
+      const ull dt = fg_atomic_load_u64(&reread_args().ctl->slot[S.k & 1].desc.v);
+      const int64_t ndesc = (int64_t)(dt - get_bases(L, S).desc);
       if (ndesc > 0) {
-        push_phase_b(P, J, S, ndesc, L, fgb_n(P));
+        push_phase_b(reread_args(), J, S, ndesc, L, fgb_n(P));
         if (!(ok = gs.sync_acquire(&L.flag))) break;
       }
-      B.desc = dt;
       S.qsel ^= 1;
     } else {
-      pull_phase(P, J, S, L);
+      pull_phase<2>(reread_args(), J, S, L);
       if (!(ok = gs.sync_acquire(&L.flag))) break;
       S.cur ^= 1;
     }
+    const BfsParams& Q = reread_args();
+    CtrSlot& C = Q.ctl->slot[S.k & 1];
     const ull qt = fg_atomic_load_u64(&C.q.v);
     const ull it = fg_atomic_load_u64(&C.insp.v);
     const ull gt = fg_atomic_load_u64(&C.deg.v);
+    const Bases B = get_bases(L, S);
     const int64_t nq = (int64_t)(qt - B.q);
     const int64_t insp = (int64_t)(it - B.insp);
-    B.q = qt;
-    B.insp = it;
     // only a pull that lists what it finds adds up the degrees
     S.qdeg = S.dir == DIR_PULL && gt - B.deg < PULL_OVER ? (int64_t)(gt - B.deg) : -1;
-    B.deg = gt;
-    set_bases(S, B);
-    trace_insp(S.k, insp, P, J);
+    set_bases(L, S, Bases{qt, fg_atomic_load_u64(&C.desc.v), it, gt});
+    trace_insp(S.k, insp, Q, J);
     S.insp_sum += insp;
     S.k++;
     S.qlen = nq;
     S.p += nq;
-    decide<MODE>(S, P);
-    trace_iter(S, P, J);
+    decide<MODE>(S, Q);
+    trace_iter(S, Q, J);
   }
   if (shared_out && ok) {
     // every test-and-set of the traversal has completed (the last level's
@@ -1816,13 +1840,13 @@ __device__ __forceinline__ void bfs_persistent_run(const BfsParams& P, Lds& L) {
   // the last workgroup out clears the control block for the next launch
   __syncthreads();
   if (threadIdx.x == 0) {
-    const uint32_t done = __hip_atomic_fetch_add(&P.ctl->exit_count, 1u, __ATOMIC_ACQ_REL,
+    const uint32_t done = __hip_atomic_fetch_add(&P0.ctl->exit_count, 1u, __ATOMIC_ACQ_REL,
                                                  __HIP_MEMORY_SCOPE_AGENT);
-    L.flag = done == fgb_n(P) - 1;
+    L.flag = done == fgb_n(P0) - 1;
   }
   __syncthreads();
   if (L.flag) {
-    uint32_t* w = (uint32_t*)P.ctl;
+    uint32_t* w = (uint32_t*)P0.ctl;
     for (int i = threadIdx.x; i < (int)(sizeof(BfsCtl) / 4); i += PB) w[i] = 0u;
   }
 }

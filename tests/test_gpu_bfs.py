@@ -293,3 +293,30 @@ def test_pull_words(fg, orc, n, edges, degs, blocks):
         for do_b in ((1, 10), (1, 1), (1000, 1)):
             check_bfs(fg, orc, g, off, col, src, "do", do_a=(1, 100000), do_b=do_b, **kw)
     g.close()
+
+
+# pushes of short frontiers of long rows, whose chunks every workgroup lists
+# itself: up to 1024 vertices of mean degree big_degree (any degree up to 64
+# vertices), and the descriptors just past each bound; consecutive levels take
+# turns between the two, so each finds the other's counters
+@pytest.mark.parametrize("width,deg", [(64, 3), (65, 63), (65, 64), (900, 70), (1023, 300),
+                                       (1024, 64), (1025, 64), (1025, 300), (5000, 66)])
+@pytest.mark.parametrize("blocks", [1, 7, 0])
+def test_push_chunks(fg, orc, width, deg, blocks):
+    # source -> `width` vertices, each with deg - 1 neighbours of its own range
+    # of 6000, then chains behind those back to one vertex
+    n = 1 + width + 6000 + 500
+    rng = np.random.default_rng(width * deg)
+    a = np.arange(1, 1 + width)
+    u = [np.zeros(width, np.int64), np.repeat(a, deg - 1)]
+    v = [a, 1 + width + rng.integers(0, 6000, width * (deg - 1))]
+    u.append(1 + width + rng.integers(0, 6000, 500))
+    v.append(1 + width + 6000 + np.arange(500))
+    off, col = orc.csr_from_edges(n, np.concatenate(u).astype(np.int32),
+                                  np.concatenate(v).astype(np.int32))
+    g = fg.Graph(off, col)
+    kw = dict(grid_blocks=blocks) if blocks else dict(blocks_per_cu=1)
+    for src in (0, n - 1, 1 + width):
+        check_bfs(fg, orc, g, off, col, src, "push", team_blocks=-1, small_edges=1, **kw)
+        check_bfs(fg, orc, g, off, col, src, "do", big_degree=33, **kw)
+    g.close()
