@@ -136,3 +136,25 @@ def test_grid4096_workload(fg, orc):
             assert st.status == 0 and st.iterations == int(d.max()) + 1
             assert orc.check_bfs(off, col, src, d, to_np(parent)) is None
     g.close()
+
+
+@pytest.mark.parametrize("extra", [0, 1, 40])
+@pytest.mark.parametrize("K,T", [(2, 3), (7, 64), (64, 1), (128, 24)])
+def test_longest_row_at_the_bound(fg, orc, extra, K, T):
+    """Rows of up to four entries take one barrier per level, a graph with one
+    of five or more two: a grid (past the one-workgroup sizes), then with
+    chords that make rows of 5 and 44."""
+    R, C = 150, 200
+    off, col = synth.grid_csr(R, C)
+    rows = np.repeat(np.arange(R * C), np.diff(off)).astype(np.int32)
+    mid = (R // 2) * C + C // 2
+    far = (np.arange(extra) * 701 + 13).astype(np.int32) % (R * C)
+    u = np.concatenate([rows, np.full(extra, mid, np.int32)])
+    v = np.concatenate([col.astype(np.int32), far])
+    off, col = orc.csr_from_edges(R * C, u, v)
+    g = fg.Graph(off, col)
+    assert int(np.diff(off).max()) == 4 + extra
+    for src in (0, mid, R * C - 1):
+        st = run(fg, orc, g, off, col, src, K, T, f"grid+{extra}", expect_fallback=T == 1)
+        assert st.grid_blocks == T or T == 1
+    g.close()
