@@ -186,7 +186,8 @@ typedef struct {
                              member's frontier outgrows its LDS room
                              (0 = level-synchronous; at most 1024)            */
   int32_t grid_blocks;    /* workgroups of the persistent launch (0 = every CU x
-                             blocks_per_cu); in fg_bfs_corun, of the list's
+                             blocks_per_cu, fewer on small graphs in
+                             FG_MODE_DO); in fg_bfs_corun, of the list's
                              share (0 = every workgroup the team leaves)     */
 } fg_bfs_opts;
 
@@ -288,7 +289,8 @@ typedef struct {
                              the whole grid (0 = default)                     */
   int32_t blocks_per_cu;  /* persistent launch width (0 = default)            */
   int32_t grid_blocks;    /* workgroups of the persistent launch (0 = every
-                             CU x blocks_per_cu); fewer make each grid barrier
+                             CU x blocks_per_cu, fewer on small graphs of
+                             mean degree > 8); fewer make each grid barrier
                              cheaper when frontiers are small              */
   uint32_t delta;         /* near-far threshold step: only vertices closer
                              than the threshold are relaxed; it grows by delta
@@ -412,7 +414,7 @@ typedef struct {
   int32_t push_div;      /* pull -> push when active vertices < n / push_div (0 = 64) */
   int32_t blocks_per_cu; /* persistent launch width (0 = default)                     */
   int32_t grid_blocks;   /* workgroups of the persistent launch (0 = every CU x
-                            blocks_per_cu)                                          */
+                            blocks_per_cu, fewer on small graphs)                   */
   int32_t team_blocks;   /* workgroups that run push levels of medium frontiers from
                             LDS queues as a team (> 1 = that many; 1 = 32 while
                             fewer than 4 lanes hold queries, 64 otherwise; 0 = as 1

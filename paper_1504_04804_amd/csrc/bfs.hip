@@ -3005,9 +3005,16 @@ static fg_status bfs_launch(const fg_graph* g, int32_t src, const fg_bfs_opts& o
   FG_HIP_TRY(hipGetDevice(&dev));
   fg_device_props pr = fg_props(dev);
   if (!pr.coop) return fg_set_error(FG_EUNSUPPORTED, "fg_bfs: device lacks cooperative launch");
-  const int grid = persistent_grid(o, pr, o.mode == FG_MODE_DO
-                                              ? persistent_blocks_per_cu<FG_MODE_DO>(dev)
-                                              : persistent_blocks_per_cu<FG_MODE_PUSH>(dev));
+  int grid = persistent_grid(o, pr, o.mode == FG_MODE_DO
+                                        ? persistent_blocks_per_cu<FG_MODE_DO>(dev)
+                                        : persistent_blocks_per_cu<FG_MODE_PUSH>(dev));
+  // direction-optimizing with a rule that pulls (a push-only traversal reads
+  // every row), 256, 128 and 64 workgroups: R-MAT with 6 to 8 edges per vertex,
+  // n = 200 k 137, 121, 118 us, 500 k 113, 99, 97; with 20, 40 k 100, 91, 86,
+  // 200 k 111, 98, 94, 500 k 136, 126, 122; with 10, 1 M 252, 237, 254
+  if (o.mode == FG_MODE_DO && o.blocks_per_cu == 0 && o.grid_blocks == 0 &&
+      o.do_a_num <= o.do_a_den)
+    grid = fg_default_width(g->n, 1 << 19, 1 << 20, grid);
   BfsParams P = bfs_params(g, src, o, lay, depth, parent, stats, pr, grid, srcs, nsrc, out_stride);
 
   if (!srcs && solo_fits(g, o)) {

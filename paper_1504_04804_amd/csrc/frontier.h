@@ -9,6 +9,15 @@ namespace fgk {
 
 typedef unsigned long long ull;
 
+// Default width of a persistent launch on a graph of n vertices: a grid
+// barrier of 64 workgroups is 1 to 2 us cheaper than one of 256 and so is their
+// launch, which on small graphs is worth more than the width.  The bounds are
+// each kernel's own (see its launch), where the wider launch catches up.
+static inline int fg_default_width(int64_t n, int64_t upto64, int64_t upto128, int full) {
+  const int w = n <= upto64 ? 64 : n <= upto128 ? 128 : full;
+  return w < full ? w : full;
+}
+
 // One 256-byte line per counter so concurrent atomics do not share a line.
 struct alignas(256) Line64 {
   ull v;

@@ -320,3 +320,19 @@ def test_push_chunks(fg, orc, width, deg, blocks):
         check_bfs(fg, orc, g, off, col, src, "push", team_blocks=-1, small_edges=1, **kw)
         check_bfs(fg, orc, g, off, col, src, "do", big_degree=33, **kw)
     g.close()
+
+
+@pytest.mark.parametrize("n,m,bfs,sssp", [(16384, 200000, 1, 64), (16385, 200000, 1, 128),
+                                          (131072, 900000, 64, 128), (131073, 900000, 64, None),
+                                          (524288, 1500000, 64, None), (524289, 1500000, 128, None)])
+def test_default_width(fg, orc, n, m, bfs, sssp):
+    """The launch is as wide as the size asks for unless an option says
+    otherwise (mean degree above 8 for the shortest paths)."""
+    off, col = _hubs(orc, n, m, [700, 40], seed=n)
+    g = fg.Graph(off, col, synth.weights(off, col))
+    full = fg.bfs(g, 5, do_a=(1001, 1000))[2].grid_blocks
+    st = check_bfs(fg, orc, g, off, col, 5, "do")
+    assert st.grid_blocks == min(bfs, full) if bfs > 1 else st.grid_blocks == 1
+    assert check_bfs(fg, orc, g, off, col, 5, "do", grid_blocks=200).grid_blocks == 200
+    assert fg.sssp(g, 5)[2].grid_blocks == (sssp or full)
+    g.close()
