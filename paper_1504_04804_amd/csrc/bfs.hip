@@ -44,7 +44,7 @@ constexpr int TEAM_MAX = 64;  // widest team (one record per lane of a wave)
 // team-mode decision exact).
 constexpr int TW_CNT = 25, TW_FLAG = 50, TW_ARR = 57;
 constexpr int64_t TW_CAP = (1 << 19) - 1;
-constexpr int LDS_MEAN_DEG = 64;  // LDS-queue levels need a frontier of mean degree
+constexpr int LDS_MEAN_DEG = 64;  // a team's levels need a frontier of mean degree
                                   // <= this (hubs are cut up by the whole grid)
 constexpr int TPV = 4;        // LDS-queue levels: vertices of degree <= TPV are
                               // expanded by TPV lanes each, without a scan
@@ -1365,7 +1365,7 @@ __device__ __forceinline__ bool lds_mode(const BfsParams& P, const BfsJob& J, St
           qd = fg_uni(L.tsum[1]);
         }
         S.qdeg = qd;
-        if (qd > LDS_MEAN_DEG * S.qlen || qd > (solo ? P.small_e : P.team_e)) return true;
+        if (solo ? qd > P.small_e : qd > LDS_MEAN_DEG * S.qlen || qd > P.team_e) return true;
       }
       __syncthreads();
     }
@@ -1499,9 +1499,10 @@ __device__ __forceinline__ bool lds_mode(const BfsParams& P, const BfsJob& J, St
     S.p += nq;
     decide<MODE>(S, P);
     trace_iter(S, P, J);
-    bool stay = nq > 0 && S.dir == DIR_PUSH && nqdeg <= LDS_MEAN_DEG * nq &&
+    bool stay = nq > 0 && S.dir == DIR_PUSH &&
                 (solo ? (nq <= P.small_q && nqdeg <= P.small_e)
-                      : (nqdeg <= P.team_e && !(nq <= P.small_q && nqdeg <= P.small_e)));
+                      : (nqdeg <= LDS_MEAN_DEG * nq && nqdeg <= P.team_e &&
+                         !(nq <= P.small_q && nqdeg <= P.small_e)));
     int64_t nover = bcnt > QCAP ? bcnt - QCAP : 0, before = 0;
     bool rebalance = false;
     if (solo) {
@@ -1684,9 +1685,12 @@ __device__ __forceinline__ void bfs_persistent_run(const BfsParams& P0, Lds& L) 
     // qdeg < 0: not known after a full-grid push; the LDS modes take it
     // on entry and hand the level back when it does not fit
     const bool qdu = S.qdeg < 0;
-    const bool lds_ok = S.dir == DIR_PUSH && (qdu || S.qdeg <= LDS_MEAN_DEG * S.qlen);
-    const bool small_ep = lds_ok && S.qlen <= P.small_q && (qdu || S.qdeg <= P.small_e);
-    const bool team_ep = !small_ep && lds_ok && P.team > 1 && (qdu || S.qdeg <= P.team_e) &&
+    // a degree sum that is one pass of workgroup 0 is so however few vertices
+    // it comes from (an R-MAT source's one hub of 400 entries: 16 us by the
+    // whole grid, 5 alone)
+    const bool small_ep = S.dir == DIR_PUSH && S.qlen <= P.small_q && (qdu || S.qdeg <= P.small_e);
+    const bool team_ep = !small_ep && S.dir == DIR_PUSH &&
+                         (qdu || S.qdeg <= LDS_MEAN_DEG * S.qlen) && P.team > 1 && (qdu || S.qdeg <= P.team_e) &&
                          S.qlen <= (int64_t)QCAP * P.team / 2;
     if (small_ep || team_ep) {
       sm_seen++;

@@ -336,3 +336,20 @@ def test_default_width(fg, orc, n, m, bfs, sssp):
     assert check_bfs(fg, orc, g, off, col, 5, "do", grid_blocks=200).grid_blocks == 200
     assert fg.sssp(g, 5)[2].grid_blocks == (sssp or full)
     g.close()
+
+
+@pytest.mark.parametrize("deg", [65, 1022, 1023, 1024, 1025, 2500])
+def test_one_hub_levels(fg, orc, deg):
+    """A frontier of one long row: up to 1024 entries workgroup 0 takes it
+    alone, whatever the mean degree, past that the whole grid does."""
+    n = 40000
+    u = np.concatenate([np.zeros(1), np.full(deg, 1), np.full(deg, n - 1), np.arange(2, 30000)])
+    v = np.concatenate([np.ones(1), 2 + 3 * np.arange(deg), 5 + 7 * np.arange(deg),
+                        np.arange(3, 30001)])
+    off, col = orc.csr_from_edges(n, u.astype(np.int32), v.astype(np.int32))
+    g = fg.Graph(off, col)
+    for src in (0, 1, n - 1):
+        for mode in ("do", "push"):
+            check_bfs(fg, orc, g, off, col, src, mode)
+        check_bfs(fg, orc, g, off, col, src, "do", do_a=(1, 100000), small_edges=deg - 1)
+    g.close()
