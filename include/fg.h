@@ -294,8 +294,10 @@ typedef struct {
                              cheaper when frontiers are small              */
   uint32_t delta;         /* near-far threshold step: only vertices closer
                              than the threshold are relaxed; it grows by delta
-                             when none is left (0 = default: 64 x mean weight
-                             / mean degree; UINT32_MAX = no threshold, plain
+                             when none is left (0 = default: a factor x mean
+                             weight / mean degree: 64; on graphs of mean degree
+                             > 8, 256 up to 2^22 entries and 24 from 2^24 on;
+                             UINT32_MAX = no threshold, plain
                              frontier Bellman-Ford).  Results do not depend
                              on it.                                          */
   int32_t team_blocks;    /* workgroups that run medium frontiers from LDS
@@ -475,9 +477,11 @@ fg_status fg_msbfs_release(fg_msbfs* b, int32_t lane);
 typedef struct fg_mssp fg_mssp;
 
 typedef struct {
-  uint32_t delta;        /* near-far threshold step of every lane (0 = the
-                            fg_sssp default on graphs of mean degree <= 8,
-                            twice it on others; UINT32_MAX = no threshold) */
+  uint32_t delta;        /* near-far threshold step of every lane (0 = a
+                            factor x mean weight / mean degree: 256 on graphs
+                            of mean degree > 8, on others 160 up to 2^19
+                            vertices and 64 past that; UINT32_MAX = no
+                            threshold)                                       */
   int32_t big_degree;    /* vertices of at least this degree are relaxed in
                             64-edge chunks by many waves (0 = 64)            */
   int32_t blocks_per_cu; /* persistent launch width (0 = default)            */

@@ -1338,9 +1338,18 @@ MpLayout mp_layout(const fg_graph* g, void* ws) {
 
 int g_mp_occ[2][64];
 
-uint32_t default_delta(const fg_graph* g) {
+// Default near-far step of a batch: a factor times the mean edge weight over
+// the mean degree of the vertices with edges; at least 1.  A batch shares its
+// levels among the lanes, so it wants a coarser step than one source: 256 on
+// graphs of mean degree > 8 (64, 128, 256: R-MAT of 300 k vertices, 64 lanes
+// 4.08, 3.74, 3.63 ms, 2.5 M 28.6, 25.0, 24.3; 100 k, 30 lanes 1.62, 1.50,
+// 1.45); on others 160 up to 2^19 vertices (grids, 64 and 160: 100 x 120, 20
+// lanes 3.21 and 2.63 ms, 600 x 600, 64 lanes 41.4 and 36.0), 64 past that
+// (1200 x 1200 94.6 and 99.8).
+uint32_t default_delta(const fg_graph* g, bool low_deg) {
   if (g->m <= 0 || g->nonzero_degree <= 0) return 1u;
-  const double d = 64.0 * ((double)g->w_sum / (double)g->m) /
+  const double f = !low_deg ? 256.0 : g->n <= 1 << 19 ? 160.0 : 64.0;
+  const double d = f * ((double)g->w_sum / (double)g->m) /
                    ((double)g->m / (double)g->nonzero_degree);
   if (d >= 4294967295.0) return DIST_INF;
   return d < 1.0 ? 1u : (uint32_t)(d + 0.5);
@@ -1447,13 +1456,8 @@ extern "C" fg_status fg_mssp_step(fg_mssp* b, int32_t k_iters, void* stream) {
     P.pend_lane[i] = b->pend_lane[i];
     P.pend_src[i] = b->pend_src[i];
   }
-  // on graphs of mean degree > 8 a batch wants a coarser step than one
-  // source (R-MAT 22, 64 lanes: 81 ms at the one-source step, 66 ms at
-  // twice it); on grids the one-source step is best
   const bool low_deg = g->m <= (int64_t)TEAM_AUTO_DEG * g->n;
-  uint32_t dd = default_delta(g);
-  if (!low_deg && dd < DIST_INF / 2) dd *= 2;
-  P.delta = b->opts.delta > 0 ? b->opts.delta : dd;
+  P.delta = b->opts.delta > 0 ? b->opts.delta : default_delta(g, low_deg);
   P.big_deg = b->opts.big_degree > 0 ? b->opts.big_degree : CHS;
   if (P.big_deg > 65536) P.big_deg = 65536;  // keeps a wave's (edge, lane) count in int32
   // lanes from which a vertex is relaxed by a wave across its lanes: a wave
