@@ -3,12 +3,14 @@
 // direction-optimizing variant with the vertex-parallel early-exit pull
 // step and the inexpensive direction rule (Sec. VI-A, Alg. 2).
 //
-// The whole traversal runs in one cooperative (co-resident) launch: every
+// Small graphs are traversed by one workgroup out of LDS (bfs_solo).  Larger
+// ones run in one cooperative (co-resident) launch: every
 // iteration's direction is decided on the device from counters the
 // iteration before produced, so the host is not involved between
 // iterations.  Levels whose frontier is small are run by workgroup 0 alone
 // (no grid barrier at all); larger levels use the whole grid and one grid
-// barrier per iteration (two when high-degree vertices are present).
+// barrier per iteration (two when many vertices, some of high degree, are
+// pushed).
 //
 // Push load balance: a vertex of degree below `big_degree` is expanded by a
 // wave-level scan-gather (each lane takes one edge per round); a vertex of

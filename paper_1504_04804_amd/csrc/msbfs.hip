@@ -1509,6 +1509,7 @@ extern "C" fg_status fg_msbfs_read(fg_msbfs* b, int32_t lane, int32_t* depth, vo
                     hipPointerGetAttributes(&at, depth) == hipSuccess &&
                     at.type == hipMemoryTypeDevice && at.device == dev;
   if (!here) {
+    (void)hipGetLastError();  // the lookup of host memory may have failed
     FG_HIP_TRY(hipMemcpyAsync(depth, row, bytes, hipMemcpyDeviceToDevice, s));
     return FG_OK;
   }

@@ -248,3 +248,21 @@ def test_pull_row_classes(fg, orc, n, deg, blocks):
             assert np.array_equal(to_np(out[o:o + n]), to_np(b.read(3)))
         b.close()
     g.close()
+
+
+def test_read_into_pinned_host_memory(fg, orc):
+    """A lane's row goes wherever the copy could put it: device memory by a
+    kernel, host memory by the runtime; no error is left behind."""
+    off, col = synth.rmat_csr(10)
+    g = fg.Graph(off, col)
+    b = fg.MsBatch(g, 4)
+    b.admit(2, 7)
+    b.run()
+    host = torch.full((g.n,), -9, dtype=torch.int32, pin_memory=True)
+    b.read(2, host)
+    torch.cuda.synchronize()
+    assert np.array_equal(host.numpy(), orc.bfs(off, col, 7)[0])
+    check_lanes(fg, orc, b, off, col, {2: 7})
+    fg.bfs(g, 3)
+    b.close()
+    g.close()
