@@ -107,16 +107,15 @@ __device__ __forceinline__ int32_t cc_root(const int32_t* p, int32_t x) {
 // a forest of pointers to smaller vertices of the same component, written
 // without atomics (the first link of the link pass).
 __global__ __launch_bounds__(CC_BT) void cc_init_kernel(int32_t n, const int4* __restrict__ head,
-                                                        const int32_t* __restrict__ off,
                                                         int32_t* __restrict__ label,
                                                         CcCtl* __restrict__ ctl,
                                                         int64_t* __restrict__ comps) {
   for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n;
        v += (int64_t)gridDim.x * blockDim.x) {
     int32_t l = (int32_t)v;
-    if (head && off[v + 1] > off[v]) {
-      const int32_t u = head[v].x;
-      if (u < l) l = u;
+    if (head) {
+      const int32_t u = head[v].x;  // -1 without entries
+      if (u >= 0 && u < l) l = u;
     }
     label[v] = l;
   }
@@ -134,15 +133,16 @@ __global__ __launch_bounds__(CC_BT) void cc_init_kernel(int32_t n, const int4* _
 // hooked.
 constexpr int LINK_FIRST = 0, LINK_SECOND = 1, LINK_REST = 2;
 __global__ __launch_bounds__(CC_BT) void cc_link_kernel(int32_t n, const int4* __restrict__ head,
-                                                        const int32_t* __restrict__ off,
                                                         int32_t what, int32_t* __restrict__ label) {
   for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n;
        v += (int64_t)gridDim.x * blockDim.x) {
     const int4 h = head[v];
-    const int32_t deg = off[v + 1] - off[v];
-    if (what != LINK_SECOND && deg > 0 && (what == LINK_FIRST ? h.x != (int32_t)v : h.x > (int32_t)v))
+    // the head entry alone tells the rows apart: -1 without entries, the
+    // second like the first with one (or twice the same, then one is enough)
+    if (h.x < 0) continue;
+    if (what != LINK_SECOND && (what == LINK_FIRST ? h.x != (int32_t)v : h.x > (int32_t)v))
       cc_unite(label, (int32_t)v, h.x);
-    if (what != LINK_FIRST && deg > 1 && h.y != (int32_t)v) cc_unite(label, (int32_t)v, h.y);
+    if (what != LINK_FIRST && h.y != h.x && h.y != (int32_t)v) cc_unite(label, (int32_t)v, h.y);
   }
 }
 
@@ -345,14 +345,14 @@ extern "C" fg_status fg_cc(const fg_graph* g, int32_t* label, int64_t* component
   // and road-like graphs that would chain every vertex to the one before
   // it, so they hook both first entries by compare-and-swap.
   const bool init_link = g->m > 8 * (int64_t)g->n;
-  cc_init_kernel<<<grid, CC_BT, 0, s>>>(g->n, init_link ? g->head : nullptr, g->off, label, ctl,
+  cc_init_kernel<<<grid, CC_BT, 0, s>>>(g->n, init_link ? g->head : nullptr, label, ctl,
                                          comps);
   if (g->m > 0) {
     if (init_link) {
-      cc_link_kernel<<<grid, CC_BT, 0, s>>>(g->n, g->head, g->off, LINK_REST, label);
+      cc_link_kernel<<<grid, CC_BT, 0, s>>>(g->n, g->head, LINK_REST, label);
     } else {
-      cc_link_kernel<<<grid, CC_BT, 0, s>>>(g->n, g->head, g->off, LINK_FIRST, label);
-      cc_link_kernel<<<grid, CC_BT, 0, s>>>(g->n, g->head, g->off, LINK_SECOND, label);
+      cc_link_kernel<<<grid, CC_BT, 0, s>>>(g->n, g->head, LINK_FIRST, label);
+      cc_link_kernel<<<grid, CC_BT, 0, s>>>(g->n, g->head, LINK_SECOND, label);
     }
     cc_compress_kernel<CC_BT><<<grid, CC_BT, 0, s>>>(g->n, label, nullptr);
     cc_sample_kernel<<<1, CC_SAMPLES, 0, s>>>(g->n, label, ctl);
