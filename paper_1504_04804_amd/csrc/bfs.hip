@@ -625,7 +625,8 @@ __device__ __forceinline__ bool push_chunks(const BfsParams& P, const BfsJob& J,
     deg = P.off[u + 1] - b;
   }
   const int32_t tot = fg_block_sum<PB>(deg, L.red32);
-  if (S.qlen > FG_WAVE && tot < P.big_deg * (int32_t)S.qlen) return false;  // the same in every workgroup
+  // the same in every workgroup
+  if (S.qlen > FG_WAVE && tot < (int64_t)P.big_deg * S.qlen) return false;
   int32_t NC = 0;
   const int32_t ex = fg_block_excl_scan<PB>((deg + CH - 1) / CH, L.red32, &NC);
   sc[tid] = ex;
@@ -1560,7 +1561,25 @@ __device__ __forceinline__ const BfsParams& reread_args() {
 // first argument.
 template <int MODE, bool MULTI>
 __device__ __forceinline__ void bfs_persistent_run(const BfsParams& P0, Lds& L) {
-  fg_grid_sync gs{P0.ctl->bar, fgb_n(P0), 0u};
+  // the barrier's address and width are read again where it is used (see
+  // reread_args), only its count stays: held throughout they were spilled in
+  // bfs_corun (44 registers, now 5; 64 sources on R-MAT 22 beside a 4096 x
+  // 4096 grid 12.96 -> 12.73 ms)
+  uint32_t passed = 0;
+  auto grid_acquire = [&] {
+    const BfsParams& P = reread_args();
+    fg_grid_sync gs{P.ctl->bar, fgb_n(P), passed};
+    const bool ok = gs.sync_acquire(&L.flag);
+    passed = gs.count;
+    return ok;
+  };
+  auto grid_sync = [&] {
+    const BfsParams& P = reread_args();
+    fg_grid_sync gs{P.ctl->bar, fgb_n(P), passed};
+    const bool ok = gs.sync(&L.flag);
+    passed = gs.count;
+    return ok;
+  };
   bool ok = true;
   // one traversal, or (MULTI, a build of its own: the loop around the
   // traversal raises the register pressure) P0.nsrc traversals in turn
@@ -1586,7 +1605,7 @@ __device__ __forceinline__ void bfs_persistent_run(const BfsParams& P0, Lds& L) 
       // below publishes the clear.  Shared outputs have to be in memory
       // before others write the same places; separate ones need no write-back
       // here (3.7 us of the 31 between two traversals of R-MAT 22)
-      if (!(P.out_stride == 0 ? gs.sync(&L.flag) : gs.sync_acquire(&L.flag))) {
+      if (!(P.out_stride == 0 ? grid_sync() : grid_acquire())) {
         ok = false;
         break;
       }
@@ -1664,7 +1683,7 @@ __device__ __forceinline__ void bfs_persistent_run(const BfsParams& P0, Lds& L) 
     for (int64_t w = tid; w < P.nwords; w += nth)
       v0[w] = (w == (src >> 6)) ? (1ull << (src & 63)) : 0ull;
     if (tid == 0) P.q[0][0] = src;
-    if (!gs.sync(&L.flag)) ok = false;
+    if (!grid_sync()) ok = false;
   }
   if (blockIdx.x == 0 && threadIdx.x == 0 && J_stats(P, J)) {
     J_stats(P, J)->t_start = (int64_t)wall_clock64();
@@ -1679,7 +1698,7 @@ __device__ __forceinline__ void bfs_persistent_run(const BfsParams& P0, Lds& L) 
     if (MODE == FG_MODE_DO && S.dir == DIR_PUSH && S.prevdir == DIR_PULL) {
       if (S.qdeg < 0) {
         bitmap_diff_to_queue(P, S, L);
-        if (!(ok = gs.sync_acquire(&L.flag))) break;
+        if (!(ok = grid_acquire())) break;
         S.auxbase = fg_atomic_load_u64(&P.ctl->aux.v);
       }
       S.prevdir = DIR_PUSH;
@@ -1692,8 +1711,8 @@ __device__ __forceinline__ void bfs_persistent_run(const BfsParams& P0, Lds& L) 
     // whole grid, 5 alone)
     const bool small_ep = S.dir == DIR_PUSH && S.qlen <= P.small_q && (qdu || S.qdeg <= P.small_e);
     const bool team_ep = !small_ep && S.dir == DIR_PUSH &&
-                         (qdu || S.qdeg <= LDS_MEAN_DEG * S.qlen) && P.team > 1 && (qdu || S.qdeg <= P.team_e) &&
-                         S.qlen <= (int64_t)QCAP * P.team / 2;
+                         (qdu || S.qdeg <= LDS_MEAN_DEG * S.qlen) && P.team > 1 &&
+                         (qdu || S.qdeg <= P.team_e) && S.qlen <= (int64_t)QCAP * P.team / 2;
     if (small_ep || team_ep) {
       sm_seen++;
       const bool member = small_ep ? blockIdx.x == 0 : blockIdx.x < (uint32_t)P.team;
@@ -1766,22 +1785,22 @@ __device__ __forceinline__ void bfs_persistent_run(const BfsParams& P0, Lds& L) 
       continue;
     }
     if ((MODE != FG_MODE_DO || S.dir == DIR_PUSH) && S.qlen <= PB &&
-               push_chunks(reread_args(), J, S, L)) {
-      if (!(ok = gs.sync_acquire(&L.flag))) break;
+        push_chunks(reread_args(), J, S, L)) {
+      if (!(ok = grid_acquire())) break;
       S.qsel ^= 1;
     } else if (MODE != FG_MODE_DO || S.dir == DIR_PUSH) {
       push_phase_a(reread_args(), J, S, L, fgb_n(P));
-      if (!(ok = gs.sync_acquire(&L.flag))) break;
+      if (!(ok = grid_acquire())) break;
       const ull dt = fg_atomic_load_u64(&reread_args().ctl->slot[S.k & 1].desc.v);
       const int64_t ndesc = (int64_t)(dt - get_bases(L, S).desc);
       if (ndesc > 0) {
         push_phase_b(reread_args(), J, S, ndesc, L, fgb_n(P));
-        if (!(ok = gs.sync_acquire(&L.flag))) break;
+        if (!(ok = grid_acquire())) break;
       }
       S.qsel ^= 1;
     } else {
       pull_phase<2>(reread_args(), J, S, L);
-      if (!(ok = gs.sync_acquire(&L.flag))) break;
+      if (!(ok = grid_acquire())) break;
       S.cur ^= 1;
     }
     const BfsParams& Q = reread_args();
