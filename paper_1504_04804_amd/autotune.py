@@ -37,7 +37,7 @@ ASYNC = [16, 32, 64, 128, 256]
 ASYNC_TEAM = [32, 48, 64]
 PULL_DIV = [4, 8, 16, 64, 256]
 PUSH_DIV = [64, 512, 4096]
-CORUN_WIDTH = [0, 184, 176, 168, 160, 152, 144, 128]
+CORUN_WIDTH = [0, 184, 176, 168, 160, 152, 144, 136, 128]
 
 TUNED_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "tuned.json")
 
