@@ -466,7 +466,7 @@ __device__ __forceinline__ void push_phase_a(const BfsParams& P, const BfsJob& J
     if (lane < per && i < S.qlen) {
       const int32_t u = Qin[i];
       const int32_t deg = P.off[u + 1] - P.off[u];
-      if (deg >= P.big_deg) nd = (deg + CH - 1) / CH;
+      if (deg >= P.big_deg) nd = fg_pieces(deg, CH);
     }
     mine += nd;
   }
@@ -496,7 +496,7 @@ __device__ __forceinline__ void push_phase_a(const BfsParams& P, const BfsJob& J
     insp += deg;
     const bool big = deg >= P.big_deg;
     // descriptors of the high-degree lanes, written cooperatively
-    const int32_t nd = big ? (deg + CH - 1) / CH : 0;
+    const int32_t nd = big ? fg_pieces(deg, CH) : 0;
     const int32_t ndi = fg_wave_incl_scan(nd);
     const int32_t ND = __shfl(ndi, FG_WAVE - 1, FG_WAVE);
     if (ND > 0) {
@@ -516,7 +516,7 @@ __device__ __forceinline__ void push_phase_a(const BfsParams& P, const BfsJob& J
           const int32_t first = sb[j] + (t - sc[j]) * CH;
           // written through: read by other workgroups after the barrier
           fg_st_shared(&P.desc[pos + t],
-                       make_int4(su[j], first, first + CH < se[j] ? first + CH : se[j], 0));
+                       make_int4(su[j], first, se[j] - first > CH ? first + CH : se[j], 0));
         }
       }
     }
@@ -585,9 +585,9 @@ __device__ __forceinline__ void push_phase_b(const BfsParams& P, const BfsJob& J
     bool ok[4], won[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const int32_t e = dsc.y + r * FG_WAVE + lane;
-      ok[r] = e < e1;
-      v[r] = P.col[ok[r] ? e : e1 - 1];
+      const int32_t k = r * FG_WAVE + lane;
+      ok[r] = k < e1 - dsc.y;
+      v[r] = P.col[ok[r] ? dsc.y + k : e1 - 1];
       pu[r] = u;
     }
     visit4(P, J, vis32, d_new, v, pu, ok, won);
@@ -628,7 +628,7 @@ __device__ __forceinline__ bool push_chunks(const BfsParams& P, const BfsJob& J,
   // the same in every workgroup
   if (S.qlen > FG_WAVE && tot < (int64_t)P.big_deg * S.qlen) return false;
   int32_t NC = 0;
-  const int32_t ex = fg_block_excl_scan<PB>((deg + CH - 1) / CH, L.red32, &NC);
+  const int32_t ex = fg_block_excl_scan<PB>(fg_pieces(deg, CH), L.red32, &NC);
   sc[tid] = ex;
   su[tid] = u;
   sb[tid] = b;
@@ -642,14 +642,14 @@ __device__ __forceinline__ bool push_chunks(const BfsParams& P, const BfsJob& J,
   for (int64_t c = gw; c < NC; c += W) {
     const int32_t j = upper_idx(sc, (int32_t)S.qlen, (int32_t)c);
     const int32_t e0 = sb[j] + ((int32_t)c - sc[j]) * CH;
-    const int32_t e1 = e0 + CH < se[j] ? e0 + CH : se[j];
+    const int32_t e1 = se[j] - e0 > CH ? e0 + CH : se[j];
     int32_t v[4], pu[4];
     bool ok[4], won[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const int32_t e = e0 + r * FG_WAVE + lane;
-      ok[r] = e < e1;
-      v[r] = P.col[ok[r] ? e : e1 - 1];
+      const int32_t k = r * FG_WAVE + lane;
+      ok[r] = k < e1 - e0;
+      v[r] = P.col[ok[r] ? e0 + k : e1 - 1];
       pu[r] = su[j];
     }
     visit4(P, J, vis32, d_new, v, pu, ok, won);
@@ -687,13 +687,13 @@ __device__ __forceinline__ int32_t probe4(const BfsParams& P, const uint64_t* Vi
   int32_t u[4];
   uint64_t wv[4];
 #pragma unroll
-  for (int j = 0; j < 4; ++j) u[j] = P.col[i0 + j < e ? i0 + j : e - 1];
+  for (int j = 0; j < 4; ++j) u[j] = P.col[j < e - i0 ? i0 + j : e - 1];
 #pragma unroll
   for (int j = 0; j < 4; ++j) wv[j] = Vin[u[j] >> 6];
   int32_t hit = -1;
 #pragma unroll
   for (int j = 3; j >= 0; --j) {
-    if (i0 + j < e && ((wv[j] >> (u[j] & 63)) & 1ull)) {
+    if (j < e - i0 && ((wv[j] >> (u[j] & 63)) & 1ull)) {
       hit = j;
       pu = u[j];
     }
@@ -769,7 +769,7 @@ __device__ __forceinline__ void pull_resume(const BfsParams& P, const BfsJob& J,
     bool shortl = mine && e - b <= 16;
     for (int32_t i0 = 4; i0 < 16 && __ballot(shortl); i0 += 4) {
       if (shortl) {
-        if (b + i0 < e) {
+        if (i0 < e - b) {
           const int32_t h = probe4(P, Vin, b + i0, e, pu);
           if (h >= 0) {
             found = true;
@@ -791,12 +791,11 @@ __device__ __forceinline__ void pull_resume(const BfsParams& P, const BfsJob& J,
       const int32_t lb = __builtin_amdgcn_readlane(b, l) + 4;
       const int32_t le = __builtin_amdgcn_readlane(e, l);
       int32_t cnt2 = 0, hu = -1;
-      for (int32_t i0 = lb; i0 < le; i0 += FG_WAVE) {
-        const int32_t i = i0 + lane;
+      for (int64_t i0 = 0; i0 < le - lb; i0 += FG_WAVE) {
         int32_t u = 0;
         bool hb = false;
-        if (i < le) {
-          u = P.col[i];
+        if (i0 + lane < le - lb) {
+          u = P.col[lb + i0 + lane];
           hb = (Vin[u >> 6] >> (u & 63)) & 1ull;
         }
         const uint64_t m = __ballot(hb);
@@ -806,7 +805,7 @@ __device__ __forceinline__ void pull_resume(const BfsParams& P, const BfsJob& J,
           hu = __builtin_amdgcn_readlane(u, f);
           break;
         }
-        cnt2 += min(FG_WAVE, le - i0);
+        cnt2 += (int32_t)min((int64_t)FG_WAVE, le - lb - i0);
       }
       if (lane == l) {
         ins += cnt2;
@@ -2092,7 +2091,7 @@ __device__ void solo_push(const BfsParams& P, SoloLds<V>& L, const SoloLevel& K,
       b = P.off[u];
       deg = P.off[u + 1] - b;
     }
-    const int32_t nch = (deg + CH - 1) / CH;
+    const int32_t nch = fg_pieces(deg, CH);
     const int32_t inc = fg_wave_incl_scan(nch);
     const int32_t NC = __builtin_amdgcn_readlane(inc, FG_WAVE - 1);
     wave_lds_fence();

@@ -291,23 +291,24 @@ __global__ __launch_bounds__(DUP_BT) void dup_step_kernel(DupArgs A) {
           // flight together (a row is otherwise a chain of dependent
           // loads); the entries read still stop at the first hit
           const int32_t e = A.off[v + 1];
-          for (int32_t i0 = A.off[v]; i0 < e && !found; i0 += 4) {
+          const int32_t b = A.off[v];
+          for (int64_t i0 = 0; i0 < e - b && !found; i0 += 4) {
             int32_t u[4];
             uint64_t wv[4];
 #pragma unroll
-            for (int k = 0; k < 4; ++k) u[k] = A.col[i0 + k < e ? i0 + k : e - 1];
+            for (int k = 0; k < 4; ++k) u[k] = A.col[k < e - b - i0 ? b + i0 + k : e - 1];
 #pragma unroll
             for (int k = 0; k < 4; ++k) wv[k] = A.visited[u[k] >> 6];
             int32_t h = -1;
 #pragma unroll
             for (int k = 3; k >= 0; --k)
-              if (i0 + k < e && ((wv[k] >> (u[k] & 63)) & 1ull)) h = k;
+              if (k < e - b - i0 && ((wv[k] >> (u[k] & 63)) & 1ull)) h = k;
             if (h >= 0) {
               found = true;
               pu = u[h];
               insp += h + 1;
             } else {
-              insp += e - i0 < 4 ? e - i0 : 4;
+              insp += e - b - i0 < 4 ? (int32_t)(e - b - i0) : 4;
             }
           }
         }
@@ -344,13 +345,13 @@ __global__ __launch_bounds__(DUP_BT) void dup_big_kernel(DupArgs A) {
     const int32_t u = A.big[i];
     const int32_t b = A.off[u];
     const int32_t deg = A.off[u + 1] - b;
-    const int64_t ntask = (deg + DUP_CHUNK - 1) / DUP_CHUNK;
+    const int64_t ntask = ((int64_t)deg + DUP_CHUNK - 1) / DUP_CHUNK;
     int64_t first = ((int64_t)blockIdx.x - base) % (int64_t)gridDim.x;
     if (first < 0) first += gridDim.x;
     for (int64_t t = first; t < ntask; t += gridDim.x) {
       const int32_t e_end = (int32_t)((t + 1) * DUP_CHUNK < deg ? (t + 1) * DUP_CHUNK : deg);
-      for (int32_t e0 = (int32_t)(t * DUP_CHUNK); e0 < e_end; e0 += DUP_BT) {
-        const int32_t e = e0 + threadIdx.x;
+      for (int64_t e0 = t * DUP_CHUNK; e0 < e_end; e0 += DUP_BT) {
+        const int64_t e = e0 + threadIdx.x;
         fwd_visit(A, e < e_end ? A.col[b + e] : -1, u, d_new, nq);
         insp += e < e_end;
       }

@@ -18,6 +18,11 @@ static inline int fg_default_width(int64_t n, int64_t upto64, int64_t upto128, i
   return w < full ? w : full;
 }
 
+// Pieces of `per` entries in a row (a row may have 2^31 - 1).
+__host__ __device__ __forceinline__ int32_t fg_pieces(int32_t entries, int32_t per) {
+  return (int32_t)(((uint32_t)entries + (uint32_t)per - 1u) / (uint32_t)per);
+}
+
 // One 256-byte line per counter so concurrent atomics do not share a line.
 struct alignas(256) Line64 {
   ull v;

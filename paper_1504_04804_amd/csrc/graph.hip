@@ -44,7 +44,7 @@ __global__ void validate_kernel(int32_t n, int64_t m, const int32_t* __restrict_
       bad |= VAL_MONO;
       continue;
     }
-    for (int32_t i = b + lane; i < e; i += FG_WAVE) {
+    for (int64_t i = (int64_t)b + lane; i < e; i += FG_WAVE) {
       int32_t v = col[i];
       if (v < 0 || v >= n) {
         bad |= VAL_COL;

@@ -279,7 +279,7 @@ __device__ void push_expand(const MsParams& P, const MsState& S, int32_t k, int6
       vcnt += fu != 0ull;
     }
     const bool big = deg >= P.big_deg;
-    const int32_t nd = big ? (deg + CH - 1) / CH : 0;
+    const int32_t nd = big ? fg_pieces(deg, CH) : 0;
     const int32_t ndi = fg_wave_incl_scan(nd);
     const int32_t ND = __shfl(ndi, FG_WAVE - 1, FG_WAVE);
     if (ND > 0) {
@@ -390,7 +390,7 @@ __device__ void put_long(const MsParams& P, int32_t* sc, int32_t* su, int32_t* s
     if (i0 + lane < cnt) {
       v = stage[i0 + lane];
       b = P.off[v] + 4;
-      nch = (P.off[v + 1] - b + CH - 1) / CH;
+      nch = fg_pieces(P.off[v + 1] - b, CH);
       fg_st_shared(&Qlong[pos + i0 + lane], v);
     }
     const int32_t inc = fg_wave_incl_scan(nch);
@@ -421,11 +421,14 @@ __device__ __forceinline__ void pull_rows(const MsParams& P, const ull* Fc, cons
   for (int32_t i0 = 0; i0 < cnt; i0 += FG_WAVE / 8) {
     const int32_t i = i0 + lane / 8;
     const int32_t ic = i < cnt ? i : cnt - 1;
-    const int32_t b = sb[ic] + lane % 8, e = se[ic];
+    const int32_t b = sb[ic], e = se[ic];
     const ull w = sf[ic];
     int32_t u[R];
 #pragma unroll
-    for (int r = 0; r < R; ++r) u[r] = P.col[8 * r < e - b ? b + 8 * r : e - 1];
+    for (int r = 0; r < R; ++r) {
+      const int32_t k = lane % 8 + 8 * r;
+      u[r] = P.col[k < e - b ? b + k : e - 1];
+    }
     ull x = 0;
 #pragma unroll
     for (int r = 0; r < R; ++r) x |= Fc[u[r]];
@@ -1080,7 +1083,7 @@ __global__ __launch_bounds__(PB) void msbfs_persistent(MsParams P) {
           }
           if (lng) lst.buf[lst.cnt + fg_mbcnt(lm)] = (int32_t)v;
           lst.cnt += __popcll(lm);
-          lch += fg_wave_sum(lng ? (e - b - 4 + CH - 1) / CH : 0);
+          lch += fg_wave_sum(lng ? fg_pieces(e - b - 4, CH) : 0);
         }
         // up to 16 further entries, then up to 60: compacted, eight lanes a row
         for (int pass = 0; pass < 2; ++pass) {
@@ -1152,13 +1155,13 @@ __global__ __launch_bounds__(PB) void msbfs_persistent(MsParams P) {
             const ull cur = fg_uni(__hip_atomic_load(&Fn[v], __ATOMIC_RELAXED,
                                                      __HIP_MEMORY_SCOPE_AGENT));
             if ((cur & want) == want) continue;  // every wanted lane already found
-            const int32_t e1 = min(dsc.y + CH, P.off[v + 1]);
-            if (lane == 0) ecnt += (uint32_t)(e1 - dsc.y);
+            const int32_t len = min(CH, P.off[v + 1] - dsc.y);
+            if (lane == 0) ecnt += (uint32_t)len;
             ull x = 0;
 #pragma unroll
             for (int r = 0; r < CH / FG_WAVE; ++r) {
-              const int32_t i2 = dsc.y + r * FG_WAVE + lane;
-              if (i2 < e1) x |= Fc[P.col[i2]];
+              const int32_t k2 = r * FG_WAVE + lane;
+              if (k2 < len) x |= Fc[P.col[dsc.y + k2]];
             }
             x = fg_wave_or64(x & want);
             if (lane == 0 && (x & ~cur)) atomicOr(&Fn[v], x);

@@ -297,10 +297,11 @@ __device__ void relax_edges(const MpParams& P, const Lds& L, int32_t u, int32_t 
   const uint32_t du = (m >> lane) & 1ull ? P.dist[(int64_t)u * MAXL + lane] : DIST_INF;
   const uint32_t Tl = L.T[lane];
   const bool may_ovf = __ballot(du != DIST_INF && du >= DIST_INF - P.w_max) != 0ull;
-  for (int32_t c = e0; c < e1; c += FG_WAVE) {
-    const int32_t k = e1 - c < FG_WAVE ? e1 - c : FG_WAVE;
-    const int32_t vl = P.col[c + (lane < k ? lane : k - 1)];
-    const uint32_t wl = P.w[c + (lane < k ? lane : k - 1)];
+  // (a row may end at 2^31 - 1: no index past an end is formed)
+  for (int32_t c = 0; c < e1 - e0; c += FG_WAVE) {
+    const int32_t k = e1 - e0 - c < FG_WAVE ? e1 - e0 - c : FG_WAVE;
+    const int32_t vl = P.col[e0 + c + (lane < k ? lane : k - 1)];
+    const uint32_t wl = P.w[e0 + c + (lane < k ? lane : k - 1)];
     uint32_t nx[EPG];
 #pragma unroll
     for (int r = 0; r < EPG; ++r)
@@ -1050,7 +1051,7 @@ __global__ __launch_bounds__(PB) void mssp_persistent(MpParams P) {
         const bool big = d >= P.big_deg;
         const bool dense = !big && d > 0 && pc >= P.dense;
         // edge chunks
-        const int32_t nch = big ? (d + CHS - 1) / CHS : 0;
+        const int32_t nch = big ? fg_pieces(d, CHS) : 0;
         const int32_t chi = fg_wave_incl_scan(nch);
         const int32_t NC = __shfl(chi, FG_WAVE - 1, FG_WAVE);
         if (NC > 0) {
@@ -1183,7 +1184,7 @@ __global__ __launch_bounds__(PB) void mssp_persistent(MpParams P) {
         if (i + W < nd) nxt = P.desc[i + W];
         nend = P.off[nxt.x + 1];
         const ull m = (ull)(uint32_t)dsc.z | ((ull)(uint32_t)dsc.w << 32);
-        const int32_t e1 = dsc.y + CHS < e_end ? dsc.y + CHS : e_end;
+        const int32_t e1 = e_end - dsc.y > CHS ? dsc.y + CHS : e_end;
         if (__popcll(m) >= P.dense) {
           relax_edges(P, L, dsc.x, dsc.y, e1, m, O, st, fst, H, nb2, ovf);
           continue;
@@ -1193,10 +1194,10 @@ __global__ __launch_bounds__(PB) void mssp_persistent(MpParams P) {
         while (mm) {
           const int l = __builtin_ctzll(mm);
           mm &= mm - 1;
-          const int32_t e = dsc.y + lane;
           bool fn = false, ff = false;
           int32_t v = 0;
-          if (e < e1) relax_one(P, L, dsc.x, l, e, O, fn, ff, v, nb2, ovf);
+          if (lane < e1 - dsc.y)
+            relax_one(P, L, dsc.x, l, dsc.y + lane, O, fn, ff, v, nb2, ovf);
           st.push(fn, v, O.qcnt, 0ull, O.Qn);
           fst.push(ff, v, O.fpos, O.fcnt, O.fbase, O.pile);
         }

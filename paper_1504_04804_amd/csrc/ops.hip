@@ -368,8 +368,8 @@ __device__ __forceinline__ void probe_row(const int32_t* col, const uint32_t* fb
   bool hit[4];
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
-    const int32_t k = c + r * width + (lane - first);
-    u[r] = k < end ? col[k] : -1;
+    const int32_t k = r * width + (lane - first);
+    u[r] = k < end - c ? col[c + k] : -1;
   }
 #pragma unroll
   for (int r = 0; r < 4; ++r) hit[r] = u[r] >= 0 && bit_of(fbits, u[r]);
@@ -445,8 +445,8 @@ __global__ __launch_bounds__(PL_BT) void pull_step_kernel(
       found = h0 || h1 || h2 || h3;
       pu = h0 ? h.x : h1 ? h.y : h2 ? h.z : h.w;
       insp += h0 ? 1 : h1 ? 2 : h2 ? 3 : d;
-      i += 4;
-      open = !found && i < e;
+      open = !found && e - i > 4;
+      if (open) i += 4;
     }
     {
       const bool listed = open && e - i > PL_LANE - 4;
@@ -461,17 +461,17 @@ __global__ __launch_bounds__(PL_BT) void pull_step_kernel(
     }
     while (__ballot(open)) {
       if (open) {
-        const int32_t l = e - 1;
-        const int32_t u0 = col[i], u1 = col[i + 1 < l ? i + 1 : l];
-        const int32_t u2 = col[i + 2 < l ? i + 2 : l], u3 = col[i + 3 < l ? i + 3 : l];
+        const int32_t l = e - 1 - i;
+        const int32_t u0 = col[i], u1 = col[i + (l < 1 ? l : 1)];
+        const int32_t u2 = col[i + (l < 2 ? l : 2)], u3 = col[i + (l < 3 ? l : 3)];
         const bool h0 = bit_of(fbits, u0), h1 = bit_of(fbits, u1);
         const bool h2 = bit_of(fbits, u2), h3 = bit_of(fbits, u3);
         const int32_t d = e - i < 4 ? e - i : 4;
         found = h0 || h1 || h2 || h3;
         pu = h0 ? u0 : h1 ? u1 : h2 ? u2 : u3;
         insp += h0 ? 1 : h1 ? 2 : h2 ? 3 : d;
-        i += 4;
-        open = !found && i < e;
+        open = !found && e - i > 4;
+        if (open) i += 4;
       }
     }
     {
@@ -496,7 +496,7 @@ __global__ __launch_bounds__(PL_BT) void pull_step_kernel(
         end = off[x.x + 1];
       }
       const int32_t stop = end - c > PL_GROUP_MAX ? c + PL_GROUP_MAX : end;
-      c += 4;
+      c = end - c > 4 ? c + 4 : end;
       bool hit = false;  // the group's row is done; it waits for the wave's others
       while (__ballot(c < stop)) {
         int32_t at, got = -1;
@@ -512,7 +512,7 @@ __global__ __launch_bounds__(PL_BT) void pull_step_kernel(
               atomicOr(&s_new[x.y], 1ull << (x.x & 63));
             }
           }
-          c = hit ? stop : c + 4 * PL_GROUP;
+          c = hit || stop - c <= 4 * PL_GROUP ? stop : c + 4 * PL_GROUP;
         }
       }
       stage.push(hit && lane == first, x.x);
@@ -530,7 +530,8 @@ __global__ __launch_bounds__(PL_BT) void pull_step_kernel(
     for (int32_t j = wid; j < nhub; j += PL_WAVES) {
       const int2 x = s_hub[j];
       const int32_t end = off[x.x + 1];
-      for (int32_t c = off[x.x] + PL_GROUP_MAX; c < end; c += 4 * FG_WAVE) {
+      for (int64_t c64 = (int64_t)off[x.x] + PL_GROUP_MAX; c64 < end; c64 += 4 * FG_WAVE) {
+        const int32_t c = (int32_t)c64;
         int32_t at, got = -1;
         probe_row(col, fbits, c, end, 0, FG_WAVE, &at, &got);
         if (at >= 0) {

@@ -137,10 +137,9 @@ __device__ __forceinline__ double seg_incl_sum(double x, int lane, int start) {
 __device__ __forceinline__ double strided_gather_sum(const double* cur, const int32_t* col,
                                                      int32_t first, int32_t end, int32_t stride) {
   double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
-  int32_t i = first;
-  // every index of a round is below `end`: i < end - 3 * stride (no
-  // overflow: end >= 0 and 3 * stride is small)
-  for (; i < end - 3 * stride; i += 4 * stride) {
+  // 64-bit places: a row may end at 2^31 - 1
+  int64_t i = first;
+  for (; i < (int64_t)end - 3 * stride; i += 4 * stride) {
     const int32_t c0 = col[i];
     const int32_t c1 = col[i + stride];
     const int32_t c2 = col[i + 2 * stride];
@@ -485,7 +484,7 @@ __global__ __launch_bounds__(PP_BT) void pp_number_kernel(int32_t n,
     __syncthreads();
     at[r] = s_wc[wid][k] + rank;
     if (d[r] >= PP_SHORT) entry[r] = atomicAdd(&s_entries, (uint32_t)d[r]);
-    if (d[r] >= PP_SEG) seg[r] = atomicAdd(&s_segs, (uint32_t)((d[r] + PP_SEG - 1) / PP_SEG));
+    if (d[r] >= PP_SEG) seg[r] = atomicAdd(&s_segs, (uint32_t)fgk::fg_pieces(d[r], PP_SEG));
     __syncthreads();
     for (int i = threadIdx.x; i < PP_BUCKETS; i += PP_BT)
       for (int w = 0; w < PP_WAVES; ++w) s_wc[w][i] = 0;
@@ -586,7 +585,8 @@ __global__ __launch_bounds__(PP_BT) void pp_columns_kernel(const int32_t* __rest
   const uint32_t rs = P->rows_seg, rl = P->rows_long, rows = P->rows, segs = P->next_seg;
   for (uint32_t x = blockIdx.x; x < rs; x += gridDim.x) {
     const int32_t d = Q.deg[x];
-    for (int32_t j = wid; j * PP_SEG < d; j += PP_WAVES) {
+    const int32_t pieces = fgk::fg_pieces(d, PP_SEG);
+    for (int32_t j = wid; j < pieces; j += PP_WAVES) {
       const int32_t at = j * PP_SEG;
       pp_segment(Q, col + Q.beg[x] + at, Q.place[x] + at, d - at < PP_SEG ? d - at : PP_SEG,
                  Q.seg0[x] + j, s_tmp[wid], s_run[wid]);
@@ -777,7 +777,7 @@ __global__ __launch_bounds__(PP_BT) void pp_iter_kernel(PrArgs A, PrPlanned Q, i
   for (uint32_t u = gw; u < u2; u += W) {
     if (u < rs) {
       // a row of several segments, a wave across its partial sums
-      const uint32_t k = (uint32_t)(Q.deg[u] + PP_SEG - 1) / PP_SEG * PP_XCD;
+      const uint32_t k = (uint32_t)fgk::fg_pieces(Q.deg[u], PP_SEG) * PP_XCD;
       const double* p = Q.part + Q.seg0[u];
       double acc = 0.0;
       for (uint32_t i = lane; i < k; i += FG_WAVE)

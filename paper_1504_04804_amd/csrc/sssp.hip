@@ -380,7 +380,7 @@ __device__ void phase_a(const SsspParams& P, const St& S, Lds& L) {
     }
     insp += deg;
     const bool big = deg >= P.big_deg;
-    const int32_t nd = big ? (deg + CH - 1) / CH : 0;
+    const int32_t nd = big ? fg_pieces(deg, CH) : 0;
     const int32_t ndi = fg_wave_incl_scan(nd);
     const int32_t ND = __shfl(ndi, FG_WAVE - 1, FG_WAVE);
     if (ND > 0) {
