@@ -1446,7 +1446,7 @@ extern "C" fg_status fg_msbfs_step(fg_msbfs* b, int32_t k_iters, void* stream) {
   // 256, 128 and 64 workgroups, 20 to 60 lanes: R-MAT of 1500 vertices 304,
   // 286, 277 us; 80 k 692, 686, 773; 150 k 434, 444, 483; grids: 100 x 120
   // 2072, 1816, 1703; 300 x 350 6065, 5313, 5764
-  if (b->opts.blocks_per_cu == 0 && b->opts.pull_div == 0)
+  if (b->opts.blocks_per_cu == 0 && b->opts.grid_blocks == 0 && b->opts.pull_div == 0)
     grid = fg_default_width(g->n, 1 << 14, 1 << 17, grid);
   if (b->opts.grid_blocks > 0 && b->opts.grid_blocks < grid) grid = b->opts.grid_blocks;
   // by default the team kernel runs on graphs of mean degree <= 8 (grids,

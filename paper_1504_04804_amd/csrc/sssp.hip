@@ -1967,7 +1967,7 @@ extern "C" fg_status fg_sssp(const fg_graph* g, int32_t src, const fg_sssp_opts*
   int grid = pr.cus * bpc;
   // R-MAT, 256, 128 and 64 workgroups: n = 1500 254, 236, 229 us; 16 k 367,
   // 347, 350; 30 k 368, 328, 342; 100 k 448, 417, 447; 150 k 523, 532, 640
-  if (o.blocks_per_cu == 0 && g->m > (int64_t)TEAM_AUTO_DEG * g->n)
+  if (o.blocks_per_cu == 0 && o.grid_blocks == 0 && g->m > (int64_t)TEAM_AUTO_DEG * g->n)
     grid = fg_default_width(g->n, 1 << 14, 1 << 17, grid);
   if (o.grid_blocks > 0 && o.grid_blocks < grid) grid = o.grid_blocks;
 

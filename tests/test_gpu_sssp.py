@@ -261,3 +261,13 @@ def test_async_team_near_vertices_without_room(fg, orc):
         for s in (0, 1, n - 1):
             assert check(fg, orc, g, off, col, w, s, delta=0xFFFFFFFF).grid_blocks <= 8
             check(fg, orc, g, off, col, w, s)
+
+
+@pytest.mark.parametrize("blocks", [1, 65, 200])
+def test_explicit_width(fg, orc, blocks):
+    """grid_blocks is the launch's width also where the default is narrower."""
+    off, col = synth.rmat_csr(13)
+    w = synth.weights(off, col)
+    g = fg.Graph(off, col, weights=w)
+    assert check(fg, orc, g, off, col, w, 3).grid_blocks == 64
+    assert check(fg, orc, g, off, col, w, 3, grid_blocks=blocks).grid_blocks == blocks
