@@ -94,8 +94,8 @@ __global__ void degree_summary_kernel(int32_t n, int32_t nwords,
       int4 h = make_int4(-1, -1, -1, -1);
       if (d > 0) {
         const int32_t l = b + d - 1;
-        h = make_int4(col[b], col[b + 1 < l ? b + 1 : l], col[b + 2 < l ? b + 2 : l],
-                      col[b + 3 < l ? b + 3 : l]);
+        h = make_int4(col[b], col[d > 1 ? b + 1 : l], col[d > 2 ? b + 2 : l],
+                      col[d > 3 ? b + 3 : l]);
       }
       head[v] = h;
     }

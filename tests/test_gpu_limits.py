@@ -29,7 +29,7 @@ def env():
 
 
 @pytest.mark.parametrize("hit", [False, True])
-@pytest.mark.parametrize("L", [3, 30, 62, 130, 300, 700])
+@pytest.mark.parametrize("L", [1, 2, 3, 30, 62, 130, 300, 700])
 def test_rows_that_end_at_the_largest_entry(env, L, hit):
     """Vertex 5 has one entry, to 6; the last vertex has L, none of them 5
     unless `hit`, then the last; 256 vertices hold all others, every one 5."""
