@@ -791,11 +791,11 @@ __device__ __forceinline__ void pull_resume(const BfsParams& P, const BfsJob& J,
       const int32_t lb = __builtin_amdgcn_readlane(b, l) + 4;
       const int32_t le = __builtin_amdgcn_readlane(e, l);
       int32_t cnt2 = 0, hu = -1;
-      for (int64_t i0 = 0; i0 < le - lb; i0 += FG_WAVE) {
+      for (int32_t i0 = lb;; i0 += FG_WAVE) {
         int32_t u = 0;
         bool hb = false;
-        if (i0 + lane < le - lb) {
-          u = P.col[lb + i0 + lane];
+        if (lane < le - i0) {
+          u = P.col[i0 + lane];
           hb = (Vin[u >> 6] >> (u & 63)) & 1ull;
         }
         const uint64_t m = __ballot(hb);
@@ -805,7 +805,8 @@ __device__ __forceinline__ void pull_resume(const BfsParams& P, const BfsJob& J,
           hu = __builtin_amdgcn_readlane(u, f);
           break;
         }
-        cnt2 += (int32_t)min((int64_t)FG_WAVE, le - lb - i0);
+        cnt2 += min(FG_WAVE, le - i0);
+        if (le - i0 <= FG_WAVE) break;
       }
       if (lane == l) {
         ins += cnt2;
@@ -1906,7 +1907,8 @@ __global__ __launch_bounds__(PB) void bfs_persistent(BfsParams P) {
 // 118 -> 64 us (0.9 us per level), 100 x 100 352 -> 215; asynchronous 122 ->
 // 64 and 284 -> 215; 180 x 180 direction-optimizing 795 -> 537.
 constexpr int32_t SOLO_N = 32768;
-constexpr int64_t SOLO_M = 2 << 20;
+constexpr int64_t SOLO_M = 2 << 20;   // where most entries are in hubs' rows
+constexpr int64_t SOLO_EM = 5 << 16;  // where rows are alike
 constexpr int32_t SOLO_KN = 20480;
 constexpr int64_t SOLO_KM = 1 << 18;
 constexpr int32_t SOLO_ROW = CH;
