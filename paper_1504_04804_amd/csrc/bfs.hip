@@ -3037,10 +3037,18 @@ static fg_status bfs_launch(const fg_graph* g, int32_t src, const fg_bfs_opts& o
   // direction-optimizing with a rule that pulls (a push-only traversal reads
   // every row), 256, 128 and 64 workgroups: R-MAT with 6 to 8 edges per vertex,
   // n = 200 k 137, 121, 118 us, 500 k 113, 99, 97; with 20, 40 k 100, 91, 86,
-  // 200 k 111, 98, 94, 500 k 136, 126, 122; with 10, 1 M 252, 237, 254
+  // 200 k 111, 98, 94, 500 k 136, 126, 122; with 7, 1 M 328, 327, 365 and 109,
+  // 108, 113; 1.5 M still 236, 224, 241.  There a pull stops at a hub; where
+  // rows are alike it reads a large part of the entries, and their number
+  // counts: uniform random, n = 262 k with 3 edges 173, 156, 156, 7 142, 136,
+  // 147, 16 144, 158, 205; 131 k with 16 123, 114, 122; 524 k with 3 190, 178,
+  // 195, 16 192, 253, 395; 1 M with 7 216, 279, 409
   if (o.mode == FG_MODE_DO && o.blocks_per_cu == 0 && o.grid_blocks == 0 &&
-      o.do_a_num <= o.do_a_den)
-    grid = fg_default_width(g->n, 1 << 19, 1 << 20, grid);
+      o.do_a_num <= o.do_a_den) {
+    const bool skewed = fg_skewed(g);
+    grid = fg_default_width(g, 1 << 19, 1 << 20, skewed ? INT64_MAX : 3 << 20,
+                            skewed ? INT64_MAX : 1 << 22, grid);
+  }
   BfsParams P = bfs_params(g, src, o, lay, depth, parent, stats, pr, grid, srcs, nsrc, out_stride);
 
   if (!srcs && solo_fits(g, o)) {

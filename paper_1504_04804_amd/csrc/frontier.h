@@ -9,12 +9,21 @@ namespace fgk {
 
 typedef unsigned long long ull;
 
-// Default width of a persistent launch on a graph of n vertices: a grid
-// barrier of 64 workgroups is 1 to 2 us cheaper than one of 256 and so is their
-// launch, which on small graphs is worth more than the width.  The bounds are
-// each kernel's own (see its launch), where the wider launch catches up.
-static inline int fg_default_width(int64_t n, int64_t upto64, int64_t upto128, int full) {
-  const int w = n <= upto64 ? 64 : n <= upto128 ? 128 : full;
+// Most entries are in rows far longer than the mean: the mean degree at an
+// entry's end is at least twice that of a vertex (grids and uniform random
+// graphs, whatever single hubs they have, 1.0 to 1.5 times; R-MAT 7 to 80,
+// still 2.6 where a quarter of all pairs are edges).
+static inline bool fg_skewed(const fg_graph* g) {
+  return (double)g->deg_sq * (double)g->n >= 2.0 * (double)g->m * (double)g->m;
+}
+
+// Default width of a persistent launch: a grid barrier of 64 workgroups is 1
+// to 2 us cheaper than one of 256 and so is their launch, which is worth more
+// than the width where vertices and entries are few.  The bounds are each
+// kernel's own (see its launch), where the wider launch catches up.
+static inline int fg_default_width(const fg_graph* g, int64_t n64, int64_t n128, int64_t m64,
+                                   int64_t m128, int full) {
+  const int w = g->n <= n64 && g->m <= m64 ? 64 : g->n <= n128 && g->m <= m128 ? 128 : full;
   return w < full ? w : full;
 }
 

@@ -80,11 +80,13 @@ __global__ void degree_summary_kernel(int32_t n, int32_t nwords,
                                       uint64_t* __restrict__ nz,
                                       int4* __restrict__ head,
                                       int32_t* __restrict__ maxdeg,
-                                      int32_t* __restrict__ nzcount) {
+                                      int32_t* __restrict__ nzcount,
+                                      unsigned long long* __restrict__ degsq) {
   const int lane = fg_lane();
   const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / FG_WAVE;
   const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) / FG_WAVE;
   int32_t mx = 0, cnt = 0;
+  unsigned long long sq = 0;
   for (int64_t wd = wave; wd < nwords; wd += nwaves) {
     int64_t v = wd * 64 + lane;
     int32_t d = 0;
@@ -103,26 +105,34 @@ __global__ void degree_summary_kernel(int32_t n, int32_t nwords,
     if (lane == 0) nz[wd] = bits;
     mx = d > mx ? d : mx;
     cnt += d > 0;
+    sq += (unsigned long long)d * (unsigned long long)d;
   }
-  // one pair of atomics per workgroup: the two counters are single addresses,
-  // and with a pair per wave the kernel took 380 us at any size above 1 M
+  // one atomic per workgroup and counter: the counters are single addresses,
+  // and with one per wave the kernel took 380 us at any size above 1 M
   // vertices, all of it in them
   __shared__ int32_t s_mx, s_cnt;
-  if (threadIdx.x == 0) s_mx = s_cnt = 0;
+  __shared__ unsigned long long s_sq;
+  if (threadIdx.x == 0) {
+    s_mx = s_cnt = 0;
+    s_sq = 0;
+  }
   __syncthreads();
   for (int s = 32; s > 0; s >>= 1) {
     int32_t o = __shfl_xor(mx, s, 64);
     mx = o > mx ? o : mx;
     cnt += __shfl_xor(cnt, s, 64);
+    sq += __shfl_xor(sq, s, 64);
   }
   if (lane == 0) {
     atomicMax(&s_mx, mx);
     atomicAdd(&s_cnt, cnt);
+    atomicAdd(&s_sq, sq);
   }
   __syncthreads();
   if (threadIdx.x == 0) {
     atomicMax(maxdeg, s_mx);
     atomicAdd(nzcount, s_cnt);
+    atomicAdd(degsq, s_sq);
   }
 }
 
@@ -260,10 +270,10 @@ extern "C" fg_status fg_graph_create_csr(int32_t n, int64_t m, const int32_t* ro
     return fail(fg_set_error(FG_ENOMEM, "hipMalloc aux"));
   g->owned[3] = aux;
   g->nzmask = (uint64_t*)aux;
-  int32_t* dsum = (int32_t*)((char*)aux + fg_align(nzb));  // maxdeg, nzcount, flags
+  int32_t* dsum = (int32_t*)((char*)aux + fg_align(nzb));  // maxdeg, nzcount, flags, weights, squares
   g->head = (int4*)((char*)aux + fg_align(nzb) + 256);
   g->resident_bytes += (int64_t)(fg_align(nzb) + 256 + fg_align(hb));
-  if (hipMemsetAsync(dsum, 0, 32, s) != hipSuccess) return fail(fg_set_error(FG_EDEVICE, "memset"));
+  if (hipMemsetAsync(dsum, 0, 40, s) != hipSuccess) return fail(fg_set_error(FG_EDEVICE, "memset"));
 
   if (flags & FG_VALIDATE) {
     if (dev) {
@@ -291,21 +301,22 @@ extern "C" fg_status fg_graph_create_csr(int32_t n, int64_t m, const int32_t* ro
   if (blocks > 2048) blocks = 2048;
   if (blocks < 1) blocks = 1;
   degree_summary_kernel<<<blocks, 256, 0, s>>>(n, g->nwords, g->off, g->col, g->nzmask, g->head,
-                                               dsum, dsum + 1);
+                                               dsum, dsum + 1, (unsigned long long*)(dsum + 8));
   if (g->w && m > 0) {
     int wb = (int)((m + 1023) / 1024);
     if (wb > 2048) wb = 2048;
     weight_summary_kernel<<<wb, 256, 0, s>>>(m, g->w, (unsigned long long*)(dsum + 4),
                                              (uint32_t*)(dsum + 6));
   }
-  int32_t hs[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  if (hipMemcpyAsync(hs, dsum, 32, hipMemcpyDeviceToHost, s) != hipSuccess ||
+  int32_t hs[10] = {};
+  if (hipMemcpyAsync(hs, dsum, 40, hipMemcpyDeviceToHost, s) != hipSuccess ||
       hipStreamSynchronize(s) != hipSuccess)
     return fail(fg_set_error(FG_EDEVICE, "degree summary failed"));
   g->max_degree = hs[0];
   g->nonzero_degree = hs[1];
   memcpy(&g->w_sum, &hs[4], 8);
   g->w_max = (uint32_t)hs[6];
+  memcpy(&g->deg_sq, &hs[8], 8);
   *out = g;
   return FG_OK;
 }

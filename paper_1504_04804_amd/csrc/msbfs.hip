@@ -1445,9 +1445,14 @@ extern "C" fg_status fg_msbfs_step(fg_msbfs* b, int32_t k_iters, void* stream) {
   int grid = pr.cus * bpc;
   // 256, 128 and 64 workgroups, 20 to 60 lanes: R-MAT of 1500 vertices 304,
   // 286, 277 us; 80 k 692, 686, 773; 150 k 434, 444, 483; grids: 100 x 120
-  // 2072, 1816, 1703; 300 x 350 6065, 5313, 5764
+  // 2072, 1816, 1703; 300 x 350 6065, 5313, 5764.  More entries, 1, 16 and 64
+  // lanes: uniform random, 60 k vertices with 32 edges each (3.8 M) 174, 237,
+  // 324; 171, 261, 348; 199, 350, 445, 130 k with 8 (2.1 M) 168, 200, 269; 153,
+  // 196, 272; 166, 245, 332; R-MAT, 60 k with 32 (3.1 M) 154, 242, 341; 133,
+  // 234, 337; 127, 259, 367, 130 k with 32 (7 M) 203, 278, 404; 171, 244, 452;
+  // 168, 252, 597
   if (b->opts.blocks_per_cu == 0 && b->opts.grid_blocks == 0 && b->opts.pull_div == 0)
-    grid = fg_default_width(g->n, 1 << 14, 1 << 17, grid);
+    grid = fg_default_width(g, 1 << 14, 1 << 17, 1 << 21, fg_skewed(g) ? 1 << 22 : 1 << 21, grid);
   if (b->opts.grid_blocks > 0 && b->opts.grid_blocks < grid) grid = b->opts.grid_blocks;
   // by default the team kernel runs on graphs of mean degree <= 8 (grids,
   // road-like graphs: long, thin push frontiers)

@@ -1966,9 +1966,13 @@ extern "C" fg_status fg_sssp(const fg_graph* g, int32_t src, const fg_sssp_opts*
   if (o.blocks_per_cu == 0 && bpc > 2) bpc = 2;
   int grid = pr.cus * bpc;
   // R-MAT, 256, 128 and 64 workgroups: n = 1500 254, 236, 229 us; 16 k 367,
-  // 347, 350; 30 k 368, 328, 342; 100 k 448, 417, 447; 150 k 523, 532, 640
+  // 347, 350; 30 k 368, 328, 342; 100 k 448, 417, 447; 150 k 523, 532, 640.
+  // More entries: 60 k with 100 edges per vertex (8.4 M) 532, 524, 616; 130 k
+  // with 64 (13 M) 617, 644, 823; uniform random: 16 k with 64 (2 M) 548, 503,
+  // 533, with 300 (9.4 M) 353, 338, 390; 10 k with 200 (3.9 M) 406, 406, 455;
+  // 60 k with 16 (1.9 M) 516, 534, 651; 130 k with 16 (4.2 M) 718, 798, 1081
   if (o.blocks_per_cu == 0 && o.grid_blocks == 0 && g->m > (int64_t)TEAM_AUTO_DEG * g->n)
-    grid = fg_default_width(g->n, 1 << 14, 1 << 17, grid);
+    grid = fg_default_width(g, 1 << 14, 1 << 17, 1 << 21, fg_skewed(g) ? 1 << 23 : 1 << 21, grid);
   if (o.grid_blocks > 0 && o.grid_blocks < grid) grid = o.grid_blocks;
 
   SsspParams P;

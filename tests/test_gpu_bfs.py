@@ -353,3 +353,24 @@ def test_one_hub_levels(fg, orc, deg):
             check_bfs(fg, orc, g, off, col, src, mode)
         check_bfs(fg, orc, g, off, col, src, "do", do_a=(1, 100000), small_edges=deg - 1)
     g.close()
+
+
+def test_default_width_by_entries(fg, orc):
+    """Where rows are alike the launch is as wide as the entries ask for;
+    where most are in hubs' rows (R-MAT) BFS goes by the vertices alone."""
+    rng = np.random.default_rng(8)
+    for n, edges, bfs, sssp in ((131072, 1900000, 128, None), (131072, 2400000, None, None),
+                                (16000, 1400000, 64, None)):
+        off, col = orc.csr_from_edges(n, *rng.integers(0, n, (2, edges)).astype(np.int32))
+        g = fg.Graph(off, col, synth.weights(off, col))
+        full = fg.bfs(g, 5, do_a=(1001, 1000))[2].grid_blocks
+        assert check_bfs(fg, orc, g, off, col, 5, "do", team_blocks=2).grid_blocks == (bfs or full)
+        assert fg.sssp(g, 5)[2].grid_blocks == (sssp or full)
+        g.close()
+    off, col = synth.rmat_csr(17)
+    assert len(col) > 3 << 20
+    g = fg.Graph(off, col, synth.weights(off, col))
+    src = int(synth.sources(off, 1)[0])
+    assert check_bfs(fg, orc, g, off, col, src, "do").grid_blocks == 64
+    assert fg.sssp(g, src)[2].grid_blocks == 128
+    g.close()
