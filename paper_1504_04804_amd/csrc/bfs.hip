@@ -1906,6 +1906,12 @@ __global__ __launch_bounds__(PB) void bfs_persistent(BfsParams P) {
 // 625 in a build without the bounds: hence SOLO_KM.  Grids, push: 31 x 33
 // 118 -> 64 us (0.9 us per level), 100 x 100 352 -> 215; asynchronous 122 ->
 // 64 and 284 -> 215; 180 x 180 direction-optimizing 795 -> 537.
+// Where rows are alike a pull reads a large part of them (uniform random, n =
+// 16 k, 0.27 M entries 102 and 70 us with the whole card and here, 0.39 M 111
+// and 132; 33 k, 0.33 M 118 and 112, 0.52 M 108 and 125, 1.3 M 116 and 268):
+// hence SOLO_EM.  Rows that a pull reads to their end (cliques of 300 to 1400
+// vertices that the source does not reach) 280-6000 and 220-4300 us; by one
+// wave per row, 64 entries per step, they took 260-8460.
 constexpr int32_t SOLO_N = 32768;
 constexpr int64_t SOLO_M = 2 << 20;   // where most entries are in hubs' rows
 constexpr int64_t SOLO_EM = 5 << 16;  // where rows are alike
@@ -2125,14 +2131,54 @@ __device__ __forceinline__ bool solo_seen(const SoloLds<SoloBits>& L, int32_t u)
   return (L.vis[u >> 5] >> (u & 31)) & 1u;
 }
 
+// The first visited entry of rows [b, e) at rb[i] / re[i], i < cnt: its place
+// from b (or -1) and its vertex, left in rb[i] / re[i].  Eight lanes take a row,
+// eight entries per lane in flight, eight rows per wave.  Every lane of the wave
+// must take part.
+__device__ __forceinline__ void solo_tails(const BfsParams& P, const SoloLds<SoloBits>& L,
+                                           int32_t* rb, int32_t* re, int32_t cnt) {
+  const int lane = fg_lane();
+  const int first = lane & ~7;
+  for (int32_t i0 = 0; i0 < cnt; i0 += FG_WAVE / 8) {
+    const int32_t i = i0 + lane / 8;
+    const int32_t b = i < cnt ? rb[i] : 0, len = i < cnt ? re[i] - b : 0;
+    int32_t hit = -1, hu = -1;
+    for (int32_t c = 0; __ballot(hit < 0 && c < len); c += 64) {
+      const bool open = hit < 0 && c < len;  // the same in a row's lanes
+      int32_t x[8];
+#pragma unroll
+      for (int r = 0; r < 8; ++r)
+        x[r] = open ? P.col[b + min(c + r * 8 + (lane & 7), len - 1)] : 0;
+#pragma unroll
+      for (int r = 7; r >= 0; --r) {
+        const bool y = open && c + r * 8 + (lane & 7) < len && solo_seen(L, x[r]);
+        const uint32_t m = (uint32_t)(__ballot(y) >> first) & 0xffu;
+        const int f = first + (m ? __builtin_ctz(m) : 0);
+        const int32_t u = __shfl(x[r], f, FG_WAVE);
+        if (m) {
+          hit = c + r * 8 + (f - first);
+          hu = u;
+        }
+      }
+    }
+    wave_lds_fence();
+    if (i < cnt && lane == first) {
+      rb[i] = hit;
+      re[i] = hu;
+    }
+  }
+}
+
 // Pull: the unvisited vertices of nonzero degree are listed, two per lane
 // probe their first four neighbours from the head table, the rest of a row
-// is read four entries at a time up to 16 and by the whole wave after that.
+// is read four entries at a time up to 16 and by eight lanes after that.
 __device__ void solo_pull(const BfsParams& P, SoloLds<SoloBits>& L, const SoloLevel& K, int32_t& insp) {
   const int lane = fg_lane();
   const int32_t nbytes = (P.n + 7) / 8;
   const uint8_t* nz8 = (const uint8_t*)P.nz;
   const uint8_t* vis8 = (const uint8_t*)L.vis;
+  int32_t* rb = L.w_b[threadIdx.x / FG_WAVE];
+  int32_t* re = L.w_e[threadIdx.x / FG_WAVE];
   for (int32_t i0 = 0; i0 < nbytes; i0 += PB) {
     const int32_t i = i0 + threadIdx.x;
     uint32_t x = i < nbytes ? (uint32_t)nz8[i] & ~(uint32_t)vis8[i] & 0xffu : 0u;
@@ -2190,27 +2236,21 @@ __device__ void solo_pull(const BfsParams& P, SoloLds<SoloBits>& L, const SoloLe
           more = h < 0 && dg > i0 + 4;
         }
       }
-      uint64_t pend = __ballot(more);
-      while (pend) {
-        const int l = __builtin_ctzll(pend);
-        pend &= pend - 1;
-        const int32_t lb = __builtin_amdgcn_readlane(b[s], l);
-        const int32_t le = __builtin_amdgcn_readlane(e[s], l);
-        int32_t hit = -1, hu = -1;
-        for (int32_t i0 = lb + 16; i0 < le && hit < 0; i0 += FG_WAVE) {
-          const int32_t i = i0 + lane;
-          const int32_t x = P.col[i < le ? i : le - 1];
-          const uint64_t m = __ballot(i < le && solo_seen(L, x));
-          if (m) {
-            const int f = __builtin_ctzll(m);
-            hit = i0 + f - lb;
-            hu = __builtin_amdgcn_readlane(x, f);
-          }
+      const uint64_t pend = __ballot(more);
+      if (pend) {
+        const int32_t at = fg_mbcnt(pend);
+        wave_lds_fence();
+        if (more) {
+          rb[at] = b[s] + 16;
+          re[at] = e[s];
         }
-        if (lane == l) {
-          ins = hit >= 0 ? hit + 1 : le - lb;
-          h = hit;
-          pu = hu;
+        wave_lds_fence();
+        solo_tails(P, L, rb, re, __popcll(pend));
+        wave_lds_fence();
+        if (more) {
+          h = rb[at];
+          pu = re[at];
+          ins = h >= 0 ? 16 + h + 1 : dg;
         }
       }
       const bool found = mine[s] && h >= 0;
@@ -2978,7 +3018,8 @@ static BfsParams bfs_params(const fg_graph* g, int32_t src, const fg_bfs_opts& o
 // One workgroup runs the traversal alone (bfs_solo): small graphs, unless the
 // caller sets how a traversal is spread over the card.  A push-only one reads
 // every row, at a quarter of the rate of the whole card, so its bound on the
-// entries is lower (and holds for a direction rule that hardly ever pulls).
+// entries is lower (and holds for a direction rule that hardly ever pulls);
+// one whose pulls no hub ends has a lower one as well.
 // The asynchronous mode is taken over where no row is long.
 static bool solo_fits(const fg_graph* g, const fg_bfs_opts& o) {
   const bool tuned = o.small_frontier || o.small_edges || o.big_degree || o.blocks_per_cu ||
@@ -2988,7 +3029,8 @@ static bool solo_fits(const fg_graph* g, const fg_bfs_opts& o) {
     return g->n <= SOLO_KN && g->m <= SOLO_KM && g->max_degree <= SOLO_ROW;
   if (o.team_blocks) return false;
   if (o.mode == FG_MODE_PUSH) return g->n <= SOLO_KN && g->m <= SOLO_KM;
-  return g->n <= SOLO_N && g->m <= (o.do_a_num <= o.do_a_den ? SOLO_M : SOLO_KM);
+  const int64_t pulls = fg_skewed(g) ? SOLO_M : SOLO_EM;
+  return g->n <= SOLO_N && g->m <= (o.do_a_num <= o.do_a_den ? pulls : SOLO_KM);
 }
 
 // Workgroups of an asynchronous team.

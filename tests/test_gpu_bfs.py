@@ -374,3 +374,42 @@ def test_default_width_by_entries(fg, orc):
     assert check_bfs(fg, orc, g, off, col, src, "do").grid_blocks == 64
     assert fg.sssp(g, src)[2].grid_blocks == 128
     g.close()
+
+
+@pytest.mark.parametrize("n,edges,solo", [(20480, 155000, True), (20480, 175000, False),
+                                          (32768, 655360, False), (8192, 800000, False)])
+def test_one_workgroup_where_rows_are_alike(fg, orc, n, edges, solo):
+    """On uniform random graphs a pull reads a large part of the entries, so
+    one workgroup takes fewer of them than where hubs end it early."""
+    rng = np.random.default_rng(n + edges)
+    off, col = orc.csr_from_edges(n, *rng.integers(0, n, (2, edges)).astype(np.int32))
+    assert (len(col) <= 5 << 16) == solo
+    g = fg.Graph(off, col)
+    for src in (0, n - 1):
+        assert (check_bfs(fg, orc, g, off, col, src, "do").grid_blocks == 1) == solo
+    g.close()
+
+
+@pytest.mark.parametrize("k", [20, 21, 52, 53, 84, 85, 149, 300])
+def test_one_workgroup_beside_dense_components(fg, orc, k):
+    """Rows that a pull reads to their end (cliques that the source does not
+    reach) and rows with their first reached entry anywhere, at the borders of
+    the steps that read them: 4, 16, then 64 entries at a time."""
+    i, j = np.triu_indices(k, 1)
+    n0, nc = 2000, 1 if k == 300 else 6
+    rng = np.random.default_rng(k)
+    # the source's component: long rows whose reached entries are few and last
+    u = [rng.integers(0, n0, 4 * n0), np.arange(40).repeat(k)]
+    v = [rng.integers(0, n0, 4 * n0), n0 - 1 - rng.integers(0, n0 // 2, 40 * k)]
+    for c in range(nc):
+        u.append(n0 + c * k + i)
+        v.append(n0 + c * k + j)
+    n = n0 + nc * k
+    off, col = orc.csr_from_edges(n, np.concatenate(u).astype(np.int32),
+                                  np.concatenate(v).astype(np.int32))
+    g = fg.Graph(off, col)
+    for src in (n0 - 1, n0 // 2, 0):
+        for da in ((1, 100), (1, 100000)):
+            st = check_bfs(fg, orc, g, off, col, src, "do", do_a=da, do_b=(1, 1000))
+            assert st.grid_blocks == 1
+    g.close()
