@@ -1901,23 +1901,25 @@ __global__ __launch_bounds__(PB) void bfs_persistent(BfsParams P) {
 // Measured, R-MAT, direction-optimizing: n = 4096 90 -> 27 us, 16 k 104-126
 // -> 40-57, 32 k (0.4 to 1.3 M entries) 106-143 -> 55-66 (the pull's 16
 // rounds of 2048 vertices; the bound on n is the LDS room of two lists);
-// push-only, one word per vertex: n = 1000 192 -> 48 us, 8 k (0.24 M
-// entries) 159 -> 137, but 16 k (0.6 M) 181 -> 283 and 32 k (1.2 M) 191 ->
-// 625 in a build without the bounds: hence SOLO_KM.  Grids, push: 31 x 33
+// push-only, one word per vertex: n = 1000 192 -> 23 us, 16 k (0.22 M
+// entries) 179 -> 87, but 16 k (0.6 M) 181 -> 283 and 32 k (1.2 M) 191 ->
+// 625 in an earlier build without the bounds: hence SOLO_KM.  Grids, push: 31 x 33
 // 118 -> 64 us (0.9 us per level), 100 x 100 352 -> 215; asynchronous 122 ->
 // 64 and 284 -> 215; 180 x 180 direction-optimizing 795 -> 537.
 // Where rows are alike a pull reads a large part of them (uniform random, n =
-// 16 k, 0.27 M entries 102 and 70 us with the whole card and here, 0.39 M 111
-// and 132; 33 k, 0.33 M 118 and 112, 0.52 M 108 and 125, 1.3 M 116 and 268):
+// 16 k, 0.27 M entries 102 and 61 us with the whole card and here, 0.44 M 108
+// and 110; 33 k, 0.33 M 119 and 108, 0.43 M 118 and 152; with rows past 16
+// entries read by one wave each, 64 entries per step, 0.39 M 246, 1.3 M 512):
 // hence SOLO_EM.  Rows that a pull reads to their end (cliques of 300 to 1400
 // vertices that the source does not reach) 280-6000 and 220-4300 us; by one
-// wave per row, 64 entries per step, they took 260-8460.
+// wave each 260-8460.
 constexpr int32_t SOLO_N = 32768;
 constexpr int64_t SOLO_M = 2 << 20;   // where most entries are in hubs' rows
-constexpr int64_t SOLO_EM = 5 << 16;  // where rows are alike
+constexpr int64_t SOLO_EM = 1 << 19;  // where rows are alike, with four per vertex
 constexpr int32_t SOLO_KN = 20480;
 constexpr int64_t SOLO_KM = 1 << 18;
 constexpr int32_t SOLO_ROW = CH;
+constexpr int32_t SOLO_LANE = 4 + 4 * 8;  // entries of a row that a pull reads in its lane
 
 // Visited set and outputs of a push-only traversal: one word per vertex,
 // depth << 16 | parent, lowered with an LDS atomicMin.  A vertex is found by
@@ -1941,10 +1943,16 @@ struct SoloBits {
 
 template <class V>
 struct SoloLds : V {
-  int32_t w_sc[PWAVES][FG_WAVE];
-  int32_t w_u[PWAVES][FG_WAVE];
-  int32_t w_b[PWAVES][FG_WAVE];
-  int32_t w_e[PWAVES][FG_WAVE];
+  union {
+    struct {
+      int32_t w_sc[PWAVES][FG_WAVE];
+      int32_t w_u[PWAVES][FG_WAVE];
+      int32_t w_b[PWAVES][FG_WAVE];
+      int32_t w_e[PWAVES][FG_WAVE];
+    };
+    int4 w_row[PWAVES][FG_WAVE];
+  };
+  alignas(4) uint8_t w_mark[PWAVES][4 * FG_WAVE];
   // per level mod 3: vertices found, entries dealt, CSR entries read, long
   // rows / pull candidates listed.  A level clears the next one's slot: its
   // last readers, two levels before, are behind the barrier in between.
@@ -2015,27 +2023,48 @@ __device__ __forceinline__ void solo_visit(const BfsParams& P, SoloLds<SoloBits>
   }
 }
 
-// Lanes hold rows (first entry b, `d` entries, vertex u) in sc / su / sb
-// (sc their prefix); the wave takes entries [t0, T) in steps of 4 x 64.
+// Visits the rows of the wave's lanes (first entry b, d entries, vertex u),
+// laid end to end, in steps of 4 x 64.  A step's row starts are marked in LDS
+// and counted (finding each entry's row by halving the prefix took six reads of
+// LDS in a chain: uniform random, n = 16 k, 0.26 M entries, push 161 -> 75 us;
+// R-MAT, 0.22 M, 151 -> 87).
 template <class V>
 __device__ __forceinline__ void solo_gather(const BfsParams& P, SoloLds<V>& L, const SoloLevel& K,
-                                            const int32_t* sc, const int32_t* su,
-                                            const int32_t* sb, int32_t T) {
+                                            int32_t d, int32_t u, int32_t b) {
   const int lane = fg_lane();
+  const int wid = threadIdx.x / FG_WAVE;
+  const int32_t inc = fg_wave_incl_scan(d);
+  const int32_t T = __builtin_amdgcn_readlane(inc, FG_WAVE - 1);
+  if (T == 0) return;
+  int4* row = L.w_row[wid];
+  uint8_t* mark = L.w_mark[wid];
+  const int32_t start = d > 0 ? inc - d : -1;
+  const int32_t at = fg_mbcnt(__ballot(d > 0));
+  wave_lds_fence();
+  if (d > 0) row[at] = make_int4(start, u, b, 0);
+  int32_t before = -1;  // rows begun before the step, less one
   for (int32_t t0 = 0; t0 < T; t0 += 4 * FG_WAVE) {
+    ((uint32_t*)mark)[lane] = 0u;
+    wave_lds_fence();
+    if (start >= t0 && start < t0 + 4 * FG_WAVE) mark[start - t0] = 1;
+    wave_lds_fence();
+    uint64_t m[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) m[r] = __ballot(mark[r * FG_WAVE + lane] != 0);
     int32_t v[4], pu[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int32_t t = t0 + r * FG_WAVE + lane;
-      const int32_t tc = t < T ? t : T - 1;
-      const int32_t j = upper_idx(sc, FG_WAVE, tc);
-      pu[r] = su[j];
-      v[r] = P.col[sb[j] + (tc - sc[j])];
+      const int4 w = row[before + fg_mbcnt(m[r]) + (int32_t)((m[r] >> lane) & 1ull)];
+      before += __popcll(m[r]);
+      pu[r] = w.y;
+      v[r] = P.col[w.z + ((t < T ? t : T - 1) - w.x)];
     }
 #pragma unroll
     for (int r = 0; r < 4; ++r)
       if (t0 + r * FG_WAVE + lane >= T) v[r] = -1;
     solo_visit<4>(P, L, K, v, pu);
+    wave_lds_fence();
   }
 }
 
@@ -2073,18 +2102,7 @@ __device__ void solo_push(const BfsParams& P, SoloLds<V>& L, const SoloLevel& K,
     const int32_t pu[4] = {u, u, u, u};
     solo_visit<4>(P, L, K, v, pu);
     // the others laid over the lanes
-    const int32_t d = big || deg <= 4 ? 0 : deg - 4;
-    const int32_t inc = fg_wave_incl_scan(d);
-    const int32_t T = __builtin_amdgcn_readlane(inc, FG_WAVE - 1);
-    if (T > 0) {
-      wave_lds_fence();
-      sc[lane] = inc - d;
-      su[lane] = u;
-      sb[lane] = b + 4;
-      wave_lds_fence();
-      solo_gather(P, L, K, sc, su, sb, T);
-      wave_lds_fence();
-    }
+    solo_gather(P, L, K, big || deg <= 4 ? 0 : deg - 4, u, b + 4);
     if (qlen <= PWAVES * per) break;
     if (lane == 0) base = atomicAdd(&L.next[K.sl], per);
     base = PWAVES * per + __builtin_amdgcn_readfirstlane(base);
@@ -2171,7 +2189,7 @@ __device__ __forceinline__ void solo_tails(const BfsParams& P, const SoloLds<Sol
 
 // Pull: the unvisited vertices of nonzero degree are listed, two per lane
 // probe their first four neighbours from the head table, the rest of a row
-// is read four entries at a time up to 16 and by eight lanes after that.
+// is read eight entries at a time up to SOLO_LANE and by eight lanes after that.
 __device__ void solo_pull(const BfsParams& P, SoloLds<SoloBits>& L, const SoloLevel& K, int32_t& insp) {
   const int lane = fg_lane();
   const int32_t nbytes = (P.n + 7) / 8;
@@ -2221,19 +2239,19 @@ __device__ void solo_pull(const BfsParams& P, SoloLds<SoloBits>& L, const SoloLe
         }
       ins = h >= 0 ? h + 1 : min(4, dg);
       bool more = mine[s] && h < 0 && dg > 4;
-      for (int32_t i0 = 4; i0 < 16 && __ballot(more); i0 += 4) {
+      for (int32_t i0 = 4; i0 < SOLO_LANE && __ballot(more); i0 += 8) {
         if (more) {
-          int32_t x[4];
+          int32_t x[8];
 #pragma unroll
-          for (int j = 0; j < 4; ++j) x[j] = P.col[min(b[s] + i0 + j, e[s] - 1)];
+          for (int j = 0; j < 8; ++j) x[j] = P.col[min(b[s] + i0 + j, e[s] - 1)];
 #pragma unroll
-          for (int j = 3; j >= 0; --j)
+          for (int j = 7; j >= 0; --j)
             if (i0 + j < dg && solo_seen(L, x[j])) {
               h = i0 + j;
               pu = x[j];
             }
-          ins = h >= 0 ? h + 1 : min(i0 + 4, dg);
-          more = h < 0 && dg > i0 + 4;
+          ins = h >= 0 ? h + 1 : min(i0 + 8, dg);
+          more = h < 0 && dg > i0 + 8;
         }
       }
       const uint64_t pend = __ballot(more);
@@ -2241,7 +2259,7 @@ __device__ void solo_pull(const BfsParams& P, SoloLds<SoloBits>& L, const SoloLe
         const int32_t at = fg_mbcnt(pend);
         wave_lds_fence();
         if (more) {
-          rb[at] = b[s] + 16;
+          rb[at] = b[s] + SOLO_LANE;
           re[at] = e[s];
         }
         wave_lds_fence();
@@ -2250,7 +2268,7 @@ __device__ void solo_pull(const BfsParams& P, SoloLds<SoloBits>& L, const SoloLe
         if (more) {
           h = rb[at];
           pu = re[at];
-          ins = h >= 0 ? 16 + h + 1 : dg;
+          ins = h >= 0 ? SOLO_LANE + h + 1 : dg;
         }
       }
       const bool found = mine[s] && h >= 0;
@@ -3029,7 +3047,7 @@ static bool solo_fits(const fg_graph* g, const fg_bfs_opts& o) {
     return g->n <= SOLO_KN && g->m <= SOLO_KM && g->max_degree <= SOLO_ROW;
   if (o.team_blocks) return false;
   if (o.mode == FG_MODE_PUSH) return g->n <= SOLO_KN && g->m <= SOLO_KM;
-  const int64_t pulls = fg_skewed(g) ? SOLO_M : SOLO_EM;
+  const int64_t pulls = fg_skewed(g) ? SOLO_M : SOLO_EM - 4 * (int64_t)g->n;
   return g->n <= SOLO_N && g->m <= (o.do_a_num <= o.do_a_den ? pulls : SOLO_KM);
 }
 

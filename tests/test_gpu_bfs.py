@@ -376,25 +376,25 @@ def test_default_width_by_entries(fg, orc):
     g.close()
 
 
-@pytest.mark.parametrize("n,edges,solo", [(20480, 155000, True), (20480, 175000, False),
+@pytest.mark.parametrize("n,edges,solo", [(20480, 215000, True), (20480, 225000, False),
                                           (32768, 655360, False), (8192, 800000, False)])
 def test_one_workgroup_where_rows_are_alike(fg, orc, n, edges, solo):
     """On uniform random graphs a pull reads a large part of the entries, so
     one workgroup takes fewer of them than where hubs end it early."""
     rng = np.random.default_rng(n + edges)
     off, col = orc.csr_from_edges(n, *rng.integers(0, n, (2, edges)).astype(np.int32))
-    assert (len(col) <= 5 << 16) == solo
+    assert (len(col) + 4 * n <= 1 << 19) == solo
     g = fg.Graph(off, col)
     for src in (0, n - 1):
         assert (check_bfs(fg, orc, g, off, col, src, "do").grid_blocks == 1) == solo
     g.close()
 
 
-@pytest.mark.parametrize("k", [20, 21, 52, 53, 84, 85, 149, 300])
+@pytest.mark.parametrize("k", [5, 6, 13, 14, 37, 38, 101, 102, 149, 300])
 def test_one_workgroup_beside_dense_components(fg, orc, k):
     """Rows that a pull reads to their end (cliques that the source does not
     reach) and rows with their first reached entry anywhere, at the borders of
-    the steps that read them: 4, 16, then 64 entries at a time."""
+    the steps that read them: 4, then 8 up to 36, then 64 entries at a time."""
     i, j = np.triu_indices(k, 1)
     n0, nc = 2000, 1 if k == 300 else 6
     rng = np.random.default_rng(k)
