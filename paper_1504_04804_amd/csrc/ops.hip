@@ -244,8 +244,16 @@ __global__ void fill_i32_kernel(int32_t* p, int64_t count, int32_t value) {
 constexpr int FT_BT = 1024;
 constexpr int FT_R = 8;                  // edges per thread and tile
 constexpr int FT_TILE = FT_BT * FT_R;
-constexpr int FT_STAGE = 2 * FT_TILE;
+constexpr int FT_STAGE = FT_TILE;
 constexpr int FT_SLOTS = 4096;           // visited words a tile combines
+constexpr int FT_SPREAD = 128;           // tiles from which a tile takes more per thread
+constexpr int FT_ONCE = 2;               // edges per thread up to which one round is enough
+
+// A word's slot: neighbouring words lie in neighbouring slots, and words 4096
+// apart (an R-MAT graph's hubs, a wide grid's column) in unrelated ones.
+__device__ __forceinline__ int ft_slot(int32_t word) {
+  return (int)((uint32_t)word ^ (((uint32_t)word >> 12) * 0x9E3779B1u >> 20)) & (FT_SLOTS - 1);
+}
 
 // Test-and-set of dst's visited bit; winners take depth / parent and are
 // appended to out_q.  The edge-frontier length is read from device memory
@@ -257,16 +265,19 @@ constexpr int FT_SLOTS = 4096;           // visited words a tile combines
 // its hubs' few words: with one test-and-set per edge whose vertex looked
 // unvisited the kernel took 279 us on 1.1 M edges (R-MAT of 1 M vertices).
 // So a workgroup combines a tile first: its bits go into a direct-mapped
-// LDS table of visited words (a word's slot is its id modulo FT_SLOTS; of
-// two words in one slot one keeps it and the other waits for another round:
-// testing its edges in memory at once cost 150 us where a hub's word was the
-// one that lost), one atomic per word takes them to memory, neighbouring
-// slots by neighbouring lanes, and the edge that set a bit in the table first
-// wins the vertex if memory says the bit is new.  That takes 64 us (tiles of
-// 4096 edges 82 us, 2048 edges over 115 us: the hot lines get one request per
-// tile and round, which is what bounds it).  The look before that reads
-// past the caches (agent scope), so vertices that other workgroups have set
-// meanwhile are not tried again.
+// LDS table of visited words (ft_slot; of two words in one slot the one whose
+// edge wrote last, most likely the busier, keeps it), one atomic per word takes
+// them to memory, neighbouring slots by neighbouring lanes, and the edge that
+// set a bit in the table first wins the vertex if memory says the bit is new.
+// Words that lost their slot get a second round in full tiles; what is left
+// then is tested in memory by itself.  On the 1.1 M edges that takes 36 us (one
+// round 43, three 37, rounds until nothing is left 42; with a slot that is the
+// word's id modulo FT_SLOTS and rounds to the end 62, and 1360 us on 512 words
+// 4096 apart, 12 here).  Short lists are spread over FT_SPREAD tiles (15 k
+// edges 10 us, as with a test per edge; one tile of 8192 edges after another
+// took 60), long ones need full tiles: the hot lines get one request per tile
+// and round.  The look before that reads past the caches (agent scope), so
+// vertices that other workgroups have set meanwhile are not tried again.
 __global__ __launch_bounds__(FT_BT) void filter_kernel(
     const int32_t* __restrict__ dst, const int32_t* __restrict__ src,
     const int64_t* __restrict__ d_len, int64_t h_len, int64_t cap,
@@ -278,17 +289,20 @@ __global__ __launch_bounds__(FT_BT) void filter_kernel(
   __shared__ int32_t s_cnt, s_base;
   int64_t len = d_len ? *d_len : h_len;
   if (len > cap) len = cap;
-  if ((int64_t)blockIdx.x * FT_TILE >= len) return;  // the whole workgroup
+  const int64_t fair = (len + (int64_t)FT_SPREAD * FT_BT - 1) / ((int64_t)FT_SPREAD * FT_BT);
+  const int per = fair < FT_R ? (int)fair : FT_R;  // edges per thread and tile
+  const int64_t tile = (int64_t)per * FT_BT;
+  if ((int64_t)blockIdx.x * tile >= len) return;  // the whole workgroup
   BlockStage<FT_BT, FT_STAGE> stage{s_buf, &s_cnt, &s_base};
   if (threadIdx.x == 0) s_cnt = 0;
-  for (int64_t t0 = (int64_t)blockIdx.x * FT_TILE; t0 < len; t0 += (int64_t)gridDim.x * FT_TILE) {
+  for (int64_t t0 = (int64_t)blockIdx.x * tile; t0 < len; t0 += (int64_t)gridDim.x * tile) {
     int32_t v[FT_R];
     uint32_t word[FT_R];
     bool open[FT_R];
 #pragma unroll
     for (int r = 0; r < FT_R; ++r) {
       const int64_t k = t0 + r * FT_BT + threadIdx.x;
-      v[r] = k < len ? dst[k] : -1;
+      v[r] = r < per && k < len ? dst[k] : -1;
     }
 #pragma unroll
     for (int r = 0; r < FT_R; ++r)
@@ -299,19 +313,17 @@ __global__ __launch_bounds__(FT_BT) void filter_kernel(
       open[r] = !((word[r] >> (v[r] & 31)) & 1u);
       any = any || open[r];
     }
-    // one round per word that shares a slot (each round settles at least the
-    // word that kept the slot, so the rounds end)
-    while (__syncthreads_or(any)) {
+    for (int round = per <= FT_ONCE ? 1 : 2; round > 0 && __syncthreads_or(any); --round) {
       for (int i = threadIdx.x; i < FT_SLOTS; i += FT_BT) s_bits[i] = 0;
 #pragma unroll
       for (int r = 0; r < FT_R; ++r)
-        if (open[r]) s_tag[(v[r] >> 5) & (FT_SLOTS - 1)] = v[r] >> 5;
+        if (open[r]) s_tag[ft_slot(v[r] >> 5)] = v[r] >> 5;
       __syncthreads();
       bool first[FT_R];
       any = false;
 #pragma unroll
       for (int r = 0; r < FT_R; ++r) {
-        const int slot = (v[r] >> 5) & (FT_SLOTS - 1);
+        const int slot = ft_slot(v[r] >> 5);
         const uint32_t bit = 1u << (v[r] & 31);
         first[r] = open[r] && s_tag[slot] == v[r] >> 5;
         open[r] = open[r] && !first[r];
@@ -328,13 +340,32 @@ __global__ __launch_bounds__(FT_BT) void filter_kernel(
 #pragma unroll
       for (int r = 0; r < FT_R; ++r) {
         const bool won =
-            first[r] && ((s_bits[(v[r] >> 5) & (FT_SLOTS - 1)] >> (v[r] & 31)) & 1u);
+            first[r] && ((s_bits[ft_slot(v[r] >> 5)] >> (v[r] & 31)) & 1u);
         if (won) {
           depth[v[r]] = d_new;
           if (parent) parent[v[r]] = src[t0 + r * FT_BT + threadIdx.x];
         }
         stage.push(won, v[r]);
       }
+    }
+    // what is left by itself: words that were always beside a busier one
+#pragma unroll
+    for (int r = 0; r < FT_R; ++r)
+      word[r] = open[r] ? fg_atomic_load_u32(&visited[v[r] >> 5]) : ~0u;
+#pragma unroll
+    for (int r = 0; r < FT_R; ++r) {
+      const uint32_t bit = 1u << (v[r] & 31);
+      open[r] = open[r] && !(word[r] & bit);
+      if (open[r]) word[r] = atomicOr(&visited[v[r] >> 5], bit);
+    }
+#pragma unroll
+    for (int r = 0; r < FT_R; ++r) {
+      const bool won = open[r] && !((word[r] >> (v[r] & 31)) & 1u);
+      if (won) {
+        depth[v[r]] = d_new;
+        if (parent) parent[v[r]] = src[t0 + r * FT_BT + threadIdx.x];
+      }
+      stage.push(won, v[r]);
     }
     __syncthreads();
     stage.flush_above(FT_STAGE - FT_TILE, out_q, out_len);
@@ -726,7 +757,7 @@ extern "C" fg_status fg_filter(const fg_graph* g, const int32_t* dst, const int3
   hipStream_t s = (hipStream_t)stream;
   fill_i32_kernel<<<1, 64, 0, s>>>(out_len, 1, 0);
   if (len > 0)
-    filter_kernel<<<grid_for(len, FT_TILE, 512), FT_BT, 0, s>>>(
+    filter_kernel<<<grid_for(len, FT_BT, 512), FT_BT, 0, s>>>(
         dst, src, len_dev, len, len, visited, iter + 1, depth, parent, out_q, out_len);
   FG_HIP_TRY(hipGetLastError());
   return FG_OK;
@@ -808,7 +839,7 @@ fg_status fg_bfs_unfused(const fg_graph* g, int32_t src, void* ws, size_t ws_byt
     fg_status st = advance_impl(g, L.q[sel], len, nullptr, L.edst, L.esrc, g->m, L.misc, L, s);
     if (st != FG_OK) return st;
     fill_i32_kernel<<<1, 64, 0, s>>>(L.len32, 1, 0);
-    filter_kernel<<<grid_for(g->m > 0 ? g->m : 1, FT_TILE, 512), FT_BT, 0, s>>>(
+    filter_kernel<<<grid_for(g->m > 0 ? g->m : 1, FT_BT, 512), FT_BT, 0, s>>>(
         L.edst, L.esrc, L.misc, 0, g->m, L.visited, k + 1, depth, parent, L.q[sel ^ 1], L.len32);
     int64_t h[1];
     int32_t nl = 0;

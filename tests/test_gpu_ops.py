@@ -301,3 +301,44 @@ def test_advance_many_tiles(fg, length):
     at = o[wsrc.long()] + torch.arange(T, device="cuda") - first
     assert torch.equal(src[:T], wsrc)
     assert torch.equal(dst[:T], torch.from_numpy(col).cuda()[at])
+
+
+def _time_us(f, reps=20):
+    f()
+    a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+    a.record()
+    for _ in range(reps):
+        f()
+    b.record()
+    torch.cuda.synchronize()
+    return a.elapsed_time(b) / reps * 1000
+
+
+@pytest.mark.parametrize("step,k", [(131072, 512), (4096, 16384), (65536 + 32, 1000),
+                                    (32 * 37, 50000)])
+def test_filter_of_spread_words(fg, step, k):
+    """Edges whose vertices lie in words far apart (a wide grid's column) are
+    filtered as well as the same number in neighbouring words, and take about
+    as long (the table's slots, of which a word has one, are 4096)."""
+    n = 1 << 26
+    g = fg.Graph(np.zeros(n + 1, np.int32), np.zeros(0, np.int32))
+    vis = torch.zeros(n // 64, dtype=torch.int64, device="cuda")
+    dep = torch.full((n,), -1, dtype=torch.int32, device="cuda")
+    par, q = torch.zeros_like(dep), torch.zeros_like(dep)
+    ln = torch.zeros(1, dtype=torch.int32, device="cuda")
+    us = {}
+    for st in (32, step):
+        v = (torch.arange(k, device="cuda") * st % n).to(torch.int32)
+        src = v + 1
+
+        def run():
+            vis.zero_()
+            fg.filter_(g, v, src, k, vis, 4, dep, par, q, ln)
+        announce(f"filter of {k} edges, {st} vertices apart")
+        dep.fill_(-1)
+        us[st] = _time_us(run)
+        assert int(ln) == k and np.array_equal(np.sort(to_np(q[:k])), np.sort(to_np(v)))
+        assert int((dep[v.long()] == 5).sum()) == k == int((dep >= 0).sum())
+        assert torch.equal(par[v.long()], src)
+    assert us[step] < 5 * us[32], us  # with a round per word of a slot 20 to 100 times
+    g.close()
