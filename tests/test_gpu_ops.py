@@ -342,3 +342,23 @@ def test_filter_of_spread_words(fg, step, k):
         assert torch.equal(par[v.long()], src)
     assert us[step] < 5 * us[32], us  # with a round per word of a slot 20 to 100 times
     g.close()
+
+
+@pytest.mark.parametrize("n", [1, 64, 5000, 300000, (1 << 21) + 77])
+def test_bitmap_to_queue_densities(fg, n):
+    """Sparse words are listed by a lane each, full ones by their wave; both
+    kinds in one bitmap, and none."""
+    g = fg.Graph(np.zeros(n + 1, np.int32), np.zeros(0, np.int32))
+    rng = np.random.default_rng(n)
+    q = torch.zeros(n, dtype=torch.int32, device="cuda")
+    ln = torch.zeros(1, dtype=torch.int32, device="cuda")
+    for dens in (0.0, 0.001, 0.05, 0.2, 0.26, 0.5, 1.0, None):
+        p = rng.choice([0.0, 0.02, 0.9], size=n // 4096 + 1).repeat(4096)[:n] if dens is None else dens
+        want = np.flatnonzero(rng.random(n) < p)
+        bits = np.zeros((n + 63) // 64 * 64, np.uint8)
+        bits[want] = 1
+        words = np.packbits(bits, bitorder="little").view(np.int64)
+        announce(f"bitmap_to_queue n={n} density {dens}")
+        fg.bitmap_to_queue(g, torch.from_numpy(words.copy()).cuda(), q, ln)
+        assert int(ln) == len(want) and np.array_equal(to_np(q[:len(want)]), want)
+    g.close()
