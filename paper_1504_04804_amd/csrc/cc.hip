@@ -48,7 +48,7 @@ constexpr int CC_LDS_OFF = 4096 + 2;    // offsets staged per task
 constexpr int CC_SAMPLES = 1024;
 constexpr int CC_CAND = FG_WAVE;        // samples that stand as candidates
 constexpr int CC_SKIP = 2;              // entries per row hooked by the link pass
-constexpr int CC_LONG = 1024;           // longer rows are hooked by the edge-balanced pass
+constexpr int CC_LONG = 64;             // longer rows are hooked by the edge-balanced pass
 constexpr int CC_FINAL_BT = 1024;       // workgroup of the counting compress pass
 
 struct CcCtl {
@@ -206,7 +206,10 @@ __global__ __launch_bounds__(CC_SAMPLES) void cc_sample_kernel(int32_t n,
 
 // Hooks the rows (of up to CC_LONG entries) of every vertex outside the
 // sampled tree: a wave takes 64 vertices, lays the rows that have entries
-// past the first two end to end and hooks 64 entries per step.
+// past the first two end to end and hooks 64 entries per step (so CC_LONG
+// bounds a wave's steps; with rows of up to 1024 two cliques of 1000 vertices
+// took 870 us, 50 of them 1056, two R-MAT graphs of 512 k vertices side by side
+// 719: 32, 199 and 181 with 64; 128 and 256 are equal or slower).
 __global__ __launch_bounds__(CC_BT) void cc_hook_rows_kernel(int32_t n,
                                                              const int32_t* __restrict__ off,
                                                              const int32_t* __restrict__ col,

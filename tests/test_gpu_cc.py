@@ -121,3 +121,44 @@ def test_workload_graphs(fg, orc, name):
     want, wc = orc.cc(off, col)
     assert np.array_equal(got, want)
     assert comps == wc
+
+
+def _cliques(sizes):
+    """CSR of disjoint cliques."""
+    deg = np.repeat(np.asarray(sizes) - 1, sizes)
+    off = np.concatenate([[0], np.cumsum(deg)]).astype(np.int32)
+    col, lo = [], 0
+    for k in sizes:
+        x = np.tile(np.arange(lo, lo + k, dtype=np.int32), (k, 1))
+        col.append(x[~np.eye(k, dtype=bool)])
+        lo += k
+    return off, np.concatenate(col)
+
+
+def test_large_components_of_medium_rows(fg, orc):
+    """Rows of some hundred entries outside the giant component cost about
+    what longer ones do (per entry), wherever the border between the passes
+    lies."""
+    us = {}
+    for k in (60, 66, 100, 300, 1000, 1500):
+        off, col = _cliques([k] * (1500 // k * 2))
+        g = fg.Graph(off, col, validate=False)
+        label = torch.empty(g.n, dtype=torch.int32, device="cuda")
+        comps = torch.zeros(1, dtype=torch.int64, device="cuda")
+        announce(f"cc cliques of {k}")
+        fg.cc_into(g, label, comps)
+        a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        a.record()
+        for _ in range(10):
+            fg.cc_into(g, label, comps)
+        b.record()
+        want, wc = orc.cc(off, col)
+        assert np.array_equal(to_np(label), want) and int(comps) == wc
+        us[k] = a.elapsed_time(b) * 100
+        g.close()
+    assert max(us.values()) < 4 * us[1500], us  # by one wave per 64 rows 26 times
+
+
+@pytest.mark.parametrize("deg", [63, 65, 66, 67, 200])
+def test_joined_by_rows_at_the_border(fg, orc, deg):
+    test_components_joined_by_long_rows_alone(fg, orc, deg)
