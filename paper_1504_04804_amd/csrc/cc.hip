@@ -54,7 +54,7 @@ constexpr int CC_FINAL_BT = 1024;       // workgroup of the counting compress pa
 struct CcCtl {
   int32_t giant;                // the sampled most frequent root
   int32_t longrows;             // set if a row past CC_LONG has to be hooked
-  int64_t comps;                // the count, for an output that is not 8-byte aligned
+  int64_t comps;                // the count, for an output that kernels cannot count in
 };
 
 // Root of x with path halving: each visited vertex is re-pointed at its
@@ -340,7 +340,10 @@ extern "C" fg_status fg_cc(const fg_graph* g, int32_t* label, int64_t* component
                         sizeof(CcCtl));
   hipStream_t s = (hipStream_t)stream;
   CcCtl* ctl = (CcCtl*)ws;
-  int64_t* const comps = ((uintptr_t)components & 7) ? &ctl->comps : components;
+  int64_t* const comps =
+      !components || (!((uintptr_t)components & 7) && fg_own_memory(components, g->device))
+          ? components
+          : &ctl->comps;
   const int cus = fg_props(g->device).cus;
   const int grid = (cus > 0 ? cus : 256) * 8;
   // On graphs with hubs (mean degree above 8) a vertex's first neighbour is

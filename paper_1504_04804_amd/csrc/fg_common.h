@@ -62,6 +62,19 @@ struct fg_device_props {
 };
 fg_device_props fg_props(int device);
 
+// p is memory of `device`, and that is the current device: its kernels may write
+// it.  Anything else (host memory, another device's) is left to the runtime's
+// copies.
+static inline bool fg_own_memory(const void* p, int device) {
+  hipPointerAttribute_t at;
+  int dev = -1;
+  const bool own = hipGetDevice(&dev) == hipSuccess && dev == device &&
+                   hipPointerGetAttributes(&at, p) == hipSuccess &&
+                   at.type == hipMemoryTypeDevice && at.device == dev;
+  if (!own) (void)hipGetLastError();  // the lookup of host memory may have failed
+  return own;
+}
+
 static inline size_t fg_align(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // Workspaces are carved into 256-byte aligned pieces from their start, so

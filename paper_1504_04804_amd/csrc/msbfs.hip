@@ -1509,15 +1509,9 @@ extern "C" fg_status fg_msbfs_read(fg_msbfs* b, int32_t lane, int32_t* depth, vo
   const int32_t* row = b->lay.depth + (size_t)lane * b->g->n;
   const size_t bytes = sizeof(int32_t) * (size_t)b->g->n;
   hipStream_t s = (hipStream_t)stream;
-  // into memory of this device by a kernel (a runtime copy of a batch's rows
+  // into memory of the batch's device by a kernel (a runtime copy of a batch's rows
   // costs the host 10 us each, a launch 3), into anything else by the runtime
-  hipPointerAttribute_t at;
-  int dev = -1;
-  const bool here = hipGetDevice(&dev) == hipSuccess &&
-                    hipPointerGetAttributes(&at, depth) == hipSuccess &&
-                    at.type == hipMemoryTypeDevice && at.device == dev;
-  if (!here) {
-    (void)hipGetLastError();  // the lookup of host memory may have failed
+  if (!fg_own_memory(depth, b->g->device)) {
     FG_HIP_TRY(hipMemcpyAsync(depth, row, bytes, hipMemcpyDeviceToDevice, s));
     return FG_OK;
   }

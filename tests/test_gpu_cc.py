@@ -162,3 +162,21 @@ def test_large_components_of_medium_rows(fg, orc):
 @pytest.mark.parametrize("deg", [63, 65, 66, 67, 200])
 def test_joined_by_rows_at_the_border(fg, orc, deg):
     test_components_joined_by_long_rows_alone(fg, orc, deg)
+
+
+def test_count_into_host_memory(fg, orc):
+    """The number of components into pinned host memory and into unaligned
+    device memory: copied there behind the kernels."""
+    off, col = synth.rmat_csr(12)
+    g = fg.Graph(off, col)
+    want, wc = orc.cc(off, col)
+    label = torch.empty(g.n, dtype=torch.int32, device="cuda")
+    host = torch.full((1,), -9, dtype=torch.int64, pin_memory=True)
+    dev = torch.zeros(24, dtype=torch.uint8, device="cuda")[4:12]
+    announce("cc count into pinned host memory")
+    for out in (host, dev):
+        for _ in range(2):
+            fg.cc_into(g, label, out)
+            assert np.array_equal(to_np(label), want)
+            assert int(out.cpu().numpy().view(np.int64)[0]) == wc
+    g.close()
