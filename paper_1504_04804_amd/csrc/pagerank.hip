@@ -19,9 +19,9 @@
 // start of the call and copies the columns once under the new numbers: the
 // contributions most entries ask for then lie together, rows of one length
 // are neighbours, and each class of rows gets the lanes that fit it.  The
-// direct one works on the CSR arrays as they are; it is taken for a single
-// iteration (the plan costs about as much as one) and where the workspace
-// has no room for the copied columns.  Every row's sum is formed in a fixed
+// direct one works on the CSR arrays as they are; it is taken for too few
+// iterations to pay for the plan and where the workspace has no room for the
+// copied columns.  Every row's sum is formed in a fixed
 // order in both, so ranks do not change from call to call.
 //
 // What bounds it (R-MAT 22, 128 M entries, 20 iterations): gathers that miss
@@ -300,9 +300,13 @@ constexpr int PP_BUCKETS = PP_LONGB + PP_SHORT;  // then one for 63, 62, ..., 0
 constexpr int PP_PER = 4;       // vertices per thread of the numbering passes
 constexpr int PP_TILE = PP_BT * PP_PER;
 constexpr int PP_PAD = PP_SHORT * FG_WAVE;  // most entries that pad the slices
-// The plan costs about what one iteration of the direct form does and each
-// iteration saves more than half of one.
-constexpr int PP_MIN_ITER = 2;
+// On large graphs the plan costs 1.5 iterations of the direct form and each
+// iteration saves two thirds of one: two iterations 2604 us direct and 2704
+// planned, three 3877 and 3119 (R-MAT 22), 573 and 584, 858 and 729 (uniform
+// random, 16.8 M entries).  On small ones an iteration's work counter costs
+// more than the plan: 9 M entries 587 and 231, 0.5 M 253 and 120.
+constexpr int PP_MIN_ITER = 3;
+constexpr int64_t PP_SMALL_M = 10 << 20;
 
 struct PrPlan {
   uint32_t count[PP_BUCKETS];   // vertices per class, then the class's first number
@@ -951,7 +955,7 @@ extern "C" fg_status fg_pagerank(const fg_graph* g, double damping, double tol, 
   A.clock_khz = pr.clock_khz;
   const int cus = pr.cus > 0 ? pr.cus : 256;
   PrPlanned Q;
-  if (max_iter >= PP_MIN_ITER && ws_bytes >= pr_planned_layout(g, ws, &Q)) {
+  if (max_iter >= (g->m <= PP_SMALL_M ? 2 : PP_MIN_ITER) && ws_bytes >= pr_planned_layout(g, ws, &Q)) {
     // one workgroup per CU (their LDS), a multiple of the column classes
     const int grid = cus >= PP_XCD ? cus / PP_XCD * PP_XCD : PP_XCD;
     pp_clear_kernel<<<1, PP_BT, 0, s>>>(A, Q.plan);
