@@ -775,11 +775,13 @@ fg_status fg_cc(const fg_graph* g, int32_t* label, int64_t* components, void* ws
  * vertex changed by at most tol times its previous rank (tol > 0), or
  * after max_iter iterations (tol = 0 runs exactly max_iter).  rank: device
  * double[n], the output.  ws: fg_workspace_bytes(g, FG_PRIM_PR, 0) bytes
- * (any contents; about 37n + 6.2m, for renumbered copies of the columns.
+ * (any contents; about 37n + 6.2m + 17 KB, for renumbered copies of the columns.
  * About 20n bytes, the minimum, are enough for a slower form).  stats (device, may be NULL): iterations run, and per
  * iteration frontier[i] = vertices whose change exceeded the threshold,
- * inspected[i] = m.  Nothing is read back: every one of the max_iter
- * iterations is enqueued and those after convergence return at once.
+ * inspected[i] = m.  Nothing is read back: with tol > 0 and a workspace of
+ * the full size one launch runs the iterations and ends with the run,
+ * otherwise every one of the max_iter iterations is enqueued (and those after
+ * convergence return at once).
  * Sums over long rows are taken in a different order than a serial loop,
  * so ranks agree with a serial evaluation to rounding, not bit for bit.
  * Errors: FG_EINVAL (damping outside [0, 1], tol < 0, max_iter outside

@@ -174,3 +174,72 @@ def test_workspace_without_room_for_the_plan(fg, orc):
     got = to_np(rank)
     assert (np.abs(got - want) / want).max() <= bound(off, it)
     g.close()
+
+
+@pytest.mark.parametrize("cut", [0, 1])
+def test_one_launch_for_runs_that_may_stop(fg, orc, cut):
+    """With a tolerance the iterations run in one launch, or, from a workspace
+    without its barrier, in one or two launches each: the same ranks, counts
+    and trace, repeatedly and from a workspace of any contents."""
+    for what, (off, col) in (("rmat13", synth.rmat_csr(13)), ("grid", synth.grid_csr(90, 77)),
+                             ("none", (np.zeros(6, np.int32), np.zeros(0, np.int32)))):
+        g = fg.Graph(off, col)
+        need = g.workspace_bytes(fg.FG_PRIM_PR)
+        ws = torch.full((need - cut,), 0x5a, dtype=torch.uint8, device="cuda")
+        rank = torch.empty(g.n, dtype=torch.float64, device="cuda")
+        for tol, most in ((1e-1, 1000), (1e-5, 200), (1e-5, 3), (1e-300, 70)):
+            want, it = orc.pagerank(off, col, 0.85, tol, most)
+            for _ in range(2):
+                stats = fg.new_stats()
+                announce(f"pagerank loop {what} tol={tol} max_iter={most} cut={cut}")
+                fg.pagerank_into(g, rank, 0.85, tol, most, ws=ws, stats=stats)
+                st = fg.read_stats(stats)
+                assert st.status == 0 and st.iterations == it
+                assert st.edges_inspected == it * len(col)
+                k = min(it, 64)
+                front = st.trace()[1]
+                assert all(f > 0 for f in front[:k - 1]) and (it == most or front[k - 1] == 0 or it > 64)
+                got = to_np(rank)
+                assert (np.abs(got - want) / want).max() <= bound(off, it)
+        g.close()
+
+
+def test_iterations_left_after_the_stop_cost_nothing(fg):
+    off, col = synth.rmat_csr(14)
+    g = fg.Graph(off, col)
+    rank = torch.empty(g.n, dtype=torch.float64, device="cuda")
+    us = {}
+    for most in (20, 2000):
+        fg.pagerank_into(g, rank, 0.85, 0.1, most)
+        a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        announce(f"pagerank of at most {most} iterations")
+        a.record()
+        for _ in range(5):
+            fg.pagerank_into(g, rank, 0.85, 0.1, most)
+        b.record()
+        torch.cuda.synchronize()
+        us[most] = a.elapsed_time(b) * 200
+    assert us[2000] < 3 * us[20], us  # with a launch or two for each some 30 times
+    g.close()
+
+
+@pytest.mark.parametrize("tol", [0.0, 1e-3])
+def test_captured(fg, tol):
+    """Replays of a captured call, with other work between them."""
+    off, col = synth.rmat_csr(12)
+    g = fg.Graph(off, col)
+    rank = torch.empty(g.n, dtype=torch.float64, device="cuda")
+    g.workspace(fg.FG_PRIM_PR)
+    fg.pagerank_into(g, rank, 0.85, tol, 30)
+    want = to_np(rank).copy()
+    graph = torch.cuda.CUDAGraph()
+    announce(f"pagerank captured tol={tol}")
+    with torch.cuda.graph(graph):
+        fg.pagerank_into(g, rank, 0.85, tol, 30)
+    for _ in range(4):
+        rank.fill_(-1.0)
+        torch.cuda.synchronize()
+        graph.replay()
+        assert np.array_equal(to_np(rank), want)
+        fg.pagerank(g, 0.5, 1e-2, 20)
+    g.close()
