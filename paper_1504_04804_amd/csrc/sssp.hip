@@ -73,6 +73,7 @@ struct AsyncCtl {
   ull rec[2][TEAM_MAX];  // per member: queue length, levels run, out of room
   ull lev_cnt[FG_TRACE_MAX];   // vertices relaxed / entries read per level
   ull lev_insp[FG_TRACE_MAX];
+  ull lev_end[FG_TRACE_MAX];   // when the last member ended the level
   uint32_t arrive;
   uint32_t exit;
   uint32_t farcnt[3];  // far pile entries, by splits so far mod 3
@@ -1448,6 +1449,7 @@ __global__ __launch_bounds__(PB) void sssp_async(SsspParams P) {
         if (tid == 0) {
           atomicAdd(&A.lev_cnt[done_levels + lev], (ull)cnt);
           if (h) atomicAdd(&A.lev_insp[done_levels + lev], (ull)h);
+          atomicMax(&A.lev_end[done_levels + lev], (ull)wall_clock64());
         }
       }
       __syncthreads();
@@ -1592,13 +1594,21 @@ __global__ __launch_bounds__(PB) void sssp_async(SsspParams P) {
   __syncthreads();
   if (P.stats && tid < FG_TRACE_MAX) {
     fg_run_stats* st = P.stats;
-    const int64_t now = (int64_t)wall_clock64();
+    // a level ends where its last member does, and not before the one before it
+    // (members drift apart, and some have no work in a level)
+    ull end = __hip_atomic_load(&A.lev_end[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    static_assert(FG_TRACE_MAX == FG_WAVE, "one lane per traced level");
+#pragma unroll
+    for (int d = 1; d < FG_WAVE; d <<= 1) {
+      const ull o = __shfl_up(end, d, FG_WAVE);
+      if (tid >= d && o > end) end = o;
+    }
     if (tid < done_levels) {
       st->frontier[tid] = (int64_t)__hip_atomic_load(&A.lev_cnt[tid], __ATOMIC_RELAXED,
                                                      __HIP_MEMORY_SCOPE_AGENT);
       st->inspected[tid] = (int64_t)__hip_atomic_load(&A.lev_insp[tid], __ATOMIC_RELAXED,
                                                       __HIP_MEMORY_SCOPE_AGENT);
-      st->t_end[tid] = now;  // levels are not timed one by one
+      st->t_end[tid] = (int64_t)end;
     }
     if (tid == 0) {
       st->status = failed ? FG_EDEVICE

@@ -271,3 +271,18 @@ def test_explicit_width(fg, orc, blocks):
     g = fg.Graph(off, col, weights=w)
     assert check(fg, orc, g, off, col, w, 3).grid_blocks == 64
     assert check(fg, orc, g, off, col, w, 3, grid_blocks=blocks).grid_blocks == blocks
+
+
+@pytest.mark.parametrize("rows,cols", [(1, 40), (40, 50), (150, 140), (700, 900)])
+def test_iteration_times(fg, rows, cols):
+    """Every traced iteration has its own end: none before the one before it,
+    the first well before the last, and together the run."""
+    off, col = synth.grid_csr(rows, cols)
+    g = fg.Graph(off, col, weights=synth.weights(off, col))
+    announce(f"sssp iteration times {rows}x{cols}")
+    st = fg.sssp(g, 0)[2]
+    k = min(st.iterations, 64)
+    us = st.iteration_us()
+    assert len(us) == k > 20 and all(u >= 0 for u in us)
+    assert sum(u > 0 for u in us) > k // 2 and max(us) < sum(us) / 2
+    g.close()
