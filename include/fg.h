@@ -327,7 +327,10 @@ void fg_sssp_opts_default(fg_sssp_opts* opts);
  * (parent[src] = src, -1 if unreachable), which is unique.  ws: at least
  * fg_workspace_bytes(g, FG_PRIM_SSSP, 0) bytes.  Errors: FG_EINVAL (graph
  * without weights, src out of range, NULL dist / ws), FG_ENOMEM,
- * FG_EDEVICE; stats->status = FG_EOVERFLOW if a distance reaches 2^32 - 1.
+ * FG_EDEVICE; stats->status = FG_EOVERFLOW if the sum of a vertex's distance
+ * and the weight of one of its edges reaches 2^32 - 1 when it is relaxed, the
+ * edge that it was reached through included (what fits is then right, but
+ * vertices may be missing).
  */
 fg_status fg_sssp(const fg_graph* g, int32_t src, const fg_sssp_opts* opts, void* ws,
                   size_t ws_bytes, uint32_t* dist, int32_t* parent, fg_run_stats* stats,
@@ -538,8 +541,9 @@ fg_status fg_mssp_step(fg_mssp* b, int32_t k_iters, void* stream);
 
 /* Synchronise `stream`; *done_lanes = admitted lanes whose query has
  * finished; *iterations = iterations run since fg_mssp_open.  Either pointer
- * may be NULL.  Returns FG_EOVERFLOW once a distance would reach 2^32 - 1
- * (the affected lane's result is then incomplete), FG_EDEVICE if a step
+ * may be NULL.  Returns FG_EOVERFLOW once the sum of a distance and an edge's
+ * weight reaches 2^32 - 1, as in fg_sssp (the affected lane's result may then
+ * be incomplete), FG_EDEVICE if a step
  * stopped early. */
 fg_status fg_mssp_poll(fg_mssp* b, uint64_t* done_lanes, int32_t* iterations, void* stream);
 

@@ -154,6 +154,7 @@ struct SsspParams {
   int32_t team;     // workgroups of a team (<= 1: no team mode)
   int64_t team_e;   // largest frontier degree sum a team takes
   const int4* __restrict__ head;  // first four neighbours per vertex
+  uint32_t ovf_from;  // asynchronous team: distances from which a sum may not fit
   int32_t behind;   // asynchronous team: the level-synchronous kernel follows;
                     // that kernel: launched behind the team
 };
@@ -1192,12 +1193,22 @@ __device__ __forceinline__ void sa_load(const SsspParams& P, SaEntry& x) {
 }
 
 // Drops the neighbour u at distance du from x's first four where x cannot
-// lower u's key (an equal distance could still lower its predecessor).
-__device__ __forceinline__ void sa_drop(SaEntry& x, int32_t u, uint32_t du) {
+// lower u's key (an equal distance could still lower its predecessor).  Returns
+// whether a way back does not fit a distance.
+__device__ __forceinline__ bool sa_drop(const SsspParams& P, SaEntry& x, int32_t u, uint32_t du) {
+  bool over = false;
+  if (x.d >= P.ovf_from) {
+    const int32_t d = x.e - x.b;
+    over = (d > 0 && x.h.x == u && sat_add(x.d, x.w.x) == DIST_INF) ||
+           (d > 1 && x.h.y == u && sat_add(x.d, x.w.y) == DIST_INF) ||
+           (d > 2 && x.h.z == u && sat_add(x.d, x.w.z) == DIST_INF) ||
+           (d > 3 && x.h.w == u && sat_add(x.d, x.w.w) == DIST_INF);
+  }
   x.h.x = x.h.x == u && sat_add(x.d, x.w.x) > du ? -1 : x.h.x;
   x.h.y = x.h.y == u && sat_add(x.d, x.w.y) > du ? -1 : x.h.y;
   x.h.z = x.h.z == u && sat_add(x.d, x.w.z) > du ? -1 : x.h.z;
   x.h.w = x.h.w == u && sat_add(x.d, x.w.w) > du ? -1 : x.h.w;
+  return over;
 }
 
 // Queues the kept lanes' entries (every lane of the wave takes part); true
@@ -1273,8 +1284,12 @@ __device__ __forceinline__ int sa_relax(const SsspParams& P, SaEntry& x, int32_t
   const ull old = atomicMin(&P.key[x.v], ((ull)x.d << 32) | (ull)(uint32_t)u);
   sa_load(P, x);
   if (x.d >= (uint32_t)(old >> 32)) return SA_NONE;
-  sa_drop(x, u, du);
-  return x.d < T ? SA_NEAR : SA_FARV;
+  const bool over = sa_drop(P, x, u, du);
+  if (x.d >= T) return SA_FARV;
+  // relaxed with this distance: a way back that does not fit is reported like
+  // any other edge
+  if (over) __hip_atomic_store(&P.ctl->overflow, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return SA_NEAR;
 }
 
 // The members' records of meeting `seq`, published and read by all: L.tot,
@@ -2022,6 +2037,7 @@ extern "C" fg_status fg_sssp(const fg_graph* g, int32_t src, const fg_sssp_opts*
   if (P.team_e > TW_CAP - 1) P.team_e = TW_CAP - 1;
   P.clock_khz = pr.clock_khz;
   P.head = g->head;
+  P.ovf_from = DIST_INF - g->w_max;
   void* args[] = {&P};
   // The asynchronous team answers where the team build would run by default,
   // unless the caller sets how frontiers are dealt with.  Its width follows

@@ -286,3 +286,37 @@ def test_iteration_times(fg, rows, cols):
     assert len(us) == k > 20 and all(u >= 0 for u in us)
     assert sum(u > 0 for u in us) > k // 2 and max(us) < sum(us) / 2
     g.close()
+
+
+@pytest.mark.parametrize("kw", [dict(), dict(team_blocks=-1), dict(team_blocks=8), dict(big_degree=2)])
+@pytest.mark.parametrize("deg,last,over", [(1, 0x7FFFFFFF, False), (1, 0x80000000, True),
+                                           (3, 0x7FFFFFFE, False), (3, 0x80000000, True),
+                                           (7, 0x80000000, True)])
+def test_way_back_past_the_largest_distance(fg, orc, kw, deg, last, over):
+    """A vertex whose way back sums to 2^32 - 2 is fine and to more is reported,
+    by every path alike, whatever the length of its row: 0 - 1, then 1 - 2 of
+    weight `last` and 2's other neighbours 3, 4, ... (past every distance that
+    fits where that way back is)."""
+    pairs = [(0, 1), (1, 2)] + [(2, 3 + i) for i in range(deg - 1)]
+    off, col = synth.from_edge_pairs(3 + deg, pairs)
+    rows = np.repeat(np.arange(3 + deg), np.diff(off))
+    w = np.ones(len(col), np.uint32)
+    w[(rows == 0) | (col == 0)] = 0
+    w[((rows == 1) & (col == 2)) | ((rows == 2) & (col == 1))] = last
+    g = fg.Graph(off, col, weights=w)
+    announce(f"sssp way back deg={deg} last={last:#x} {kw}")
+    for delta in (0, 1, 0xFFFFFFFF):
+        d, p, st = fg.sssp(g, 0, delta=delta, **kw)
+        assert st.status == (fg.FG_EOVERFLOW if over else 0), (delta, st.status)
+        d = to_np(d).astype(np.uint32)
+        assert d[:3].tolist() == [0, 0, last] and (d[3:2 + deg] == last + 1).all()
+    b = fg.MsspBatch(g, 2)
+    b.admit(1, 0)
+    b.step(100)
+    if over:
+        with pytest.raises(fg.FGError) as e:
+            b.poll()
+        assert e.value.status == fg.FG_EOVERFLOW
+    else:
+        assert b.poll()[0] & 2
+    g.close()
