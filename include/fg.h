@@ -303,11 +303,12 @@ typedef struct {
   int32_t team_blocks;    /* workgroups that run medium frontiers from LDS
                              queues as a team (0 = no team on graphs of mean
                              degree > 8; on others 32, or with every field
-                             but delta 0 and no row over 256 entries an
-                             asynchronous team of up to 64, as wide as the
-                             vertex count asks for, that makes its splits
-                             itself and hands over to the whole grid where
-                             fronts are wide; -1 = no team)                  */
+                             but delta 0 an asynchronous team of up to 64, as
+                             wide as the vertex count asks for, that makes its
+                             splits itself and hands over to the whole grid
+                             where fronts are wide: where no row has more than
+                             4 entries, past 16384 vertices 8, below 256 up to
+                             2^16 entries; -1 = no team)                     */
   int32_t team_edges;     /* ... while the frontier's degree sum is at most
                              this (0 = 65536)                                */
 } fg_sssp_opts;

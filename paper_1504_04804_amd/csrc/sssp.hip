@@ -154,6 +154,7 @@ struct SsspParams {
   int32_t team;     // workgroups of a team (<= 1: no team mode)
   int64_t team_e;   // largest frontier degree sum a team takes
   const int4* __restrict__ head;  // first four neighbours per vertex
+  int32_t symmetric;
   uint32_t ovf_from;  // asynchronous team: distances from which a sum may not fit
   int32_t behind;   // asynchronous team: the level-synchronous kernel follows;
                     // that kernel: launched behind the team
@@ -1107,17 +1108,23 @@ __device__ bool team_mode(const SsspParams& P, St& S, Lds& L, uint32_t T, TeamSy
 // A queue entry carries what its relaxation needs: distance, row, the first
 // four neighbours and their weights, loaded by the lane that queues the
 // vertex while its atomicMin is on its way.  A level is then one trip (the
-// atomics, with those loads beside them) instead of three.  Neighbours that
-// the entry's distance cannot improve (the vertex it was reached from) are
-// dropped from the entry.  Vertices that improve to the threshold or more
-// are collected in LDS and entered in the far pile when the member runs out
-// of near work, with the membership bits that keep every vertex in the pile
-// once, off the chain.
+// atomics, with those loads beside them) instead of three, and one barrier.
+// Neighbours that the entry's distance cannot improve (the vertex it was
+// reached from) are dropped from the entry, and with the last one the entry.
+// Vertices that improve to the threshold or more are collected in LDS and
+// entered in the far pile when the member runs out of near work, with the
+// membership bits that keep every vertex in the pile once, off the chain.
+//
+// Where fronts are wide (and behind rows of more than four entries) vertices
+// are queued alone, ten times as many: their rows are loaded when their level
+// comes, by one block scan over all entries, and those that have been lowered
+// since are left out.  Members meet every SA_KWIDE levels then, and at once
+// when a queue weighs twice a member's share, so the shares stay even.
 //
 // When the members meet and no near work is left, the pile is split by all
 // of them (as elsewhere: below the old threshold stale, below the new one
 // near, the rest kept), without leaving the kernel.  A near vertex that finds
-// its LDS queue full goes to the far pile instead, and the next split keeps
+// its LDS queues full goes to the far pile instead, and the next split keeps
 // the threshold and takes everything below it as near (an entry that is stale
 // is then relaxed once more, which changes nothing).
 //
@@ -1134,17 +1141,25 @@ __device__ bool team_mode(const SsspParams& P, St& S, Lds& L, uint32_t T, TeamSy
 // wide front takes more rounds of fewer members); with 8, 16, 32 levels
 // between meetings (64 members): 7.3, 6.5, 6.4 ms, 300 x 250: 1.19, 1.11,
 // 1.09 ms, and the second source 4.6, 4.2, 4.5 ms.
+// Uniform random, one member per 2000 vertices or so (the whole grid, the team
+// without the queue of vertices alone and the even shares, and with them): 6
+// neighbours, n = 4000 211, 373, 193 us, 9000 278, 525, 251, 16 k 377, 900, 360;
+// 8 neighbours, 16 k 420, 1300, 380; a tree of 200 children, 16 k 162, 297, 50.
 
-constexpr int SQ = 1280;       // LDS queue entries per member
+constexpr int SQ = 512;        // LDS queue entries per member ...
+constexpr int SQ2 = 5376;      // ... and vertices beside them, without their rows
 constexpr int SA_FAR = 2048;   // far vertices collected per member
-constexpr int SA_K = 16;       // levels between two meetings
+constexpr int SA_K = 16;       // levels between two meetings ...
+constexpr int SA_KWIDE = 2;    // ... while members have more than a round's work
 constexpr int SA_ROUND = PB / 4;  // vertices a level takes at once
-constexpr int SA_BREAK = 1024; // queue length from which a member meets at once
+constexpr int SA_BREAK = 1024; // least weight of a queue from which a member meets at once
 constexpr int SA_WIDE = 512;   // near vertices per member from which it hands over
 constexpr int SA_T = 64;       // most members
 constexpr int SA_SIDE = 16;    // one member per so many vertices of a square's side
 constexpr int SA_GIVE_UP = 16; // members from which wide fronts are left to the whole grid
-constexpr int32_t SA_DEG = 256;  // largest degree of the graphs it is tried on
+constexpr int32_t SA_DEG = 256;  // largest degree of the graphs it is tried on ...
+constexpr int32_t SA_ROAD = 8;   // ... from SA_GIVE_UP members on
+constexpr int64_t SA_SMALL_M = 1 << 16;  // most entries where rows may be long, below
 
 struct SaLds {
   int32_t qv[2][SQ];
@@ -1153,17 +1168,24 @@ struct SaLds {
   int32_t qe[2][SQ];
   int4 qh[2][SQ];
   uint4 qw[2][SQ];
+  int32_t q2v[2][SQ2];
+  uint32_t q2d[2][SQ2];
   int32_t fb[SA_FAR];
   int32_t b_sc[PB];
   int32_t b_u[PB];
   int32_t b_b[PB];
   uint32_t b_d[PB];
-  int32_t cnt[2];
-  int32_t big[2];  // by level parity: a vertex of degree > 4 is in the queue
+  // by level mod 3: entries with and without their rows, entries of the rows
+  // longer than four.  Last read at the level's start, cleared in the level
+  // after it, so a level needs one barrier.
+  int32_t cnt[3];
+  int32_t cnt2[3];
+  int32_t edg[3];
   int32_t fcnt;
   int32_t ovf;
   int32_t flag;
-  int32_t tot, pre, mx, lev, anyo;
+  int32_t tot, pre, lev, anyo;
+  int32_t load, mxload;
   uint32_t redm[PWAVES];
   int32_t red32[PWAVES + 1];
   int64_t red[PWAVES + 1];
@@ -1193,40 +1215,87 @@ __device__ __forceinline__ void sa_load(const SsspParams& P, SaEntry& x) {
 }
 
 // Drops the neighbour u at distance du from x's first four where x cannot
-// lower u's key (an equal distance could still lower its predecessor).  Returns
-// whether a way back does not fit a distance.
-__device__ __forceinline__ bool sa_drop(const SsspParams& P, SaEntry& x, int32_t u, uint32_t du) {
-  bool over = false;
-  if (x.d >= P.ovf_from) {
-    const int32_t d = x.e - x.b;
-    over = (d > 0 && x.h.x == u && sat_add(x.d, x.w.x) == DIST_INF) ||
-           (d > 1 && x.h.y == u && sat_add(x.d, x.w.y) == DIST_INF) ||
-           (d > 2 && x.h.z == u && sat_add(x.d, x.w.z) == DIST_INF) ||
-           (d > 3 && x.h.w == u && sat_add(x.d, x.w.w) == DIST_INF);
-  }
+// lower u's key (an equal distance could still lower its predecessor); *over:
+// the way back to it does not fit a distance.  Returns whether x has other
+// neighbours.
+__device__ __forceinline__ bool sa_drop(const SsspParams& P, SaEntry& x, int32_t u, uint32_t du,
+                                        bool* over) {
+  const int32_t d = x.e - x.b;
+  *over = false;
+  if (x.d >= P.ovf_from)
+    *over = (d > 0 && x.h.x == u && sat_add(x.d, x.w.x) == DIST_INF) ||
+            (d > 1 && x.h.y == u && sat_add(x.d, x.w.y) == DIST_INF) ||
+            (d > 2 && x.h.z == u && sat_add(x.d, x.w.z) == DIST_INF) ||
+            (d > 3 && x.h.w == u && sat_add(x.d, x.w.w) == DIST_INF);
   x.h.x = x.h.x == u && sat_add(x.d, x.w.x) > du ? -1 : x.h.x;
   x.h.y = x.h.y == u && sat_add(x.d, x.w.y) > du ? -1 : x.h.y;
   x.h.z = x.h.z == u && sat_add(x.d, x.w.z) > du ? -1 : x.h.z;
   x.h.w = x.h.w == u && sat_add(x.d, x.w.w) > du ? -1 : x.h.w;
-  return over;
+  return d > 4 || (d > 0 && x.h.x >= 0) || (d > 1 && x.h.y >= 0) || (d > 2 && x.h.z >= 0) ||
+         (d > 3 && x.h.w >= 0);
 }
 
-// Queues the kept lanes' entries (every lane of the wave takes part); true
-// where there was no room.
-__device__ __forceinline__ bool sa_put(SaLds& L, int q, bool keep, const SaEntry& x) {
-  const int32_t pos = wave_reserve(keep ? 1 : 0, &L.cnt[q]);
+// Places of the kept lanes behind *counter (every lane of the wave takes part).
+__device__ __forceinline__ int32_t sa_place(uint64_t m, int32_t* counter) {
+  int32_t pos = 0;
+  if (fg_lane() == 0) pos = atomicAdd(counter, __popcll(m));
+  return __builtin_amdgcn_readfirstlane(pos) + fg_mbcnt(m);
+}
+
+// Queues the kept lanes' vertices without their rows (of `edges` entries) in
+// queue q with counter slot c (every lane of the wave takes part); true where
+// there was no room.
+__device__ __forceinline__ bool sa_put2(SaLds& L, int q, int c, bool keep, int32_t v, uint32_t d,
+                                        int32_t edges) {
+  const uint64_t m = __ballot(keep);
+  if (!m) return false;
+  const int32_t pos = sa_place(m, &L.cnt2[c]);
+  const int32_t all = fg_wave_sum(keep && edges > 4 ? edges : 0);
+  if (fg_lane() == 0 && all) atomicAdd(&L.edg[c], all);
   if (!keep) return false;
-  if (pos >= SQ) {
+  if (pos >= SQ2) {
     L.ovf = 1;
     return true;
   }
-  L.qv[q][pos] = x.v;
-  L.qd[q][pos] = x.d;
-  L.qb[q][pos] = x.b;
-  L.qe[q][pos] = x.e;
-  L.qh[q][pos] = x.h;
-  L.qw[q][pos] = x.w;
+  L.q2v[q][pos] = v;
+  L.q2d[q][pos] = d;
   return false;
+}
+
+// Queues the kept lanes' entries, those past SQ without their rows (every lane
+// of the wave takes part); true where there was no room.
+__device__ __forceinline__ bool sa_put(SaLds& L, int q, int c, bool keep, const SaEntry& x) {
+  const uint64_t m = __ballot(keep);
+  if (!m) return false;
+  const int32_t pos = sa_place(m, &L.cnt[c]);
+  const int32_t d = x.e - x.b;
+  if (keep && pos < SQ) {
+    L.qv[q][pos] = x.v;
+    L.qd[q][pos] = x.d;
+    L.qb[q][pos] = x.b;
+    L.qe[q][pos] = x.e;
+    L.qh[q][pos] = x.h;
+    L.qw[q][pos] = x.w;
+  }
+  if (!__ballot(keep && (d > 4 || pos >= SQ))) return false;
+  const int32_t all = fg_wave_sum(keep && d > 4 && pos < SQ ? d : 0);
+  if (fg_lane() == 0 && all) atomicAdd(&L.edg[c], all);
+  return sa_put2(L, q, c, keep && pos >= SQ, x.v, x.d, d);
+}
+
+// Entries with and without their rows by counter slot c, what they weigh (an
+// eighth of a vertex per entry of a long row), and the i-th one's vertex.
+__device__ __forceinline__ int32_t sa_full(const SaLds& L, int c) {
+  return L.cnt[c] < SQ ? L.cnt[c] : SQ;
+}
+__device__ __forceinline__ int32_t sa_bare(const SaLds& L, int c) {
+  return L.cnt2[c] < SQ2 ? L.cnt2[c] : SQ2;
+}
+__device__ __forceinline__ int32_t sa_weight(const SaLds& L, int c) {
+  return sa_full(L, c) + sa_bare(L, c) + L.edg[c] / 8;
+}
+__device__ __forceinline__ int32_t sa_vertex(const SaLds& L, int q, int32_t full, int32_t i) {
+  return i < full ? L.qv[q][i] : L.q2v[q][i - full];
 }
 
 // Enters the kept lanes' vertices that are not in it yet into the far pile
@@ -1252,7 +1321,9 @@ __device__ __forceinline__ void sa_enter(const SsspParams& P, uint32_t split, bo
 // once.
 __device__ __forceinline__ void sa_far(const SsspParams& P, SaLds& L, uint32_t split, bool keep,
                                        int32_t v) {
-  const int32_t pos = wave_reserve(keep ? 1 : 0, &L.fcnt);
+  const uint64_t m = __ballot(keep);
+  if (!m) return;
+  const int32_t pos = sa_place(m, &L.fcnt);
   if (keep && pos < SA_FAR) L.fb[pos] = v;
   if (__ballot(keep && pos >= SA_FAR)) sa_enter(P, split, keep && pos >= SA_FAR, v);
 }
@@ -1271,6 +1342,13 @@ __device__ __forceinline__ void sa_flush(const SsspParams& P, SaLds& L, uint32_t
 
 enum { SA_NONE = 0, SA_NEAR = 1, SA_FARV = 2 };
 
+// u has been lowered since it was queued with distance du, and with that been
+// queued again.
+__device__ __forceinline__ bool sa_stale(const SsspParams& P, int32_t u, uint32_t du) {
+  return (uint32_t)(__hip_atomic_load(&P.key[u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >>
+                    32) < du;
+}
+
 // Relaxes x.v through u with candidate distance du + wt; x gets its entry's
 // fields while the atomic is on its way.
 __device__ __forceinline__ int sa_relax(const SsspParams& P, SaEntry& x, int32_t u, uint32_t du,
@@ -1284,26 +1362,68 @@ __device__ __forceinline__ int sa_relax(const SsspParams& P, SaEntry& x, int32_t
   const ull old = atomicMin(&P.key[x.v], ((ull)x.d << 32) | (ull)(uint32_t)u);
   sa_load(P, x);
   if (x.d >= (uint32_t)(old >> 32)) return SA_NONE;
-  const bool over = sa_drop(P, x, u, du);
-  if (x.d >= T) return SA_FARV;
-  // relaxed with this distance: a way back that does not fit is reported like
-  // any other edge
-  if (over) __hip_atomic_store(&P.ctl->overflow, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  return SA_NEAR;
+  bool over;
+  const bool left = sa_drop(P, x, u, du, &over);
+  if (x.d < T) {
+    // relaxed with this distance: a way back that does not fit is reported
+    // like any other edge
+    if (over) __hip_atomic_store(&P.ctl->overflow, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return left ? SA_NEAR : SA_NONE;
+  }
+  return left || over ? SA_FARV : SA_NONE;
+}
+
+// Relaxes R edges per thread u[r] -> v[r] (where in[r]) from distance du[r];
+// the vertices that improve are queued without their rows.  For levels of more
+// edges than threads, whose trips to memory overlap: their number counts, not
+// what they carry.  Every lane must take part.
+template <int R>
+__device__ __forceinline__ void sa_relax_bare(const SsspParams& P, SaLds& L, int nxt, int ni,
+                                              uint32_t split, uint32_t T, const bool (&in)[R],
+                                              const int32_t (&v)[R], const int32_t (&u)[R],
+                                              const uint32_t (&du)[R], const uint32_t (&wt)[R]) {
+  uint32_t d[R];
+  ull old[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    d[r] = sat_add(du[r], wt[r]);
+    if (in[r] && d[r] == DIST_INF)
+      __hip_atomic_store(&P.ctl->overflow, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    old[r] = 0;
+    if (in[r] && d[r] != DIST_INF && v[r] != P.src)
+      old[r] = atomicMin(&P.key[v[r]], ((ull)d[r] << 32) | (ull)(uint32_t)u[r]);
+  }
+  bool won[R];
+  int32_t deg[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    won[r] = d[r] < (uint32_t)(old[r] >> 32);
+    deg[r] = won[r] ? P.off[v[r] + 1] - P.off[v[r]] : 0;
+  }
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    // nothing but a way back to a vertex that it cannot lower
+    if (deg[r] == 0 || (deg[r] == 1 && P.symmetric && wt[r] > 0 && d[r] < P.ovf_from))
+      won[r] = false;
+    const bool full = sa_put2(L, nxt, ni, won[r] && d[r] < T, v[r], d[r], deg[r]);
+    sa_far(P, L, split, full || (won[r] && d[r] >= T), v[r]);
+  }
 }
 
 // The members' records of meeting `seq`, published and read by all: L.tot,
-// L.pre (entries of the members before this one), L.mx, L.lev, L.anyo
-// (members that ran out of room since the meeting before).
+// L.pre (entries of the members before this one), L.load / L.mxload (what they
+// weigh, in all and the heaviest), L.lev, L.anyo (members that ran out of room
+// since the meeting before).
 __device__ __forceinline__ bool sa_meet(const SsspParams& P, SaLds& L, TeamSync& ts, uint32_t seq,
-                                        int32_t c, int32_t lev) {
+                                        int32_t c, int32_t load, int32_t lev) {
   AsyncCtl& A = P.ctl->as;
   const uint32_t T = ts.T;
+  static_assert(SQ + SQ2 < 1 << 16 && SA_K < 1 << 8, "fields of a record");
   if (T > 1) {
     if (threadIdx.x == 0) {
       __hip_atomic_store(&A.rec[seq & 1][blockIdx.x],
-                         ((ull)(L.ovf ? 1 : 0) << 63) | ((ull)(uint32_t)lev << 32) |
-                             (ull)(uint32_t)c,
+                         ((ull)(L.ovf ? 1 : 0) << 63) | ((ull)(uint32_t)lev << 52) |
+                             ((ull)(uint32_t)load << 16) | (ull)(uint32_t)c,
                          __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       L.ovf = 0;
     }
@@ -1313,10 +1433,11 @@ __device__ __forceinline__ bool sa_meet(const SsspParams& P, SaLds& L, TeamSync&
       if (threadIdx.x < T)
         r = __hip_atomic_load(&A.rec[seq & 1][threadIdx.x], __ATOMIC_RELAXED,
                               __HIP_MEMORY_SCOPE_AGENT);
-      const int32_t n = (int32_t)(uint32_t)r;
+      const int32_t n = (int32_t)(r & 0xffffu);
       const int32_t incl = fg_wave_incl_scan(n);
       const int32_t o = fg_wave_sum((int32_t)(r >> 63));
-      int32_t mx = n, ml = (int32_t)((r >> 32) & 0x7fffffffu);
+      int32_t mx = (int32_t)((r >> 16) & 0xfffffffffull), ml = (int32_t)((r >> 52) & 0x7ffu);
+      const int32_t all = fg_wave_sum(mx);
 #pragma unroll
       for (int d = FG_WAVE / 2; d > 0; d >>= 1) {
         const int32_t a = __shfl_xor(mx, d, FG_WAVE), b = __shfl_xor(ml, d, FG_WAVE);
@@ -1327,13 +1448,15 @@ __device__ __forceinline__ bool sa_meet(const SsspParams& P, SaLds& L, TeamSync&
       if (threadIdx.x == 0) {
         L.tot = __builtin_amdgcn_readlane(incl, FG_WAVE - 1);
         L.pre = before;
-        L.mx = mx;
+        L.load = all;
+        L.mxload = mx;
         L.lev = ml;
         L.anyo = o;
       }
     }
   } else if (threadIdx.x == 0) {
-    L.tot = L.mx = c;
+    L.tot = c;
+    L.load = L.mxload = load;
     L.pre = 0;
     L.lev = lev;
     L.anyo = L.ovf;
@@ -1343,6 +1466,9 @@ __device__ __forceinline__ bool sa_meet(const SsspParams& P, SaLds& L, TeamSync&
   return true;
 }
 
+// LONG: the graph has rows of more than four entries (their code costs the others
+// 3 % of a level).
+template <bool LONG>
 __global__ __launch_bounds__(PB) void sssp_async(SsspParams P) {
   __shared__ SaLds L;
   const int tid = threadIdx.x;
@@ -1359,7 +1485,8 @@ __global__ __launch_bounds__(PB) void sssp_async(SsspParams P) {
     fg_st_shared(&P.key[v], v == P.src ? (ull)(uint32_t)P.src : KEY_INF);
   for (int64_t i = gt; i < P.nw32; i += gn) fg_st_shared(&P.infar[i], 0u);
   if (tid == 0) {
-    L.cnt[0] = L.cnt[1] = L.big[0] = L.big[1] = L.fcnt = L.ovf = 0;
+    for (int i = 0; i < 3; ++i) L.cnt[i] = L.cnt2[i] = L.edg[i] = 0;
+    L.fcnt = L.ovf = 0;
     if (blockIdx.x == 0) {
       SaEntry x;
       x.v = P.src;
@@ -1372,12 +1499,16 @@ __global__ __launch_bounds__(PB) void sssp_async(SsspParams P) {
       L.qh[0][0] = x.h;
       L.qw[0][0] = x.w;
       L.cnt[0] = 1;
+      L.edg[0] = x.e - x.b > 4 ? x.e - x.b : 0;
     }
   }
   bool ok = T == 1 || ts.sync_acquire(&L.flag);
   __syncthreads();
 
   int cur = 0;
+  int ci = 0;              // counter slot of queue `cur`
+  int32_t limit = SA_BREAK;  // weight from which a member meets at once
+  int32_t most = SA_K;       // levels before the next meeting
   uint32_t Tn = P.delta;   // near threshold
   uint32_t Tnext = sat_add(P.delta, P.delta);
   int32_t done_levels = 0; // levels before this super-step (the longest member's)
@@ -1390,70 +1521,97 @@ __global__ __launch_bounds__(PB) void sssp_async(SsspParams P) {
   // keeps the kernel finite
   for (uint32_t step = 0; ok && step < 0x40000000u; ++step) {
     int32_t lev = 0;
-    for (; lev < SA_K; ++lev) {
-      const int32_t cnt = L.cnt[cur] < SQ ? L.cnt[cur] : SQ;
+    for (; lev < most; ++lev) {
       // (the same in every thread: behind a barrier)
-      if (cnt == 0 || (lev > 0 && T > 1 && cnt > SA_BREAK)) break;
+      const int32_t rows = sa_full(L, ci), cnt = rows + sa_bare(L, ci);
+      const int32_t edges = L.edg[ci];
+      // a queue past twice a member's share is dealt out first
+      if (cnt == 0 || (lev > 0 && T > 1 && cnt + edges / 8 > limit)) break;
       const int nxt = cur ^ 1;
-      const int par = lev & 1;
+      const int ni = ci == 2 ? 0 : ci + 1;
+      if (tid == 0) {
+        const int cl = ni == 2 ? 0 : ni + 1;
+        L.cnt[cl] = L.cnt2[cl] = L.edg[cl] = 0;
+      }
       int64_t here = 0;
-      bool big = false;
-      for (int32_t c0 = 0; c0 < cnt; c0 += PB / 4) {
+      for (int32_t c0 = 0; c0 < (LONG ? rows : cnt); c0 += PB / 4) {
         const int32_t i = c0 + tid / 4;
         const int j = tid & 3;
-        int32_t d = 0;
-        if (i < cnt) d = L.qe[cur][i] - L.qb[cur][i];
-        big |= d > 4;
         int r = SA_NONE;
         SaEntry x;
-        x.v = 0;
-        if (j < d && d <= 4) {
-          x.v = ((const int32_t*)&L.qh[cur][i])[j];
-          if (x.v >= 0) {
-            r = sa_relax(P, x, L.qv[cur][i], L.qd[cur][i], ((const uint32_t*)&L.qw[cur][i])[j], Tn);
-            here++;
+        x.v = -1;
+        int32_t u = 0;
+        uint32_t du = 0, wt = 0;
+        if (i < rows) {
+          const int32_t d = L.qe[cur][i] - L.qb[cur][i];
+          if (j < d && (!LONG || d <= 4)) {
+            x.v = ((const int32_t*)&L.qh[cur][i])[j];
+            u = L.qv[cur][i];
+            du = L.qd[cur][i];
+            wt = ((const uint32_t*)&L.qw[cur][i])[j];
+          }
+        } else if (!LONG && i < cnt) {
+          u = L.q2v[cur][i - rows];
+          du = L.q2d[cur][i - rows];
+          const int32_t b = P.off[u];
+          if (j < P.off[u + 1] - b && !sa_stale(P, u, du)) {
+            x.v = ((const int32_t*)&P.head[u])[j];
+            wt = P.w[b + j];
           }
         }
-        const bool full = sa_put(L, nxt, r == SA_NEAR, x);
+        if (x.v >= 0) {
+          r = sa_relax(P, x, u, du, wt, Tn);
+          here++;
+        }
+        const bool full = sa_put(L, nxt, ni, r == SA_NEAR, x);
         sa_far(P, L, split, full || r == SA_FARV, x.v);
       }
-      if (big) L.big[par] = 1;
-      __syncthreads();
-      if (tid == 0) {
-        L.cnt[cur] = 0;  // every thread has read it
-        L.big[par ^ 1] = 0;
-      }
-      if (L.big[par]) {
-        // longer rows: block scan-gather over their entries
+      if (LONG && (edges > 0 || cnt > rows)) {
+        // longer rows, and those of vertices queued alone: block scan-gather
+        // over their entries
         for (int32_t c0 = 0; c0 < cnt; c0 += PB) {
           const int32_t i = c0 + tid;
           int32_t d = 0;
-          if (i < cnt) {
+          if (i < rows) {
             d = L.qe[cur][i] - L.qb[cur][i];
+            if (d <= 4) d = 0;
             L.b_u[tid] = L.qv[cur][i];
             L.b_b[tid] = L.qb[cur][i];
             L.b_d[tid] = L.qd[cur][i];
+          } else if (i < cnt) {
+            const int32_t u = L.q2v[cur][i - rows];
+            const uint32_t du = L.q2d[cur][i - rows];
+            const int32_t b = P.off[u];
+            d = P.off[u + 1] - b;
+            if (sa_stale(P, u, du)) d = 0;
+            L.b_u[tid] = u;
+            L.b_b[tid] = b;
+            L.b_d[tid] = du;
           }
-          if (d <= 4) d = 0;
           int32_t all = 0;
           const int32_t ex = fg_block_excl_scan<PB>(d, L.red32, &all);
           L.b_sc[tid] = ex;
           __syncthreads();
           const int32_t nc = cnt - c0 < PB ? cnt - c0 : PB;
-          for (int32_t t0 = 0; t0 < all; t0 += PB) {
-            const int32_t t = t0 + tid;
-            int r = SA_NONE;
-            SaEntry x;
-            x.v = 0;
-            if (t < all) {
-              const int32_t jj = upper_idx(L.b_sc, nc, t);
-              const int32_t e = L.b_b[jj] + (t - L.b_sc[jj]);
-              x.v = P.col[e];
-              r = sa_relax(P, x, L.b_u[jj], L.b_d[jj], P.w[e], Tn);
-              here++;
+          constexpr int R = 1;
+          for (int32_t t0 = 0; t0 < all; t0 += R * PB) {
+            bool in[R];
+            int32_t v[R], u[R];
+            uint32_t du[R], wt[R];
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+              const int32_t t = t0 + r * PB + tid;
+              in[r] = t < all;
+              const int32_t tc = in[r] ? t : all - 1;
+              const int32_t jj = upper_idx(L.b_sc, nc, tc);
+              const int32_t e = L.b_b[jj] + (tc - L.b_sc[jj]);
+              v[r] = P.col[e];
+              wt[r] = P.w[e];
+              u[r] = L.b_u[jj];
+              du[r] = L.b_d[jj];
+              here += in[r];
             }
-            const bool full = sa_put(L, nxt, r == SA_NEAR, x);
-            sa_far(P, L, split, full || r == SA_FARV, x.v);
+            sa_relax_bare<R>(P, L, nxt, ni, split, Tn, in, v, u, du, wt);
           }
           __syncthreads();
         }
@@ -1469,17 +1627,19 @@ __global__ __launch_bounds__(PB) void sssp_async(SsspParams P) {
       }
       __syncthreads();
       cur = nxt;
+      ci = ni;
     }
     // every append of the levels is behind a barrier here
-    const int32_t mine = L.cnt[cur] < SQ ? L.cnt[cur] : SQ;
+    const int32_t rows = sa_full(L, ci), mine = rows + sa_bare(L, ci);
     if (mine == 0) sa_flush(P, L, split);
-    if (!(ok = sa_meet(P, L, ts, seq++, mine, lev))) break;
+    if (!(ok = sa_meet(P, L, ts, seq++, mine, sa_weight(L, ci), lev))) break;
     spilled = spilled || L.anyo > 0;
     done_levels += L.lev;
     if (P.behind && (int64_t)L.tot > (int64_t)T * SA_WIDE && L.tot <= P.n) {
       // hand over: near vertices to the global queue, collected far ones to
       // the pile
-      for (int32_t i = tid; i < mine; i += PB) fg_st_shared(&P.q[0][L.pre + i], L.qv[cur][i]);
+      for (int32_t i = tid; i < mine; i += PB)
+        fg_st_shared(&P.q[0][L.pre + i], sa_vertex(L, cur, rows, i));
       sa_flush(P, L, split);
       wide = true;
       break;
@@ -1520,7 +1680,7 @@ __global__ __launch_bounds__(PB) void sssp_async(SsspParams P) {
           near = !keep && (again || x.d >= Tn);
           if (keep) mn = x.d < mn ? x.d : mn;
         }
-        if (sa_put(L, cur, near, x)) keep = true;  // no room: it stays in the pile
+        if (sa_put(L, cur, ci, near, x)) keep = true;  // no room: it stays in the pile
         if (listed && !keep) atomicAnd(&P.infar[x.v >> 5], ~(1u << (x.v & 31)));
         // kept entries move to the other pile, their bits stay set
         const uint64_t m = __ballot(keep);
@@ -1534,8 +1694,8 @@ __global__ __launch_bounds__(PB) void sssp_async(SsspParams P) {
       mn = block_min(mn, L.redm);
       if (tid == 0 && mn != DIST_INF) atomicMin(&A.fmin[split % 3], mn);
       __syncthreads();
-      const int32_t got = L.cnt[cur] < SQ ? L.cnt[cur] : SQ;
-      if (!(ok = sa_meet(P, L, ts, seq++, got, 0))) break;
+      const int32_t got = sa_full(L, ci) + sa_bare(L, ci);
+      if (!(ok = sa_meet(P, L, ts, seq++, got, sa_weight(L, ci), 0))) break;
       spilled = L.anyo > 0;
       if (!again) {
         Tn = Tnew;
@@ -1547,23 +1707,36 @@ __global__ __launch_bounds__(PB) void sssp_async(SsspParams P) {
       split++;
     }
     if (!ok || finished) break;
+    const int32_t share = 2 * (L.load / (int32_t)T);
+    limit = share > SA_BREAK ? share : SA_BREAK;
+    most = share > 2 * SA_ROUND ? SA_KWIDE : SA_K;
     // even shares where one member holds more than a round's work and more
     // than twice its share
-    if (T > 1 && L.mx > SA_ROUND && (int64_t)L.mx * T > 2 * (int64_t)L.tot && L.tot <= P.n) {
-      const int32_t have = L.cnt[cur] < SQ ? L.cnt[cur] : SQ;
+    if (T > 1 && L.mxload > SA_ROUND && L.mxload > share && L.tot <= P.n) {
+      const int32_t hrows = sa_full(L, ci), have = hrows + sa_bare(L, ci);
       const int32_t pre = L.pre, tot = L.tot;
       int32_t* G = P.q[0];
-      for (int32_t i = tid; i < have; i += PB) fg_st_shared(&G[pre + i], L.qv[cur][i]);
+      for (int32_t i = tid; i < have; i += PB)
+        fg_st_shared(&G[pre + i], sa_vertex(L, cur, hrows, i));
       if (!(ok = ts.sync_acquire(&L.flag))) break;
+      if (tid == 0) L.edg[ci] = 0;
+      __syncthreads();
       const int32_t lo = (int32_t)((int64_t)tot * blockIdx.x / T);
       const int32_t hi = (int32_t)((int64_t)tot * (blockIdx.x + 1) / T);
+      int32_t edges = 0;
       for (int32_t i = tid; i < hi - lo; i += PB) {
         SaEntry x;
         x.v = G[lo + i];
         // the key may be lower by now than when the vertex was queued
         x.d = (uint32_t)(__hip_atomic_load(&P.key[x.v], __ATOMIC_RELAXED,
                                            __HIP_MEMORY_SCOPE_AGENT) >> 32);
+        if (i >= SQ) {
+          L.q2v[cur][i - SQ] = x.v;
+          L.q2d[cur][i - SQ] = x.d;
+          continue;
+        }
         sa_load(P, x);
+        if (x.e - x.b > 4) edges += x.e - x.b;
         L.qv[cur][i] = x.v;
         L.qd[cur][i] = x.d;
         L.qb[cur][i] = x.b;
@@ -1571,8 +1744,12 @@ __global__ __launch_bounds__(PB) void sssp_async(SsspParams P) {
         L.qh[cur][i] = x.h;
         L.qw[cur][i] = x.w;
       }
-      __syncthreads();
-      if (tid == 0) L.cnt[cur] = hi - lo;
+      edges = fg_wave_sum(edges);
+      if (fg_lane() == 0 && edges) atomicAdd(&L.edg[ci], edges);
+      if (tid == 0) {
+        L.cnt[ci] = hi - lo < SQ ? hi - lo : SQ;
+        L.cnt2[ci] = hi - lo < SQ ? 0 : hi - lo - SQ;
+      }
     }
     __syncthreads();
   }
@@ -2037,25 +2214,35 @@ extern "C" fg_status fg_sssp(const fg_graph* g, int32_t src, const fg_sssp_opts*
   if (P.team_e > TW_CAP - 1) P.team_e = TW_CAP - 1;
   P.clock_khz = pr.clock_khz;
   P.head = g->head;
+  P.symmetric = g->symmetric;
   P.ovf_from = DIST_INF - g->w_max;
   void* args[] = {&P};
   // The asynchronous team answers where the team build would run by default,
   // unless the caller sets how frontiers are dealt with.  Its width follows
   // the width of a front (a member per 16 vertices of the side of a square
   // of n vertices): a level is one trip up to 256 vertices per member, and
-  // members more than that only meet more slowly.  Rows past SA_DEG entries
-  // are left to the whole grid from the start.
+  // members more than that only meet more slowly.  Fronts are known to be thin
+  // where no row has more than four entries; elsewhere (random graphs, trees of
+  // many children) the whole grid catches up: below SA_GIVE_UP members, which
+  // never hand over, at 2^16 entries (uniform random, 54 k 251 us and 278 by the
+  // whole grid, 96 k 360 and 330, 125 k 380 and 345), above at rows of more than
+  // eight (60 k vertices, 120 k entries 406 and 383, 0.48 M 471 and 458; with
+  // no row past eight they may be roads).
   const bool tuned = o.small_frontier > 0 || o.small_edges > 0 || o.big_degree > 0 ||
                      o.blocks_per_cu > 0 || o.grid_blocks > 0 || o.team_blocks != 0 ||
                      o.team_edges > 0;
-  if (low_deg && !tuned && g->max_degree <= SA_DEG) {
-    int T = 1;
-    while (T < SA_T && (int64_t)T * SA_SIDE * T * SA_SIDE < (int64_t)g->n) T *= 2;
-    if (T > pr.cus) T = pr.cus;
+  int T = 1;
+  while (T < SA_T && (int64_t)T * SA_SIDE * T * SA_SIDE < (int64_t)g->n) T *= 2;
+  if (T > pr.cus) T = pr.cus;
+  const bool thin = g->max_degree <= 4 ||
+                    (T < SA_GIVE_UP ? g->max_degree <= SA_DEG && g->m <= SA_SMALL_M
+                                    : g->max_degree <= SA_ROAD);
+  if (low_deg && !tuned && thin) {
     // below SA_GIVE_UP members (16 k vertices) the team never gives up
     P.behind = T >= SA_GIVE_UP ? 1 : 0;
-    FG_HIP_TRY(hipLaunchCooperativeKernel((const void*)sssp_async, dim3(T), dim3(PB), args, 0,
-                                          (hipStream_t)stream));
+    FG_HIP_TRY(hipLaunchCooperativeKernel(g->max_degree > 4 ? (const void*)sssp_async<true>
+                                                            : (const void*)sssp_async<false>,
+                                          dim3(T), dim3(PB), args, 0, (hipStream_t)stream));
     if (!P.behind) return FG_OK;
   }
   const void* kern = P.team > 1 ? (const void*)sssp_persistent<true>

@@ -320,3 +320,68 @@ def test_way_back_past_the_largest_distance(fg, orc, kw, deg, last, over):
     else:
         assert b.poll()[0] & 2
     g.close()
+
+
+def _random_graph(orc, n, edges, seed):
+    eu, ev = np.random.default_rng(seed).integers(0, n, (2, edges)).astype(np.int32)
+    return orc.csr_from_edges(n, eu, ev)
+
+
+def _tree(orc, n, children):
+    return orc.csr_from_edges(n, np.arange(1, n, dtype=np.int32),
+                              (np.arange(n - 1) // children).astype(np.int32))
+
+
+@pytest.mark.parametrize("kind,n,arg,blocks", [
+    ("random", 4000, 12000, 4), ("random", 9000, 27000, 8), ("random", 16000, 60000, 256),
+    ("tree", 16000, 200, 8), ("tree", 250000, 200, 256), ("tree", 60000, 3, None),
+    ("random", 60000, 60000, 256)])
+def test_wide_fronts_of_low_degree_graphs(fg, orc, kind, n, arg, blocks):
+    """Fronts of a large part of the graph: queues of vertices alone, even
+    shares, leaves that are not queued at all; not slower than the whole grid
+    from the start."""
+    off, col = _random_graph(orc, n, arg, n) if kind == "random" else _tree(orc, n, arg)
+    w = synth.weights(off, col)
+    g = fg.Graph(off, col, weights=w)
+    srcs = [int(s) for s in synth.sources(off, 3, seed=n)] + [0]
+    for s in srcs:
+        st = check(fg, orc, g, off, col, w, s)
+        assert blocks is None or st.grid_blocks == blocks
+    dist, parent = (torch.empty(n, dtype=torch.int32, device="cuda") for _ in range(2))
+    us = []
+    for opts in (fg.sssp_opts(), fg.sssp_opts(team_blocks=32)):
+        fg.sssp_into(g, srcs[0], dist, parent, opts)
+        a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        a.record()
+        for _ in range(10):
+            fg.sssp_into(g, srcs[0], dist, parent, opts)
+        b.record()
+        torch.cuda.synchronize()
+        us.append(a.elapsed_time(b) * 100)
+    assert us[0] < 1.5 * us[1], us
+    g.close()
+
+
+@pytest.mark.parametrize("deg", [1, 4, 5, 40, 256])
+@pytest.mark.parametrize("wmax", [0, 1, 64])
+def test_queues_of_vertices_alone(fg, orc, deg, wmax):
+    """A front past the entries that carry their rows (512 per member) and past
+    those that do not, zero weights (equal distances still lower a predecessor)
+    and directed rows."""
+    hubs = 900
+    n = hubs * deg + hubs + 1
+    kids = np.arange(1 + hubs, n, dtype=np.int32)
+    ring = np.arange(1, 1 + hubs, dtype=np.int32)
+    eu = np.concatenate([ring[:-1], 1 + (kids - 1 - hubs) // deg, kids[:-1][kids[:-1] % 3 == 0]])
+    ev = np.concatenate([ring[1:], kids, kids[:-1][kids[:-1] % 3 == 0] + 1])
+    # the hubs hang on a tree of four children each, so they are met together
+    eu = np.concatenate([eu, ring]).astype(np.int32)
+    ev = np.concatenate([ev, (ring - 1) // 4]).astype(np.int32)
+    off, col = orc.csr_from_edges(n, eu, ev)
+    w = synth.weights(off, col) % np.uint32(wmax + 1)
+    for sym in (True, False):
+        g = fg.Graph(off, col, weights=w, symmetric=sym)
+        for delta in (0, 3, 0xFFFFFFFF):
+            for s in (0, 450, n - 1):
+                check(fg, orc, g, off, col, w, s, delta=delta)
+        g.close()
