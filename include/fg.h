@@ -468,8 +468,8 @@ fg_status fg_msbfs_poll(fg_msbfs* b, uint64_t* done_lanes, int32_t* iterations, 
 fg_status fg_msbfs_read(fg_msbfs* b, int32_t lane, int32_t* depth, void* stream);
 
 /* Synchronise `stream`; work done since fg_msbfs_open: *edges = adjacency
- * entries read (push: whole lists of active vertices; pull: the first four,
- * further ones where those leave lanes open), *verts = vertex visits (push: active vertices; pull: every vertex
+ * entries read (push: whole lists of active vertices; pull: up to the early
+ * exit), *verts = vertex visits (push: active vertices; pull: every vertex
  * of the graph per pull level).  Either pointer may be NULL. */
 fg_status fg_msbfs_counts(fg_msbfs* b, uint64_t* edges, uint64_t* verts, void* stream);
 

@@ -43,6 +43,7 @@ constexpr int MAXL = 64;
 // words, so one wave would scan them all); they are listed and their lists
 // cut into CH-entry chunks that every wave takes in turn.
 constexpr int32_t LONG_PULL = 64;
+constexpr int EXACT_PULL = 32;  // rows whose entries are counted up to the early end
 // Team mode (push levels of medium frontiers; see team_levels): LDS queue
 // entries per member, widest team, packed team word fields, frontier shape.
 constexpr int QCAP = 2048;
@@ -411,12 +412,14 @@ __device__ void put_long(const MsParams& P, int32_t* sc, int32_t* su, int32_t* s
 
 // Rows of the pull with more than the head's four entries and no early end
 // among them, R * 8 further entries each at most: eight lanes take a row, R
-// entries per lane in flight together.  sc / su / sb / sf hold the rows
-// (owner lane, first entry left, end, wanted lanes) at places [0, cnt); the
-// lanes found go back to sf.  Every lane of the wave must take part.
+// entries per lane in flight together.  sb / se / sf hold the rows (first entry
+// left, end, wanted lanes) at places [0, cnt); the lanes found go back to sf,
+// and to se the entries up to the early end: of rows of up to EXACT_PULL entries
+// four by four as if they were read so, of longer ones all.  Every lane of the
+// wave must take part.
 template <int R>
 __device__ __forceinline__ void pull_rows(const MsParams& P, const ull* Fc, const int32_t* sb,
-                                          const int32_t* se, ull* sf, int32_t cnt) {
+                                          int32_t* se, ull* sf, int32_t cnt) {
   const int lane = fg_lane();
   for (int32_t i0 = 0; i0 < cnt; i0 += FG_WAVE / 8) {
     const int32_t i = i0 + lane / 8;
@@ -429,13 +432,37 @@ __device__ __forceinline__ void pull_rows(const MsParams& P, const ull* Fc, cons
       const int32_t k = lane % 8 + 8 * r;
       u[r] = P.col[k < e - b ? b + k : e - 1];
     }
+    ull y[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) y[r] = Fc[u[r]] & w;
+    constexpr int C = R < EXACT_PULL / 8 ? R : EXACT_PULL / 8;
     ull x = 0;
+    int32_t read = e - b;
 #pragma unroll
-    for (int r = 0; r < R; ++r) x |= Fc[u[r]];
-    x &= w;
+    for (int r = 0; r < C; ++r) {
+      ull a = y[r];
+      a |= __shfl_xor(a, 1, FG_WAVE);
+      a |= __shfl_xor(a, 2, FG_WAVE);
+      const ull o = __shfl_xor(a, 4, FG_WAVE);
+      if (x != w) {
+        x |= lane & 4 ? o : a;
+        if (x == w) read = 8 * r + 4;
+        x |= a | o;
+        if (x == w && read > 8 * r + 8) read = 8 * r + 8;
+      }
+    }
+    ull z = 0;
 #pragma unroll
-    for (int d = 1; d < 8; d <<= 1) x |= __shfl_xor(x, d, FG_WAVE);
-    if (lane % 8 == 0 && i < cnt) sf[i] = x;
+    for (int r = C; r < R; ++r) z |= y[r];
+    if (C < R) {
+#pragma unroll
+      for (int d = 1; d < 8; d <<= 1) z |= __shfl_xor(z, d, FG_WAVE);
+    }
+    wave_lds_fence();
+    if (lane % 8 == 0 && i < cnt) {
+      sf[i] = x | z;
+      se[i] = e - b > EXACT_PULL - 4 || read > e - b ? e - b : read;
+    }
   }
 }
 
@@ -1096,7 +1123,6 @@ __global__ __launch_bounds__(PB) void msbfs_persistent(MsParams P) {
             L.w_b[wid][at] = b + 4;
             L.w_u[wid][at] = e;
             L.w_f[wid][at] = want & ~nw;
-            ecnt += (uint32_t)(e - b - 4);
           }
           wave_lds_fence();
           if (pass == 0)
@@ -1104,7 +1130,10 @@ __global__ __launch_bounds__(PB) void msbfs_persistent(MsParams P) {
           else
             pull_rows<8>(P, Fc, L.w_b[wid], L.w_u[wid], L.w_f[wid], cnt);
           wave_lds_fence();
-          if (mine) nw |= L.w_f[wid][at];
+          if (mine) {
+            nw |= L.w_f[wid][at];
+            ecnt += (uint32_t)L.w_u[wid][at];
+          }
         }
         if (v < P.n) {
           if (nw && !lng) fg_st_shared(&P.visit[v], vis | nw);

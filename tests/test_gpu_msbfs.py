@@ -266,3 +266,66 @@ def test_read_into_pinned_host_memory(fg, orc):
     fg.bfs(g, 3)
     b.close()
     g.close()
+
+
+def _pull_work(off, col, srcs):
+    """Entries read and vertex visits of a batch that only pulls, by the
+    counting rule: the first four entries, then up to the early exit, four at a
+    time in rows of up to 32, all of a row of up to 64."""
+    n = len(off) - 1
+    seen, front = [0] * n, [0] * n
+    for lane, s in enumerate(srcs):
+        seen[s] |= 1 << lane
+        front[s] |= 1 << lane
+    live = (1 << len(srcs)) - 1
+    edges = verts = 0
+    while live:
+        new = [0] * n
+        verts += n
+        for v in range(n):
+            row = col[off[v]:off[v + 1]]
+            want = live & ~seen[v]
+            if not want or not len(row):
+                continue
+            got = 0
+            for at in range(0, len(row) if len(row) <= 32 else 4, 4):
+                edges += len(row[at:at + 4])
+                for u in row[at:at + 4]:
+                    got |= front[u] & want
+                if got == want:
+                    break
+            if len(row) > 32 and got != want:
+                edges += len(row) - 4
+                for u in row[4:]:
+                    got |= front[u] & want
+            new[v] = got
+        live = 0
+        for v in range(n):
+            seen[v] |= new[v]
+            live |= new[v]
+        front = new
+    return edges, verts
+
+
+@pytest.mark.parametrize("lanes", [1, 3, 64])
+@pytest.mark.parametrize("most", [6, 22, 34, 64])
+def test_pull_counts(fg, orc, lanes, most):
+    """fg_msbfs_counts of a batch that only pulls, rows of every length up to
+    the one that is cut into chunks."""
+    n = 700
+    rng = np.random.default_rng(most)
+    deg = rng.integers(0, most // 2, n)
+    u = np.repeat(np.arange(n), deg)
+    off, col = orc.csr_from_edges(n, u.astype(np.int32), rng.integers(0, n, len(u)).astype(np.int32))
+    assert np.diff(off).max() <= 64
+    g = fg.Graph(off, col)
+    srcs = [int(s) for s in rng.choice(n, lanes)]
+    b = fg.MsBatch(g, lanes, fg.msbfs_opts(pull_div=1 << 30, push_div=1 << 30))
+    announce(f"msbfs pull counts lanes={lanes} rows up to {np.diff(off).max()}")
+    for lane, s in enumerate(srcs):
+        b.admit(lane, s)
+    b.run(k_iters=3)
+    for lane, s in enumerate(srcs):
+        assert np.array_equal(to_np(b.read(lane)), orc.bfs(off, col, s)[0])
+    assert b.counts() == _pull_work(off.tolist(), col.tolist(), srcs)
+    b.close()
