@@ -133,6 +133,7 @@ struct MsParams {
   int32_t team;      // workgroups of a team (<= 1: no team mode)
   int64_t team_e;    // largest frontier degree sum a team takes
   int32_t has_long;  // the graph has rows of more than LONG_PULL entries
+  int32_t near;      // mean degree <= 8: neighbours' numbers are often near
 };
 
 struct Lds {
@@ -1070,8 +1071,12 @@ __global__ __launch_bounds__(PB) void msbfs_persistent(MsParams P) {
       int32_t lch = 0;                                 // ... their chunks
       // at most one piece per wave: spread over the workgroups; more: a
       // workgroup's pieces adjacent (grid 400 x 500, 64 lanes: 9.27 ms
-      // spread, 9.05 adjacent; R-MAT of 60 000, 30 lanes: 454 and 463 us)
-      const int64_t first = P.n <= W * FG_WAVE ? gwm : (int64_t)blockIdx.x * PWAVES + wid;
+      // spread, 9.05 adjacent; R-MAT of 60 000, 30 lanes: 454 and 463 us), and
+      // so from half of that on where neighbours are near (400 x 400, 64 lanes:
+      // 7.83 and 7.54 ms; 200 x 200 3.36 and 3.66)
+      const bool spread =
+          P.n <= W * FG_WAVE && !(P.near && 2 * (int64_t)P.n > W * FG_WAVE);
+      const int64_t first = spread ? gwm : (int64_t)blockIdx.x * PWAVES + wid;
       for (int64_t v0 = first * FG_WAVE; v0 < P.n; v0 += W * FG_WAVE) {
         const int64_t v = v0 + lane;
         ull vis = ~0ull, nw = 0;
@@ -1466,12 +1471,14 @@ extern "C" fg_status fg_msbfs_step(fg_msbfs* b, int32_t k_iters, void* stream) {
   }
   P.big_deg = b->opts.big_degree > 0 ? b->opts.big_degree : 64;
   P.has_long = g->max_degree > LONG_PULL;
+  P.near = g->m <= (int64_t)TEAM_AUTO_DEG * g->n;
   P.pull_div = b->opts.pull_div > 0 ? b->opts.pull_div : 64;
   // back to push at the same size as the switch to pull (grid 2048², 64
   // lanes: 105 ms, against 125 ms at n / 512; R-MAT 23 flat at 6.8-7.0 ms)
   P.push_div = b->opts.push_div > 0 ? b->opts.push_div : 64;
   void* args[] = {&P};
   int grid = pr.cus * bpc;
+  const int lanes_in = __builtin_popcountll(b->admitted);
   // 256, 128 and 64 workgroups, 20 to 60 lanes: R-MAT of 1500 vertices 304,
   // 286, 277 us; 80 k 692, 686, 773; 150 k 434, 444, 483; grids: 100 x 120
   // 2072, 1816, 1703; 300 x 350 6065, 5313, 5764.  More entries, 1, 16 and 64
@@ -1479,13 +1486,17 @@ extern "C" fg_status fg_msbfs_step(fg_msbfs* b, int32_t k_iters, void* stream) {
   // 324; 171, 261, 348; 199, 350, 445, 130 k with 8 (2.1 M) 168, 200, 269; 153,
   // 196, 272; 166, 245, 332; R-MAT, 60 k with 32 (3.1 M) 154, 242, 341; 133,
   // 234, 337; 127, 259, 367, 130 k with 32 (7 M) 203, 278, 404; 171, 244, 452;
-  // 168, 252, 597
-  if (b->opts.blocks_per_cu == 0 && b->opts.grid_blocks == 0 && b->opts.pull_div == 0)
-    grid = fg_default_width(g, 1 << 14, 1 << 17, 1 << 21, fg_skewed(g) ? 1 << 22 : 1 << 21, grid);
+  // 168, 252, 597; few lanes stop early at hubs (100 k with 15 M, 1 and 8
+  // lanes: 147, 240; 127, 204)
+  if (b->opts.blocks_per_cu == 0 && b->opts.grid_blocks == 0 && b->opts.pull_div == 0) {
+    const bool hubs = fg_skewed(g);
+    grid = hubs && lanes_in <= 8
+               ? fg_default_width(g, 1 << 14, 1 << 17, INT64_MAX, INT64_MAX, grid)
+               : fg_default_width(g, 1 << 14, 1 << 17, 1 << 21, hubs ? 1 << 22 : 1 << 21, grid);
+  }
   if (b->opts.grid_blocks > 0 && b->opts.grid_blocks < grid) grid = b->opts.grid_blocks;
   // by default the team kernel runs on graphs of mean degree <= 8 (grids,
   // road-like graphs: long, thin push frontiers)
-  const int lanes_in = __builtin_popcountll(b->admitted);
   const bool low_deg = g->m <= (int64_t)TEAM_AUTO_DEG * g->n;
   const int32_t tbo = b->opts.team_blocks;
   P.team = tbo > 1 ? tbo
