@@ -296,7 +296,8 @@ typedef struct {
                              than the threshold are relaxed; it grows by delta
                              when none is left (0 = default: a factor x mean
                              weight / mean degree: 64; on graphs of mean degree
-                             > 8, 256 up to 2^22 entries and 24 from 2^24 on;
+                             > 8, 24 where rows are alike and from 2^24 entries
+                             on, else 256 up to 2^22 entries;
                              UINT32_MAX = no threshold, plain
                              frontier Bellman-Ford).  Results do not depend
                              on it.                                          */

@@ -2107,20 +2107,24 @@ int g_sssp_occ[64];
 // degree of the vertices with edges; at least 1.  A larger step relaxes more
 // edges again, a smaller one splits the far pile more often.  64 (about a
 // wave's worth of edges per frontier vertex) on low-degree graphs and between
-// the bounds; up to 2^22 entries the splits cost more (R-MAT, 64 and over 256:
-// 200 k vertices 501 and 475 us, 60 k 394 and 371, 10 k 313 and 292), from
-// 2^24 on the relaxations do (64 and 24: R-MAT of 4 M vertices 3.14, 3.00 and
-// 3.38 ms and 2.89, 2.81 and 2.68 from three sources, 3 M 2.41, 2.93, 2.52
-// and 2.21, 2.41, 1.97, 1 M with 24 M entries 1.31, 1.00, 0.96 and 0.98,
-// 1.02, 0.96, 2 M with 68 M entries 1.70, 1.75, 1.42 and 1.74, 1.74, 1.77;
-// random graphs of mean degree 16 and 48, 2 M vertices: 3.41 and 1.78, 5.33
-// and 2.91).
+// the bounds; up to 2^22 entries the splits cost more where hubs hold most of
+// them (R-MAT, 64 and over 256: 200 k vertices 501 and 475 us, 60 k 394 and 371,
+// 10 k 313 and 292), from 2^24 on the relaxations do (64 and 24: R-MAT of 4 M
+// vertices 3.14, 3.00 and 3.38 ms and 2.89, 2.81 and 2.68 from three sources,
+// 3 M 2.41, 2.93, 2.52 and 2.21, 2.41, 1.97, 1 M with 24 M entries 1.31, 1.00,
+// 0.96 and 0.98, 1.02, 0.96, 2 M with 68 M entries 1.70, 1.75, 1.42 and 1.74,
+// 1.74, 1.77), and everywhere where rows are alike (24, 64 and 256, uniform
+// random: 10 k vertices with 1.3 M entries 360, 386, 433 us, 60 k with 1.9 M 473,
+// 500, 537 and 3.8 M 603, 601, 703, 1 M with 16 M 1236, 1811, 1912).
 uint32_t fg_sssp_default_delta(const fg_graph* g) {
   if (g->m <= 0 || g->nonzero_degree <= 0) return 1u;
   const double mean_w = (double)g->w_sum / (double)g->m;
   const double mean_deg = (double)g->m / (double)g->nonzero_degree;
   const bool low_deg = g->m <= (int64_t)TEAM_AUTO_DEG * g->n;
-  const double f = low_deg ? 64.0 : g->m <= 1 << 22 ? 256.0 : g->m < 1 << 24 ? 64.0 : 24.0;
+  const double f = low_deg                                 ? 64.0
+                   : !fg_skewed(g) || g->m >= 1 << 24 ? 24.0
+                   : g->m <= 1 << 22                       ? 256.0
+                                                           : 64.0;
   const double d = f * mean_w / mean_deg;
   if (d >= 4294967295.0) return DIST_INF;
   return d < 1.0 ? 1u : (uint32_t)(d + 0.5);

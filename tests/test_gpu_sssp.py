@@ -322,6 +322,22 @@ def test_way_back_past_the_largest_distance(fg, orc, kw, deg, last, over):
     g.close()
 
 
+@pytest.mark.parametrize("n,deg", [(16000, 100), (60000, 40)])
+def test_default_delta_where_rows_are_alike(fg, orc, n, deg):
+    """Uniform random graphs take small steps by default: no more relaxations,
+    to a few percent (their order is not fixed), than 24 x mean weight / mean degree."""
+    off, col = _random_graph(orc, n, n * deg // 2, deg)
+    w = synth.weights(off, col)
+    g = fg.Graph(off, col, weights=w)
+    announce(f"sssp default delta n={n} deg={deg}")
+    step = round(24 * float(w.mean()) * n / len(col))
+    least = min(check(fg, orc, g, off, col, w, 0, delta=step).edges_inspected for _ in range(3))
+    st = check(fg, orc, g, off, col, w, 0)
+    coarse = check(fg, orc, g, off, col, w, 0, delta=256 * step // 24)
+    assert st.edges_inspected <= 1.05 * least < coarse.edges_inspected
+    g.close()
+
+
 def _random_graph(orc, n, edges, seed):
     eu, ev = np.random.default_rng(seed).integers(0, n, (2, edges)).astype(np.int32)
     return orc.csr_from_edges(n, eu, ev)
