@@ -158,3 +158,56 @@ def test_longest_row_at_the_bound(fg, orc, extra, K, T):
         st = run(fg, orc, g, off, col, src, K, T, f"grid+{extra}", expect_fallback=T == 1)
         assert st.grid_blocks == T or T == 1
     g.close()
+
+
+@pytest.mark.parametrize("what", ["grid1x1", "grid1x300", "grid40x61", "tiny", "er3000"])
+def test_team_on_small_graphs(fg, orc, what):
+    """Graphs that one workgroup takes by default, by the team (an option of
+    the level-synchronous kernel behind it keeps it): tiny, of one vertex, not
+    connected; and as the second query of fg_bfs_corun."""
+    if what.startswith("grid"):
+        off, col = synth.grid_csr(*map(int, what[4:].split("x")))
+    elif what == "tiny":
+        off, col = orc.csr_from_edges(9, np.array([0, 1, 5], np.int32), np.array([1, 2, 6], np.int32))
+    else:
+        eu, ev = np.random.default_rng(5).integers(0, 3000, (2, 4000)).astype(np.int32)
+        off, col = orc.csr_from_edges(3000, eu, ev)
+    g = fg.Graph(off, col)
+    for src in sorted({0, min(3, g.n - 1), g.n - 1}):
+        want, _, cnt, _ = orc.bfs(off, col, src)
+        for K, T in ((2, 1), (2, 3), (8, 24), (64, 64)):
+            announce(f"async small {what} src={src} K={K} T={T}")
+            o = fg.bfs_opts(mode=fg.FG_MODE_PUSH, async_levels=K, team_blocks=T, small_frontier=64)
+            depth, parent, st = fg.bfs(g, src, opts=o)
+            assert st.grid_blocks == T and st.status == 0 and st.iterations == len(cnt)
+            assert np.array_equal(to_np(depth), want)
+            assert np.array_equal(to_np(parent).astype(np.int64),
+                                  canonical_parents(off, col, want, src))
+            d2 = torch.full((g.n,), -7, dtype=torch.int32, device="cuda")
+            p2 = torch.full((g.n,), -7, dtype=torch.int32, device="cuda")
+            s2 = fg.new_stats()
+            fg.bfs_corun_into(g, torch.zeros(0, dtype=torch.int32, device="cuda"), depth, parent,
+                              None, None, None, g, src, d2, p2, o,
+                              ws2=g.workspace(fg.FG_PRIM_BFS, 1), stats2=s2)
+            assert fg.read_stats(s2).status == 0
+            assert np.array_equal(to_np(d2), want)
+            assert orc.check_bfs(off, col, src, to_np(d2), to_np(p2)) is None
+    g.close()
+
+
+def test_modes_interleaved_past_one_workgroup(fg, orc):
+    """Team, level-synchronous and direction-optimizing calls on one workspace
+    of a graph that no workgroup takes alone: each leaves the control block
+    ready for the next."""
+    off, col = synth.grid_csr(150, 200)
+    g = fg.Graph(off, col)
+    for i in range(6):
+        src = (i * 9770) % g.n
+        want = orc.bfs(off, col, src)[0]
+        assert run(fg, orc, g, off, col, src, 8, 24, "grid150x200").grid_blocks == 24
+        for mode in (fg.FG_MODE_PUSH, fg.FG_MODE_DO):
+            depth, parent, st = fg.bfs(g, src, opts=fg.bfs_opts(mode=mode, blocks_per_cu=1))
+            assert np.array_equal(to_np(depth), want)
+            assert orc.check_bfs(off, col, src, to_np(depth), to_np(parent)) is None
+            assert st.status == 0 and st.grid_blocks > 1
+    g.close()
