@@ -77,3 +77,29 @@ def test_noalloc_rejects(fg):
     with pytest.raises(fg.FGError) as e:
         fg.bfs_noalloc_into(g2, g2.n, d2)
     assert e.value.status == fg.FG_EINVAL
+
+
+def test_noalloc_layouts_in_turn(fg, orc):
+    """Graphs whose scratch layouts differ, none of them one workgroup's work,
+    in turn on the same scratch, also after calls that force the team and the
+    LDS modes."""
+    graphs = [synth.rmat_csr(20), synth.rmat_csr(16)]
+    gs = [fg.Graph(*c) for c in graphs]
+    depth = torch.empty(gs[0].n, dtype=torch.int32, device="cuda")
+
+    def both(i, opts):
+        off, col = graphs[i]
+        src = int(synth.sources(off, 1)[0])
+        _pair(fg, orc, gs[i], off, col, src, opts)
+        st = fg.new_stats()
+        fg.bfs_noalloc_into(gs[i], src, depth, None, opts, stats=st)
+        assert fg.read_stats(st).grid_blocks > 1
+
+    for mode in (fg.FG_MODE_DO, fg.FG_MODE_PUSH):
+        o = fg.bfs_opts(mode=mode)
+        for i in (0, 1, 0):
+            both(i, o)
+        both(1, fg.bfs_opts(mode=mode, team_blocks=3, small_edges=1))
+        both(0, o)
+        both(1, fg.bfs_opts(mode=mode, team_blocks=-1, small_edges=1 << 18))
+        both(0, o)
