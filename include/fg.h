@@ -184,7 +184,9 @@ typedef struct {
                              smallest-id neighbour one level closer); the
                              level-synchronous kernel takes over if a
                              member's frontier outgrows its LDS room
-                             (0 = level-synchronous; at most 1024)            */
+                             (0 = level-synchronous; at most 1024); neither
+                             counts on small graphs that fg_bfs gives to one
+                             workgroup                                        */
   int32_t grid_blocks;    /* workgroups of the persistent launch (0 = every CU x
                              blocks_per_cu, fewer on small graphs in
                              FG_MODE_DO); in fg_bfs_corun, of the list's
@@ -199,10 +201,13 @@ void fg_bfs_opts_default(fg_bfs_opts* opts);
  * FG_MODE_DO).  depth: device int32[n], receives the hop distance from src
  * or -1.  parent: device int32[n] or NULL; receives a BFS-tree predecessor
  * (parent[src] = src, -1 if unreached); which of several valid parents is
- * chosen may differ between runs.  Small graphs (up to 32768 vertices, or
- * 20480 vertices and 2^18 entries in FG_MODE_PUSH) are traversed by one
- * workgroup unless an option says how to spread a traversal over the card;
- * with async_levels, where no row has more than 256 entries.  ws: device workspace of at least
+ * chosen may differ between runs.  Small graphs are traversed by one
+ * workgroup unless small_frontier .. grid_blocks say how to spread a traversal
+ * over the card: up to 32768 vertices and 2^21 entries where hubs hold most of
+ * them, else 2^19 - 4 n (2^18 with do_a > 1); in FG_MODE_PUSH up to 20480
+ * vertices and 2^18 entries, where async_levels > 1 and its team_blocks do not
+ * count as such options if no row has more than 256 entries (the workgroup is
+ * faster than any team).  ws: device workspace of at least
  * fg_workspace_bytes(g, FG_PRIM_BFS or FG_PRIM_BFS_UNFUSED, 0) bytes.
  * stats: device fg_run_stats* or NULL.  opts may be NULL (defaults).
  * Errors: FG_EINVAL (src out of range, NULL depth/ws, bad opts),

@@ -76,6 +76,13 @@ def _time_bfs(g, srcs, opts, reps=2):
     return a.elapsed_time(b) / (reps * len(srcs))
 
 
+def _one_workgroup(g, srcs, kw):
+    """Whether fg_bfs gives asynchronous calls with options `kw` to one
+    workgroup (a small graph, nothing set but mode and thresholds)."""
+    o = fg.bfs_opts(**dict(kw, async_levels=ASYNC[0], team_blocks=2))
+    return fg.bfs(g, int(srcs[0]), opts=o)[2].grid_blocks == 1
+
+
 def tune_bfs(g, srcs, mode=fg.FG_MODE_DO, log=None, do_a=None, do_b=None, big_deg=None,
              team=None, async_levels=None, async_team=None):
     """Returns (best kwargs for fg.bfs_opts, ms per traversal).  The search
@@ -102,8 +109,9 @@ def tune_bfs(g, srcs, mode=fg.FG_MODE_DO, log=None, do_a=None, do_b=None, big_de
             log(f"bfs {kw}: {ms:.4f} ms")
         if ms < best[1]:
             best = (kw, ms)
-    # stage 3 (push, one source per call): the asynchronous team
-    if mode == fg.FG_MODE_PUSH:
+    # stage 3 (push, one source per call): the asynchronous team, unless one
+    # workgroup takes such calls whatever the team asked for
+    if mode == fg.FG_MODE_PUSH and not _one_workgroup(g, srcs, best[0]):
         for k, tm in itertools.product(ASYNC if async_levels is None else async_levels,
                                        ASYNC_TEAM if async_team is None else async_team):
             kw = dict(best[0], async_levels=k, team_blocks=tm)

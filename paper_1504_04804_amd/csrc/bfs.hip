@@ -3038,7 +3038,10 @@ static BfsParams bfs_params(const fg_graph* g, int32_t src, const fg_bfs_opts& o
 // every row, at a quarter of the rate of the whole card, so its bound on the
 // entries is lower (and holds for a direction rule that hardly ever pulls);
 // one whose pulls no hub ends has a lower one as well.
-// The asynchronous mode is taken over where no row is long.
+// The asynchronous mode is taken over where no row is long, whatever its
+// team_blocks: one workgroup is faster than a team of any width there (grids from
+// a corner, teams of 2 to 64 and one workgroup: 31 x 33 119-121 and 82 us, 100 x
+// 100 286-293 and 255, 140 x 146 377-412 and 367).
 static bool solo_fits(const fg_graph* g, const fg_bfs_opts& o) {
   const bool tuned = o.small_frontier || o.small_edges || o.big_degree || o.blocks_per_cu ||
                      o.team_edges || o.grid_blocks;

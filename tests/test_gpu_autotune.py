@@ -48,6 +48,20 @@ def test_tune_bfs_small(env, orc, tmp_path):
         assert orc.check_bfs(off, col, s, to_np(d), to_np(p)) is None
 
 
+@pytest.mark.parametrize("rows,tried", [(40, False), (300, True)])
+def test_tune_push_skips_teams_that_do_not_count(env, rows, tried):
+    """No asynchronous candidates where one workgroup takes every one of them."""
+    fg, at = env
+    g = fg.Graph(*synth.grid_csr(rows, 200))
+    announce(f"autotune push grid{rows}x200")
+    lines = []
+    # no level-synchronous candidate with a balance cut, which would keep the team
+    at.tune_bfs(g, [0], fg.FG_MODE_PUSH, lines.append, big_deg=[], async_levels=[8, 32],
+                async_team=[8, 16])
+    assert len(lines) == (5 if tried else 1)
+    assert any("async_levels" in x for x in lines) == tried
+
+
 def test_tune_push_async_small(env, orc):
     """Push tuning includes the asynchronous team; the winner's options give
     the oracle's depths (Manhattan distances on a grid)."""
