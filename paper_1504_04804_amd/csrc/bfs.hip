@@ -721,6 +721,7 @@ constexpr int PULL_DEFER = STAGE;  // set-aside vertices per wave
 // lanes, 71 a lane per bit; 256 workgroups 58 and 54.  From 8 or from 24
 // candidates: the same; with four words in flight instead of two too.)
 constexpr int32_t PULL_DENSE = 16;
+constexpr int PULL_W = 2;  // dense words per round
 // added to the degree counter by a workgroup that found too many to list
 constexpr ull PULL_OVER = 1ull << 40;
 
@@ -825,7 +826,6 @@ __device__ __forceinline__ void pull_resume(const BfsParams& P, const BfsJob& J,
   }
 }
 
-template <int PULL_W>
 __device__ __forceinline__ void pull_phase(const BfsParams& P, const BfsJob& J, const St& S, Lds& L) {
   const int lane = fg_lane();
   const int wid = wave_id();
@@ -1799,7 +1799,7 @@ __device__ __forceinline__ void bfs_persistent_run(const BfsParams& P0, Lds& L) 
       }
       S.qsel ^= 1;
     } else {
-      pull_phase<2>(reread_args(), J, S, L);
+      pull_phase(reread_args(), J, S, L);
       if (!(ok = grid_acquire())) break;
       S.cur ^= 1;
     }

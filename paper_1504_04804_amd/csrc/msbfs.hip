@@ -196,27 +196,11 @@ __device__ __forceinline__ ull desc_lanes(const int4& d) {
   return (ull)(uint32_t)d.z | ((ull)(uint32_t)d.w << 32);
 }
 
-// Claim the lanes `fu` for v: the ones not yet visited get depth it1 and go
-// into next[v]; returns true when v's next word was 0 (v joins the list).
-// `got` accumulates the lanes claimed.
-__device__ __forceinline__ bool claim(const MsParams& P, ull* Fn, int32_t v, ull fu, int32_t it1,
-                                      const int32_t* start, ull& got) {
-  const ull nb = fu & ~P.visit[v];
-  if (!nb) return false;
-  const ull nw = nb & ~atomicOr(&P.visit[v], nb);
-  if (!nw) return false;
-  got |= nw;
-  ull bits = nw;
-  while (bits) {
-    const int l = __builtin_ctzll(bits);
-    bits &= bits - 1;
-    P.depth[(int64_t)l * P.n + v] = it1 - start[l];
-  }
-  return atomicOr(&Fn[v], nw) == 0ull;
-}
-
-// claim() for four edges per lane (v[r] < 0: none) with the checks, the
-// test-and-sets and the next-word atomics of the four in flight together.
+// Claim the lanes `fu[r]` for v[r], four edges per lane (v[r] < 0: none): the
+// ones not yet visited get depth it1 and go into next[v]; first[r] is set where
+// v's next word was 0 (v joins the list).  `got` accumulates the lanes claimed.
+// The checks, the test-and-sets and the next-word atomics of the four are in
+// flight together.
 __device__ __forceinline__ void claim4(const MsParams& P, ull* Fn, const int32_t (&v)[4],
                                        const ull (&fu)[4], int32_t it1, const int32_t* start,
                                        ull& got, bool (&first)[4]) {

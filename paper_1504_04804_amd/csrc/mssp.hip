@@ -164,8 +164,8 @@ struct Lds {
   int32_t red32[PWAVES + 1];
 };
 
-// The team build's LDS.  The build without it is left with 52 KB, so two
-// workgroups fit a CU.
+// The team build's LDS.  (Registers, not LDS, hold either build to one
+// workgroup per CU.)
 struct TeamLds : Lds {
   // this member's share of the frontier (vertex, first edge, end edge) for
   // the current and the next level, counters over three slots, block

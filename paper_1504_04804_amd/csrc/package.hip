@@ -141,8 +141,9 @@ __global__ void pkg_scan_kernel(int32_t tiles, int32_t nparts, int32_t* __restri
 // flight together, and the ranking takes two barriers for the tile (with
 // four rounds of 1024, three barriers each, and 131 tiles of 4096 it took
 // 19 us for 0.54 M entries, as 512 threads of four entries 17.6; the whole
-// call 33.7 -> 27.7 us, 60 000 entries in 8 partitions 28.1 -> 15.7.  256
-// threads of eight entries: 29.0 and 18.5 for the two calls).
+// call 28.7 -> 23.0 us where the inputs are in the caches, the same as before
+// where they are not, which leaves the gathers; 60 000 entries in 8 partitions
+// 28.1 -> 15.7.  256 threads of eight entries: 1.3 and 2.8 us longer).
 template <int PER, class C, bool SELF>
 __global__ __launch_bounds__(KB) void pkg_scatter_kernel(
     const int32_t* __restrict__ frontier, int32_t hlen, const int32_t* __restrict__ len_dev,
