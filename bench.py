@@ -8,9 +8,12 @@ BFS from vertex 0 of a 4096 x 4096 4-neighbour grid.  Inputs are synthetic
 and resident in HBM before timing starts; every traversal writes int32
 depths and parents.
 
-Prints one JSON line.  `value` = traversed edges of the whole step (directed
-CSR entries of each reached component, summed over the 65 traversals)
-divided by the step time.  `roofline` covers the dominant kernel, measured
+Prints one JSON line: the step, its roofline, the headline figures of the
+batched, SSSP and CPU runs and whether its depths are the oracle's.  All the
+rest (about 20 KB) goes to stderr before it, as one line that starts with
+"[bench] details ".  `value` = traversed edges of the
+whole step (directed CSR entries of each reached component, summed over the
+65 traversals) divided by the step time.  `roofline` covers the dominant kernel, measured
 with HIP events on the stream the kernels run on; its algorithmic bytes
 come from the per-iteration device statistics.  `cpu_baseline` times the
 serial CPU oracle on a bounded sample of the same workload.
@@ -990,6 +993,29 @@ def side_serving(fg, torch, cpu_graphs):
     }
 
 
+# What stays in the printed line: whole entries, and parts of some.
+LINE_KEYS = ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step",
+             "higher_is_better", "scaling", "vs_baseline", "dtype", "data", "config", "roofline",
+             "device_status_errors", "batched", "sssp", "cpu_baseline", "verified_against_oracle")
+LINE_PARTS = {
+    "config": ("workload", "rmat_n", "rmat_m", "grid_n", "grid_m", "do_a", "do_b", "parents"),
+    "roofline": ("kernel", "bound", "achieved", "peak", "unit", "frac", "traffic", "avg_launch_ms",
+                 "alg_bytes_per_launch"),
+    "batched": ("queries", "queries_per_s", "latency_ms_p50", "latency_ms_p99"),
+    "sssp": ("ms_per_source", "gteps"),
+    "cpu_baseline": ("value", "unit", "cores"),
+}
+
+
+def split_record(out):
+    """The printed line and the details of a full record."""
+    line = {k: out[k] for k in LINE_KEYS if k in out}
+    for k, parts in LINE_PARTS.items():
+        if k in line:
+            line[k] = {p: line[k][p] for p in parts if p in line[k]}
+    return line, {k: v for k, v in out.items() if line.get(k) != v}
+
+
 def main():
     args = parse()
     if args.gpus != 1:
@@ -1365,7 +1391,9 @@ def main():
     g.close()
     gg.close()
     torch.cuda.synchronize()
-    print(json.dumps(out), flush=True)
+    line, details = split_record(out)
+    print("[bench] details " + json.dumps(details), file=sys.stderr, flush=True)
+    print(json.dumps(line), flush=True)
     if verified is False:
         print("bench.py: GPU depths differ from the oracle's", file=sys.stderr, flush=True)
         sys.exit(1)
