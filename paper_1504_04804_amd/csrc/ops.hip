@@ -391,16 +391,16 @@ __device__ __forceinline__ bool bit_of(const uint32_t* bits, int32_t u) {
 // its place from c (-1 = none) in *at and its vertex in *got.  The lanes of
 // a group pass the same c and end; `first` is the group's first lane.  A
 // group without a row passes c >= end.
-__device__ __forceinline__ void probe_row(const int32_t* col, const uint32_t* fbits, int32_t c,
-                                          int32_t end, int first, int width, int32_t* at,
+__device__ __forceinline__ void probe_row(const int32_t* col, const uint32_t* fbits, uint32_t c,
+                                          uint32_t end, int first, int width, int32_t* at,
                                           int32_t* got) {
   const int lane = fg_lane();
   int32_t u[4];
   bool hit[4];
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
-    const int32_t k = r * width + (lane - first);
-    u[r] = k < end - c ? col[c + k] : -1;
+    const uint32_t k = c + r * width + (lane - first);
+    u[r] = k < end ? col[k] : -1;
   }
 #pragma unroll
   for (int r = 0; r < 4; ++r) hit[r] = u[r] >= 0 && bit_of(fbits, u[r]);
@@ -418,6 +418,7 @@ __device__ __forceinline__ void probe_row(const int32_t* col, const uint32_t* fb
   }
 }
 
+// Places in the columns are unsigned: one past a row's end may pass 2^31 - 1.
 // One early-exit backward step: a lane per unvisited vertex of nonzero
 // degree.  The first four entries come from the head table (one coalesced
 // load instead of a random line per vertex); rows of up to PL_LANE entries
@@ -461,7 +462,8 @@ __global__ __launch_bounds__(PL_BT) void pull_step_kernel(
     if (threadIdx.x == 0) s_nlong = s_nhub = 0;
     __syncthreads();
     const int32_t v = (int32_t)(w * 64 + lane);
-    int32_t i = 0, e = 0, pu = -1;
+    uint32_t i = 0, e = 0;
+    int32_t pu = -1;
     bool open = (act >> lane) & 1ull;
     bool found = false;
     if (open) {
@@ -476,8 +478,8 @@ __global__ __launch_bounds__(PL_BT) void pull_step_kernel(
       found = h0 || h1 || h2 || h3;
       pu = h0 ? h.x : h1 ? h.y : h2 ? h.z : h.w;
       insp += h0 ? 1 : h1 ? 2 : h2 ? 3 : d;
-      open = !found && e - i > 4;
-      if (open) i += 4;
+      i += 4;
+      open = !found && i < e;
     }
     {
       const bool listed = open && e - i > PL_LANE - 4;
@@ -492,17 +494,17 @@ __global__ __launch_bounds__(PL_BT) void pull_step_kernel(
     }
     while (__ballot(open)) {
       if (open) {
-        const int32_t l = e - 1 - i;
-        const int32_t u0 = col[i], u1 = col[i + (l < 1 ? l : 1)];
-        const int32_t u2 = col[i + (l < 2 ? l : 2)], u3 = col[i + (l < 3 ? l : 3)];
+        const uint32_t l = e - 1;
+        const int32_t u0 = col[i], u1 = col[i + 1 < l ? i + 1 : l];
+        const int32_t u2 = col[i + 2 < l ? i + 2 : l], u3 = col[i + 3 < l ? i + 3 : l];
         const bool h0 = bit_of(fbits, u0), h1 = bit_of(fbits, u1);
         const bool h2 = bit_of(fbits, u2), h3 = bit_of(fbits, u3);
         const int32_t d = e - i < 4 ? e - i : 4;
         found = h0 || h1 || h2 || h3;
         pu = h0 ? u0 : h1 ? u1 : h2 ? u2 : u3;
         insp += h0 ? 1 : h1 ? 2 : h2 ? 3 : d;
-        open = !found && e - i > 4;
-        if (open) i += 4;
+        i += 4;
+        open = !found && i < e;
       }
     }
     {
@@ -520,14 +522,14 @@ __global__ __launch_bounds__(PL_BT) void pull_step_kernel(
       const int first = lane & ~(PL_GROUP - 1);
       const int32_t j = j0 + lane / PL_GROUP;
       int2 x = make_int2(0, 0);
-      int32_t c = 0, end = 0;
+      uint32_t c = 0, end = 0;
       if (j < nlong) {
         x = s_long[j];
         c = off[x.x];
         end = off[x.x + 1];
       }
-      const int32_t stop = end - c > PL_GROUP_MAX ? c + PL_GROUP_MAX : end;
-      c = end - c > 4 ? c + 4 : end;
+      const uint32_t stop = end - c > PL_GROUP_MAX ? c + PL_GROUP_MAX : end;
+      c += 4;
       bool hit = false;  // the group's row is done; it waits for the wave's others
       while (__ballot(c < stop)) {
         int32_t at, got = -1;
@@ -535,7 +537,7 @@ __global__ __launch_bounds__(PL_BT) void pull_step_kernel(
         if (c < stop) {
           hit = at >= 0;
           if (lane == first) {
-            const int32_t took = stop - c < 4 * PL_GROUP ? stop - c : 4 * PL_GROUP;
+            const int32_t took = stop - c < 4 * PL_GROUP ? (int32_t)(stop - c) : 4 * PL_GROUP;
             insp += hit ? at + 1 : took;
             if (hit) {
               depth[x.x] = d_new;
@@ -543,7 +545,7 @@ __global__ __launch_bounds__(PL_BT) void pull_step_kernel(
               atomicOr(&s_new[x.y], 1ull << (x.x & 63));
             }
           }
-          c = hit || stop - c <= 4 * PL_GROUP ? stop : c + 4 * PL_GROUP;
+          c = hit ? stop : c + 4 * PL_GROUP;
         }
       }
       stage.push(hit && lane == first, x.x);
@@ -560,9 +562,8 @@ __global__ __launch_bounds__(PL_BT) void pull_step_kernel(
     const int32_t nhub = s_nhub;
     for (int32_t j = wid; j < nhub; j += PL_WAVES) {
       const int2 x = s_hub[j];
-      const int32_t end = off[x.x + 1];
-      for (int64_t c64 = (int64_t)off[x.x] + PL_GROUP_MAX; c64 < end; c64 += 4 * FG_WAVE) {
-        const int32_t c = (int32_t)c64;
+      const uint32_t end = off[x.x + 1];
+      for (uint32_t c = off[x.x] + PL_GROUP_MAX; c < end; c += 4 * FG_WAVE) {
         int32_t at, got = -1;
         probe_row(col, fbits, c, end, 0, FG_WAVE, &at, &got);
         if (at >= 0) {
@@ -575,7 +576,7 @@ __global__ __launch_bounds__(PL_BT) void pull_step_kernel(
           stage.push(lane == 0, x.x);
           break;
         }
-        if (lane == 0) insp += end - c < 4 * FG_WAVE ? end - c : 4 * FG_WAVE;
+        if (lane == 0) insp += end - c < 4 * FG_WAVE ? (int32_t)(end - c) : 4 * FG_WAVE;
       }
     }
     __syncthreads();
