@@ -290,25 +290,24 @@ __global__ __launch_bounds__(DUP_BT) void dup_step_kernel(DupArgs A) {
           // four entries per step, their column and visited-word loads in
           // flight together (a row is otherwise a chain of dependent
           // loads); the entries read still stop at the first hit
-          const int32_t e = A.off[v + 1];
-          const int32_t b = A.off[v];
-          for (int64_t i0 = 0; i0 < e - b && !found; i0 += 4) {
+          const uint32_t e = A.off[v + 1];  // (unsigned places: a row may end at 2^31 - 1)
+          for (uint32_t i0 = A.off[v]; i0 < e && !found; i0 += 4) {
             int32_t u[4];
             uint64_t wv[4];
 #pragma unroll
-            for (int k = 0; k < 4; ++k) u[k] = A.col[k < e - b - i0 ? b + i0 + k : e - 1];
+            for (int k = 0; k < 4; ++k) u[k] = A.col[i0 + k < e ? i0 + k : e - 1];
 #pragma unroll
             for (int k = 0; k < 4; ++k) wv[k] = A.visited[u[k] >> 6];
             int32_t h = -1;
 #pragma unroll
             for (int k = 3; k >= 0; --k)
-              if (k < e - b - i0 && ((wv[k] >> (u[k] & 63)) & 1ull)) h = k;
+              if (i0 + k < e && ((wv[k] >> (u[k] & 63)) & 1ull)) h = k;
             if (h >= 0) {
               found = true;
               pu = u[h];
               insp += h + 1;
             } else {
-              insp += e - b - i0 < 4 ? (int32_t)(e - b - i0) : 4;
+              insp += e - i0 < 4 ? (int32_t)(e - i0) : 4;
             }
           }
         }
@@ -349,9 +348,9 @@ __global__ __launch_bounds__(DUP_BT) void dup_big_kernel(DupArgs A) {
     int64_t first = ((int64_t)blockIdx.x - base) % (int64_t)gridDim.x;
     if (first < 0) first += gridDim.x;
     for (int64_t t = first; t < ntask; t += gridDim.x) {
-      const int32_t e_end = (int32_t)((t + 1) * DUP_CHUNK < deg ? (t + 1) * DUP_CHUNK : deg);
-      for (int64_t e0 = t * DUP_CHUNK; e0 < e_end; e0 += DUP_BT) {
-        const int64_t e = e0 + threadIdx.x;
+      const uint32_t e_end = (uint32_t)((t + 1) * DUP_CHUNK < deg ? (t + 1) * DUP_CHUNK : deg);
+      for (uint32_t e0 = (uint32_t)(t * DUP_CHUNK); e0 < e_end; e0 += DUP_BT) {
+        const uint32_t e = e0 + threadIdx.x;
         fwd_visit(A, e < e_end ? A.col[b + e] : -1, u, d_new, nq);
         insp += e < e_end;
       }

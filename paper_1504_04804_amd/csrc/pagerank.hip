@@ -135,11 +135,12 @@ __device__ __forceinline__ double seg_incl_sum(double x, int lane, int start) {
 // and the longest row held its workgroup for most of an iteration; eight
 // partial sums measured no faster); the order of the additions is fixed.
 __device__ __forceinline__ double strided_gather_sum(const double* cur, const int32_t* col,
-                                                     int32_t first, int32_t end, int32_t stride) {
+                                                     uint32_t first, uint32_t end, uint32_t stride) {
   double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
-  // 64-bit places: a row may end at 2^31 - 1
-  int64_t i = first;
-  for (; i < (int64_t)end - 3 * stride; i += 4 * stride) {
+  // unsigned places: a row may end at 2^31 - 1
+  uint32_t i = first;
+  const uint32_t last = end > 3 * stride ? end - 3 * stride : 0u;
+  for (; i < last; i += 4 * stride) {
     const int32_t c0 = col[i];
     const int32_t c1 = col[i + stride];
     const int32_t c2 = col[i + 2 * stride];
@@ -183,7 +184,7 @@ __global__ __launch_bounds__(PR_BT) void pr_iter_kernel(PrArgs A, int32_t it) {
       // one long row, the whole workgroup
       const int32_t v = A.longrows[item];
       const int32_t b = A.off[v], e = A.off[v + 1];
-      double acc = strided_gather_sum(cur, A.col, b + (int32_t)threadIdx.x, e, PR_BT);
+      double acc = strided_gather_sum(cur, A.col, (uint32_t)b + threadIdx.x, e, PR_BT);
       acc = wave_sum_f64(acc);
       if (lane == 0) s_red[wid] = acc;
       __syncthreads();
@@ -251,7 +252,7 @@ __global__ __launch_bounds__(PR_BT) void pr_iter_kernel(PrArgs A, int32_t it) {
       const int32_t ub = __shfl(b, l, FG_WAVE);
       const int32_t ud = __shfl(deg, l, FG_WAVE);
       double acc = 0.0;
-      acc = strided_gather_sum(cur, A.col, ub + lane, ub + ud, FG_WAVE);
+      acc = strided_gather_sum(cur, A.col, (uint32_t)ub + lane, ub + ud, FG_WAVE);
       acc = wave_sum_f64(acc);
       if (lane == l) nc += pr_update(A, nxt, v, ud, acc);
     }
