@@ -1898,8 +1898,8 @@ __global__ __launch_bounds__(PB) void bfs_persistent(BfsParams P) {
 // takes one piece of the frontier, then further ones through an LDS counter.
 // Same levels, directions and counts as the kernel above; no workspace is
 // touched.
-// Measured, R-MAT, direction-optimizing: n = 4096 90 -> 27 us, 16 k 104-126
-// -> 40-57, 32 k (0.4 to 1.3 M entries) 106-143 -> 55-66 (the pull's 16
+// Measured, R-MAT, direction-optimizing: n = 4096 98 -> 22 us, 16 k 101-134
+// -> 33-58, 32 k (0.3 to 1.6 M entries) 103-154 -> 48-92 (the pull's 16
 // rounds of 2048 vertices; the bound on n is the LDS room of two lists);
 // push-only, one word per vertex: n = 1000 192 -> 23 us, 16 k (0.22 M
 // entries) 179 -> 87, but 16 k (0.6 M) 181 -> 283 and 32 k (1.2 M) 191 ->

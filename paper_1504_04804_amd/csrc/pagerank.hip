@@ -874,7 +874,11 @@ __global__ __launch_bounds__(PP_BT) void pp_iter_kernel(PrArgs A, PrPlanned Q, i
 // All iterations in one co-resident launch, for runs that may stop early: the
 // launches left after the stop cost 3.4 us each, and the planned form has two
 // per iteration (at most 1000 iterations, stopped after 7: 7.0 ms on 20 k
-// vertices, 3.3 with the direct form's one).
+// vertices, 3.3 with the direct form's one).  An iteration takes 5 to 30 us
+// longer for its barriers, with which at most 100 iterations break even after
+// about ten: 300 k vertices, 3, 7 and 18 of them 370, 633 and 1350 us, as
+// launches 618, 720 and 1125.  (Stores past the L2 in place of its write-back
+// at the barriers: 2 to 12 % less up to 20 k vertices, 4 to 48 % more above.)
 __global__ __launch_bounds__(PP_BT) void pp_loop_kernel(PrArgs A, PrPlanned Q, int32_t max_iter,
                                                         int32_t longs) {
   __shared__ double s_hot[PP_HOT];
