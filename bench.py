@@ -42,29 +42,29 @@ GRID = 4096
 # the kernel sources they were taken with: `traffic` is null when these files
 # hash differently.
 TRAFFIC_SOURCES = ('csrc/bfs.hip', 'csrc/fg_common.h', 'csrc/frontier.h', 'csrc/graph.hip')
-TRAFFIC_SHA256 = "d7e11b0c7b09457a9ec3dfee26ead57bed4c403bc272de2c8c42e7233b5a2b82"
-TRAFFIC_BYTES = {"bfs_corun<DO>": 16018289594, "bfs_persistent<DO,many> (alone)": 13697249920,
-                 "bfs_async (alone)": 2287475844}
+TRAFFIC_SHA256 = "28a2d6dbb9db1f7b29dbce8b534f6b66cd86eba71cad8bcca2fb0ba25bb231bb"
+TRAFFIC_BYTES = {"bfs_corun<DO>": 16000351099, "bfs_persistent<DO,many> (alone)": 13685387192,
+                 "bfs_async (alone)": 2287654024}
 # The same for the side workloads' kernels (per launch; PageRank per
 # iteration), from the same two passes
 # (profiles/side_kernels_hbm_counters.md), each guarded by a hash of the
 # sources its kernel is built from.
 _COMMON = ('csrc/fg_common.h', 'csrc/frontier.h', 'csrc/graph.hip')
 SIDE_TRAFFIC = {
-    "sssp": (('csrc/sssp.hip',) + _COMMON, 12003036508),
-    "c4_rmat23": (('csrc/msbfs.hip',) + _COMMON, 21975272384),
-    "c4_grid2048": (('csrc/msbfs.hip',) + _COMMON, 518201394218),
-    "mssp_rmat22": (('csrc/mssp.hip',) + _COMMON, 129373865696),
-    "mssp_grid2048": (('csrc/mssp.hip',) + _COMMON, 578499057440),
-    "pagerank_iter": (('csrc/pagerank.hip',) + _COMMON, 1620474250),
+    "sssp": (('csrc/sssp.hip',) + _COMMON, 12019689325),
+    "c4_rmat23": (('csrc/msbfs.hip',) + _COMMON, 22043160224),
+    "c4_grid2048": (('csrc/msbfs.hip',) + _COMMON, 519205099242),
+    "mssp_rmat22": (('csrc/mssp.hip',) + _COMMON, 129842571824),
+    "mssp_grid2048": (('csrc/mssp.hip',) + _COMMON, 576824149984),
+    "pagerank_iter": (('csrc/pagerank.hip',) + _COMMON, 1620210612),
 }
 SIDE_TRAFFIC_SHA256 = {
-    "sssp": "bd1218b6eed2e97a8b583587e2cb1ec12626d5710ccd56a24ef24da2be988556",
-    "c4_rmat23": "2a752dc945f91589cd00135b655dfd0b35f82b0d16dfde4f245f4b54417be549",
-    "c4_grid2048": "2a752dc945f91589cd00135b655dfd0b35f82b0d16dfde4f245f4b54417be549",
-    "mssp_rmat22": "4a79ddbb9014edd64ead332ccba6d5eb5908a714843e77eddf47a241bd364f8b",
-    "mssp_grid2048": "4a79ddbb9014edd64ead332ccba6d5eb5908a714843e77eddf47a241bd364f8b",
-    "pagerank_iter": "45305a56f9ba5cd476aa9b7375c346abe1299dab9e7278e7ee3e7681d18cb0f9",
+    "sssp": "19a134815772ec3102f25d2b5e79cf95802f4e3c5126d7e7761583dfe886cae7",
+    "c4_rmat23": "7f74fe9d096345b7d0dc7ab4783ef46e61babe7fa3b74b2f67294154db8de4e5",
+    "c4_grid2048": "7f74fe9d096345b7d0dc7ab4783ef46e61babe7fa3b74b2f67294154db8de4e5",
+    "mssp_rmat22": "19e497f6996627152552836a3d8950571eec0c4622435dc7b99c5731e0d40c7d",
+    "mssp_grid2048": "19e497f6996627152552836a3d8950571eec0c4622435dc7b99c5731e0d40c7d",
+    "pagerank_iter": "ede4aea2d02ef2bb929d02ad37ecf2990c7033c0a2a0ccc8efddf60e6acb581a",
 }
 
 
