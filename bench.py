@@ -64,7 +64,7 @@ SIDE_TRAFFIC_SHA256 = {
     "c4_grid2048": "7f74fe9d096345b7d0dc7ab4783ef46e61babe7fa3b74b2f67294154db8de4e5",
     "mssp_rmat22": "19e497f6996627152552836a3d8950571eec0c4622435dc7b99c5731e0d40c7d",
     "mssp_grid2048": "19e497f6996627152552836a3d8950571eec0c4622435dc7b99c5731e0d40c7d",
-    "pagerank_iter": "ede4aea2d02ef2bb929d02ad37ecf2990c7033c0a2a0ccc8efddf60e6acb581a",
+    "pagerank_iter": "bd5205b300a8e033eeaf0ab6f8f706a9ceaacd57d895acb5d7c6d049d987a407",
 }
 
 

@@ -11,9 +11,9 @@
 // atomics), so each vertex's new rank is final when its row is done.
 // Convergence (the threshold ratio): the run stops after an iteration in
 // which every vertex changed by at most tol times its previous rank; tol = 0
-// runs max_iter iterations.  Every iteration is a launch that returns at
-// once when the run has already stopped, so the host enqueues all of them
-// without reading anything back.
+// runs max_iter iterations.  The host enqueues everything without reading
+// back: an iteration is a launch that returns at once when the run has already
+// stopped, or all are one launch that ends there.
 //
 // Two forms.  The planned one renumbers the vertices by falling degree at the
 // start of the call and copies the columns once under the new numbers: the
